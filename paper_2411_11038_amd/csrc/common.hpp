@@ -192,8 +192,10 @@ struct ProfScope {
 // Eq. 6 scores of every row of w [c_out][block] (double precision), and the Top-K launch, shared by the select and
 // the combined weight-side entry points
 int launch_row_importance(const float* w, int64_t c_out, int64_t block, double* scores, hipStream_t st);
-void launch_topk(const double* scores, int64_t n, int64_t k, int32_t* idx, hipStream_t st);
-int launch_topk_profiled(const double* scores, int64_t n, int64_t k, int32_t* idx, hipStream_t st);
+// ws: topk_ws_bytes(n) bytes, 256-byte aligned (0 bytes for inputs that one block selects from)
+size_t topk_ws_bytes(int64_t n);
+void launch_topk(const double* scores, int64_t n, int64_t k, int32_t* idx, void* ws, hipStream_t st);
+int launch_topk_profiled(const double* scores, int64_t n, int64_t k, int32_t* idx, void* ws, hipStream_t st);
 
 // Forward product on int8 matrix cores: y[m][n] = S_x * S_w[n] * sum_k (x_codes[m][k] - round(Z_x)) * w_codes[n][k].
 // K, lda, ldb multiples of 16; wsum[n] = sum_k w_codes[n][k].

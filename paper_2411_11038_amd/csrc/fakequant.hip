@@ -466,7 +466,10 @@ extern "C" int efqat_weight_quant_select(const float* w, int64_t c_out, int64_t 
       ((uintptr_t)scale % 4) != 0 || ((uintptr_t)idx % 4) != 0 || ((uintptr_t)scores % 8) != 0)
     return EFQAT_ERR_ALIGNMENT;
   hipStream_t st = (hipStream_t)stream;
-  double* sc = scores ? scores : (double*)ws;
+  WsCarver carve(ws);
+  double* own = (double*)carve.take((size_t)c_out * sizeof(double));
+  void* sel_ws = carve.take(topk_ws_bytes(c_out));
+  double* sc = scores ? scores : own;
   bool scores_done = false;
   int rc = run_fakequant<float>(w, c_out, block, EFQAT_QUANT_W_PER_ROW_SYM, bits, init_minmax, scale, nullptr, codes,
                                 clip_bits, nullptr, nullptr, st, init_minmax ? sc : nullptr, &scores_done);
@@ -476,5 +479,5 @@ extern "C" int efqat_weight_quant_select(const float* w, int64_t c_out, int64_t 
     if (rc) return rc;
   }
   if (k == 0) return EFQAT_OK;
-  return launch_topk_profiled(sc, c_out, k, idx, st);
+  return launch_topk_profiled(sc, c_out, k, idx, sel_ws, st);
 }

@@ -2,6 +2,8 @@
 // key (score descending, index ascending) by radix select, output compacted in ascending index order.
 #include "common.hpp"
 
+#include <algorithm>
+
 namespace efqat {
 
 // I[c] = (1/n) sum_j |w[c][j]|, fp64 accumulation, one wavefront per channel, fixed reduction order.
@@ -25,310 +27,554 @@ __global__ __launch_bounds__(256) void k_row_importance(const float* __restrict_
   if (lane == 0) scores[row] = acc / (double)n;
 }
 
-// Exact Top-K by radix select, one block of NTH threads.  Scores are non-negative doubles, so their bit
-// patterns order like the values.  Passes over 8-bit digits of the 64-bit key, from the highest bit on which
-// two keys differ downwards, find the key T of the k-th largest score and `need`, the number of scores equal
-// to T that still belong to the selection (as soon as at most 64 candidates remain they are ranked directly); then one ordered sweep writes every index whose score is > T, plus the first `need` indices
-// (ascending) whose score equals T: ties go to the lower index, output is ascending.  Integer counting only,
-// so the result does not depend on thread scheduling.
-// Where the keys live between the passes: up to KPT per thread in registers (n <= KPT * NTH); else, with in_lds, in a
-// dynamic LDS array of n keys (8 n bytes); else they are re-read from memory in every pass.
-template <int NTH, int KPT>
-__global__ __launch_bounds__(NTH) void k_topk_radix(const double* __restrict__ scores, int64_t n, int64_t k,
-                                                     int32_t* __restrict__ idx, int in_lds) {
-  extern __shared__ __attribute__((aligned(16))) unsigned long long lkeys[];
-  constexpr int NW = NTH / 64;                        // wavefronts
-  __shared__ unsigned int hist[NW][256];              // one histogram per wavefront: less atomic contention
-  __shared__ unsigned int total[256];
-  __shared__ unsigned long long s_prefix, s_or[NW], s_and[NW];
-  __shared__ long long s_need;
-  __shared__ int wsum_gt[NW], wsum_eq[NW];
-  __shared__ long long s_base_gt, s_base_eq;
-  __shared__ unsigned long long cand_key[64];
-  __shared__ int cand_idx[64];
-  __shared__ int s_bin_count, s_ncand;
-  __shared__ int scan_gt[KPT * NW + 64], scan_eq[KPT * NW + 64]; // KPT x wavefronts (cached case), padded to whole lanes
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  // Up to KPT keys per thread stay in registers for all passes (n <= KPT * NTH); longer inputs are re-read.
-  constexpr int EPL = (KPT * NW + 63) / 64;           // scan entries per lane of the ordered output
-  unsigned long long keys[KPT];
-  const bool cached = n <= (int64_t)KPT * NTH;
-  // Keys are taken relative to the smallest one (order and equality are unchanged): the scores of a layer lie in a
-  // narrow band, and without the offset a band that straddles a power of two would put its highest differing bit
-  // in the exponent, so that the first digit window would split the keys into two or three crowded bins.  With it
-  // the first window starts at the top bit of (max - min) and spreads the keys over all 256 bins.
-  unsigned long long vmin = ~0ull;
-  if (cached) {
+// ------------------------------------------------------------------------------------------------
+// Exact Top-K.  Scores are non-negative doubles, so their bit patterns order like the values; keys are taken relative
+// to the smallest one (order and equality unchanged), which puts the first digit window right below the top bit of
+// (largest - smallest): the scores of a layer lie in a narrow band, and the first window of 12 bits already leaves a
+// handful of them around the threshold.  The selection under (score descending, index ascending) is a threshold pair
+// (T, I): element i belongs to it iff key > T or (key == T and i <= I).  Integer counting only, so the result does not
+// depend on thread scheduling.
+typedef unsigned long long u64;
+constexpr int kSelBits = 12, kSelBins = 1 << kSelBits;   // digit windows (10 bits where at most 256 keys are looked at)
+constexpr int64_t kTopkBlockKeys = 16384;             // one block selects from up to this many
+constexpr int kSelRank = 64;                          // this few candidates are ranked directly by one wavefront
+
+__device__ __forceinline__ u64 score_key(double s) { return (u64)__double_as_longlong(s); }
+
+// Where a selected index goes.
+//   plain:      idx[pos] = c
+//   layer_off:  one Top-K over the channels of several layers: idx[pos] = c - first channel of its layer, and
+//               per_layer[layer] counts (zeroed by an earlier phase);  flags (blocks are whole layers): per_layer[c] =
+//               channels of layer c if it is selected, else 0
+struct SelectOut {
+  int32_t* idx;
+  const int64_t* layer_off;
+  int64_t n_layers;
+  int32_t* per_layer;
+  int flags;
+};
+
+// wavefront-wide reductions in registers (DPP): a shuffle through the LDS unit costs several times the latency
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned int dpp(unsigned int old, unsigned int v) {
+  return (unsigned int)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROWS, 0xf, false);
+}
+template <class F>
+__device__ __forceinline__ unsigned int wave_scan(unsigned int v, unsigned int id, F f) {   // inclusive, lane 63: total
+  v = f(v, dpp<0x111, 0xf>(id, v));                   // row_shr:1, 2, 4, 8: within rows of 16
+  v = f(v, dpp<0x112, 0xf>(id, v));
+  v = f(v, dpp<0x114, 0xf>(id, v));
+  v = f(v, dpp<0x118, 0xf>(id, v));
+  v = f(v, dpp<0x142, 0xa>(id, v));                   // row_bcast:15 into rows 1 and 3
+  return f(v, dpp<0x143, 0xc>(id, v));                // row_bcast:31 into rows 2 and 3
+}
+__device__ __forceinline__ unsigned int wave_scan_add(unsigned int v) {
+  return wave_scan(v, 0u, [](unsigned int a, unsigned int b) { return a + b; });
+}
+
+template <int NTH, int BITS = kSelBits>
+struct SelShared {
+  static constexpr int kBits = BITS, kBins = 1 << BITS, kBpt = kBins / NTH;
+  unsigned int hist[kBins];
+  unsigned int wave_tot[NTH / 64];
+  unsigned int lo[NTH / 64], hi[NTH / 64];
+  u64 cand_key[kSelRank];
+  int cand_idx[kSelRank];
+  unsigned int rank[kSelRank];
+  int ncand, bin, need, count;
+  u64 T;
+  int I;
+};
+
+// What is taken off every key: the upper half of the smallest one, and in *top how many bits the differences need.
+// (Halves are enough: the window loses at most a bit.)  lo, hi: smallest and largest upper half of this thread's keys.
+template <class SH>
+__device__ __forceinline__ u64 block_base(SH& sh, unsigned int lo, unsigned int hi, int* top) {
+  constexpr int NW = sizeof(sh.lo) / sizeof(sh.lo[0]);
+  lo = wave_scan(lo, ~0u, [](unsigned int a, unsigned int b) { return a < b ? a : b; });
+  hi = wave_scan(hi, 0u, [](unsigned int a, unsigned int b) { return a > b ? a : b; });
+  if ((threadIdx.x & 63) == 63) { sh.lo[threadIdx.x >> 6] = lo; sh.hi[threadIdx.x >> 6] = hi; }
+  __syncthreads();
+  lo = ~0u; hi = 0u;
 #pragma unroll
-    for (int q = 0; q < KPT; ++q) {
-      const int64_t i = (int64_t)q * NTH + tid;
-      keys[q] = 0ull;
-      if (i < n) {
-        keys[q] = (unsigned long long)__double_as_longlong(scores[i]);
-        vmin = keys[q] < vmin ? keys[q] : vmin;
+  for (int w = 0; w < NW; ++w) { lo = sh.lo[w] < lo ? sh.lo[w] : lo; hi = sh.hi[w] > hi ? sh.hi[w] : hi; }
+  *top = 32 + (hi > lo ? 32 - __clz((int)(hi - lo)) : 0);
+  return (u64)lo << 32;
+}
+
+// Finds the bin in which the need-th largest element lies: sh.bin, sh.need (still to take inside it), sh.count (its
+// size).  bins[]: this thread's kBpt consecutive bins.  Ends with a barrier.
+template <class SH>
+__device__ __forceinline__ void search_bins(SH& sh, const unsigned int (&bins)[SH::kBpt], int need) {
+  constexpr int BPT = SH::kBpt, NW = sizeof(sh.wave_tot) / sizeof(sh.wave_tot[0]);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  unsigned int tot = 0;
+#pragma unroll
+  for (int u = 0; u < BPT; ++u) tot += bins[u];
+  const unsigned int inc = wave_scan_add(tot);
+  if (lane == 63) sh.wave_tot[wv] = inc;
+  __syncthreads();
+  int above = -(int)inc;                              // elements in higher bins
+#pragma unroll
+  for (int w = 0; w < NW; ++w) above += w >= wv ? (int)sh.wave_tot[w] : 0;
+  if (above < need && need <= above + (int)tot) {     // exactly one thread holds the crossing
+#pragma unroll
+    for (int u = BPT - 1; u >= 0; --u) {
+      const int h = (int)bins[u];
+      if (above < need && need <= above + h) {
+        sh.bin = (int)threadIdx.x * BPT + u; sh.need = need - above; sh.count = h;
       }
-    }
-  } else {
-    for (int64_t i = tid; i < n; i += NTH) {
-      const unsigned long long key = (unsigned long long)__double_as_longlong(scores[i]);
-      if (in_lds) lkeys[i] = key;                      // each thread re-reads only what it wrote until the next barrier
-      vmin = key < vmin ? key : vmin;
+      above += h;
     }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long t = __shfl_xor(vmin, o, kWave);
-    vmin = t < vmin ? t : vmin;
-  }
-  if (lane == 0) s_and[wv] = vmin;
   __syncthreads();
-  vmin = ~0ull;
-  for (int i = 0; i < NW; ++i) vmin = s_and[i] < vmin ? s_and[i] : vmin;
-  const unsigned long long kmin = vmin;
-  // Leading bits on which all (offset) keys agree need no pass: they are the zero bits above the top bit of the OR.
-  unsigned long long vor = 0ull;
-  if (cached) {
-#pragma unroll
-    for (int q = 0; q < KPT; ++q) {
-      const int64_t i = (int64_t)q * NTH + tid;
-      if (i < n) { keys[q] -= kmin; vor |= keys[q]; }
+}
+
+// Threshold pair of element number `need` (from 1) under (key descending, index ascending) among the `count` elements
+// with key >> top == prefix; each(f) calls f(key, index) for every element this thread holds, at least those elements.
+// Windows of BITS bits from `top` downwards until few elements are left; equal keys are told apart by their index, the
+// last windows.
+template <int NTH, int BITS, class Each>
+__device__ __forceinline__ void find_threshold(SelShared<NTH, BITS>& sh, Each each, u64 prefix, int top, int need,
+                                               int count) {
+  constexpr int BINS = 1 << BITS, BPT = BINS / NTH;
+  const int tid = threadIdx.x;
+  bool on_index = false;                              // all remaining elements have key T: the windows run over ~index
+  u64 T = 0;
+  if (tid == 0) sh.ncand = 0;
+  if (tid < kSelRank) sh.rank[tid] = 0u;
+  while (count > kSelRank) {
+    if (top == 0) {                                   // equal keys, more of them than are ranked directly
+      T = prefix; on_index = true; prefix = 0; top = 32;
     }
-  } else if (in_lds) {
-    for (int64_t i = tid; i < n; i += NTH) { const unsigned long long key = lkeys[i] - kmin; lkeys[i] = key; vor |= key; }
-  } else {
-    for (int64_t i = tid; i < n; i += NTH) vor |= (unsigned long long)__double_as_longlong(scores[i]) - kmin;
-  }
-  // offset key of element i for the passes below (not for the register-resident case)
-  auto key_at = [&](int64_t i) -> unsigned long long {
-    return in_lds ? lkeys[i] : (unsigned long long)__double_as_longlong(scores[i]) - kmin;
-  };
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) vor |= __shfl_xor(vor, o, kWave);
-  if (lane == 0) s_or[wv] = vor;
-  __syncthreads();
-  vor = 0ull;
-  for (int i = 0; i < NW; ++i) vor |= s_or[i];
-  const unsigned long long diff = vor;                 // the smallest offset key is 0: every set bit differs somewhere
-  // The first 8-bit digit window ends at the highest bit on which two keys differ, so the first pass already
-  // spreads the keys over the bins; below it the windows follow each other down to bit 0 (the last one may be
-  // narrower).  `top` = first bit above the current window; the bits from `top` upwards are the prefix.
-  const int hb = diff ? 63 - __clzll((long long)diff) : 7;
-  int top = (hb >= 7 ? hb : 7) + 1;
-  if (tid == 0) {
-    s_prefix = top >= 64 ? 0ull : (vor >> top);         // shared by all keys
-    s_need = k;
-    s_bin_count = 1 << 30;
-  }
-  for (int b = tid; b < NW * 256; b += NTH) (&hist[0][0])[b] = 0u;
-  __syncthreads();
-  while (top > 0) {
-    const int width = top < 8 ? top : 8;
-    const int shift = top - width;                      // the window is bits [shift, top)
-    const unsigned long long dmask = (1ull << width) - 1ull;
-    const unsigned long long prefix = s_prefix;
-    if (cached) {
-#pragma unroll
-      for (int q = 0; q < KPT; ++q) {
-        const int64_t i = (int64_t)q * NTH + tid;
-        const unsigned long long key = keys[q];
-        const bool match = (top >= 64) || ((key >> top) == prefix);
-        if (i < n && match) atomicAdd(&hist[wv][(key >> shift) & dmask], 1u);
-      }
+    const int width = top < BITS ? top : BITS, shift = top - width;
+    const u64 mask = (1ull << width) - 1ull;
+    for (int b = tid; b < BINS; b += NTH) sh.hist[b] = 0u;
+    __syncthreads();
+    if (prefix == 0 && !on_index) {                   // nothing above the window: no element to leave out but larger ones
+      each([&](u64 key, int) {
+        const u64 b = key >> shift;
+        if (b <= mask) atomicAdd(&sh.hist[b], 1u);
+      });
     } else {
-      for (int64_t i = tid; i < n; i += NTH) {
-        const unsigned long long key = key_at(i);
-        const bool match = (top >= 64) || ((key >> top) == prefix);
-        if (match) atomicAdd(&hist[wv][(key >> shift) & dmask], 1u);
-      }
+      each([&](u64 key, int i) {
+        const u64 v = on_index ? (u64)(unsigned int)~i : key;
+        if ((!on_index || key == T) && (v >> top) == prefix) atomicAdd(&sh.hist[(v >> shift) & mask], 1u);
+      });
     }
     __syncthreads();
-    if (tid < 256) {                                    // fold the per-wave histograms, clear them for the next pass
-      unsigned int t = 0;
-      for (int w = 0; w < NW; ++w) { t += hist[w][tid]; hist[w][tid] = 0u; }
-      total[tid] = t;
-    }
-    __syncthreads();
-    if (wv == 0) {
-      // digit search by the first wavefront: lane l owns bins 4l..4l+3; suffix sums (bins above) by shuffles
-      const int need = (int)s_need;                     // counts fit 32 bits: n <= INT32_MAX
-      const int h0 = (int)total[4 * lane], h1 = (int)total[4 * lane + 1], h2 = (int)total[4 * lane + 2],
-                h3 = (int)total[4 * lane + 3];
-      const int tot = h0 + h1 + h2 + h3;
-      int inc = tot;                                    // inclusive suffix sum over lanes >= l
+    unsigned int bins[BPT];
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_down(inc, o, kWave);
-        if (lane + o < 64) inc += t;
-      }
-      int a = inc - tot;                                // keys in bins above this lane's four
-      if (a < need && need <= a + tot) {                // exactly one lane holds the crossing
-        int d;
-        if (a + h3 >= need) d = 3;
-        else { a += h3; if (a + h2 >= need) d = 2; else { a += h2; if (a + h1 >= need) d = 1; else { a += h1; d = 0; } } }
-        s_need = need - a;                              // still to take among keys whose digit equals d
-        s_prefix = (prefix << width) | (unsigned long long)(4 * lane + d);
-        s_bin_count = d == 3 ? h3 : d == 2 ? h2 : d == 1 ? h1 : h0;
-      }
-      if (lane == 0) s_ncand = 0;
-    }
-    __syncthreads();
-    // Few keys left under the chosen prefix: finish at once instead of one pass per remaining byte.  The
-    // candidates are gathered (in any order) and ranked by one wavefront under (key descending, index ascending).
-    top = shift;                                        // the prefix now reaches down to `shift`
-    if (top > 0 && s_bin_count <= 64) {
-      const unsigned long long np = s_prefix;
-      if (cached) {
-#pragma unroll
-        for (int q = 0; q < KPT; ++q) {
-          const int64_t i = (int64_t)q * NTH + tid;
-          if (i < n && (keys[q] >> top) == np) {
-            const int slot = atomicAdd(&s_ncand, 1);
-            cand_key[slot] = keys[q]; cand_idx[slot] = (int)i;
-          }
-        }
-      } else {
-        for (int64_t i = tid; i < n; i += NTH) {
-          const unsigned long long key = key_at(i);
-          if ((key >> top) == np) {
-            const int slot = atomicAdd(&s_ncand, 1);
-            cand_key[slot] = key; cand_idx[slot] = (int)i;
-          }
-        }
-      }
-      __syncthreads();
-      if (wv == 0) {
-        const int nc = s_ncand;                         // == s_bin_count
-        const int need = (int)s_need;                   // 1 .. nc
-        const bool on = lane < nc;
-        const unsigned long long mk = on ? cand_key[lane] : 0ull;
-        const int mi = on ? cand_idx[lane] : 0;
-        int rank = 0;
-        for (int j = 0; j < nc; ++j) {
-          const unsigned long long kj = cand_key[j];
-          const int ij = cand_idx[j];
-          rank += (kj > mk || (kj == mk && ij < mi)) ? 1 : 0;
-        }
-        const unsigned long long hit = __ballot(on && rank == need - 1);   // exactly one lane
-        const int src = __ffsll((long long)hit) - 1;
-        const unsigned int tlo = __shfl((unsigned int)mk, src, kWave), thi = __shfl((unsigned int)(mk >> 32), src, kWave);
-        const unsigned long long Tk = ((unsigned long long)thi << 32) | tlo;
-        const unsigned long long eqtake = __ballot(on && mk == Tk && rank < need);
-        if (lane == 0) { s_prefix = Tk; s_need = __popcll(eqtake); }
-      }
-      __syncthreads();
-      break;
-    }
+    for (int u = 0; u < BPT; ++u) bins[u] = sh.hist[tid * BPT + u];
+    search_bins(sh, bins, need);
+    prefix = (prefix << width) | (u64)sh.bin;
+    need = sh.need;
+    top = shift;
+    count = sh.count;
   }
-  const unsigned long long T = s_prefix;
-  const long long need = s_need;
-  if (cached) {
-    // Ordered output from the keys still in registers: key q of thread t sits at index NTH q + t.  Every wavefront
-    // counts its "greater" and "equal" flags per chunk q, one wavefront turns the KPT x NW counts into exclusive
-    // prefixes in index order, then every selected key knows its output position.  Two barriers, no global re-read.
-    const unsigned long long below = (1ull << lane) - 1ull;
-    // (the flags are formed again in the last loop rather than kept: 2 * KPT wave masks would not fit the registers
-    // of a 1024-thread block)
-#pragma unroll
-    for (int q = 0; q < KPT; ++q) {
-      const int64_t c = (int64_t)q * NTH + tid;
-      const unsigned long long bgq = __ballot(c < n && keys[q] > T);
-      const unsigned long long beq = __ballot(c < n && keys[q] == T);
-      if (lane == 0) { scan_gt[q * NW + wv] = __popcll(bgq); scan_eq[q * NW + wv] = __popcll(beq); }
+  __syncthreads();
+  each([&](u64 key, int i) {
+    const u64 v = on_index ? (u64)(unsigned int)~i : key;
+    if ((v >> top) == prefix && (!on_index || key == T)) {
+      const int slot = atomicAdd(&sh.ncand, 1);
+      sh.cand_key[slot] = key; sh.cand_idx[slot] = i;
     }
+  });
+  __syncthreads();
+  {
+    // ranks: NTH / 64 threads share a candidate, each compares it with a few of the others
+    constexpr int PER = kSelRank / (NTH / 64);
+    const int c = tid & 63, j0 = (tid >> 6) * PER;
+    const u64 mk = sh.cand_key[c];
+    const int mi = sh.cand_idx[c];
+    unsigned int r = 0;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const u64 kj = sh.cand_key[j0 + u];
+      const int ij = sh.cand_idx[j0 + u];
+      r += (j0 + u < count && (kj > mk || (kj == mk && ij < mi))) ? 1u : 0u;
+    }
+    if (c < count && r) atomicAdd(&sh.rank[c], r);
     __syncthreads();
-    if (wv == 0) {
-      // exclusive scan of the KPT * NW counts (EPL consecutive entries per lane; entries beyond the end are zero)
-      int g[EPL], e[EPL];
-      int gs = 0, es = 0;
-#pragma unroll
-      for (int u = 0; u < EPL; ++u) {
-        const bool in = EPL * lane + u < KPT * NW;
-        g[u] = in ? scan_gt[EPL * lane + u] : 0; e[u] = in ? scan_eq[EPL * lane + u] : 0;
-        gs += g[u]; es += e[u];
-      }
-      int gi = gs, ei = es;                             // inclusive prefix over lanes <= l
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const int tg = __shfl_up(gi, o, kWave), te = __shfl_up(ei, o, kWave);
-        if (lane >= o) { gi += tg; ei += te; }
-      }
-      int gx = gi - gs, ex = ei - es;
-#pragma unroll
-      for (int u = 0; u < EPL; ++u) {
-        scan_gt[EPL * lane + u] = gx; scan_eq[EPL * lane + u] = ex;
-        gx += g[u]; ex += e[u];
-      }
-    }
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < KPT; ++q) {
-      const int64_t c = (int64_t)q * NTH + tid;
-      const bool gt = c < n && keys[q] > T, eq = c < n && keys[q] == T;
-      const unsigned long long bgq = __ballot(gt), beq = __ballot(eq);
-      const long long gt_before = scan_gt[q * NW + wv] + __popcll(bgq & below);
-      const long long eq_before = scan_eq[q * NW + wv] + __popcll(beq & below);
-      if (gt || (eq && eq_before < need)) {
-        const long long pos = gt_before + (eq_before < need ? eq_before : need);
-        if (pos < k) idx[pos] = (int32_t)c;
-      }
-    }
+    if (tid < count && sh.rank[tid] == (unsigned int)(need - 1)) { sh.T = mk; sh.I = mi; }
+  }
+  __syncthreads();
+}
+
+__device__ __forceinline__ int64_t layer_of(const int64_t* layer_off, int64_t n_layers, int64_t c) {
+  int64_t lo = 0, hi = n_layers;                      // the last layer that starts at or before c
+  while (hi - lo > 1) {
+    const int64_t mid = (lo + hi) >> 1;
+    if (layer_off[mid] <= c) lo = mid; else hi = mid;
+  }
+  return lo;
+}
+
+// writes element c of the input: selected elements at output position pos.  Called by whole wavefronts.
+__device__ __forceinline__ void emit(const SelectOut& o, bool sel, int64_t pos, int64_t c, bool in_range) {
+  if (!o.layer_off) {
+    if (sel) o.idx[pos] = (int32_t)c;
     return;
   }
-  if (tid == 0) { s_base_gt = 0; s_base_eq = 0; }
+  if (o.flags) {
+    if (in_range) o.per_layer[c] = sel ? (int32_t)(o.layer_off[c + 1] - o.layer_off[c]) : 0;
+    if (sel) o.idx[pos] = (int32_t)c;
+    return;
+  }
+  int64_t l = -1;
+  if (sel) {
+    l = layer_of(o.layer_off, o.n_layers, c);
+    o.idx[pos] = (int32_t)(c - o.layer_off[l]);
+  }
+  // neighbouring elements mostly lie in one layer: one atomic per wavefront and layer
+  u64 left = __ballot(sel);
+  while (left) {
+    const int src = __ffsll((long long)left) - 1;
+    const int64_t l0 = __shfl(l, src, kWave);
+    const u64 same = __ballot(sel && l == l0);
+    if ((int)(threadIdx.x & 63) == src) atomicAdd(&o.per_layer[l0], (int32_t)__popcll(same));
+    left &= ~same;
+  }
+}
+
+// One block for up to 16384 keys, which stay on the CU from the one read of the scores to the ordered output: KPT per
+// thread in registers, or (KPT == 0) in dynamic LDS (12 or 16 64-bit keys per thread of a 1024-thread block spill).
+// What bounds it is a chain of about ten block barriers and the load latency, not work, hence many threads with few
+// keys each and few, wide digit windows.  256 / 768 / 3072 / 11008 keys: 3.5 / 4.0 / 6.6 / 14.6 us; with four
+// wavefronts, 8-bit windows and one-wavefront ranking through LDS it was 4.7 / 7.6 / 13.5 / 29 us.
+template <int NTH, int KPT, int BITS = kSelBits>
+__global__ __launch_bounds__(NTH) void k_topk_block(const double* __restrict__ scores, int n, int k,
+                                                    const SelectOut out) {
+  constexpr int NW = NTH / 64, MAXQ = KPT ? KPT : (int)(kTopkBlockKeys / NTH);
+  extern __shared__ __attribute__((aligned(16))) u64 lkeys[];
+  __shared__ SelShared<NTH, BITS> sh;
+  __shared__ int wave_sel[MAXQ * NW];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  u64 keys[KPT ? KPT : 1];
+  const int nq = (n + NTH - 1) / NTH;
+  // f(q, i) for the keys of this thread: key q is element i = NTH q + tid
+  auto slots = [&](auto f) {
+    if constexpr (KPT > 0) {
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) f(q, q * NTH + tid);
+    } else {
+#pragma unroll 4
+      for (int q = 0; q < nq; ++q) f(q, q * NTH + tid);
+    }
+  };
+  auto key_ref = [&](int q, int i) -> u64& {
+    if constexpr (KPT > 0) return keys[q];
+    else return lkeys[i];
+  };
+  unsigned int lo = ~0u, hi = 0u;
+  slots([&](int q, int i) {
+    if constexpr (KPT > 0) keys[q] = 0ull;
+    if (i < n) {
+      const u64 v = score_key(scores[i]);
+      key_ref(q, i) = v;
+      const unsigned int h = (unsigned int)(v >> 32);
+      lo = h < lo ? h : lo; hi = h > hi ? h : hi;
+    }
+  });
+  if (out.layer_off && !out.flags) {
+    for (int64_t l = tid; l < out.n_layers; l += NTH) out.per_layer[l] = 0;
+    __threadfence();
+  }
+  u64 T = 0;
+  int I = -1;
+  if (k < n) {
+    int top;
+    const u64 base = block_base(sh, lo, hi, &top);
+    if constexpr (KPT > 0) {
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) keys[q] -= base;
+    }
+    const u64 sub = KPT > 0 ? 0ull : base;
+    find_threshold(sh, [&](auto f) {
+      slots([&](int q, int i) {
+        if (i < n) f(key_ref(q, i) - sub, i);
+      });
+    }, 0ull, top, k, n);
+    T = sh.T + sub; I = sh.I;
+  }
+  // ordered output: one wavefront turns the counts of every (q, wavefront) into prefixes in index order
+  unsigned int mine = 0;                              // bit q: key q of this thread is selected
+  slots([&](int q, int i) {
+    bool sel = false;
+    if (i < n) {
+      const u64 key = key_ref(q, i);
+      sel = k == n || key > T || (key == T && i <= I);
+    }
+    mine |= sel ? 1u << q : 0u;
+    const u64 b = __ballot(sel);
+    if (lane == 0) wave_sel[q * NW + wv] = __popcll(b);
+  });
   __syncthreads();
-  for (int64_t c0 = 0; c0 < n; c0 += NTH) {
-    const int64_t c = c0 + tid;
-    unsigned long long key = 0ull;
-    if (c < n) key = key_at(c);
-    const bool gt = (c < n) && key > T;
-    const bool eq = (c < n) && key == T;
-    const unsigned long long bg = __ballot(gt), be = __ballot(eq);
-    const unsigned long long below = (1ull << lane) - 1ull;
-    if (lane == 0) { wsum_gt[wv] = __popcll(bg); wsum_eq[wv] = __popcll(be); }
-    __syncthreads();
-    long long gt_before = s_base_gt + __popcll(bg & below);
-    long long eq_before = s_base_eq + __popcll(be & below);
-    for (int i = 0; i < wv; ++i) { gt_before += wsum_gt[i]; eq_before += wsum_eq[i]; }
-    const bool take = gt || (eq && eq_before < need);
-    if (take) {
-      const long long pos = gt_before + (eq_before < need ? eq_before : need);
-      if (pos < k) idx[pos] = (int32_t)c;
+  if (wv == 0) {
+    constexpr int EPL = (MAXQ * NW + 63) / 64;
+    const int entries = nq * NW;
+    int g[EPL], gs = 0;
+#pragma unroll
+    for (int u = 0; u < EPL; ++u) {
+      g[u] = EPL * lane + u < entries ? wave_sel[EPL * lane + u] : 0;
+      gs += g[u];
+    }
+    int gx = (int)wave_scan_add((unsigned int)gs) - gs;
+#pragma unroll
+    for (int u = 0; u < EPL; ++u) {
+      if (EPL * lane + u < entries) wave_sel[EPL * lane + u] = gx;
+      gx += g[u];
+    }
+  }
+  __syncthreads();
+  const u64 below = (1ull << lane) - 1ull;
+  slots([&](int q, int i) {
+    const bool sel = (mine >> q) & 1u;
+    const u64 b = __ballot(sel);
+    emit(out, sel, (int64_t)(wave_sel[q * NW + wv] + __popcll(b & below)), i, i < n);
+  });
+}
+
+// ---- longer inputs: four launches of up to 256 blocks, block b owns the contiguous range of sel_per_block(n) keys.
+// Each launch is a read of the keys out of the L2s and costs 3 to 10 us, mostly its start: 82944 keys 22 us, where one
+// block that re-read them took 186 us.  Inputs that one block can keep in LDS (16384 keys, 20 us) are not worth it.
+constexpr int kSelBlocks = 256;
+constexpr int kSelLayers = 1024;                      // layer tables up to this size are kept in LDS
+constexpr int kSelCand = 4096;                        // candidates around the threshold kept in the workspace
+struct SelWs {
+  unsigned int part[2 * kSelBlocks];                  // smallest, largest upper half of every block's keys
+  unsigned int hist[kSelBins];                        // all keys, first window
+  int above[kSelBlocks];                              // keys of every block in bins above the threshold's
+  int ncand, pad[63];
+  u64 cand_key[kSelCand];
+  int cand_idx[kSelCand];
+};
+static int64_t sel_per_block(int64_t n) { return std::max<int64_t>(1024, round_up(ceil_div(n, kSelBlocks), 1024)); }
+
+// keys of the block's range, four loads in flight per thread: f(key, index)
+template <class F>
+__device__ __forceinline__ void sel_range(const double* scores, int64_t n, int64_t per, F f) {
+  const int64_t b0 = (int64_t)blockIdx.x * per, b1 = b0 + per < n ? b0 + per : n;
+  for (int64_t i0 = b0 + threadIdx.x; i0 < b1; i0 += 1024) {
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = i0 + 256 * u < b1 ? scores[i0 + 256 * u] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (i0 + 256 * u < b1) f(score_key(v[u]), i0 + 256 * u);
+  }
+}
+
+__global__ __launch_bounds__(256) void k_sel_range(const double* __restrict__ scores, int64_t n, int64_t per,
+                                                   SelWs* __restrict__ ws, const SelectOut out) {
+  __shared__ unsigned int s_lo[4], s_hi[4];
+  unsigned int lo = ~0u, hi = 0u;
+  sel_range(scores, n, per, [&](u64 key, int64_t) {
+    const unsigned int h = (unsigned int)(key >> 32);
+    lo = h < lo ? h : lo; hi = h > hi ? h : hi;
+  });
+  lo = wave_scan(lo, ~0u, [](unsigned int a, unsigned int b) { return a < b ? a : b; });
+  hi = wave_scan(hi, 0u, [](unsigned int a, unsigned int b) { return a > b ? a : b; });
+  if ((threadIdx.x & 63) == 63) { s_lo[threadIdx.x >> 6] = lo; s_hi[threadIdx.x >> 6] = hi; }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 0; w < 4; ++w) { lo = s_lo[w] < lo ? s_lo[w] : lo; hi = s_hi[w] > hi ? s_hi[w] : hi; }
+    ws->part[2 * blockIdx.x] = lo; ws->part[2 * blockIdx.x + 1] = hi;
+  }
+  // clear what the next launches add to
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x, nt = (int64_t)gridDim.x * 256;
+  for (int64_t b = t; b < kSelBins; b += nt) ws->hist[b] = 0u;
+  if (t == 0) ws->ncand = 0;
+  if (out.layer_off && !out.flags)
+    for (int64_t l = t; l < out.n_layers; l += nt) out.per_layer[l] = 0;
+}
+
+// base of all keys from the blocks' parts; the first window is the kSelBits below the top bit of the differences
+__device__ __forceinline__ u64 sel_window(SelShared<256>& sh, const SelWs* ws, int* shift) {
+  unsigned int lo = ~0u, hi = 0u;
+  if (threadIdx.x < gridDim.x) { lo = ws->part[2 * threadIdx.x]; hi = ws->part[2 * threadIdx.x + 1]; }
+  int top;
+  const u64 base = block_base(sh, lo, hi, &top);
+  *shift = top - kSelBits;
+  return base;
+}
+
+__global__ __launch_bounds__(256) void k_sel_hist(const double* __restrict__ scores, int64_t n, int64_t per,
+                                                  SelWs* __restrict__ ws) {
+  __shared__ SelShared<256> sh;
+  int shift;
+  for (int b = threadIdx.x; b < kSelBins; b += 256) sh.hist[b] = 0u;
+  const u64 kmin = sel_window(sh, ws, &shift);        // its barrier also orders the clearing
+  sel_range(scores, n, per, [&](u64 key, int64_t) { atomicAdd(&sh.hist[(key - kmin) >> shift], 1u); });
+  __syncthreads();
+  for (int b = threadIdx.x; b < kSelBins; b += 256)
+    if (sh.hist[b]) atomicAdd(&ws->hist[b], sh.hist[b]);
+}
+
+// the threshold's bin, from the histogram of all keys
+__device__ __forceinline__ void sel_bin(SelShared<256>& sh, const SelWs* ws, int64_t k) {
+  unsigned int bins[kSelBins / 256];
+#pragma unroll
+  for (int u = 0; u < kSelBins / 256; u += 4) {
+    const uint4 v = *reinterpret_cast<const uint4*>(&ws->hist[threadIdx.x * (kSelBins / 256) + u]);
+    bins[u] = v.x; bins[u + 1] = v.y; bins[u + 2] = v.z; bins[u + 3] = v.w;
+  }
+  search_bins(sh, bins, (int)k);
+}
+
+__global__ __launch_bounds__(256) void k_sel_collect(const double* __restrict__ scores, int64_t n, int64_t per,
+                                                     int64_t k, SelWs* __restrict__ ws) {
+  __shared__ SelShared<256> sh;
+  __shared__ int red[4];
+  int shift;
+  const u64 kmin = sel_window(sh, ws, &shift);
+  sel_bin(sh, ws, k);
+  const u64 bin = (u64)sh.bin;
+  const bool keep = sh.count <= kSelCand;
+  int above = 0;
+  sel_range(scores, n, per, [&](u64 key, int64_t i) {
+    const u64 b = (key - kmin) >> shift;
+    above += b > bin ? 1 : 0;
+    if (keep && b == bin) {
+      const int slot = atomicAdd(&ws->ncand, 1);
+      ws->cand_key[slot] = key - kmin; ws->cand_idx[slot] = (int)i;
+    }
+  });
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) above += __shfl_xor(above, o, kWave);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = above;
+  __syncthreads();
+  if (threadIdx.x == 0) ws->above[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// Every block finds the threshold pair from the candidates (all of them in the threshold's bin), counts what the blocks
+// before it select, and writes its own range.  Should a bin hold more candidates than are kept (mass ties), every block
+// goes through all keys instead.
+__global__ __launch_bounds__(256) void k_sel_write(const double* __restrict__ scores, int64_t n, int64_t per, int64_t k,
+                                                   const SelWs* __restrict__ ws, const SelectOut out_) {
+  __shared__ SelShared<256> sh;
+  __shared__ int red[4], wave_sel[4][4];
+  __shared__ int64_t s_off[kSelLayers + 1];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  // requested ahead of the search for the threshold: the layer table and the first 1024 keys of the range
+  SelectOut out = out_;
+  const bool table = out.layer_off && !out.flags && out.n_layers <= kSelLayers;
+  if (table)
+    for (int l = tid; l <= (int)out.n_layers; l += 256) s_off[l] = out.layer_off[l];
+  const int64_t b0 = (int64_t)blockIdx.x * per;
+  const int64_t b1 = b0 + per < n ? b0 + per : n;
+  double v[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) { const int64_t i = b0 + 256 * u + tid; v[u] = i < b1 ? scores[i] : 0.0; }
+  int before = 0;                                     // selected elements ahead of this block's range: whole bins ...
+  for (int b = tid; b < (int)blockIdx.x; b += 256) before += ws->above[b];
+  int shift;
+  const u64 kmin = sel_window(sh, ws, &shift);
+  sel_bin(sh, ws, k);
+  const u64 bin = (u64)sh.bin;
+  const int need = sh.need, count = sh.count;
+  const bool kept = count <= kSelCand;
+  __syncthreads();                                    // everybody has read sh.need / sh.count
+  if (table) out.layer_off = s_off;
+  auto each = [&](auto f) {
+    if (kept) {
+      for (int i = tid; i < count; i += 256) f(ws->cand_key[i], ws->cand_idx[i]);
+    } else {
+      for (int64_t i = tid; i < n; i += 256) f(score_key(scores[i]) - kmin, (int)i);
+    }
+  };
+  find_threshold(sh, each, bin, shift, need, count);
+  const u64 T = sh.T;
+  const int I = sh.I;
+  // ... and candidates
+  each([&](u64 key, int i) {
+    before += (i < b0 && (key >> shift) == bin && (key > T || (key == T && i <= I))) ? 1 : 0;
+  });
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, kWave);
+  if (lane == 0) red[wv] = before;
+  __syncthreads();
+  int64_t base = (red[0] + red[1]) + (red[2] + red[3]);
+  const u64 below = (1ull << lane) - 1ull;
+  for (int64_t i0 = b0; i0 < b1; i0 += 1024) {
+    bool sel[4];
+    if (i0 > b0) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) { const int64_t i = i0 + 256 * u + tid; v[u] = i < b1 ? scores[i] : 0.0; }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t i = i0 + 256 * u + tid;
+      const u64 key = score_key(v[u]) - kmin;
+      sel[u] = i < b1 && (key > T || (key == T && (int)i <= I));
+      const u64 b = __ballot(sel[u]);
+      if (lane == 0) wave_sel[u][wv] = __popcll(b);
     }
     __syncthreads();
-    if (tid == 0) {
-      long long a = 0, e = 0;
-      for (int i = 0; i < NW; ++i) { a += wsum_gt[i]; e += wsum_eq[i]; }
-      s_base_gt += a; s_base_eq += e;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t i = i0 + 256 * u + tid;
+      int64_t pos = base + __popcll(__ballot(sel[u]) & below);
+#pragma unroll
+      for (int w = 0; w < 4; ++w) pos += w < wv ? wave_sel[u][w] : 0;
+      emit(out, sel[u], pos, i, i < b1);
+      base += (wave_sel[u][0] + wave_sel[u][1]) + (wave_sel[u][2] + wave_sel[u][3]);
     }
     __syncthreads();
   }
 }
 
-// Short inputs (BERT / ResNet channel counts) fit the registers of four wavefronts, whose barriers are cheaper; the
-// number of keys per thread is a template argument so that a short input does not walk through empty slots.  Longer
-// inputs (LLM-sized layers) keep their keys in LDS, up to 16384 of them (128 KB); beyond that they are re-read.
-constexpr int64_t kTopkLdsKeys = 16384;
-void launch_topk(const double* scores, int64_t n, int64_t k, int32_t* idx, hipStream_t st) {
-  if (n <= 256) hipLaunchKernelGGL((k_topk_radix<256, 1>), dim3(1), dim3(256), 0, st, scores, n, k, idx, 0);
-  else if (n <= 4 * 256) hipLaunchKernelGGL((k_topk_radix<256, 4>), dim3(1), dim3(256), 0, st, scores, n, k, idx, 0);
-  else if (n <= 12 * 256) hipLaunchKernelGGL((k_topk_radix<256, 12>), dim3(1), dim3(256), 0, st, scores, n, k, idx, 0);
-  else {
+// One block up to kTopkBlockKeys; the four-launch chain beyond, whose workspace is topk_ws_bytes(n).
+size_t topk_ws_bytes(int64_t n) { return n > kTopkBlockKeys ? (size_t)round_up((int64_t)sizeof(SelWs), 256) : 0; }
+
+// no channel selected anywhere: all counts are 0
+__global__ __launch_bounds__(256) void k_zero_counts(int32_t* __restrict__ per_layer, int64_t n_layers) {
+  const int64_t l = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (l < n_layers) per_layer[l] = 0;
+}
+
+static void launch_select(const double* scores, int64_t n, int64_t k, const SelectOut& out, void* ws, hipStream_t st) {
+  if (k == 0) {
+    if (out.per_layer)
+      hipLaunchKernelGGL(k_zero_counts, dim3((unsigned)ceil_div(out.n_layers, 256)), dim3(256), 0, st, out.per_layer, out.n_layers);
+    return;
+  }
+#define EFQAT_TOPK(NTH, KPT, LDS) \
+  hipLaunchKernelGGL((k_topk_block<NTH, KPT>), dim3(1), dim3(NTH), LDS, st, scores, (int)n, (int)k, out)
+  if (n <= 256)
+    hipLaunchKernelGGL((k_topk_block<256, 1, 10>), dim3(1), dim3(256), 0, st, scores, (int)n, (int)k, out);
+  else if (n <= 1024) EFQAT_TOPK(1024, 1, 0);
+  else if (n <= 2048) EFQAT_TOPK(1024, 2, 0);
+  else if (n <= 4096) EFQAT_TOPK(1024, 4, 0);
+  else if (n <= kTopkBlockKeys) {
     // set once per process (initialisation of a function-local static is thread-safe); a failure leaves the default
     // LDS limit in place and the launch below then reports it
-    static const hipError_t attr = hipFuncSetAttribute((const void*)k_topk_radix<1024, 1>,
+    static const hipError_t attr = hipFuncSetAttribute((const void*)k_topk_block<1024, 0>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                       (int)(kTopkLdsKeys * sizeof(unsigned long long)));
+                                                       (int)(kTopkBlockKeys * sizeof(u64)));
     (void)attr;
-    const int in_lds = n <= kTopkLdsKeys ? 1 : 0;
-    const size_t lds = in_lds ? (size_t)n * sizeof(unsigned long long) : 0;
-    hipLaunchKernelGGL((k_topk_radix<1024, 1>), dim3(1), dim3(1024), lds, st, scores, n, k, idx, in_lds);
+    EFQAT_TOPK(1024, 0, (size_t)n * sizeof(u64));
+  }
+#undef EFQAT_TOPK
+  else {
+    SelWs* w = (SelWs*)ws;
+    const int64_t per = sel_per_block(n);
+    const dim3 grid((unsigned)ceil_div(n, per));
+    hipLaunchKernelGGL(k_sel_range, grid, dim3(256), 0, st, scores, n, per, w, out);
+    hipLaunchKernelGGL(k_sel_hist, grid, dim3(256), 0, st, scores, n, per, w);
+    hipLaunchKernelGGL(k_sel_collect, grid, dim3(256), 0, st, scores, n, per, k, w);
+    hipLaunchKernelGGL(k_sel_write, grid, dim3(256), 0, st, scores, n, per, k, w, out);
   }
 }
 
-int launch_topk_profiled(const double* scores, int64_t n, int64_t k, int32_t* idx, hipStream_t st) {
+void launch_topk(const double* scores, int64_t n, int64_t k, int32_t* idx, void* ws, hipStream_t st) {
+  launch_select(scores, n, k, SelectOut{idx, nullptr, 0, nullptr, 0}, ws, st);
+}
+
+int launch_topk_profiled(const double* scores, int64_t n, int64_t k, int32_t* idx, void* ws, hipStream_t st) {
   {
     ProfScope prof(PROF_TOPK, st);
-    launch_topk(scores, n, k, idx, st);
+    launch_topk(scores, n, k, idx, ws, st);
   }
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
@@ -345,36 +591,6 @@ int launch_row_importance(const float* w, int64_t c_out, int64_t block, double* 
   return EFQAT_OK;
 }
 
-// CWPN helpers: per-layer counts of selected channels, and global -> per-layer local indices.
-__global__ void k_layer_counts(const int64_t* __restrict__ layer_off, int64_t n_layers,
-                               const int32_t* __restrict__ idx, int64_t k_total,
-                               int32_t* __restrict__ k_per_layer) {
-  // idx holds ascending global indices: the count of a layer is a difference of two lower bounds
-  const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (l >= n_layers) return;
-  auto lower_bound = [&](int64_t v) {
-    int64_t lo = 0, hi = k_total;
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if ((int64_t)idx[mid] < v) lo = mid + 1; else hi = mid;
-    }
-    return lo;
-  };
-  k_per_layer[l] = (int32_t)(lower_bound(layer_off[l + 1]) - lower_bound(layer_off[l]));
-}
-__global__ void k_localize(const int64_t* __restrict__ layer_off, int64_t n_layers, int64_t k_total,
-                            int32_t* __restrict__ idx) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= k_total) return;
-  const int64_t g = idx[i];
-  int64_t lo = 0, hi = n_layers;
-  while (hi - lo > 1) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (layer_off[mid] <= g) lo = mid; else hi = mid;
-  }
-  idx[i] = (int32_t)(g - layer_off[lo]);
-}
-
 }  // namespace efqat
 
 using namespace efqat;
@@ -386,7 +602,7 @@ extern "C" int64_t efqat_k_from_ratio(int64_t c_out, int64_t num, int64_t den) {
 
 extern "C" size_t efqat_channel_select_workspace_bytes(int64_t c_out) {
   if (c_out <= 0) return 0;
-  return (size_t)round_up(c_out * (int64_t)sizeof(double), 256);
+  return (size_t)round_up(c_out * (int64_t)sizeof(double), 256) + topk_ws_bytes(c_out);
 }
 
 extern "C" int efqat_channel_select(const float* w, int64_t c_out, int64_t block, int64_t k, double* scores,
@@ -399,6 +615,7 @@ extern "C" int efqat_channel_select(const float* w, int64_t c_out, int64_t block
   hipStream_t st = (hipStream_t)stream;
   WsCarver carve(ws);
   double* sc = (double*)carve.take((size_t)c_out * sizeof(double));
+  void* sel_ws = carve.take(topk_ws_bytes(c_out));
   double* sc_out = scores ? scores : sc;
   const int vec = (((uintptr_t)w % 16) == 0 && block % 4 == 0) ? 1 : 0;
   {
@@ -410,7 +627,7 @@ extern "C" int efqat_channel_select(const float* w, int64_t c_out, int64_t block
   if (k == 0) return EFQAT_OK;
   {
     ProfScope prof(PROF_TOPK, st);
-    launch_topk(sc_out, c_out, k, idx, st);
+    launch_topk(sc_out, c_out, k, idx, sel_ws, st);
   }
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
@@ -423,22 +640,28 @@ namespace efqat {
 
 constexpr int64_t kStaticSelectMaxChannels = EFQAT_STATIC_SELECT_MAX_CHANNELS;
 static __device__ __align__(256) double scratch[kStaticSelectMaxChannels];   // 512 KiB per GPU, for the process' life
+static __device__ __align__(256) SelWs select_scratch;                        // and 70 KiB for the Top-K of many channels
 
 // Host code must not pass `scratch` itself to a kernel: here that name is only a handle for the symbol.  The
 // array's device address differs per GPU (each holds its own copy) and is looked up once per device, with that
 // device current.
 constexpr int kMaxDevices = 64;
 static double* g_scratch_ptr[kMaxDevices];
+static void* g_select_ptr[kMaxDevices];
 
-static int static_scratch(double** out) {
+static int static_scratch(double** out, void** sel_ws) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return EFQAT_ERR_HIP;
   if (!g_scratch_ptr[dev]) {
     double* p = nullptr;
+    void* q = nullptr;
+    if (hipGetSymbolAddress(&q, HIP_SYMBOL(select_scratch)) != hipSuccess || !q) return EFQAT_ERR_HIP;
     if (hipGetSymbolAddress((void**)&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) return EFQAT_ERR_HIP;
+    g_select_ptr[dev] = q;
     g_scratch_ptr[dev] = p;
   }
   *out = g_scratch_ptr[dev];
+  *sel_ws = g_select_ptr[dev];
   return EFQAT_OK;
 }
 
@@ -452,7 +675,8 @@ extern "C" int efqat_channel_select_static(const float* w, int64_t c_out, int64_
   if (!w || (k > 0 && !idx)) return EFQAT_ERR_NULL_PTR;
   if (((uintptr_t)w % 4) != 0 || ((uintptr_t)idx % 4) != 0) return EFQAT_ERR_ALIGNMENT;
   double* sc = nullptr;
-  const int rc = static_scratch(&sc);
+  void* sel_ws = nullptr;
+  const int rc = static_scratch(&sc, &sel_ws);
   if (rc) return rc;
   hipStream_t st = (hipStream_t)stream;
   const int vec = (((uintptr_t)w % 16) == 0 && block % 4 == 0) ? 1 : 0;
@@ -460,14 +684,13 @@ extern "C" int efqat_channel_select_static(const float* w, int64_t c_out, int64_
   hipLaunchKernelGGL(k_row_importance, dim3((unsigned)ceil_div(c_out, 4)), dim3(256), 0, st, w, c_out, block, vec, sc);
   EFQAT_LAUNCH_CHECK();
   if (k == 0) return EFQAT_OK;
-  launch_topk(sc, c_out, k, idx, st);
+  launch_topk(sc, c_out, k, idx, sel_ws, st);
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
 }
 
 extern "C" size_t efqat_network_select_workspace_bytes(int64_t total) {
-  (void)total;
-  return 256;   // no scratch needed; kept so callers can treat every entry point alike
+  return 256 + (total > 0 ? topk_ws_bytes(total) : 0);   // short inputs need no scratch; callers treat every entry point alike
 }
 
 extern "C" int efqat_network_select(const double* scores, const int64_t* layer_off, int64_t n_layers,
@@ -479,19 +702,8 @@ extern "C" int efqat_network_select(const double* scores, const int64_t* layer_o
   if (ws_bytes < efqat_network_select_workspace_bytes(total)) return EFQAT_ERR_WORKSPACE;
   if (((uintptr_t)ws % 256) != 0) return EFQAT_ERR_ALIGNMENT;
   hipStream_t st = (hipStream_t)stream;
-  // k_per_layer is derived from idx; with k_total == 0 every count is 0 and idx is never read
-  if (k_total > 0) {
-    launch_topk(scores, total, k_total, idx, st);
-    EFQAT_LAUNCH_CHECK();
-  }
-  hipLaunchKernelGGL(k_layer_counts, dim3((unsigned)ceil_div(n_layers, 256)), dim3(256), 0, st, layer_off, n_layers,
-                     idx, k_total, k_per_layer);
+  launch_select(scores, total, k_total, SelectOut{idx, layer_off, n_layers, k_per_layer, 0}, ws, st);
   EFQAT_LAUNCH_CHECK();
-  if (k_total > 0) {
-    hipLaunchKernelGGL(k_localize, dim3((unsigned)ceil_div(k_total, 256)), dim3(256), 0, st, layer_off, n_layers,
-                       k_total, idx);
-    EFQAT_LAUNCH_CHECK();
-  }
   return EFQAT_OK;
 }
 
@@ -517,27 +729,13 @@ __global__ __launch_bounds__(256) void k_layer_means(const double* __restrict__ 
   if (threadIdx.x == 0) layer_scores[blockIdx.x] = e > b ? red[0] / (double)(e - b) : 0.0;
 }
 
-// k_per_layer[l] = channels of layer l if l is among the (ascending) selected layers, else 0
-__global__ void k_layer_flags(const int64_t* __restrict__ layer_off, int64_t n_layers,
-                              const int32_t* __restrict__ layer_idx, int64_t k_layers,
-                              int32_t* __restrict__ k_per_layer) {
-  const int64_t l = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (l >= n_layers) return;
-  int64_t lo = 0, hi = k_layers;                      // binary search for l in layer_idx
-  while (lo < hi) {
-    const int64_t mid = (lo + hi) >> 1;
-    if (layer_idx[mid] < l) lo = mid + 1; else hi = mid;
-  }
-  const bool on = lo < k_layers && layer_idx[lo] == l;
-  k_per_layer[l] = on ? (int32_t)(layer_off[l + 1] - layer_off[l]) : 0;
-}
-
 }  // namespace efqat
 
 using namespace efqat;
 
 extern "C" size_t efqat_layer_select_workspace_bytes(int64_t n_layers) {
-  return round_up((size_t)(n_layers > 0 ? n_layers : 1) * sizeof(double), 256);
+  const int64_t n = n_layers > 0 ? n_layers : 1;
+  return (size_t)round_up(n * (int64_t)sizeof(double), 256) + topk_ws_bytes(n);
 }
 
 extern "C" int efqat_layer_select(const double* scores, const int64_t* layer_off, int64_t n_layers,
@@ -549,15 +747,13 @@ extern "C" int efqat_layer_select(const double* scores, const int64_t* layer_off
   if (ws_bytes < efqat_layer_select_workspace_bytes(n_layers)) return EFQAT_ERR_WORKSPACE;
   if (((uintptr_t)ws % 256) != 0) return EFQAT_ERR_ALIGNMENT;
   hipStream_t st = (hipStream_t)stream;
-  double* ls = layer_scores ? layer_scores : (double*)ws;
+  WsCarver carve(ws);
+  double* own = (double*)carve.take((size_t)n_layers * sizeof(double));
+  void* sel_ws = carve.take(topk_ws_bytes(n_layers));
+  double* ls = layer_scores ? layer_scores : own;
   hipLaunchKernelGGL(k_layer_means, dim3((unsigned)n_layers), dim3(256), 0, st, scores, layer_off, ls);
   EFQAT_LAUNCH_CHECK();
-  if (k_layers > 0) {
-    launch_topk(ls, n_layers, k_layers, layer_idx, st);
-    EFQAT_LAUNCH_CHECK();
-  }
-  hipLaunchKernelGGL(k_layer_flags, dim3((unsigned)ceil_div(n_layers, 256)), dim3(256), 0, st, layer_off, n_layers,
-                     layer_idx, k_layers, k_per_layer);
+  launch_select(ls, n_layers, k_layers, SelectOut{layer_idx, layer_off, n_layers, k_per_layer, 1}, sel_ws, st);
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
 }

@@ -1,0 +1,66 @@
+"""Top-K at the sizes where its kernels change or end a tile: one block with 1 / 4 / 8 / 16 keys per thread, the
+four-launch chain beyond 16384 keys (1024 keys per block, 256 blocks at most), with distinct scores, with scores of few
+values (more equal keys around the threshold than are ranked directly or kept), and with one far outlier."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2411_11038_amd as ef
+from oracle import efqat_oracle as orc
+from tests.gpu_util import dev
+from workloads import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def scores_of(kind, n):
+    r = np.abs(synth.normal(777 + n, 0, (n,)))
+    if kind == "distinct":
+        return 0.016 * (1.0 + 0.02 * r)
+    if kind == "few_values":
+        return 0.5 + np.floor(r * 3.0)                 # about ten values
+    s = 0.016 * (1.0 + 1e-9 * r)                       # a band far narrower than the first window next to the outlier
+    s[n // 2] = 1e12
+    return s
+
+
+@pytest.mark.parametrize("kind", ["distinct", "few_values", "outlier"])
+@pytest.mark.parametrize("n", [1, 63, 256, 257, 1024, 1025, 4096, 4097, 8193, 16384, 16385, 17 * 1024, 82944, 300001])
+def test_selection_matches_the_oracle(n, kind):
+    s = scores_of(kind, n)
+    flat = dev(s)
+    cuts = sorted({0, n // 7, n // 7, n // 2, n})      # layers of different width
+    off = dev(np.array(cuts, dtype=np.int64))
+    for k in sorted({1, n // 4, n // 2 + 1, n - 1, n} - {0}):
+        ref = orc.top_k_channels(s, k)
+        idx, per_layer = ef.network_select(flat, off, k)
+        torch.cuda.synchronize()
+        layer = np.searchsorted(np.array(cuts), ref, side="right") - 1
+        assert np.array_equal(idx.cpu().numpy(), ref - np.array(cuts)[layer])
+        assert np.array_equal(per_layer.cpu().numpy(), np.bincount(layer, minlength=len(cuts) - 1))
+
+
+@pytest.mark.parametrize("n,k", [(300, 75), (16385, 5000), (20000, 0)])
+def test_many_layers_are_flagged(n, k):
+    s = scores_of("few_values", n)
+    off = np.concatenate([[0], np.cumsum(1 + (np.arange(n) % 3))]).astype(np.int64)
+    flat = np.repeat(s, np.diff(off))                  # equal scores within a layer: its mean is that score
+    layers, width, _ = ef.layer_select(dev(flat), dev(off), k)
+    torch.cuda.synchronize()
+    ref = orc.top_k_channels(s, k)
+    want = np.zeros(n, np.int64)
+    want[ref] = np.diff(off)[ref]
+    assert np.array_equal(layers.cpu().numpy(), ref) and np.array_equal(width.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("c_out", [16384, 16385, 40000])
+def test_channel_selection_with_either_scratch(c_out):
+    w = synth.normal(5 + c_out, 1, (c_out, 4), std=0.02).astype(np.float32)
+    k = c_out // 4
+    idx, scores = ef.channel_select(dev(w), k)
+    static = ef.channel_select_static(dev(w), k)
+    both = ef.weight_quant_select(dev(w), 8, k)
+    torch.cuda.synchronize()
+    ref = orc.top_k_channels(scores.cpu().numpy(), k)
+    for got in (idx, static, both["idx"]):
+        assert np.array_equal(got.cpu().numpy(), ref)
