@@ -3,7 +3,115 @@
 // once per output element in the epilogue.
 #include "common.hpp"
 
+#include <type_traits>
+
 namespace efqat {
+
+typedef int intx4_t __attribute__((ext_vector_type(4)));
+
+// The product for few tokens (decoding, short batches): a pass over the weight codes, HBM bound.  No tile of 64 or more
+// columns fills the chip at such sizes, and every byte of W is used once, so nothing is staged: a block takes 16 NT
+// weight rows, its 8 wavefronts split K, every lane loads its 16-byte MFMA fragments straight from memory (16 rows x 64
+// contiguous bytes per load, v_mfma_i32_16x16x64_i8) with a batch of loads in flight, and the int32 sums meet in LDS.
+// sum_k w, which the zero point needs, is taken from the same fragments.  Rows of any length and alignment.
+// One launch of 1 / 16 / 32 / 64 tokens, 4096 -> 11008 (45 MB of weight codes): 10 / 14 / 19 / 21 us; with 128 x 128
+// tiles on 86 CUs after a pass for the row sums it was 40 - 42 us.  NT = 1 spreads the rows over most blocks and wins at
+// up to 32 tokens (11008 -> 4096, 16 tokens: 13 us, NT = 2 18 us, NT = 4 28 us); at 64 tokens the token fragments are the
+// larger part of the loads, so NT = 4 shares them among more rows where that still leaves a block for most CUs (21 us,
+// NT = 1 30 us; 11008 -> 4096, too few rows for that: 44 us, NT = 1 28 us).
+constexpr int kSkinnyWaves = 8;
+template <int MT, int NT, int BATCH>
+__global__ __launch_bounds__(64 * kSkinnyWaves) void k_fwd_skinny(
+    const uint8_t* __restrict__ x, const int8_t* __restrict__ w, int T, int c_out, int K, const float* __restrict__ s_x,
+    const float* __restrict__ z_x, const float* __restrict__ s_w, void* __restrict__ y, int y_dtype) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int NW = kSkinnyWaves, COLS = 16 * NT;
+  __shared__ int red[NW][MT * NT * 4][64];
+  __shared__ int red_w[NW][COLS];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, kg = lane >> 4;
+  const int n0 = (int)blockIdx.x * COLS;
+  const int steps = (K + 63) / 64, per = (steps + NW - 1) / NW;
+  const int s_end = (wave + 1) * per < steps ? (wave + 1) * per : steps;
+  const uint8_t* xp[MT];
+  const uint8_t* wp[NT];
+#pragma unroll
+  for (int i = 0; i < MT; ++i) xp[i] = x + (int64_t)(16 * i + l16 < T ? 16 * i + l16 : T - 1) * K;
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+    wp[j] = (const uint8_t*)w + (int64_t)(n0 + 16 * j + l16 < c_out ? n0 + 16 * j + l16 : c_out - 1) * K;
+  // 16 bytes of a row from column k on, zeros past the end of the row
+  auto load16 = [&](const uint8_t* row, int k) {
+    intx4_t v = {0, 0, 0, 0};
+    if (k + 16 <= K) __builtin_memcpy(&v, row + k, 16);
+    else if (k < K) {
+#pragma unroll
+      for (int b = 0; b < 15; ++b)
+        if (k + b < K) v[b >> 2] |= (int)((unsigned)row[k + b] << (8 * (b & 3)));
+    }
+    return v;
+  };
+  intx4_t acc[MT][NT];
+  int wsum[NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    wsum[j] = 0;
+#pragma unroll
+    for (int i = 0; i < MT; ++i) acc[i][j] = (intx4_t){0, 0, 0, 0};
+  }
+  for (int s0 = wave * per; s0 < s_end; s0 += BATCH) {
+    intx4_t a[BATCH][MT], b[BATCH][NT];
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      const int k = s0 + u < s_end ? (s0 + u) * 64 + kg * 16 : K;   // past the slice: zeros
+#pragma unroll
+      for (int j = 0; j < NT; ++j) b[u][j] = load16(wp[j], k);
+#pragma unroll
+      for (int i = 0; i < MT; ++i) a[u][i] = load16(xp[i], k);
+    }
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i) a[u][i] ^= (int)0x80808080;      // unsigned codes - 128
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) wsum[j] = __builtin_amdgcn_sdot4(b[u][j][q], 0x01010101, wsum[j], false);
+#pragma unroll
+        for (int i = 0; i < MT; ++i) acc[i][j] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[u][i], b[u][j], acc[i][j], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    wsum[j] += __shfl_xor(wsum[j], 16, kWave);
+    wsum[j] += __shfl_xor(wsum[j], 32, kWave);
+    if (kg == 0) red_w[wave][16 * j + l16] = wsum[j];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave][(i * NT + j) * 4 + r][lane] = acc[i][j][r];
+  }
+  __syncthreads();
+  const float sx = s_x[0];
+  const long long zc = 128 - (long long)rintf(z_x[0]);
+  // accumulator layout: column lane & 15, rows 4 (lane / 16) + r
+  for (int o = tid; o < MT * NT * 4 * 64; o += 64 * NW) {
+    const int ln = o & 63, q = o >> 6, r = q & 3, j = (q >> 2) % NT, i = (q >> 2) / NT;
+    const int col = 16 * j + (ln & 15), m = 16 * i + 4 * (ln >> 4) + r;
+    long long sum = 0, ws = 0;
+#pragma unroll
+    for (int v = 0; v < NW; ++v) { sum += red[v][q][ln]; ws += red_w[v][col]; }
+    if (m < T && n0 + col < c_out) {
+      const float out = sx * s_w[n0 + col] * (float)(sum + zc * ws);
+      const int64_t e = (int64_t)m * c_out + n0 + col;
+      if (y_dtype == EFQAT_F32) ((float*)y)[e] = out;
+      else ((bf16_t*)y)[e] = f32_to_bf16(out);
+    }
+  }
+#endif
+}
 
 // wsum[c] = sum_i w_codes[c][i]  (exact, int32).  One wavefront per output channel.
 __global__ __launch_bounds__(256) void k_row_sum_i8(const int8_t* __restrict__ w, int64_t rows, int64_t cols,
@@ -38,6 +146,8 @@ __global__ __launch_bounds__(256) void k_pad_rows_u8(const uint8_t* __restrict__
     out[e] = j < cols ? in[r * cols + j] : (uint8_t)0;
   }
 }
+
+constexpr int64_t kSkinnyTokens = 64;
 
 struct FwdPlan {
   int64_t ldk;       // C_in rounded up to 16
@@ -83,6 +193,19 @@ extern "C" int efqat_linear_fwd(const uint8_t* x_codes, const float* s_x, const 
   // the tile loads are 16-byte vectors when the codes are used in place
   if (!p.pad && ((((uintptr_t)x_codes) % 16) != 0 || (((uintptr_t)w_codes) % 16) != 0)) return EFQAT_ERR_ALIGNMENT;
   hipStream_t st = (hipStream_t)stream;
+  if (T <= kSkinnyTokens) {
+    ProfScope prof(PROF_FWD, st);
+#define EFQAT_SKINNY(MT, NT, BATCH)                                                                                  \
+  hipLaunchKernelGGL((k_fwd_skinny<MT, NT, BATCH>), dim3((unsigned)ceil_div(c_out, 16 * NT)), dim3(64 * kSkinnyWaves), 0, \
+                     st, x_codes, w_codes, (int)T, (int)c_out, (int)c_in, s_x, z_x, s_w, y, y_dtype)
+    if (T <= 16) EFQAT_SKINNY(1, 1, 4);
+    else if (T <= 32) EFQAT_SKINNY(2, 1, 4);
+    else if (c_out >= 8192) EFQAT_SKINNY(4, 4, 1);
+    else EFQAT_SKINNY(4, 1, 2);
+#undef EFQAT_SKINNY
+    EFQAT_LAUNCH_CHECK();
+    return EFQAT_OK;
+  }
   WsCarver cv(ws);
   int32_t* wsum = (int32_t*)cv.take(p.b_wsum);
   uint8_t* xpad = (uint8_t*)cv.take(p.b_xpad);

@@ -1,0 +1,27 @@
+"""Int8 forward product at the token counts where its kernel changes (16, 32, 64 and beyond) and at row lengths that end
+inside a 16-byte fragment, a 64-byte step or a wavefront's slice of K, against exact integer arithmetic."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2411_11038_amd as ef
+from tests.gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("c_in,c_out", [(1, 1), (15, 17), (64, 16), (65, 100), (511, 33), (512, 64), (1003, 515), (4096, 48),
+                                        (96, 8192), (100, 8209)])
+@pytest.mark.parametrize("T", [1, 16, 17, 32, 33, 64, 65])
+def test_forward_matches_integer_arithmetic(T, c_in, c_out):
+    r = np.random.default_rng(1000 * T + c_in)
+    x = r.integers(0, 256, (T, c_in)).astype(np.uint8)
+    w = r.integers(-127, 128, (c_out, c_in)).astype(np.int8)
+    sx, z = np.float32(0.013), np.float32(117.0)
+    sw = (r.random(c_out) * 0.01 + 0.001).astype(np.float32)
+    got = ef.linear_fwd(dev(x), dev(np.array([sx])), dev(np.array([z])), dev(w), dev(sw), y_dtype=torch.float32)
+    torch.cuda.synchronize()
+    sums = (x.astype(np.int64) - 117) @ w.astype(np.int64).T
+    ref = sums.astype(np.float32) * (sx * sw)[None, :]            # two fp32 roundings, in this order
+    # the sums are exact integers: only the roundings of the scale product and of the result are left (2^-24 each)
+    assert np.abs(got.cpu().numpy() - ref).max() <= 2.0 ** -22 * np.abs(ref).max()
