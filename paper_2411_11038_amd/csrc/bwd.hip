@@ -52,20 +52,17 @@ struct TransposeExtra {
   ConvGeom g;
 };
 
+typedef bf16_t TransposeTile[64][66];                  // tile[i][j] of a block
+
+// tile (bx, by) of tap `tap`
 template <typename T>
-__global__ __launch_bounds__(256) void k_transpose_bf16(const T* __restrict__ in, int64_t ld_in, int64_t R,
-                                                        int64_t Cn, const int32_t* __restrict__ colmap,
-                                                        const float* __restrict__ rowscale,
-                                                        const float* __restrict__ subz, bf16_t* __restrict__ out,
-                                                        int64_t ldo, int64_t out_off, int64_t i_pad, int vec,
-                                                        uint32_t* __restrict__ zero_page, const TransposeExtra ex) {
-  __shared__ bf16_t tile[64][66];                     // tile[i][j]
-  // optional by-product: 256 bytes of zeros for a later kernel of the same call (saves a launch)
-  if (zero_page && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x < 64)
-    zero_page[threadIdx.x] = 0u;
-  const int64_t i0 = (int64_t)blockIdx.x * 64, j0 = (int64_t)blockIdx.y * 64;
+__device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int by, int tap, const T* __restrict__ in,
+                                                int64_t ld_in, int64_t R, int64_t Cn, const int32_t* __restrict__ colmap,
+                                                const float* __restrict__ rowscale, const float* __restrict__ subz,
+                                                bf16_t* __restrict__ out, int64_t ldo, int64_t out_off, int64_t i_pad,
+                                                int vec, const TransposeExtra& ex) {
+  const int64_t i0 = (int64_t)bx * 64, j0 = (int64_t)by * 64;
   const float sub = subz ? rintf(subz[0]) : 0.0f;
-  const int tap = blockIdx.z;
   in += (int64_t)tap * ex.z_in;
   out += (int64_t)tap * ex.z_out + (int64_t)tap * ex.z_orow * ldo;
   // source row of logical row i, or -1: contributes zeros
@@ -132,22 +129,58 @@ __global__ __launch_bounds__(256) void k_transpose_bf16(const T* __restrict__ in
   }
 }
 
-// Row-wise cast/copy to bf16 with zero-padded pitch: out[m][j] = bf16(in[rm(m)][j]), j < Cn; 0 up to ldo.
+// zero_page: optional by-product, 256 zero bytes
+template <typename T>
+__global__ __launch_bounds__(256) void k_transpose_bf16(const T* __restrict__ in, int64_t ld_in, int64_t R,
+                                                        int64_t Cn, const int32_t* __restrict__ colmap,
+                                                        const float* __restrict__ rowscale,
+                                                        const float* __restrict__ subz, bf16_t* __restrict__ out,
+                                                        int64_t ldo, int64_t out_off, int64_t i_pad, int vec,
+                                                        uint32_t* __restrict__ zero_page, const TransposeExtra ex) {
+  __shared__ TransposeTile tile;
+  if (zero_page && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x < 64)
+    zero_page[threadIdx.x] = 0u;
+  transpose_block<T>(tile, blockIdx.x, blockIdx.y, blockIdx.z, in, ld_in, R, Cn, colmap, rowscale, subz, out, ldo,
+                     out_off, i_pad, vec, ex);
+}
+
+// Row-wise cast/copy to bf16 with zero-padded pitch: out[m][j] = bf16(in[rm(m)][j]), j < Cn; 0 up to ldo (a multiple of
+// 8).  flat: no padding, no row map and 16-byte aligned rows, i.e. one run of 8-element chunks; else a wavefront per row,
+// two elements per lane and step.  block b of nb.
+template <typename T>
+__device__ __forceinline__ void rows_block(int64_t b, int64_t nb, const T* __restrict__ in, int64_t ld_in, int64_t R,
+                                           int64_t Cn, const int32_t* __restrict__ rowmap, bf16_t* __restrict__ out,
+                                           int64_t ldo, int flat) {
+  if (flat) {
+    const int64_t n8 = R * (ldo >> 3);
+    for (int64_t e = b * 256 + threadIdx.x; e < n8; e += nb * 256) {
+      if constexpr (sizeof(T) == 4) {
+        const float4 p = *reinterpret_cast<const float4*>(in + e * 8), q = *reinterpret_cast<const float4*>(in + e * 8 + 4);
+        *reinterpret_cast<uint4*>(out + e * 8) =
+            make_uint4(pack_bf16x2(p.x, p.y), pack_bf16x2(p.z, p.w), pack_bf16x2(q.x, q.y), pack_bf16x2(q.z, q.w));
+      } else {
+        *reinterpret_cast<uint4*>(out + e * 8) = *reinterpret_cast<const uint4*>(in + e * 8);
+      }
+    }
+    return;
+  }
+  const int lane = threadIdx.x & 63;
+  for (int64_t m = b * 4 + (threadIdx.x >> 6); m < R; m += nb * 4) {
+    const T* src = in + (rowmap ? (int64_t)rowmap[m] : m) * ld_in;
+#pragma unroll 4
+    for (int64_t j = 2 * lane; j < ldo; j += 128) {
+      const float v0 = j < Cn ? rd<T>(src, j) : 0.0f, v1 = j + 1 < Cn ? rd<T>(src, j + 1) : 0.0f;
+      *reinterpret_cast<uint32_t*>(out + m * ldo + j) = pack_bf16x2(v0, v1);
+    }
+  }
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void k_rows_bf16(const T* __restrict__ in, int64_t ld_in, int64_t R, int64_t Cn,
                                                    const int32_t* __restrict__ rowmap, bf16_t* __restrict__ out,
                                                    int64_t ldo) {
-  const int64_t total = R * ldo;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t m = e / ldo, j = e - m * ldo;
-    float v = 0.0f;
-    if (j < Cn) v = rd<T>(in, (rowmap ? (int64_t)rowmap[m] : m) * ld_in + j);
-    out[e] = f32_to_bf16(v);
-  }
+  rows_block<T>(blockIdx.x, gridDim.x, in, ld_in, R, Cn, rowmap, out, ldo, 0);
 }
-
-// 256 zero bytes that tile loads read in place of rows / columns outside an operand
-__global__ void k_zero_page(uint32_t* __restrict__ p) { p[threadIdx.x] = 0u; }
 
 // Compaction of the selected output channels of a token-major dY (the channel extraction step of Alg. 1, done
 // once per call):  out[t][m] = bf16(dY[t][idx[m]]), m < k;  0 for k <= m < kp.
@@ -156,14 +189,14 @@ __global__ void k_zero_page(uint32_t* __restrict__ p) { p[threadIdx.x] = 0u; }
 // contiguous bytes.  The four wavefronts of a block take every fourth token row of the block's row range.
 constexpr int kGatherRows = 32;                       // token rows per block
 template <typename T>
-__global__ __launch_bounds__(256) void k_gather_cols(const T* __restrict__ dy, int64_t ld, int64_t rows,
-                                                     const int32_t* __restrict__ idx, int64_t k,
-                                                     bf16_t* __restrict__ out, int64_t kp) {
+__device__ __forceinline__ void gather_block(int bx, int by, int nby, const T* __restrict__ dy, int64_t ld, int64_t rows,
+                                             const int32_t* __restrict__ idx, int64_t k, bf16_t* __restrict__ out,
+                                             int64_t kp) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t m0 = 2 * ((int64_t)blockIdx.x * 64 + lane);
+  const int64_t m0 = 2 * ((int64_t)bx * 64 + lane);
   if (m0 >= kp) return;
   const int64_t c0 = m0 < k ? (int64_t)idx[m0] : -1, c1 = m0 + 1 < k ? (int64_t)idx[m0 + 1] : -1;
-  for (int64_t t0 = (int64_t)blockIdx.y * kGatherRows; t0 < rows; t0 += (int64_t)gridDim.y * kGatherRows) {
+  for (int64_t t0 = (int64_t)by * kGatherRows; t0 < rows; t0 += (int64_t)nby * kGatherRows) {
     float a[kGatherRows / 4], b[kGatherRows / 4];
 #pragma unroll
     for (int r = 0; r < kGatherRows / 4; ++r) {
@@ -177,6 +210,44 @@ __global__ __launch_bounds__(256) void k_gather_cols(const T* __restrict__ dy, i
       if (t < rows) *reinterpret_cast<uint32_t*>(out + t * kp + m0) = pack_bf16x2(a[r], b[r]);
     }
   }
+}
+template <typename T>
+__global__ __launch_bounds__(256) void k_gather_cols(const T* __restrict__ dy, int64_t ld, int64_t rows,
+                                                     const int32_t* __restrict__ idx, int64_t k,
+                                                     bf16_t* __restrict__ out, int64_t kp) {
+  gather_block<T>(blockIdx.x, blockIdx.y, gridDim.y, dy, ld, rows, idx, k, out, kp);
+}
+
+// Everything that has to be laid out ahead of the two products, in one launch: the compaction of the selected dY columns,
+// the bf16 copy of a token-major dY that cannot be used in place, the bf16 W_q^T.  They do not depend on each other, and
+// each alone is at most a few microseconds that end with the chip draining (about 4.5 us a launch, whatever it does).
+// Blocks [0, n_gather) compact, the next n_rows copy, the rest transpose; a part that is not needed has no blocks.
+struct PrepArgs {
+  const void* dy; int64_t c_out, t_out;
+  const int32_t* idx; int64_t k; bf16_t* sel; int64_t kp;          // compaction
+  bf16_t* dyn; int64_t ldc; int rows_flat;                          // copy
+  const int8_t* w_codes; const float* s_w; bf16_t* wqT;             // W_q^T
+  int64_t w_ld, c_in, w_ldo; int w_vec;
+  TransposeExtra w_ex;
+  int n_gather, gather_x, n_rows, n_w, w_x, w_y;
+};
+template <typename T>
+__global__ __launch_bounds__(256) void k_prep(const PrepArgs p) {
+  __shared__ TransposeTile tile;
+  int b = blockIdx.x;
+  if (b < p.n_gather) {
+    gather_block<T>(b % p.gather_x, b / p.gather_x, p.n_gather / p.gather_x, (const T*)p.dy, p.c_out, p.t_out, p.idx, p.k,
+                    p.sel, p.kp);
+    return;
+  }
+  b -= p.n_gather;
+  if (b < p.n_rows) {
+    rows_block<T>(b, p.n_rows, (const T*)p.dy, p.c_out, p.t_out, p.c_out, nullptr, p.dyn, p.ldc, p.rows_flat);
+    return;
+  }
+  b -= p.n_rows;
+  transpose_block<int8_t>(tile, b % p.w_x, (b / p.w_x) % p.w_y, b / (p.w_x * p.w_y), p.w_codes, p.w_ld, p.c_out, p.c_in,
+                          nullptr, p.s_w, nullptr, p.wqT, p.w_ldo, 0, p.ldc, p.w_vec, p.w_ex);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -416,7 +487,7 @@ struct BwdPlan {
   int dx8_tile;
   int64_t kp;      // k rounded up to 8 (pitch of the compacted dY columns)
   GemmPlan plan_dx, plan_dw;
-  size_t b_wqT, b_dyn, b_colA, b_part_dx, b_xcT, b_sel, b_part_dw, b_zero, total;
+  size_t b_wqT, b_dyn, b_colA, b_part_dx, b_xcT, b_sel, b_part_dw, total;
 };
 
 // dxk: the caller's choice of the dX kernel (EFQAT_DX_KERNEL_*); it changes workspace sizes, so the size query takes
@@ -479,7 +550,6 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
   cv.take(p.b_part_dx);
   p.b_xcT = (k > 0 && !p.tn && !p.rdw) ? (size_t)p.Nw * p.ldt * 2 : 0; cv.take(p.b_xcT);
   p.b_sel = p.need_sel ? (p.tn ? (size_t)T_out * p.kp * 2 : (size_t)k * p.ldt * 2) : 0; cv.take(p.b_sel);
-  p.b_zero = 256; cv.take(p.b_zero);
   p.b_part_dw = k > 0 ? (size_t)p.plan_dw.split_k * k * p.Nw * sizeof(float) : 0; cv.take(p.b_part_dw);
   p.total = cv.off;
   return p;
@@ -543,32 +613,13 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   float* part_dx = (float*)cv.take(p.b_part_dx);
   bf16_t* xcT = (bf16_t*)cv.take(p.b_xcT);
   bf16_t* sel = (bf16_t*)cv.take(p.b_sel);
-  void* zero_page = cv.take(p.b_zero);
   float* part_dw = (float*)cv.take(p.b_part_dw);
   int rc;
 
-  ProfScope prep(PROF_PREP, st);                       // operand preparation ahead of the dX product
-  // ---- W_q^T in bf16:  wqT[ci][tap*ldc + co] = S_w[co] * code[co][tap][ci], zero for co in [c_out, ldc)
-  if (!p.dx8 && io.w_operand) {
-    // made beforehand by efqat_linear_bwd_weight_operand (same kernel, same bits), with its own zero page behind it
-    wqT = (bf16_t*)const_cast<void*>(io.w_operand);
-    zero_page = (char*)const_cast<void*>(io.w_operand) + round_up((int64_t)p.b_wqT, 256);
-  } else if (p.dx8) {
-    hipLaunchKernelGGL(k_zero_page, dim3(1), dim3(64), 0, st, (uint32_t*)zero_page);
-    EFQAT_LAUNCH_CHECK();
-  } else {
-    TransposeExtra ex{};
-    ex.z_in = c_in; ex.z_out = p.ldc;                 // one launch for all taps
-    rc = transpose_to_bf16<int8_t>(io.w_codes, (int64_t)taps * c_in, c_out, c_in, nullptr, io.s_w, nullptr, wqT,
-                                   p.Kx, 0, p.ldc, st, p.b_zero ? (uint32_t*)zero_page : nullptr, taps, &ex);
-    if (rc) return rc;
-  }
-
   // ---- optional second stream.  The weight-gradient branch (compaction of the selected columns of dY, dW product)
-  // reads the call's inputs and the zero page only, so it may run beside the dX product: blocks of the two products
-  // then share the compute units, and neither leaves a partly filled last round behind.  It is forked here, behind
-  // everything the caller's stream held before the call and behind the zero page, and joined before the second
-  // pass of the weight gradient.
+  // reads the call's inputs only, so it may run beside the dX product: blocks of the two products then share the compute
+  // units, and neither leaves a partly filled last round behind.  It is forked here, behind everything the caller's
+  // stream held before the call, and joined before the second pass of the weight gradient.
   const bool use_side = io.side && io.side != st && io.k > 0 && (p.tn || p.rdw);
   hipStream_t st2 = st;
   SideEvents ev{};
@@ -580,18 +631,41 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
     st2 = io.side;
   }
 
-  // ---- dY as a token-major bf16 matrix [T_out][ldc] (A operand of the dX product)
+  ProfScope prep(PROF_PREP, st);                       // operand preparation ahead of the dX product
+  const bool own_wqT = !p.dx8 && !io.w_operand;
+  // made beforehand by efqat_linear_bwd_weight_operand (same kernel, same bits)
+  if (!p.dx8 && io.w_operand) wqT = (bf16_t*)const_cast<void*>(io.w_operand);
+  const bool gather = p.tn && !p.tn_direct;
+  const bool copy_dy = p.need_dyn && io.dy_layout == EFQAT_DY_TOKEN_MAJOR;
+  const dim3 ggrid((unsigned)ceil_div(p.kp, 128), (unsigned)std::min<int64_t>(ceil_div(T_out, kGatherRows), 65535));
+  if (own_wqT || copy_dy || (gather && !use_side)) {
+    PrepArgs a{};
+    a.dy = io.dy; a.c_out = c_out; a.t_out = T_out; a.ldc = p.ldc;
+    if (gather && !use_side) {
+      a.idx = io.idx; a.k = io.k; a.sel = sel; a.kp = p.kp;
+      a.gather_x = (int)ggrid.x; a.n_gather = (int)(ggrid.x * ggrid.y);
+    }
+    if (copy_dy) {
+      // dY as a token-major bf16 matrix [T_out][ldc] (A operand of the dX product)
+      a.dyn = dyn; a.rows_flat = p.ldc == c_out ? 1 : 0;
+      a.n_rows = (int)std::min<int64_t>(a.rows_flat ? ceil_div(T_out * p.ldc, 256 * 16) : ceil_div(T_out, 4), 4096);
+    }
+    if (own_wqT) {
+      // W_q^T in bf16:  wqT[ci][tap*ldc + co] = S_w[co] * code[co][tap][ci], zero for co in [c_out, ldc)
+      a.w_codes = io.w_codes; a.s_w = io.s_w; a.wqT = wqT; a.w_ld = (int64_t)taps * c_in; a.c_in = c_in; a.w_ldo = p.Kx;
+      a.w_ex.z_in = c_in; a.w_ex.z_out = p.ldc;
+      a.w_vec = ((a.w_ld % 4) == 0 && (c_in % 4) == 0 && ((uintptr_t)io.w_codes % 4) == 0) ? 1 : 0;
+      a.w_x = (int)ceil_div(p.ldc, 64); a.w_y = (int)ceil_div(c_in, 64);
+      a.n_w = a.w_x * a.w_y * taps;
+    }
+    const dim3 grid((unsigned)(a.n_gather + a.n_rows + a.n_w));
+    if (io.dy_dtype == EFQAT_F32) hipLaunchKernelGGL((k_prep<float>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_prep<bf16_t>), grid, dim3(256), 0, st, a);
+    EFQAT_LAUNCH_CHECK();
+  }
   const bf16_t* dy_tok = (const bf16_t*)io.dy;
   if (p.need_dyn) {
-    if (io.dy_layout == EFQAT_DY_TOKEN_MAJOR) {
-      if (io.dy_dtype == EFQAT_F32)
-        hipLaunchKernelGGL((k_rows_bf16<float>), dim3(grid1d(T_out * p.ldc)), dim3(256), 0, st, (const float*)io.dy,
-                           c_out, T_out, c_out, nullptr, dyn, p.ldc);
-      else
-        hipLaunchKernelGGL((k_rows_bf16<bf16_t>), dim3(grid1d(T_out * p.ldc)), dim3(256), 0, st,
-                           (const bf16_t*)io.dy, c_out, T_out, c_out, nullptr, dyn, p.ldc);
-      EFQAT_LAUNCH_CHECK();
-    } else {
+    if (io.dy_layout == EFQAT_DY_CHANNEL_MAJOR) {
       // channel-major [c_out][T_out] -> [T_out][ldc]
       if (io.dy_dtype == EFQAT_F32)
         rc = transpose_to_bf16<float>((const float*)io.dy, T_out, c_out, T_out, nullptr, nullptr, nullptr, dyn,
@@ -617,15 +691,15 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   GemmEpilogueDx epi{io.x_codes, io.x_clip, io.x, io.x_dtype, io.s_x, io.z_x, io.dx, io.dx_dtype, part_dx};
   if (p.dx8) {
     if (p.cmx)
-      rc = launch_gemm_dx8_cm((const bf16_t*)io.dy, T_out, io.w_codes, c_in, io.s_w, zero_page, p.Mx, c_in, c_out,
+      rc = launch_gemm_dx8_cm((const bf16_t*)io.dy, T_out, io.w_codes, c_in, io.s_w, p.Mx, c_in, c_out,
                               p.dx8_tile, epi, st);
     else
-      rc = launch_gemm_dx8(dy_tok, c_out, io.w_codes, c_in, io.s_w, zero_page, p.Mx, c_in, c_out, p.dx8_tile, epi, st);
+      rc = launch_gemm_dx8(dy_tok, c_out, io.w_codes, c_in, io.s_w, p.Mx, c_in, c_out, p.dx8_tile, epi, st);
   } else if (p.cdx) {
-    const ConvDxMap cm{cg->H, cg->W, cg->Ho, cg->Wo, cg->KW, cg->pad, zero_page};
+    const ConvDxMap cm{cg->H, cg->W, cg->Ho, cg->Wo, cg->KW, cg->pad};
     rc = launch_gemm_nt_conv_dx(dy_tok, p.ldc, wqT, p.Kx, p.Mx, c_in, p.Kx, cm, p.plan_dx, epi, st);
   } else if (p.kk) {
-    rc = launch_gemm_kk(A, lda, wqT, p.Kx, zero_page, p.Mx, c_in, p.Kx, p.plan_dx, nullptr, &epi, st);
+    rc = launch_gemm_kk(A, lda, wqT, p.Kx, p.Mx, c_in, p.Kx, p.plan_dx, nullptr, &epi, st);
   } else {
     rc = launch_gemm_nt(A, lda, nullptr, wqT, p.Kx, p.Mx, c_in, p.Kx, p.plan_dx, nullptr, &epi, st);
   }
@@ -643,30 +717,31 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
     // itself when every channel is selected), B = the uint8 codes; transposition happens in the LDS reads
     const bf16_t* At = (const bf16_t*)io.dy;
     int64_t ldat = c_out, acols = c_out;
-    if (!p.tn_direct) {
-      ProfScope gat(PROF_PREP, st2);
-      const dim3 ggrid((unsigned)ceil_div(p.kp, 128), (unsigned)std::min<int64_t>(ceil_div(T_out, kGatherRows), 65535));
-      if (io.dy_dtype == EFQAT_F32)
-        hipLaunchKernelGGL((k_gather_cols<float>), ggrid, dim3(256), 0, st2, (const float*)io.dy, c_out, T_out, io.idx,
-                           io.k, sel, p.kp);
-      else
-        hipLaunchKernelGGL((k_gather_cols<bf16_t>), ggrid, dim3(256), 0, st2, (const bf16_t*)io.dy, c_out, T_out,
-                           io.idx, io.k, sel, p.kp);
-      EFQAT_LAUNCH_CHECK();
+    if (gather) {
+      if (use_side) {
+        ProfScope gat(PROF_PREP, st2);
+        if (io.dy_dtype == EFQAT_F32)
+          hipLaunchKernelGGL((k_gather_cols<float>), ggrid, dim3(256), 0, st2, (const float*)io.dy, c_out, T_out, io.idx,
+                             io.k, sel, p.kp);
+        else
+          hipLaunchKernelGGL((k_gather_cols<bf16_t>), ggrid, dim3(256), 0, st2, (const bf16_t*)io.dy, c_out, T_out,
+                             io.idx, io.k, sel, p.kp);
+        EFQAT_LAUNCH_CHECK();
+      }
       At = sel; ldat = p.kp; acols = p.kp;
     }
     if (p.cdw) {
       const ConvDwMap cm{cg->H, cg->W, cg->Ho, cg->Wo, cg->KW, cg->stride, cg->pad, (int)c_in};
-      rc = launch_gemm_tn_conv(At, ldat, acols, io.x_codes, cm, zero_page, io.z_x, io.k, p.Nw, T_out, p.plan_dw,
+      rc = launch_gemm_tn_conv(At, ldat, acols, io.x_codes, cm, io.z_x, io.k, p.Nw, T_out, p.plan_dw,
                                part_dw, st2);
     } else {
-      rc = launch_gemm_tn(At, ldat, acols, io.x_codes, c_in, c_in, zero_page, io.z_x, io.k, p.Nw, T_out, p.plan_dw,
+      rc = launch_gemm_tn(At, ldat, acols, io.x_codes, c_in, c_in, io.z_x, io.k, p.Nw, T_out, p.plan_dw,
                           part_dw, st2);
     }
     if (rc) return rc;
   } else if (p.rdw) {
     // ---- channel-major dY: the selected rows are gathered by the tile loads, the codes are read as they lie
-    rc = launch_gemm_dw_rows((const bf16_t*)io.dy, T_out, io.idx, io.x_codes, c_in, zero_page, io.z_x, io.k, p.Nw,
+    rc = launch_gemm_dw_rows((const bf16_t*)io.dy, T_out, io.idx, io.x_codes, c_in, io.z_x, io.k, p.Nw,
                              T_out, p.plan_dw, part_dw, st2);
     if (rc) return rc;
   } else {
@@ -689,10 +764,10 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
     Aw = (const bf16_t*)io.dy; ldaw = T_out; a_rows = io.idx;
   } else if (io.dy_layout == EFQAT_DY_CHANNEL_MAJOR) {
     if (io.dy_dtype == EFQAT_F32)
-      hipLaunchKernelGGL((k_rows_bf16<float>), dim3(grid1d(io.k * p.ldt)), dim3(256), 0, st, (const float*)io.dy,
+      hipLaunchKernelGGL((k_rows_bf16<float>), dim3(grid1d(io.k, 4)), dim3(256), 0, st, (const float*)io.dy,
                          T_out, io.k, T_out, io.idx, sel, p.ldt);
     else
-      hipLaunchKernelGGL((k_rows_bf16<bf16_t>), dim3(grid1d(io.k * p.ldt)), dim3(256), 0, st, (const bf16_t*)io.dy,
+      hipLaunchKernelGGL((k_rows_bf16<bf16_t>), dim3(grid1d(io.k, 4)), dim3(256), 0, st, (const bf16_t*)io.dy,
                          T_out, io.k, T_out, io.idx, sel, p.ldt);
     EFQAT_LAUNCH_CHECK();
     Aw = sel; ldaw = p.ldt; a_rows = nullptr;

@@ -126,30 +126,29 @@ int launch_gemm_nt(const bf16_t* A, int64_t lda, const int32_t* a_rows, const bf
                    const GemmEpilogueDx* epi, hipStream_t stream);
 
 // The same product as launch_gemm_nt (no row gather) by the kernel with a hand-pinned instruction order:
-// plan.tile 256 or 192; A, B and zero_page (>= 256 zero bytes) 16-byte aligned.
-int launch_gemm_kk(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, const void* zero_page, int64_t M,
+// plan.tile 192 or 128; A and B 16-byte aligned.
+int launch_gemm_kk(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M,
                    int64_t N, int64_t K, const GemmPlan& plan, float* out_partial, const GemmEpilogueDx* epi,
                    hipStream_t stream);
 
 // Weight-gradient product from token-major operands (no transposed copies):
 //   out[s][m][n] = sum over the K-slice s of A[t][m] * (B[t][n] - round(z_x)),  A bf16 [K][lda], B uint8 [K][ldb].
-// Columns >= a_cols / b_cols and rows >= K are taken as zero (read from zero_page: 256 zero bytes, 256-byte
-// aligned).  plan.tile must be 256 or 128.
+// Columns >= a_cols / b_cols and rows >= K are taken as zero.  plan.tile must be 256 or 128.
 int launch_gemm_tn(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* B, int64_t ldb, int64_t b_cols,
-                   const void* zero_page, const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
+                   const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
                    float* out_partial, hipStream_t stream);
 // dW product of a convolution without a materialised im2col matrix: A = compacted dY columns [N*Ho*Wo][lda] as in
 // launch_gemm_tn, B = the activation codes x_codes NHWC gathered with the tap map inside the tile loads.
 // N = KH*KW*c_in, c_in % 128 == 0 (a 128-wide column tile lies inside one tap), plan.tile == 128.
 struct ConvDwMap { int H, W, Ho, Wo, KW, stride, pad, c_in; };
 int launch_gemm_tn_conv(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* x_codes, const ConvDwMap& cm,
-                        const void* zero_page, const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
+                        const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
                         float* out_partial, hipStream_t stream);
 // dX product of a stride-1 convolution without a materialised im2col matrix: row m of the A operand is the input
 // pixel (n, h, w); its K = (tap, c_out) elements are gathered from the token-major dY [N*Ho*Wo][ldc] inside the
-// tile loads (zero_page, 256 zero bytes, stands in for taps that fall outside the output image).  ldc % 64 == 0,
-// K = KH*KW*ldc, plan.tile 192 or 128, no split-K.
-struct ConvDxMap { int H, W, Ho, Wo, KW, pad; const void* zero_page; };
+// tile loads (zeros for taps that fall outside the output image).  ldc % 64 == 0, K = KH*KW*ldc, plan.tile 192 or
+// 128, no split-K.
+struct ConvDxMap { int H, W, Ho, Wo, KW, pad; };
 int launch_gemm_nt_conv_dx(const bf16_t* dy_tok, int64_t ldc, const bf16_t* wqT, int64_t ldb, int64_t M, int64_t N,
                            int64_t K, const ConvDxMap& cm, const GemmPlan& plan, const GemmEpilogueDx& epi,
                            hipStream_t stream);
@@ -157,18 +156,18 @@ int launch_gemm_nt_conv_dx(const bf16_t* dy_tok, int64_t ldc, const bf16_t* wqT,
 // registers, fused dX epilogue.  dy: bf16 [M][lda]; N = C_in multiple of 16; tile 256 or 128.  The partial-sum
 // array of the epilogue needs ceil(M / tile) * ceil(N / tile) pairs.
 int launch_gemm_dx8(const bf16_t* dy, int64_t lda, const int8_t* w_codes, int64_t ldb, const float* s_w,
-                    const void* zero_page, int64_t M, int64_t N, int64_t K, int tile, const GemmEpilogueDx& epi,
+                    int64_t M, int64_t N, int64_t K, int tile, const GemmEpilogueDx& epi,
                     hipStream_t stream);
 // The same product for a channel-major dY [C_out][lda] (lda >= M = T, T % 8 == 0): both operands have the contraction
 // index C_out as their row and are transposed by the LDS reads; no copy of dY or W_q is made.
 int launch_gemm_dx8_cm(const bf16_t* dy_cm, int64_t lda, const int8_t* w_codes, int64_t ldb, const float* s_w,
-                       const void* zero_page, int64_t M, int64_t N, int64_t K, int tile, const GemmEpilogueDx& epi,
+                       int64_t M, int64_t N, int64_t K, int tile, const GemmEpilogueDx& epi,
                        hipStream_t stream);
 // dW product for a channel-major bf16 dY [C_out][lda] (lda >= K = T, K % 8 == 0): row m of the A operand is row
 // idx[m] of dY, read through the index list in the tile loads; B = the uint8 codes [K][ldb] as they lie.
 //   out[s][m][n] = sum over the K-slice s of dY[idx[m]][t] * (codes[t][n] - round(z_x)),  plan.tile 256 or 128.
 int launch_gemm_dw_rows(const bf16_t* dy_cm, int64_t lda, const int32_t* idx, const uint8_t* x_codes, int64_t ldb,
-                        const void* zero_page, const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
+                        const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
                         float* out_partial, hipStream_t stream);
 // Event timing of kernel classes (benchmarks only, off by default): a ProfScope brackets the launches made during its
 // lifetime with two HIP events on the stream they go to.  Classes = the `which` argument of efqat_profile_read.

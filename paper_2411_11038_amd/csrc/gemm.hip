@@ -14,13 +14,12 @@
 #include <type_traits>
 
 #include "gemm_epilogue.hpp"
+#include "lds_copy.hpp"
 
 namespace efqat {
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef int intx4_t __attribute__((ext_vector_type(4)));
 typedef int intx16_t __attribute__((ext_vector_type(16)));
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
 #ifndef EFQAT_GEMM_GM
 #define EFQAT_GEMM_GM 8   // row tiles per group of the block -> tile walk
@@ -144,7 +143,7 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const GemmArgs g) {
       const int ho = (cv_hw[j] >> 16) + g.cv_pad - kh, wo = (cv_hw[j] & 0xFFFF) + g.cv_pad - kw;
       const bool ok = (unsigned)ho < (unsigned)g.cv_Ho && (unsigned)wo < (unsigned)g.cv_Wo;
       const int64_t pix = (int64_t)cv_q0[j] + ho * g.cv_Wo + wo;
-      return ok ? (const char*)g.A + (pix * g.lda + cst * 64) * 2 + lch * 16 : (const char*)g.cv_zero;
+      return ok ? (const char*)g.A + (pix * g.lda + cst * 64) * 2 + lch * 16 : zero_page();
     } else {
       return a_ptr[j] + kt * 128;
     }
@@ -517,7 +516,6 @@ int launch_gemm_nt_conv_dx(const bf16_t* dy_tok, int64_t ldc, const bf16_t* wqT,
   if (M <= 0 || N <= 0 || K <= 0 || (ldc % 64) || (K % 64) || (ldb % 8) || cm.H > 65535 || cm.W > 65535)
     return EFQAT_ERR_BAD_SHAPE;
   if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX || plan.split_k != 1) return EFQAT_ERR_BAD_SHAPE;
-  if (((uintptr_t)cm.zero_page % 256) != 0) return EFQAT_ERR_ALIGNMENT;
   GemmArgs a{};
   a.A = dy_tok; a.lda = ldc; a.a_rows = nullptr; a.B = wqT; a.ldb = ldb;
   a.M = (int)M; a.N = (int)N; a.K = (int)K;
@@ -527,7 +525,7 @@ int launch_gemm_nt_conv_dx(const bf16_t* dy_tok, int64_t ldc, const bf16_t* wqT,
   a.epi_vec = gemm_epilogue_vec_ok(epi, N) ? 1 : 0;
   a.tiles_m = plan.tiles_m; a.tiles_n = plan.tiles_n;
   a.cv_H = cm.H; a.cv_W = cm.W; a.cv_Ho = cm.Ho; a.cv_Wo = cm.Wo; a.cv_KW = cm.KW; a.cv_pad = cm.pad;
-  a.cv_spt = (int)(ldc / 64); a.cv_zero = cm.zero_page;
+  a.cv_spt = (int)(ldc / 64);
   a.cv_m_spt = (1ull << 32) / (uint64_t)a.cv_spt + 1; a.cv_m_kw = (1ull << 32) / (uint64_t)cm.KW + 1;
   switch (plan.tile) {
     case 192: return nt_epilogue_fast(a, epi, 192) ? launch_cfg<192, 192, EPI_DXF, false, true>(a, 1, stream)

@@ -43,7 +43,6 @@ struct KkCfg {
 
 struct GemmKkArgs {
   GemmArgs g;              // A, lda, B, ldb, M, N, K, k_per_split, tiles, out or the fused dX epilogue fields
-  const void* zero_page;   // >= 256 zero bytes
 };
 
 // CONV: the A operand is gathered from a token-major dY with the im2col map of a stride-1 convolution, as in
@@ -79,7 +78,7 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const GemmKkArgs ga) {
   const int K = k_end_ > k_begin ? k_end_ - k_begin : 0;
   const int nk = (K + 63) / 64;
   const int nfull = K / 64;
-  const char* zero = (const char*)ga.zero_page;
+  const char* zero = zero_page();
 
   // ---- global -> LDS copies with running pointers.  Slot j of an operand covers tile rows (wave + 4 j) * 8 .. + 7;
   // lane l lands in row l / 8, physical chunk l % 8, and fetches the logical chunk that the swizzle puts there.
@@ -339,18 +338,16 @@ static int launch_kk_cfg(const GemmKkArgs& a, int split_k, hipStream_t st) {
   return EFQAT_OK;
 }
 
-int launch_gemm_kk(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, const void* zero_page, int64_t M,
+int launch_gemm_kk(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M,
                    int64_t N, int64_t K, const GemmPlan& plan, float* out_partial, const GemmEpilogueDx* epi,
                    hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0 || (K % 8) || (lda % 8) || (ldb % 8)) return EFQAT_ERR_BAD_SHAPE;
   if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX) return EFQAT_ERR_BAD_SHAPE;
-  if (!zero_page) return EFQAT_ERR_NULL_PTR;
-  if (((uintptr_t)A % 16) || ((uintptr_t)B % 16) || ((uintptr_t)zero_page % 16)) return EFQAT_ERR_ALIGNMENT;
+  if (((uintptr_t)A % 16) || ((uintptr_t)B % 16)) return EFQAT_ERR_ALIGNMENT;
   const int split_k = plan.split_k;
   if (epi && split_k != 1) return EFQAT_ERR_BAD_SHAPE;
   GemmKkArgs ka{};
   GemmArgs& a = ka.g;
-  ka.zero_page = zero_page;
   a.A = A; a.lda = lda; a.a_rows = nullptr; a.B = B; a.ldb = ldb;
   a.M = (int)M; a.N = (int)N; a.K = (int)K;
   a.k_per_split = (int)(ceil_div(ceil_div(K, 64), split_k) * 64);   // slices start on whole K-stages
@@ -384,11 +381,10 @@ int launch_gemm_kk(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, c
 // dX product of a stride-1 convolution on 128 x 128 tiles with the three-stage ring; `a` as launch_gemm_nt_conv_dx
 // fills it (K a whole number of 64-channel stages, no split-K).
 int launch_gemm_kk_conv128(const GemmArgs& a, bool fast, hipStream_t stream) {
-  if ((a.K % 64) != 0 || !a.cv_zero || ((uintptr_t)a.cv_zero % 16) != 0) return EFQAT_ERR_BAD_SHAPE;
+  if ((a.K % 64) != 0) return EFQAT_ERR_BAD_SHAPE;
   GemmKkArgs ka{};
   ka.g = a;
   ka.g.k_per_split = a.K;
-  ka.zero_page = a.cv_zero;
   return fast ? launch_kk_cfg<128, 2, 2, EPI_DXF, true>(ka, 1, stream) : launch_kk_cfg<128, 2, 2, EPI_DX, true>(ka, 1, stream);
 }
 

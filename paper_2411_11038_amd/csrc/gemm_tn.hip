@@ -25,7 +25,6 @@ struct GemmTnArgs {
   const bf16_t* A; int64_t lda;       // [K][lda], lda multiple of 8; columns >= a_cols are not read
   const uint8_t* B; int64_t ldb;      // [K][ldb], ldb multiple of 16
   int a_cols, b_cols;                 // readable widths (multiples of 8 / 16): beyond them the zero page is read
-  const void* zero_page;              // >= 256 bytes of zeros, 256-byte aligned
   const float* z_x;
   int M, N, K;
   int k_per_split;                    // multiple of 64
@@ -97,7 +96,7 @@ __global__ __launch_bounds__(256) void k_gemm_tn(const GemmTnArgs g) {
   // stage (64 token rows) after each use; slots whose columns lie outside the operand sit on the zero page with
   // stride 0, so the steady-state loads need no predicate and no multiply.
   constexpr int RPIA = 1024 / C::RA, RPIB = 1024 / C::RB;
-  const char* zero = (const char*)g.zero_page;
+  const char* zero = zero_page();
   const int a_r0 = lane / C::CA, b_r0 = lane / C::CB;
   const char* a_ptr[C::A_G];
   const char* b_ptr[C::B_G];
@@ -433,7 +432,6 @@ struct GemmDx8Args {
   GemmArgs g;              // dX: A = dY, B = weight codes, M = T, N = C_in, K = C_out, fused dX epilogue fields
                            // dW: A = dY channel-major with a_rows = idx, B = activation codes, M = k, N = C_in, K = T
   int b_cols;              // readable width of B (multiple of 16)
-  const void* zero_page;   // >= 256 zero bytes
 };
 
 // FAST (dX only): the straight-line epilogue for bf16 x / dX and whole tiles (epilogue_dx_fast).
@@ -466,7 +464,7 @@ __global__ __launch_bounds__(256) void k_gemm_dx8(const GemmDx8Args ga) {
   const int K = k_end_ > k_begin ? k_end_ - k_begin : 0;
   const int nk = (K + 63) / 64;
   const int nfull = K / 64;
-  const char* zero = (const char*)ga.zero_page;
+  const char* zero = zero_page();
 
   // ---- global -> LDS copies with running pointers (one 64-bit add per copy; slots outside the operands rest on
   // the zero page with stride 0).  A: slot j covers tile rows (wave + 4 j) * 8 .. + 7, lane l lands in row l / 8,
@@ -783,16 +781,15 @@ static int launch_tn_cfg(const GemmTnArgs& a, int split_k, hipStream_t st) {
   return EFQAT_OK;
 }
 
-int launch_gemm_tn(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* B, int64_t ldb, int64_t b_cols,
-                   const void* zero_page, const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
+int launch_gemm_tn(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* B, int64_t ldb, int64_t b_cols, const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
                    float* out_partial, hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0 || (lda % 8) || (ldb % 16) || (a_cols % 8) || (b_cols % 16)) return EFQAT_ERR_BAD_SHAPE;
   if (lda >= (1 << 24) || ldb >= (1 << 24)) return EFQAT_ERR_BAD_SHAPE;   // 32-bit per-stage pointer strides
   if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX || a_cols > lda || b_cols > ldb) return EFQAT_ERR_BAD_SHAPE;
-  if (((uintptr_t)A % 16) || ((uintptr_t)B % 16) || ((uintptr_t)zero_page % 256)) return EFQAT_ERR_ALIGNMENT;
+  if (((uintptr_t)A % 16) || ((uintptr_t)B % 16)) return EFQAT_ERR_ALIGNMENT;
   GemmTnArgs a{};
   a.A = A; a.lda = lda; a.B = B; a.ldb = ldb; a.a_cols = (int)a_cols; a.b_cols = (int)b_cols;
-  a.zero_page = zero_page; a.z_x = z_x;
+  a.z_x = z_x;
   a.M = (int)M; a.N = (int)N; a.K = (int)K;
   a.k_per_split = (int)(ceil_div(ceil_div(K, 64), plan.split_k) * 64);
   a.tiles_m = plan.tiles_m; a.tiles_n = plan.tiles_n; a.group_m = tile_group_m(plan.tile);
@@ -826,12 +823,11 @@ static bool dx8_epilogue_fast(const GemmArgs& g, const GemmEpilogueDx& epi, int 
          (g.N % tile) == 0 && (int64_t)g.M * g.N <= (int64_t)INT32_MAX;
 }
 
-int launch_gemm_dx8_cm(const bf16_t* dy_cm, int64_t lda, const int8_t* w_codes, int64_t ldb, const float* s_w,
-                       const void* zero_page, int64_t M, int64_t N, int64_t K, int tile, const GemmEpilogueDx& epi,
+int launch_gemm_dx8_cm(const bf16_t* dy_cm, int64_t lda, const int8_t* w_codes, int64_t ldb, const float* s_w, int64_t M, int64_t N, int64_t K, int tile, const GemmEpilogueDx& epi,
                        hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0 || (M % 8) || (lda % 8) || (ldb % 16) || (N % 16)) return EFQAT_ERR_BAD_SHAPE;
   if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX || ldb >= (1 << 24) || lda >= (1 << 24)) return EFQAT_ERR_BAD_SHAPE;
-  if (((uintptr_t)dy_cm % 16) || ((uintptr_t)w_codes % 16) || ((uintptr_t)s_w % 4) || ((uintptr_t)zero_page % 256))
+  if (((uintptr_t)dy_cm % 16) || ((uintptr_t)w_codes % 16) || ((uintptr_t)s_w % 4))
     return EFQAT_ERR_ALIGNMENT;
   GemmDx8Args a{};
   a.g.A = dy_cm; a.g.lda = lda; a.g.B = w_codes; a.g.ldb = ldb;
@@ -842,7 +838,6 @@ int launch_gemm_dx8_cm(const bf16_t* dy_cm, int64_t lda, const int8_t* w_codes, 
   a.g.epi_vec = gemm_epilogue_vec_ok(epi, N) ? 1 : 0;
   a.g.tiles_m = (int)ceil_div(M, tile); a.g.tiles_n = (int)ceil_div(N, tile); a.g.group_m = tile_group_m(tile);
   a.a_cols = (int)M; a.b_cols = (int)N;
-  a.zero_page = zero_page;
   switch (tile) {
     case 256: return dx8_epilogue_fast(a.g, epi, 256) ? launch_dx8_cfg<256, false, true, true>(a, 1, stream)
                                                       : launch_dx8_cfg<256, false, true>(a, 1, stream);
@@ -852,12 +847,11 @@ int launch_gemm_dx8_cm(const bf16_t* dy_cm, int64_t lda, const int8_t* w_codes, 
   }
 }
 
-int launch_gemm_dw_rows(const bf16_t* dy_cm, int64_t lda, const int32_t* idx, const uint8_t* x_codes, int64_t ldb,
-                        const void* zero_page, const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
+int launch_gemm_dw_rows(const bf16_t* dy_cm, int64_t lda, const int32_t* idx, const uint8_t* x_codes, int64_t ldb, const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
                         float* out_partial, hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0 || (K % 8) || (lda % 8) || (ldb % 16) || (N % 16)) return EFQAT_ERR_BAD_SHAPE;
   if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX || ldb >= (1 << 24)) return EFQAT_ERR_BAD_SHAPE;
-  if (((uintptr_t)dy_cm % 16) || ((uintptr_t)x_codes % 16) || ((uintptr_t)zero_page % 256)) return EFQAT_ERR_ALIGNMENT;
+  if (((uintptr_t)dy_cm % 16) || ((uintptr_t)x_codes % 16)) return EFQAT_ERR_ALIGNMENT;
   GemmDx8Args a{};
   a.g.A = dy_cm; a.g.lda = lda; a.g.a_rows = idx; a.g.B = x_codes; a.g.ldb = ldb;
   a.g.M = (int)M; a.g.N = (int)N; a.g.K = (int)K;
@@ -865,7 +859,6 @@ int launch_gemm_dw_rows(const bf16_t* dy_cm, int64_t lda, const int32_t* idx, co
   a.g.z_x = z_x; a.g.out = out_partial;
   a.g.tiles_m = plan.tiles_m; a.g.tiles_n = plan.tiles_n; a.g.group_m = tile_group_m(plan.tile);
   a.b_cols = (int)N;
-  a.zero_page = zero_page;
   switch (plan.tile) {
     case 256: return launch_dx8_cfg<256, true>(a, plan.split_k, stream);
     case 128: return launch_dx8_cfg<128, true>(a, plan.split_k, stream);
@@ -873,16 +866,15 @@ int launch_gemm_dw_rows(const bf16_t* dy_cm, int64_t lda, const int32_t* idx, co
   }
 }
 
-int launch_gemm_tn_conv(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* x_codes, const ConvDwMap& cm,
-                        const void* zero_page, const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
+int launch_gemm_tn_conv(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* x_codes, const ConvDwMap& cm, const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
                         float* out_partial, hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0 || (lda % 8) || (a_cols % 8) || a_cols > lda || lda >= (1 << 24)) return EFQAT_ERR_BAD_SHAPE;
   if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX || plan.tile != 128 || (cm.c_in % 128) != 0)
     return EFQAT_ERR_BAD_SHAPE;
-  if (((uintptr_t)A % 16) || ((uintptr_t)x_codes % 16) || ((uintptr_t)zero_page % 256)) return EFQAT_ERR_ALIGNMENT;
+  if (((uintptr_t)A % 16) || ((uintptr_t)x_codes % 16)) return EFQAT_ERR_ALIGNMENT;
   GemmTnArgs a{};
   a.A = A; a.lda = lda; a.B = x_codes; a.ldb = 0; a.a_cols = (int)a_cols; a.b_cols = INT32_MAX;
-  a.zero_page = zero_page; a.z_x = z_x;
+  a.z_x = z_x;
   a.M = (int)M; a.N = (int)N; a.K = (int)K;
   a.k_per_split = (int)(ceil_div(ceil_div(K, 64), plan.split_k) * 64);
   a.tiles_m = plan.tiles_m; a.tiles_n = plan.tiles_n; a.group_m = tile_group_m(plan.tile);
@@ -894,12 +886,11 @@ int launch_gemm_tn_conv(const bf16_t* A, int64_t lda, int64_t a_cols, const uint
   return launch_tn_cfg<128, true>(a, plan.split_k, stream);
 }
 
-int launch_gemm_dx8(const bf16_t* dy, int64_t lda, const int8_t* w_codes, int64_t ldb, const float* s_w,
-                    const void* zero_page, int64_t M, int64_t N, int64_t K, int tile, const GemmEpilogueDx& epi,
+int launch_gemm_dx8(const bf16_t* dy, int64_t lda, const int8_t* w_codes, int64_t ldb, const float* s_w, int64_t M, int64_t N, int64_t K, int tile, const GemmEpilogueDx& epi,
                     hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0 || (K % 8) || (lda % 8) || (ldb % 16) || (N % 16)) return EFQAT_ERR_BAD_SHAPE;
   if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX || ldb >= (1 << 24)) return EFQAT_ERR_BAD_SHAPE;
-  if (((uintptr_t)dy % 16) || ((uintptr_t)w_codes % 16) || ((uintptr_t)s_w % 4) || ((uintptr_t)zero_page % 256))
+  if (((uintptr_t)dy % 16) || ((uintptr_t)w_codes % 16) || ((uintptr_t)s_w % 4))
     return EFQAT_ERR_ALIGNMENT;
   GemmDx8Args a{};
   a.g.A = dy; a.g.lda = lda; a.g.B = w_codes; a.g.ldb = ldb;
@@ -910,7 +901,6 @@ int launch_gemm_dx8(const bf16_t* dy, int64_t lda, const int8_t* w_codes, int64_
   a.g.epi_vec = gemm_epilogue_vec_ok(epi, N) ? 1 : 0;
   a.g.tiles_m = (int)ceil_div(M, tile); a.g.tiles_n = (int)ceil_div(N, tile); a.g.group_m = tile_group_m(tile);
   a.b_cols = (int)N;
-  a.zero_page = zero_page;
   switch (tile) {
     case 256: return dx8_epilogue_fast(a.g, epi, 256) ? launch_dx8_cfg<256, false, false, true>(a, 1, stream)
                                                       : launch_dx8_cfg<256>(a, 1, stream);

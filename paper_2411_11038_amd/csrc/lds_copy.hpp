@@ -10,6 +10,11 @@ typedef short shortx4_t __attribute__((ext_vector_type(4)));
 typedef int intx2_t __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
+// 256 zero bytes that tile copies read in place of rows / columns outside an operand, so that no copy needs a predicate.
+// Part of the library image: no launch has to clear a page in the workspace ahead of every product.
+static __device__ __attribute__((aligned(256))) uint32_t g_zero_page[64];
+__device__ __forceinline__ const char* zero_page() { return (const char*)g_zero_page; }
+
 // One wave-wide global -> LDS copy: lane l moves 16 bytes from its own src to lds_dst + 16 l.  Written as inline
 // assembly on purpose: the compiler models the LDS transpose-read builtins as possible LDS writes and would make
 // every one of them wait for all copies in flight (s_waitcnt vmcnt(0)), which serialises the pipeline.  The
