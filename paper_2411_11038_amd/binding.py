@@ -1,7 +1,12 @@
-"""ctypes loader and thin wrappers for libefqat.so (see include/efqat.h for the contract)."""
+"""Loader and thin wrappers for libefqat.so (see include/efqat.h for the contract).
+
+Sizes and other host-only calls go through ctypes; the calls that take tensors go through the native marshalling module
+(csrc/torch_glue.cpp), which takes the tensors themselves, None for NULL and Ellipsis for the current stream."""
 from __future__ import annotations
 
 import ctypes as C
+import importlib.machinery
+import importlib.util
 import os
 
 import torch
@@ -122,13 +127,33 @@ def lib():
     return L
 
 
+_NATIVE = None
+
+
+def _native():
+    """The marshalling module (built next to libefqat.so)."""
+    global _NATIVE
+    if _NATIVE is None:
+        lib()
+        path = os.path.join(HERE, "lib", "_efqat_torch.so")
+        if not os.path.exists(path):
+            raise FileNotFoundError(f"{path} not built: run `python -m paper_2411_11038_amd.build`")
+        loader = importlib.machinery.ExtensionFileLoader("_efqat_torch", path)
+        mod = importlib.util.module_from_spec(importlib.util.spec_from_loader("_efqat_torch", loader))
+        loader.exec_module(mod)
+        _NATIVE = mod
+    return _NATIVE
+
+
 # ------------------------------------------------------------------ marshalling helpers
+_DTYPES = {torch.float32: F32, torch.bfloat16: BF16}
+
+
 def _dt(t: torch.Tensor) -> int:
-    if t.dtype == torch.float32:
-        return F32
-    if t.dtype == torch.bfloat16:
-        return BF16
-    raise TypeError(f"unsupported dtype {t.dtype}")
+    code = _DTYPES.get(t.dtype)
+    if code is None:
+        raise TypeError(f"unsupported dtype {t.dtype}")
+    return code
 
 
 def _p(t):
@@ -141,8 +166,7 @@ def _p(t):
     return t.data_ptr()
 
 
-def _stream():
-    return torch.cuda.current_stream().cuda_stream
+_STREAM = ...                                          # the current stream
 
 
 def _ws(nbytes: int, like: torch.Tensor) -> torch.Tensor:
@@ -202,8 +226,8 @@ def fakequant_fwd(x: torch.Tensor, mode: int, bits: int, init_minmax: bool = Tru
         xq = torch.empty(x.shape, dtype=torch.bfloat16, device=dev)
     if ws is None:
         ws = _ws(L.efqat_fakequant_fwd_workspace_bytes(rows, cols, mode), x)
-    rc = L.efqat_fakequant_fwd(_p(x), _dt(x), rows, cols, mode, bits, int(bool(init_minmax)), _p(scale),
-                               _p(zero_point), _p(codes), _p(clip), _p(xq), _p(ws), ws.numel(), _stream())
+    rc = _native().fakequant_fwd(x, _dt(x), rows, cols, mode, bits, bool(init_minmax), scale, zero_point, codes, clip,
+                                 xq, ws, ws.numel(), _STREAM)
     _check(rc, "efqat_fakequant_fwd")
     return dict(codes=codes, clip_bits=clip, scale=scale, zero_point=zero_point, xq=xq)
 
@@ -222,8 +246,7 @@ def channel_select(w: torch.Tensor, k: int, want_scores: bool = True, ws=None, o
         idx = torch.empty(max(k, 0), dtype=torch.int32, device=w.device)
     if ws is None:
         ws = _ws(L.efqat_channel_select_workspace_bytes(c_out), w)
-    rc = L.efqat_channel_select(_p(w), c_out, block, k, _p(scores), _p(idx) if k > 0 else None, _p(ws),
-                                ws.numel(), _stream())
+    rc = _native().channel_select(w, c_out, block, k, scores, idx if k > 0 else None, ws, ws.numel(), _STREAM)
     _check(rc, "efqat_channel_select")
     return idx, scores
 
@@ -254,8 +277,8 @@ def weight_quant_select(w: torch.Tensor, bits: int, k: int, init_minmax: bool = 
         idx = torch.empty(max(k, 0), dtype=torch.int32, device=dev)
     if ws is None:
         ws = _ws(L.efqat_weight_quant_select_workspace_bytes(c_out), w)
-    rc = L.efqat_weight_quant_select(_p(w), c_out, block, bits, int(bool(init_minmax)), _p(scale), _p(codes), _p(clip),
-                                     k, _p(scores), _p(idx) if k > 0 else None, _p(ws), ws.numel(), _stream())
+    rc = _native().weight_quant_select(w, c_out, block, bits, bool(init_minmax), scale, codes, clip, k, scores,
+                                       idx if k > 0 else None, ws, ws.numel(), _STREAM)
     _check(rc, "efqat_weight_quant_select")
     return dict(codes=codes, clip_bits=clip, scale=scale, scores=scores, idx=idx)
 
@@ -266,7 +289,7 @@ def channel_select_static(w: torch.Tensor, k: int, out=None):
     c_out = w.shape[0]
     block = w[0].numel()
     idx = out if out is not None else torch.empty(max(k, 0), dtype=torch.int32, device=w.device)
-    rc = lib().efqat_channel_select_static(_p(w), c_out, block, k, _p(idx) if k > 0 else None, _stream())
+    rc = _native().channel_select_static(w, c_out, block, k, idx if k > 0 else None, _STREAM)
     _check(rc, "efqat_channel_select_static")
     return idx
 
@@ -280,8 +303,8 @@ def network_select(scores: torch.Tensor, layer_off: torch.Tensor, k_total: int, 
     kpl = torch.empty(n_layers, dtype=torch.int32, device=scores.device)
     if ws is None:
         ws = _ws(L.efqat_network_select_workspace_bytes(total), scores)
-    rc = L.efqat_network_select(_p(scores), _p(layer_off), n_layers, total, k_total,
-                                _p(idx) if k_total > 0 else None, _p(kpl), _p(ws), ws.numel(), _stream())
+    rc = _native().network_select(scores, layer_off, n_layers, total, k_total, idx if k_total > 0 else None, kpl, ws,
+                                  ws.numel(), _STREAM)
     _check(rc, "efqat_network_select")
     return idx, kpl
 
@@ -298,8 +321,8 @@ def layer_select(scores: torch.Tensor, layer_off: torch.Tensor, k_layers: int, w
     ls = torch.empty(n_layers, dtype=torch.float64, device=scores.device)
     if ws is None:
         ws = _ws(L.efqat_layer_select_workspace_bytes(n_layers), scores)
-    rc = L.efqat_layer_select(_p(scores), _p(layer_off), n_layers, k_layers, _p(ls),
-                              _p(lidx) if k_layers > 0 else None, _p(kpl), _p(ws), ws.numel(), _stream())
+    rc = _native().layer_select(scores, layer_off, n_layers, k_layers, ls, lidx if k_layers > 0 else None, kpl, ws,
+                                ws.numel(), _STREAM)
     _check(rc, "efqat_layer_select")
     return lidx, kpl, ls
 
@@ -316,7 +339,7 @@ def bias_grad(dy: torch.Tensor, dy_layout=DY_TOKEN_MAJOR, ws=None, out=None):
     db = out if out is not None else torch.empty(c_out, dtype=torch.float32, device=dy.device)
     if ws is None:
         ws = _ws(L.efqat_bias_grad_workspace_bytes(T, c_out, dy_layout), dy)
-    rc = L.efqat_bias_grad(_p(dy), _dt(dy), dy_layout, T, c_out, _p(db), _p(ws), ws.numel(), _stream())
+    rc = _native().bias_grad(dy, _dt(dy), dy_layout, T, c_out, db, ws, ws.numel(), _STREAM)
     _check(rc, "efqat_bias_grad")
     return db
 
@@ -355,8 +378,7 @@ def linear_bwd_weight_operand(w_codes, s_w, T, dy_dtype=BF16, dy_layout=DY_TOKEN
         return None
     if out is None:
         out = torch.empty(need, dtype=torch.uint8, device=w_codes.device)
-    rc = L.efqat_linear_bwd_weight_operand(_p(w_codes), _p(s_w), T, c_in, c_out, dy_dtype, dy_layout, _p(out),
-                                           out.numel(), _stream())
+    rc = _native().linear_bwd_weight_operand(w_codes, s_w, T, c_in, c_out, dy_dtype, dy_layout, out, out.numel(), _STREAM)
     _check(rc, "efqat_linear_bwd_weight_operand")
     return out
 
@@ -370,7 +392,7 @@ def linear_bwd(dy, x_codes, x_clip, x, s_x, z_x, w_codes, w_clip, w, s_w, idx, d
     w_operand: the tensor made by linear_bwd_weight_operand for these weights.
     dx_kernel: DX_KERNEL_* (tests and measurements).
     side_stream: a torch.cuda.Stream on which the weight-gradient branch may run beside the dX product.
-    Any of the four routes the call to efqat_linear_bwd_ex."""
+    """
     L = lib()
     T, c_in = x_codes.shape
     c_out = w_codes.shape[0]
@@ -382,16 +404,12 @@ def linear_bwd(dy, x_codes, x_clip, x, s_x, z_x, w_codes, w_clip, w, s_w, idx, d
         dx, dw, ds_w, ds_x, dz_x = out["dx"], out["dw"], out["ds_w"], out["ds_x"], out["dz_x"]
     if ws is None:
         ws = _ws(L.efqat_linear_bwd_workspace_bytes_ex(T, c_in, c_out, k, _dt(dy), dy_layout, dx_kernel), x)
-    args = (_p(dy), _dt(dy), dy_layout, T, c_in, c_out, _p(x_codes), _p(x_clip), _p(x), _dt(x),
-            _p(s_x), _p(z_x), _p(w_codes), _p(w_clip), _p(w), _p(s_w),
-            _p(idx) if k > 0 else None, k, _p(dx), _dt(dx), _p(dw) if k > 0 and dw is not None else None,
-            int(bool(scatter)), _p(ds_w) if k > 0 and ds_w is not None else None, _p(ds_x), _p(dz_x))
-    if step is None and w_operand is None and dx_kernel == DX_KERNEL_AUTO and side_stream is None:
-        rc = L.efqat_linear_bwd(*args, _p(ws), ws.numel(), _stream())
-    else:
-        st = _step_struct(step) if step is not None else None
-        rc = L.efqat_linear_bwd_ex(*args, _p(w_operand), C.byref(st) if st is not None else None, dx_kernel,
-                                   _p(ws), ws.numel(), _stream(), side_stream.cuda_stream if side_stream else None)
+    st = _step_struct(step) if step is not None else None
+    rc = _native().linear_bwd_ex(dy, _dt(dy), dy_layout, T, c_in, c_out, x_codes, x_clip, x, _dt(x), s_x, z_x, w_codes,
+                                 w_clip, w, s_w, idx if k > 0 else None, k, dx, _dt(dx), dw if k > 0 else None,
+                                 bool(scatter), ds_w if k > 0 else None, ds_x, dz_x, w_operand,
+                                 C.addressof(st) if st is not None else None, dx_kernel, ws, ws.numel(), _STREAM,
+                                 side_stream.cuda_stream if side_stream else None)
     _check(rc, "efqat_linear_bwd")
     return dict(dx=dx, dw=dw, ds_w=ds_w, ds_x=ds_x, dz_x=dz_x)
 
@@ -404,8 +422,7 @@ def linear_fwd(x_codes, s_x, z_x, w_codes, s_w, y_dtype=torch.bfloat16, ws=None,
     y = out if out is not None else torch.empty((T, c_out), dtype=y_dtype, device=x_codes.device)
     if ws is None:
         ws = _ws(L.efqat_linear_fwd_workspace_bytes(T, c_in, c_out), x_codes)
-    rc = L.efqat_linear_fwd(_p(x_codes), _p(s_x), _p(z_x), _p(w_codes), _p(s_w), T, c_in, c_out, _p(y), _dt(y),
-                            _p(ws), ws.numel(), _stream())
+    rc = _native().linear_fwd(x_codes, s_x, z_x, w_codes, s_w, T, c_in, c_out, y, _dt(y), ws, ws.numel(), _STREAM)
     _check(rc, "efqat_linear_fwd")
     return y
 
@@ -426,15 +443,11 @@ def conv_bwd(dy, x_codes, x_clip, x, s_x, z_x, w_codes, w_clip, w, s_w, idx, str
     if ws is None:
         ws = _ws(L.efqat_conv_bwd_workspace_bytes_ex(N, H, W, c_in, c_out, KH, KW, stride, pad, k, _dt(dy), dy_layout,
                                                      dx_kernel), x)
-    args = (_p(dy), _dt(dy), dy_layout, N, H, W, c_in, c_out, KH, KW, stride, pad, _p(x_codes),
-            _p(x_clip), _p(x), _dt(x), _p(s_x), _p(z_x), _p(w_codes), _p(w_clip), _p(w), _p(s_w),
-            _p(idx) if k > 0 else None, k, _p(dx), _dt(dx), _p(dw) if k > 0 and dw is not None else None,
-            int(bool(scatter)), _p(ds_w) if k > 0 and ds_w is not None else None, _p(ds_x), _p(dz_x))
-    if step is None and dx_kernel == DX_KERNEL_AUTO and side_stream is None:
-        rc = L.efqat_conv_bwd(*args, _p(ws), ws.numel(), _stream())
-    else:
-        st = _step_struct(step) if step is not None else None
-        rc = L.efqat_conv_bwd_ex(*args, C.byref(st) if st is not None else None, dx_kernel, _p(ws), ws.numel(),
-                                 _stream(), side_stream.cuda_stream if side_stream else None)
+    st = _step_struct(step) if step is not None else None
+    rc = _native().conv_bwd_ex(dy, _dt(dy), dy_layout, N, H, W, c_in, c_out, KH, KW, stride, pad, x_codes, x_clip, x,
+                               _dt(x), s_x, z_x, w_codes, w_clip, w, s_w, idx if k > 0 else None, k, dx, _dt(dx),
+                               dw if k > 0 else None, bool(scatter), ds_w if k > 0 else None, ds_x, dz_x,
+                               C.addressof(st) if st is not None else None, dx_kernel, ws, ws.numel(), _STREAM,
+                               side_stream.cuda_stream if side_stream else None)
     _check(rc, "efqat_conv_bwd")
     return dict(dx=dx, dw=dw, ds_w=ds_w, ds_x=ds_x, dz_x=dz_x)

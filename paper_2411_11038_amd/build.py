@@ -48,7 +48,23 @@ def build(verbose: bool = False) -> str:
     subprocess.run(cmd, check=True)
     for o in objs:
         os.remove(o)
+    build_glue()
     return LIB_PATH
+
+
+def build_glue() -> str:
+    """The native argument marshalling of the Python binding (host code only, against torch's headers)."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    path = os.path.join(LIB_DIR, "_efqat_torch.so")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+           f"-I{root}/include", f"-I{root}/include/torch/csrc/api/include", "-I/opt/rocm/include",
+           f"-I{sysconfig.get_paths()['include']}", os.path.join(CSRC, "torch_glue.cpp"), "-o", path, f"-L{LIB_DIR}",
+           "-lefqat", f"-L{root}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"]
+    subprocess.run(cmd, check=True)
+    return path
 
 
 if __name__ == "__main__":
