@@ -145,23 +145,34 @@ __global__ __launch_bounds__(256) void k_transpose_bf16(const T* __restrict__ in
 }
 
 // Row-wise cast/copy to bf16 with zero-padded pitch: out[m][j] = bf16(in[rm(m)][j]), j < Cn; 0 up to ldo (a multiple of
-// 8).  flat: no padding, no row map and 16-byte aligned rows, i.e. one run of 8-element chunks; else a wavefront per row,
-// two elements per lane and step.  block b of nb.
+// 8).  flat == 1: no padding, no row map and 16-byte aligned rows, i.e. one run of 8-element chunks; flat = 2 .. 64, a power
+// of two: aligned rows of whole chunks with a padded pitch, that many lanes to a row; 0: a wavefront per row, two elements
+// per lane and step.  block b of nb.
 template <typename T>
 __device__ __forceinline__ void rows_block(int64_t b, int64_t nb, const T* __restrict__ in, int64_t ld_in, int64_t R,
                                            int64_t Cn, const int32_t* __restrict__ rowmap, bf16_t* __restrict__ out,
                                            int64_t ldo, int flat) {
+  auto chunk = [](const T* src, bf16_t* dst) {
+    if constexpr (sizeof(T) == 4) {
+      const float4 p = *reinterpret_cast<const float4*>(src), q = *reinterpret_cast<const float4*>(src + 4);
+      *reinterpret_cast<uint4*>(dst) =
+          make_uint4(pack_bf16x2(p.x, p.y), pack_bf16x2(p.z, p.w), pack_bf16x2(q.x, q.y), pack_bf16x2(q.z, q.w));
+    } else {
+      *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
+    }
+  };
+  if (flat > 1) {
+    const int sub = threadIdx.x & (flat - 1), per = 256 / flat;
+    for (int64_t m = b * per + threadIdx.x / flat; m < R; m += nb * per)
+      for (int64_t j = 8 * sub; j < ldo; j += 8 * flat) {
+        if (j < Cn) chunk(in + m * ld_in + j, out + m * ldo + j);
+        else *reinterpret_cast<uint4*>(out + m * ldo + j) = make_uint4(0, 0, 0, 0);
+      }
+    return;
+  }
   if (flat) {
     const int64_t n8 = R * (ldo >> 3);
-    for (int64_t e = b * 256 + threadIdx.x; e < n8; e += nb * 256) {
-      if constexpr (sizeof(T) == 4) {
-        const float4 p = *reinterpret_cast<const float4*>(in + e * 8), q = *reinterpret_cast<const float4*>(in + e * 8 + 4);
-        *reinterpret_cast<uint4*>(out + e * 8) =
-            make_uint4(pack_bf16x2(p.x, p.y), pack_bf16x2(p.z, p.w), pack_bf16x2(q.x, q.y), pack_bf16x2(q.z, q.w));
-      } else {
-        *reinterpret_cast<uint4*>(out + e * 8) = *reinterpret_cast<const uint4*>(in + e * 8);
-      }
-    }
+    for (int64_t e = b * 256 + threadIdx.x; e < n8; e += nb * 256) chunk(in + e * 8, out + e * 8);
     return;
   }
   const int lane = threadIdx.x & 63;
@@ -229,12 +240,12 @@ struct PrepArgs {
   const int8_t* w_codes; const float* s_w; bf16_t* wqT;             // W_q^T
   int64_t w_ld, c_in, w_ldo; int w_vec;
   TransposeExtra w_ex;
-  int n_gather, gather_x, n_rows, n_w, w_x, w_y;
+  int n_gather, gather_x, n_rows, n_w, w_x, w_y;                   // blocks of the three parts
 };
 template <typename T>
 __global__ __launch_bounds__(256) void k_prep(const PrepArgs p) {
   __shared__ TransposeTile tile;
-  int b = blockIdx.x;
+  int b = blockIdx.x + blockIdx.y * gridDim.x;
   if (b < p.n_gather) {
     gather_block<T>(b % p.gather_x, b / p.gather_x, p.n_gather / p.gather_x, (const T*)p.dy, p.c_out, p.t_out, p.idx, p.k,
                     p.sel, p.kp);
@@ -246,6 +257,7 @@ __global__ __launch_bounds__(256) void k_prep(const PrepArgs p) {
     return;
   }
   b -= p.n_rows;
+  if (b >= p.n_w) return;
   transpose_block<int8_t>(tile, b % p.w_x, (b / p.w_x) % p.w_y, b / (p.w_x * p.w_y), p.w_codes, p.w_ld, p.c_out, p.c_in,
                           nullptr, p.s_w, nullptr, p.wqT, p.w_ldo, 0, p.ldc, p.w_vec, p.w_ex);
 }
@@ -482,6 +494,7 @@ struct BwdPlan {
   bool rdw;        // channel-major dY: dW product from the selected rows of dY and the uint8 codes, nothing staged
   bool cdw;        // convolution dW product with the im2col gather of the codes inside the tile loads
   bool cdx;        // convolution dX product with the im2col gather inside the tile loads (no im2col matrix)
+  bool cdxs;       // ... of a convolution with a stride: rows sorted by (h mod stride, w mod stride)
   bool dx8;        // dX product with the weight operand read from the int8 codes (no bf16 W_q^T copy)
   bool kk;         // dX product from the bf16 copies by the 192 x 192 kernel with the pinned instruction order
   int dx8_tile;
@@ -489,6 +502,10 @@ struct BwdPlan {
   GemmPlan plan_dx, plan_dw;
   size_t b_wqT, b_dyn, b_colA, b_part_dx, b_xcT, b_sel, b_part_dw, total;
 };
+
+static ConvDxStridedMap strided_map(const ConvGeom& g) {
+  return ConvDxStridedMap{g.N, g.H, g.W, g.Ho, g.Wo, g.KH, g.KW, g.stride, g.pad};
+}
 
 // dxk: the caller's choice of the dX kernel (EFQAT_DX_KERNEL_*); it changes workspace sizes, so the size query takes
 // it as well.  io_bf16: x and dX are both bf16 (known at the call, not at the workspace query: nothing it changes
@@ -499,8 +516,12 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
   BwdPlan p{};
   p.Mx = T_in; p.Tw = T_out; p.Nw = (int64_t)taps * c_in;
   p.ldc = round_up(c_out, 8); p.ldt = round_up(T_out, 8);
+  // A convolution whose channel count is no whole number of 64-channel K stages gets them by zero channels in the bf16
+  // copy of dY (one copy instead of an im2col matrix of KH KW copies), unless that would more than double the product.
+  if (im2col && cg && cg->stride <= kMaxConvStride && dxk != EFQAT_DX_KERNEL_BF16_PINNED && round_up(c_out, 64) <= 2 * c_out)
+    p.ldc = round_up(c_out, 64);
   p.Kx = (int64_t)taps * p.ldc;
-  const bool direct_tok = dy_layout == EFQAT_DY_TOKEN_MAJOR && dy_dtype == EFQAT_BF16 && (c_out % 8) == 0;
+  const bool direct_tok = dy_layout == EFQAT_DY_TOKEN_MAJOR && dy_dtype == EFQAT_BF16 && p.ldc == c_out;
   p.need_dyn = !direct_tok;
   const bool direct_rows = dy_layout == EFQAT_DY_CHANNEL_MAJOR && dy_dtype == EFQAT_BF16 && (T_out % 8) == 0;
   p.cdw = k > 0 && dy_layout == EFQAT_DY_TOKEN_MAJOR && im2col && cg && (c_in % 128) == 0;
@@ -513,7 +534,16 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
   p.need_sel = k > 0 && !direct_rows && !p.tn_direct;
   // stride-1 convolutions whose channel pitch is a multiple of the 64-element K stage gather dY in the tile loads
   p.cdx = im2col && cg && cg->stride == 1 && (p.ldc % 64) == 0 && cg->H <= 65535 && cg->W <= 65535;
+  // Strides 2 to 4 (a 3 x 3 kernel at stride 2 forms 9 products per 4 pixels instead of 36, and no im2col matrix of 9
+  // copies of dY: 32 x 28 x 28, 128 -> 256 channels, fp32: the im2col pass took 42 us, the backward call 108 -> 51 us); larger
+  // strides have too many phases to sort the rows for.
+  p.cdxs = im2col && cg && cg->stride > 1 && cg->stride <= kMaxConvStride && (p.ldc % 64) == 0 && cg->H <= 65535 && cg->W <= 65535 &&
+           dxk != EFQAT_DX_KERNEL_BF16_PINNED;
   p.plan_dx = gemm_plan(p.Mx, c_in, p.Kx, false, true, !p.cdx);
+  if (p.cdxs) {
+    p.cdx = true;
+    p.plan_dx = GemmPlan{128, 1, (int)conv_dx_strided_row_tiles(strided_map(*cg), 128), (int)ceil_div(c_in, 128)};
+  }
   p.dx8 = false; p.dx8_tile = 0;
   // Large products (the planner's 256 x 256 case) with a bf16 token-major dY read the weight operand straight
   // from the int8 codes: same speed as the bf16 kernel on these shapes, and no transposed bf16 copy of W_q.
@@ -637,7 +667,8 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   if (!p.dx8 && io.w_operand) wqT = (bf16_t*)const_cast<void*>(io.w_operand);
   const bool gather = p.tn && !p.tn_direct;
   const bool copy_dy = p.need_dyn && io.dy_layout == EFQAT_DY_TOKEN_MAJOR;
-  const dim3 ggrid((unsigned)ceil_div(p.kp, 128), (unsigned)std::min<int64_t>(ceil_div(T_out, kGatherRows), 65535));
+  const int64_t gx = std::max<int64_t>(1, ceil_div(p.kp, 128));
+  const dim3 ggrid((unsigned)gx, (unsigned)std::min(ceil_div(T_out, kGatherRows), std::max<int64_t>(1, std::min<int64_t>(65535, (1 << 24) / gx))));
   if (own_wqT || copy_dy || (gather && !use_side)) {
     PrepArgs a{};
     a.dy = io.dy; a.c_out = c_out; a.t_out = T_out; a.ldc = p.ldc;
@@ -648,6 +679,8 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
     if (copy_dy) {
       // dY as a token-major bf16 matrix [T_out][ldc] (A operand of the dX product)
       a.dyn = dyn; a.rows_flat = p.ldc == c_out ? 1 : 0;
+      if (!a.rows_flat && (c_out % 8) == 0)
+        for (a.rows_flat = 2; a.rows_flat < 64 && a.rows_flat < p.ldc / 8;) a.rows_flat *= 2;
       a.n_rows = (int)std::min<int64_t>(a.rows_flat ? ceil_div(T_out * p.ldc, 256 * 16) : ceil_div(T_out, 4), 4096);
     }
     if (own_wqT) {
@@ -658,7 +691,9 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
       a.w_x = (int)ceil_div(p.ldc, 64); a.w_y = (int)ceil_div(c_in, 64);
       a.n_w = a.w_x * a.w_y * taps;
     }
-    const dim3 grid((unsigned)(a.n_gather + a.n_rows + a.n_w));
+    // a grid dimension holds less than 2^32 work items
+    const int64_t blocks = (int64_t)a.n_gather + a.n_rows + a.n_w, bx = std::min<int64_t>(blocks, 1 << 22);
+    const dim3 grid((unsigned)bx, (unsigned)ceil_div(blocks, bx));
     if (io.dy_dtype == EFQAT_F32) hipLaunchKernelGGL((k_prep<float>), grid, dim3(256), 0, st, a);
     else hipLaunchKernelGGL((k_prep<bf16_t>), grid, dim3(256), 0, st, a);
     EFQAT_LAUNCH_CHECK();
@@ -695,6 +730,8 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
                               p.dx8_tile, epi, st);
     else
       rc = launch_gemm_dx8(dy_tok, c_out, io.w_codes, c_in, io.s_w, p.Mx, c_in, c_out, p.dx8_tile, epi, st);
+  } else if (p.cdxs) {
+    rc = launch_gemm_conv_dx_strided(dy_tok, p.ldc, wqT, p.Kx, p.Mx, c_in, strided_map(*cg), p.plan_dx, epi, st);
   } else if (p.cdx) {
     const ConvDxMap cm{cg->H, cg->W, cg->Ho, cg->Wo, cg->KW, cg->pad};
     rc = launch_gemm_nt_conv_dx(dy_tok, p.ldc, wqT, p.Kx, p.Mx, c_in, p.Kx, cm, p.plan_dx, epi, st);

@@ -152,6 +152,14 @@ struct ConvDxMap { int H, W, Ho, Wo, KW, pad; };
 int launch_gemm_nt_conv_dx(const bf16_t* dy_tok, int64_t ldc, const bf16_t* wqT, int64_t ldb, int64_t M, int64_t N,
                            int64_t K, const ConvDxMap& cm, const GemmPlan& plan, const GemmEpilogueDx& epi,
                            hipStream_t stream);
+// The same for a stride of 2 to 4: rows sorted by (h mod stride, w mod stride), plan.tile 128, plan.tiles_m =
+// conv_dx_strided_row_tiles (whole tiles per phase).
+constexpr int kMaxConvStride = 4;
+struct ConvDxStridedMap { int N, H, W, Ho, Wo, KH, KW, stride, pad; };
+int64_t conv_dx_strided_row_tiles(const ConvDxStridedMap& cm, int tile);
+int launch_gemm_conv_dx_strided(const bf16_t* dy_tok, int64_t ldc, const bf16_t* wqT, int64_t ldb, int64_t M, int64_t N,
+                                const ConvDxStridedMap& cm, const GemmPlan& plan, const GemmEpilogueDx& epi,
+                                hipStream_t stream);
 // dX product with the weight operand read from the int8 codes (K-major [C_out][ldb]) and scaled by s_w[c] in
 // registers, fused dX epilogue.  dy: bf16 [M][lda]; N = C_in multiple of 16; tile 256 or 128.  The partial-sum
 // array of the epilogue needs ceil(M / tile) * ceil(N / tile) pairs.

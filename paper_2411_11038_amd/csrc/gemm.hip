@@ -77,9 +77,10 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 // EPI: EPI_RAW fp32 partial tiles (split-K), EPI_DX fused dX epilogue, EPI_FWD forward epilogue.
 // I8: operands are int8 codes (A unsigned, re-biased by 128 in registers) on v_mfma_i32_32x32x32_i8; else bf16.
-// CONV: the A operand is gathered from a token-major dY with the im2col map of a stride-1 convolution (see GemmArgs).
-template <int BM, int BN, int EPI, bool I8, bool CONV = false>
-__global__ __launch_bounds__(256) void k_gemm_nt(const GemmArgs g) {
+// CONV = 1: the A operand is gathered from a token-major dY with the im2col map of a stride-1 convolution (see GemmArgs);
+// CONV = 2: of a convolution with a stride, rows sorted by phase (see ConvPhase).
+template <int BM, int BN, int EPI, bool I8, int CONV = 0>
+__global__ __launch_bounds__(256) void k_gemm_nt(const typename ConvArgs<CONV>::type g) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the body uses gfx950-only builtins; the host pass needs only the launch stub
   constexpr int S = 2;
   constexpr int ESZ = I8 ? 1 : 2;                       // bytes per K element
@@ -102,8 +103,10 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const GemmArgs g) {
   const int group = pid / per_group;
   const int first_m = group * GM;
   const int gsize = (g.tiles_m - first_m) < GM ? (g.tiles_m - first_m) : GM;
-  const int tm = first_m + (pid % per_group) % gsize;
-  const int tn = (pid % per_group) / gsize;
+  int tm = first_m + (pid % per_group) % gsize;
+  int tn = (pid % per_group) / gsize;
+  ConvPhase ph;
+  if constexpr (CONV == 2) strided_tile(g, blockIdx.x, &ph, &tm, &tn);
   const int m0 = tm * BM, n0 = tn * BN;
   const int lm0 = m0, ln0 = n0;
 
@@ -121,8 +124,12 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const GemmArgs g) {
 #pragma unroll
   for (int j = 0; j < C::A_G; ++j) {
     int gm = lm0 + (wave + 4 * j) * C::RPI + lrow;
-    gm = gm < g.M ? gm : g.M - 1;                       // rows past the edge re-read a valid row
-    if constexpr (CONV) {
+    const int rows = CONV == 2 ? ph.rows : g.M;
+    gm = gm < rows ? gm : rows - 1;                     // rows past the edge re-read a valid row
+    if constexpr (CONV == 2) {
+      strided_pixel(g, ph, gm, &cv_q0[j], &cv_hw[j]);
+      a_ptr[j] = nullptr;
+    } else if constexpr (CONV) {
       const int hw = g.cv_H * g.cv_W;
       const int n = gm / hw, rem = gm - n * hw;
       const int h = rem / g.cv_W, w = rem - h * g.cv_W;
@@ -136,7 +143,14 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const GemmArgs g) {
   }
   // source of this lane's 16 bytes of A-slot j in stage kt
   auto a_src = [&](int j, int kt) -> const char* {
-    if constexpr (CONV) {
+    if constexpr (CONV == 2) {
+      int a, b, cst;
+      strided_stage(g, ph, kt, &a, &b, &cst);
+      const int ho = (cv_hw[j] >> 16) + ph.dh0 - a, wo = (cv_hw[j] & 0xFFFF) + ph.dw0 - b;
+      const bool ok = (unsigned)ho < (unsigned)g.cv_Ho && (unsigned)wo < (unsigned)g.cv_Wo;
+      const int64_t pix = (int64_t)cv_q0[j] + ho * g.cv_Wo + wo;
+      return ok ? (const char*)g.A + (pix * g.lda + cst * 64) * 2 + lch * 16 : zero_page();
+    } else if constexpr (CONV) {
       const int sidx = k_begin / 64 + kt;              // 64-channel stage index along K = (tap, channel)
       const int tap = (int)(((uint64_t)(uint32_t)sidx * g.cv_m_spt) >> 32), cst = sidx - tap * g.cv_spt;
       const int kh = (int)(((uint64_t)(uint32_t)tap * g.cv_m_kw) >> 32), kw = tap - kh * g.cv_KW;
@@ -154,7 +168,18 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const GemmArgs g) {
     gn = gn < g.N ? gn : g.N - 1;
     b_ptr[j] = (const char*)g.B + ((int64_t)gn * g.ldb + k_begin) * ESZ + lch * 16;
   }
-  const int span = k_end - k_begin;
+  // byte offset of stage kt in a B row: the stages of a strided convolution's phase skip the other phases' taps
+  auto b_off = [&](int kt) -> int64_t {
+    if constexpr (CONV == 2) {
+      int a, b, cst;
+      strided_stage(g, ph, kt, &a, &b, &cst);
+      const int tap = (ph.kh0 + g.cv_stride * a) * g.cv_KW + ph.kw0 + g.cv_stride * b;
+      return (int64_t)(tap * g.cv_spt + cst) * 128;
+    } else {
+      return kt * 128;
+    }
+  };
+  const int span = CONV == 2 ? ph.ntap * g.cv_spt * 64 : k_end - k_begin;
   const int nfull = span > 0 ? span / BKT : 0;         // stages that need no predicate
   const int nk = span > 0 ? (span + BKT - 1) / BKT : 0;
 
@@ -162,13 +187,12 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const GemmArgs g) {
   auto issue_direct = [&](int kt, int buf) {           // a full, unpredicated stage
     char* sa = smem + buf * C::LDS_STAGE;
     char* sb = sa + C::LDS_A;
-    const int koff = kt * 128;                          // bytes
 #pragma unroll
     for (int j = 0; j < C::A_G; ++j)
       __builtin_amdgcn_global_load_lds(a_src(j, kt), (lds_ptr_t)(sa + (wave + 4 * j) * 1024), 16, 0, 0);
 #pragma unroll
     for (int j = 0; j < C::B_G; ++j)
-      __builtin_amdgcn_global_load_lds(b_ptr[j] + koff, (lds_ptr_t)(sb + (wave + 4 * j) * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(b_ptr[j] + b_off(kt), (lds_ptr_t)(sb + (wave + 4 * j) * 1024), 16, 0, 0);
   };
   // any stage: a ragged last stage goes through registers.  K is a multiple of 8, so a 16-byte chunk is
   // all in or all out; missing chunks are written as zeros.
@@ -187,7 +211,7 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const GemmArgs g) {
       }
 #pragma unroll
       for (int j = 0; j < C::B_G; ++j) {
-        const uint4 v = ok ? *reinterpret_cast<const uint4*>(b_ptr[j] + koff) : make_uint4(0, 0, 0, 0);
+        const uint4 v = ok ? *reinterpret_cast<const uint4*>(b_ptr[j] + b_off(kt)) : make_uint4(0, 0, 0, 0);
         *reinterpret_cast<uint4*>(sb + (wave + 4 * j) * 1024 + lane * 16) = v;
       }
     }
@@ -249,13 +273,12 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const GemmArgs g) {
   auto issue_range = [&](int kt, int buf, int t0, int t1) {
     char* sa = smem + buf * C::LDS_STAGE;
     char* sb = sa + C::LDS_A;
-    const int koff = kt * 128;                          // bytes
 #pragma unroll
     for (int t = t0; t < t1; ++t) {
       if (t < C::A_G)
         __builtin_amdgcn_global_load_lds(a_src(t, kt), (lds_ptr_t)(sa + (wave + 4 * t) * 1024), 16, 0, 0);
       else
-        __builtin_amdgcn_global_load_lds(b_ptr[t - C::A_G] + koff,
+        __builtin_amdgcn_global_load_lds(b_ptr[t - C::A_G] + b_off(kt),
                                          (lds_ptr_t)(sb + (wave + 4 * (t - C::A_G)) * 1024), 16, 0, 0);
     }
   };
@@ -265,6 +288,15 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const GemmArgs g) {
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
   };
+
+  // CONV = 2: the matrix row of every tile row, behind the stages in LDS
+  int* rowmap = reinterpret_cast<int*>(smem + C::LDS_BYTES);
+  if constexpr (CONV == 2) {
+    if (tid < BM) {
+      int q0, hw;
+      rowmap[tid] = m0 + tid < ph.rows ? strided_pixel(g, ph, m0 + tid, &q0, &hw) : -1;
+    }
+  }
 
   if (nk > 0) issue(0, 0);
   wait_vmcnt<0>();
@@ -335,7 +367,7 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const GemmArgs g) {
         }
       }
   } else if constexpr (EPI == EPI_DX) {
-    epilogue_dx<C>(g, acc, smem, m0, n0, wm, wn);
+    epilogue_dx<C, CONV == 2>(g, acc, smem, m0, n0, wm, wn, rowmap);
   } else if constexpr (EPI == EPI_DXF) {
     epilogue_dx_fast<C>(g, acc, smem, m0, n0, wm, wn);
   } else {
@@ -453,17 +485,18 @@ bool gemm_epilogue_vec_ok(const GemmEpilogueDx& e, int64_t N) {
   return (N % 8) == 0 && ((uintptr_t)e.x_codes % 8) == 0 && ((uintptr_t)e.x % 16) == 0 && ((uintptr_t)e.dx % 16) == 0;
 }
 
-template <int BM, int BN, int EPI, bool I8, bool CONV = false>
-static int launch_cfg(const GemmArgs& a, int split_k, hipStream_t st) {
+template <int BM, int BN, int EPI, bool I8, int CONV = 0>
+static int launch_cfg(const typename ConvArgs<CONV>::type& a, int split_k, hipStream_t st) {
   using C = TileCfg<BM, BN, 2>;
+  constexpr int kLds = C::LDS_BYTES + (CONV == 2 ? BM * (int)sizeof(int) : 0);
   // set once per process (initialisation of a function-local static is thread-safe)
-  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_nt<BM, BN, EPI, I8, CONV>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
+  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_nt<BM, BN, EPI, I8, CONV>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return EFQAT_ERR_HIP;
   dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)split_k);
   constexpr int kProf = (EPI == EPI_DX || EPI == EPI_DXF) ? PROF_DX : (EPI == EPI_RAW ? PROF_DW : PROF_FWD);
   {
     ProfScope prof(kProf, st);
-    hipLaunchKernelGGL((k_gemm_nt<BM, BN, EPI, I8, CONV>), grid, dim3(256), C::LDS_BYTES, st, a);
+    hipLaunchKernelGGL((k_gemm_nt<BM, BN, EPI, I8, CONV>), grid, dim3(256), kLds, st, a);
   }
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
@@ -528,15 +561,79 @@ int launch_gemm_nt_conv_dx(const bf16_t* dy_tok, int64_t ldc, const bf16_t* wqT,
   a.cv_spt = (int)(ldc / 64);
   a.cv_m_spt = (1ull << 32) / (uint64_t)a.cv_spt + 1; a.cv_m_kw = (1ull << 32) / (uint64_t)cm.KW + 1;
   switch (plan.tile) {
-    case 192: return nt_epilogue_fast(a, epi, 192) ? launch_cfg<192, 192, EPI_DXF, false, true>(a, 1, stream)
-                                                   : launch_cfg<192, 192, EPI_DX, false, true>(a, 1, stream);
+    case 192: return nt_epilogue_fast(a, epi, 192) ? launch_cfg<192, 192, EPI_DXF, false, 1>(a, 1, stream)
+                                                   : launch_cfg<192, 192, EPI_DX, false, 1>(a, 1, stream);
     case 128:
       // at most one block per compute unit anyway: the three-stage ring hides the load latency a lone block sees
       if ((int64_t)a.tiles_m * a.tiles_n <= 256) return launch_gemm_kk_conv128(a, nt_epilogue_fast(a, epi, 128), stream);
-      return nt_epilogue_fast(a, epi, 128) ? launch_cfg<128, 128, EPI_DXF, false, true>(a, 1, stream)
-                                           : launch_cfg<128, 128, EPI_DX, false, true>(a, 1, stream);
+      return nt_epilogue_fast(a, epi, 128) ? launch_cfg<128, 128, EPI_DXF, false, 1>(a, 1, stream)
+                                           : launch_cfg<128, 128, EPI_DX, false, 1>(a, 1, stream);
     default: return EFQAT_ERR_BAD_SHAPE;
   }
+}
+
+// Phases of a convolution with stride s <= kMaxConvStride, most taps first; returns the row tiles in all.
+static int64_t conv_phases(const ConvDxStridedMap& cm, int tile, ConvPhase* out, int* nphase) {
+  ConvPhase p[kMaxConvStride * kMaxConvStride];
+  int n = 0;
+  const int s = cm.stride;
+  // taps kh with (ph + pad - kh) % s == 0: kh0 = (ph + pad) % s, kh0 + s, ...; the first reaches output row hi + dh0
+  auto taps = [s](int K, int first) { return first < K ? (K - first + s - 1) / s : 0; };
+  for (int ph = 0; ph < s; ++ph)
+    for (int pw = 0; pw < s; ++pw) {
+      ConvPhase c{};
+      c.ph = ph; c.pw = pw;
+      c.Hp = cm.H > ph ? (cm.H - ph + s - 1) / s : 0;
+      c.Wp = cm.W > pw ? (cm.W - pw + s - 1) / s : 0;
+      c.rows = cm.N * c.Hp * c.Wp;
+      c.kh0 = (ph + cm.pad) % s; c.kw0 = (pw + cm.pad) % s;
+      c.dh0 = (ph + cm.pad) / s; c.dw0 = (pw + cm.pad) / s;
+      const int nkh = taps(cm.KH, c.kh0);
+      c.nkw = taps(cm.KW, c.kw0);
+      c.ntap = nkh * c.nkw;
+      if (c.nkw == 0) c.nkw = 1;                        // never divided by
+      c.tiles = (int)ceil_div(c.rows, tile);
+      if (c.rows > 0) p[n++] = c;
+    }
+  int64_t total = 0;
+  for (int i = 0; i < n; ++i) {                         // selection by taps, stable
+    int best = -1;
+    for (int j = 0; j < n; ++j)
+      if (p[j].tiles >= 0 && (best < 0 || p[j].ntap > p[best].ntap)) best = j;
+    ConvPhase c = p[best];
+    p[best].tiles = -1;
+    c.tile0 = (int)total;
+    total += c.tiles;
+    if (out) out[i] = c;
+  }
+  if (nphase) *nphase = n;
+  return total;
+}
+
+int64_t conv_dx_strided_row_tiles(const ConvDxStridedMap& cm, int tile) { return conv_phases(cm, tile, nullptr, nullptr); }
+
+int launch_gemm_conv_dx_strided(const bf16_t* dy_tok, int64_t ldc, const bf16_t* wqT, int64_t ldb, int64_t M, int64_t N,
+                                const ConvDxStridedMap& cm, const GemmPlan& plan, const GemmEpilogueDx& epi,
+                                hipStream_t stream) {
+  if (M <= 0 || N <= 0 || (ldc % 64) || (ldb % 8) || cm.H > 65535 || cm.W > 65535 || cm.stride < 2 ||
+      cm.stride > kMaxConvStride || plan.tile != 128 || plan.split_k != 1 || M > INT32_MAX || N > INT32_MAX)
+    return EFQAT_ERR_BAD_SHAPE;
+  GemmStridedArgs a{};
+  a.A = dy_tok; a.lda = ldc; a.B = wqT; a.ldb = ldb;
+  a.M = (int)M; a.N = (int)N;
+  a.x_codes = epi.x_codes; a.x_clip = epi.x_clip; a.x = epi.x; a.x_dtype = epi.x_dtype;
+  a.s_x = epi.s_x; a.z_x = epi.z_x; a.dx = epi.dx; a.dx_dtype = epi.dx_dtype; a.partial = epi.partial;
+  a.epi_vec = gemm_epilogue_vec_ok(epi, N) ? 1 : 0;
+  a.cv_H = cm.H; a.cv_W = cm.W; a.cv_Ho = cm.Ho; a.cv_Wo = cm.Wo; a.cv_KW = cm.KW; a.cv_pad = cm.pad;
+  a.cv_stride = cm.stride;
+  a.cv_spt = (int)(ldc / 64);
+  a.cv_m_spt = (1ull << 32) / (uint64_t)a.cv_spt + 1;
+  a.tiles_n = plan.tiles_n;
+  a.tiles_m = (int)conv_phases(cm, plan.tile, a.phase, &a.nphase);
+  if (a.tiles_m != plan.tiles_m) return EFQAT_ERR_BAD_SHAPE;
+  // as at stride 1: a lone block per compute unit takes the three-stage ring, more share a unit in pairs
+  if ((int64_t)a.tiles_m * a.tiles_n <= 256) return launch_gemm_kk_conv128_strided(a, stream);
+  return launch_cfg<128, 128, EPI_DX, false, 2>(a, 1, stream);
 }
 
 int launch_gemm_fwd_i8(const uint8_t* x_codes, int64_t lda, const int8_t* w_codes, int64_t ldb, int64_t M, int64_t N,

@@ -29,8 +29,48 @@ struct GemmArgs {
   uint64_t cv_m_spt, cv_m_kw;   // floor(2^32 / d) + 1 for d = cv_spt, cv_KW: n / d = (n * m) >> 32 for n * d < 2^32
 };
 
-// dX product of a stride-1 convolution on 128 x 128 tiles by the kernel with the three-stage ring (gemm_kk.hip)
+// dX product of a convolution with a stride: the input pixels are sorted into stride x stride phases (h mod s, w mod s),
+// and a row tile lies inside one phase, whose pixels all receive the same taps kh = kh0 + s a, kw = kw0 + s b from the
+// output pixel (hi + dh0 - a, wi + dw0 - b), hi = h / s, wi = w / s.  K of a tile = the taps of its phase, so no products
+// with the zeros between the strides are formed (3 of 4 at stride 2); a phase without taps has K = 0 and dX = 0.
+struct ConvPhase { int tile0, tiles, rows, Hp, Wp, ph, pw, ntap, nkw, kh0, kw0, dh0, dw0; };
+struct GemmStridedArgs : GemmArgs {
+  int cv_stride, nphase;
+  ConvPhase phase[kMaxConvStride * kMaxConvStride];    // most taps first: the longest tiles start first
+};
+template <int CONV> struct ConvArgs { typedef GemmArgs type; };
+template <> struct ConvArgs<2> { typedef GemmStridedArgs type; };
+
+// dX product of a convolution on 128 x 128 tiles by the kernel with the three-stage ring (gemm_kk.hip)
 int launch_gemm_kk_conv128(const GemmArgs& a, bool fast, hipStream_t stream);
+int launch_gemm_kk_conv128_strided(const GemmStridedArgs& a, hipStream_t stream);
+
+// phase and phase-local row tile / column tile of a block: each XCD gets a contiguous range of every phase's tiles
+__device__ __forceinline__ void strided_tile(const GemmStridedArgs& g, int block, ConvPhase* ph, int* tm, int* tn) {
+  int f = 0;
+  while (f + 1 < g.nphase && block >= g.phase[f + 1].tile0 * g.tiles_n) ++f;
+  *ph = g.phase[f];
+  const int pid = xcd_contiguous_index(block - ph->tile0 * g.tiles_n, ph->tiles * g.tiles_n);
+  *tm = pid / g.tiles_n;
+  *tn = pid - *tm * g.tiles_n;
+}
+// (n * Ho * Wo) and (hi << 16 | wi) of phase-local row r; its input pixel
+__device__ __forceinline__ int strided_pixel(const GemmStridedArgs& g, const ConvPhase& ph, int r, int* q0, int* hw) {
+  const int per = ph.Hp * ph.Wp;
+  const int n = r / per, rem = r - n * per;
+  const int hi = rem / ph.Wp, wi = rem - hi * ph.Wp;
+  *q0 = n * g.cv_Ho * g.cv_Wo;
+  *hw = (hi << 16) | wi;
+  return (n * g.cv_H + hi * g.cv_stride + ph.ph) * g.cv_W + wi * g.cv_stride + ph.pw;
+}
+// (a, b) of the phase's tap and the channel stage of K stage sidx
+__device__ __forceinline__ void strided_stage(const GemmStridedArgs& g, const ConvPhase& ph, int sidx, int* a, int* b,
+                                              int* cst) {
+  const int t = (int)(((uint64_t)(uint32_t)sidx * g.cv_m_spt) >> 32);
+  *cst = sidx - t * g.cv_spt;
+  *a = t / ph.nkw;
+  *b = t - *a * ph.nkw;
+}
 
 // Block barrier that orders LDS traffic only.  __syncthreads() also fences global memory, i.e. waits for every
 // outstanding global load and store of the wavefront; between the staging writes and reads of an epilogue that
@@ -44,9 +84,11 @@ __device__ __forceinline__ void lds_barrier() {
 // Fused epilogue of the dX product for a 256-thread block whose wavefront (wm, wn) holds the C::WM x C::WN
 // sub-tile at (m0 + wm * C::WM, n0 + wn * C::WN) of an M x N output in C::TM x C::TN 32x32 MFMA accumulators.
 // smem: at least 4 * 32 * (C::WN + 8) floats, no longer used by the main loop (the caller has synchronised).
-template <class C>
+// MAP: the matrix row of the block's row r is rowmap[r] (LDS, -1 past the last row) instead of m0 + r.
+template <class C, bool MAP = false>
 __device__ __forceinline__ void epilogue_dx(const GemmArgs& g, floatx16_t (&acc)[C::TM][C::TN], char* smem, int m0,
-                                            int n0, int wm, int wn) {
+                                            int n0, int wm, int wn, const int* rowmap = nullptr) {
+  auto row_of = [&](int r) -> int { if constexpr (MAP) return rowmap[r]; else return m0 + r; };
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int fr = lane & 31, fh = lane >> 5;
@@ -77,8 +119,8 @@ __device__ __forceinline__ void epilogue_dx(const GemmArgs& g, floatx16_t (&acc)
 #pragma unroll
       for (int p = 0; p < NPASS; ++p) {
         const int row_l = p * RPP + row_l0;
-        const int grow = m0 + wm * C::WM + i * 32 + row_l;
-        if (lane_on && row_l < 32 && grow < g.M) {
+        const int grow = row_l < 32 ? row_of(wm * C::WM + i * 32 + row_l) : -1;
+        if (lane_on && grow >= 0 && grow < g.M) {
           const int64_t e = (int64_t)grow * g.N + gcol;
           in[b][p].mb = g.x_clip[(int64_t)grow * wpr + (gcol >> 5)] >> (gcol & 31);
           in[b][p].cw = *reinterpret_cast<const uint2*>(g.x_codes + e);
@@ -106,8 +148,8 @@ __device__ __forceinline__ void epilogue_dx(const GemmArgs& g, floatx16_t (&acc)
 #pragma unroll
       for (int p = 0; p < NPASS; ++p) {
         const int row_l = p * RPP + row_l0;
-        const int grow = m0 + wm * C::WM + i * 32 + row_l;
-        if (lane_on && row_l < 32 && grow < g.M) {
+        const int grow = row_l < 32 ? row_of(wm * C::WM + i * 32 + row_l) : -1;
+        if (lane_on && grow >= 0 && grow < g.M) {
           const float4 a0 = *reinterpret_cast<const float4*>(stage + row_l * PITCH + ch * 8);
           const float4 a1 = *reinterpret_cast<const float4*>(stage + row_l * PITCH + ch * 8 + 4);
           const float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
@@ -163,8 +205,8 @@ __device__ __forceinline__ void epilogue_dx(const GemmArgs& g, floatx16_t (&acc)
 #pragma unroll
       for (int p = 0; p < NPASS; ++p) {
         const int row_l = p * RPP + row_l0;
-        const int grow = m0 + wm * C::WM + i * 32 + row_l;
-        if (lane_on && row_l < 32 && grow < g.M) {
+        const int grow = row_l < 32 ? row_of(wm * C::WM + i * 32 + row_l) : -1;
+        if (lane_on && grow >= 0 && grow < g.M) {
           const int64_t e = (int64_t)grow * g.N + gcol;
 #pragma unroll
           for (int t = 0; t < 8; ++t) {

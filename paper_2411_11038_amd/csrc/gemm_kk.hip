@@ -41,18 +41,14 @@ struct KkCfg {
   static_assert(WGM * WGN == 4 && WM % 32 == 0 && WN % 32 == 0 && BM % 32 == 0, "tile / wavefront grid");
 };
 
-struct GemmKkArgs {
-  GemmArgs g;              // A, lda, B, ldb, M, N, K, k_per_split, tiles, out or the fused dX epilogue fields
-};
-
-// CONV: the A operand is gathered from a token-major dY with the im2col map of a stride-1 convolution, as in
+// CONV = 1: the A operand is gathered from a token-major dY with the im2col map of a stride-1 convolution, as in
 // k_gemm_nt (see GemmArgs): every copy slot keeps (n, h, w) of its input pixel and forms its source address per stage
-// from the stage's tap; K = taps * ldc is a whole number of stages.
-template <int T, int WGM, int WGN, int EPI, bool CONV = false>
-__global__ __launch_bounds__(256) void k_gemm_kk(const GemmKkArgs ga) {
+// from the stage's tap; K = taps * ldc is a whole number of stages.  CONV = 2: a convolution with a stride, rows sorted
+// by phase (see ConvPhase); W_q^T is read at the stage's tap as well.
+template <int T, int WGM, int WGN, int EPI, int CONV = 0>
+__global__ __launch_bounds__(256) void k_gemm_kk(const typename ConvArgs<CONV>::type g) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using C = KkCfg<T, WGM, WGN>;
-  const GemmArgs& g = ga.g;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -69,13 +65,15 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const GemmKkArgs ga) {
   const int group = pid / per_group;
   const int first_m = group * GM;
   const int gsize = (g.tiles_m - first_m) < GM ? (g.tiles_m - first_m) : GM;
-  const int tm = first_m + (pid % per_group) % gsize;
-  const int tn = (pid % per_group) / gsize;
+  int tm = first_m + (pid % per_group) % gsize;
+  int tn = (pid % per_group) / gsize;
+  ConvPhase ph;
+  if constexpr (CONV == 2) strided_tile(g, blockIdx.x, &ph, &tm, &tn);
   const int m0 = tm * C::BM, n0 = tn * C::BN;
 
   const int k_begin = split * g.k_per_split;
   const int k_end_ = (k_begin + g.k_per_split) < g.K ? (k_begin + g.k_per_split) : g.K;
-  const int K = k_end_ > k_begin ? k_end_ - k_begin : 0;
+  const int K = CONV == 2 ? ph.ntap * g.cv_spt * 64 : (k_end_ > k_begin ? k_end_ - k_begin : 0);
   const int nk = (K + 63) / 64;
   const int nfull = K / 64;
   const char* zero = zero_page();
@@ -90,8 +88,12 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const GemmKkArgs ga) {
 #pragma unroll
   for (int j = 0; j < C::A_G; ++j) {
     int gm = m0 + (wave + 4 * j) * 8 + c_lrow;
-    gm = gm < g.M ? gm : g.M - 1;
-    if constexpr (CONV) {
+    const int rows = CONV == 2 ? ph.rows : g.M;
+    gm = gm < rows ? gm : rows - 1;
+    if constexpr (CONV == 2) {
+      strided_pixel(g, ph, gm, &cv_q0[j], &cv_hw[j]);
+      a_ptr[j] = nullptr;
+    } else if constexpr (CONV) {
       const int hw = g.cv_H * g.cv_W;
       const int n = gm / hw, rem = gm - n * hw;
       const int h = rem / g.cv_W, w = rem - h * g.cv_W;
@@ -104,6 +106,14 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const GemmKkArgs ga) {
   }
   // CONV: source of this lane's 16 bytes of A slot j in stage kt (the zero page when the tap falls outside the image)
   auto a_src_conv = [&](int j, int kt) -> const char* {
+    if constexpr (CONV == 2) {
+      int a, b, cst;
+      strided_stage(g, ph, kt, &a, &b, &cst);
+      const int ho = (cv_hw[j] >> 16) + ph.dh0 - a, wo = (cv_hw[j] & 0xFFFF) + ph.dw0 - b;
+      const bool ok = (unsigned)ho < (unsigned)g.cv_Ho && (unsigned)wo < (unsigned)g.cv_Wo;
+      const int64_t pix = (int64_t)cv_q0[j] + ho * g.cv_Wo + wo;
+      return ok ? (const char*)g.A + (pix * g.lda + cst * 64) * 2 + c_lch * 16 : zero;
+    } else {
     const int sidx = k_begin / 64 + kt;                // 64-channel stage index along K = (tap, channel)
     const int tap = (int)(((uint64_t)(uint32_t)sidx * g.cv_m_spt) >> 32), cst = sidx - tap * g.cv_spt;
     const int kh = (int)(((uint64_t)(uint32_t)tap * g.cv_m_kw) >> 32), kw = tap - kh * g.cv_KW;
@@ -111,6 +121,7 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const GemmKkArgs ga) {
     const bool ok = (unsigned)ho < (unsigned)g.cv_Ho && (unsigned)wo < (unsigned)g.cv_Wo;
     const int64_t pix = (int64_t)cv_q0[j] + ho * g.cv_Wo + wo;
     return ok ? (const char*)g.A + (pix * g.lda + cst * 64) * 2 + c_lch * 16 : zero;
+    }
   };
 #pragma unroll
   for (int j = 0; j < C::B_G; ++j) {
@@ -136,8 +147,15 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const GemmKkArgs ga) {
         }
       } else {
         const int u = t - C::A_G;
-        dma16(off ? zero : b_ptr[u], sb + (wave + 4 * u) * 1024);
-        b_ptr[u] += 128;
+        if constexpr (CONV == 2) {
+          int a, b, cst;
+          strided_stage(g, ph, kt, &a, &b, &cst);
+          const int tap = (ph.kh0 + g.cv_stride * a) * g.cv_KW + ph.kw0 + g.cv_stride * b;
+          dma16(b_ptr[u] + (int64_t)(tap * g.cv_spt + cst) * 128, sb + (wave + 4 * u) * 1024);
+        } else {
+          dma16(off ? zero : b_ptr[u], sb + (wave + 4 * u) * 1024);
+          b_ptr[u] += 128;
+        }
       }
     }
   };
@@ -283,6 +301,15 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const GemmKkArgs ga) {
   using Steady = std::integral_constant<bool, true>;
   using Drain = std::integral_constant<bool, false>;
 
+  // CONV = 2: the matrix row of every tile row, behind the stages in LDS
+  int* rowmap = reinterpret_cast<int*>(smem + C::LDS_BYTES);
+  if constexpr (CONV == 2) {
+    if (tid < C::BM) {
+      int q0, hw;
+      rowmap[tid] = m0 + tid < ph.rows ? strided_pixel(g, ph, m0 + tid, &q0, &hw) : -1;
+    }
+  }
+
   if (nk > 0) issue_range(Checked{}, 0, 0, 0, LPS);
   if (nk > 1) issue_range(Checked{}, 1, 1, 0, LPS);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -303,7 +330,7 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const GemmKkArgs ga) {
   __syncthreads();
 
   if constexpr (EPI == EPI_DX) {
-    epilogue_dx<C>(g, acc, smem, m0, n0, wm, wn);
+    epilogue_dx<C, CONV == 2>(g, acc, smem, m0, n0, wm, wn, rowmap);
   } else if constexpr (EPI == EPI_DXF) {
     epi.run(g, acc, smem, blockIdx.x);
   } else {
@@ -323,16 +350,17 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const GemmKkArgs ga) {
 #endif
 }
 
-template <int T, int WGM, int WGN, int EPI, bool CONV = false>
-static int launch_kk_cfg(const GemmKkArgs& a, int split_k, hipStream_t st) {
+template <int T, int WGM, int WGN, int EPI, int CONV = 0>
+static int launch_kk_cfg(const typename ConvArgs<CONV>::type& a, int split_k, hipStream_t st) {
   using C = KkCfg<T, WGM, WGN>;
   // set once per process (initialisation of a function-local static is thread-safe)
-  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_kk<T, WGM, WGN, EPI, CONV>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
+  constexpr int kLds = C::LDS_BYTES + (CONV == 2 ? C::BM * (int)sizeof(int) : 0);
+  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_kk<T, WGM, WGN, EPI, CONV>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return EFQAT_ERR_HIP;
-  dim3 grid((unsigned)(a.g.tiles_m * a.g.tiles_n), (unsigned)split_k);
+  dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)split_k);
   {
     ProfScope prof(EPI == EPI_RAW ? PROF_DW : PROF_DX, st);
-    hipLaunchKernelGGL((k_gemm_kk<T, WGM, WGN, EPI, CONV>), grid, dim3(256), C::LDS_BYTES, st, a);
+    hipLaunchKernelGGL((k_gemm_kk<T, WGM, WGN, EPI, CONV>), grid, dim3(256), kLds, st, a);
   }
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
@@ -346,8 +374,7 @@ int launch_gemm_kk(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, i
   if (((uintptr_t)A % 16) || ((uintptr_t)B % 16)) return EFQAT_ERR_ALIGNMENT;
   const int split_k = plan.split_k;
   if (epi && split_k != 1) return EFQAT_ERR_BAD_SHAPE;
-  GemmKkArgs ka{};
-  GemmArgs& a = ka.g;
+  GemmArgs a{};
   a.A = A; a.lda = lda; a.a_rows = nullptr; a.B = B; a.ldb = ldb;
   a.M = (int)M; a.N = (int)N; a.K = (int)K;
   a.k_per_split = (int)(ceil_div(ceil_div(K, 64), split_k) * 64);   // slices start on whole K-stages
@@ -361,17 +388,17 @@ int launch_gemm_kk(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, i
   a.tiles_n = plan.tiles_n;
   switch (plan.tile) {
     case 192: {
-      if (!epi) return launch_kk_cfg<192, 2, 2, EPI_RAW>(ka, split_k, stream);
+      if (!epi) return launch_kk_cfg<192, 2, 2, EPI_RAW>(a, split_k, stream);
       // nothing to decide at run time: the straight-line epilogue
       const bool fast = a.epi_vec && epi->x_dtype == EFQAT_BF16 && epi->dx_dtype == EFQAT_BF16 && (M % 192) == 0 &&
                         (N % 192) == 0 && M * N <= (int64_t)INT32_MAX;
-      return fast ? launch_kk_cfg<192, 2, 2, EPI_DXF>(ka, 1, stream) : launch_kk_cfg<192, 2, 2, EPI_DX>(ka, 1, stream);
+      return fast ? launch_kk_cfg<192, 2, 2, EPI_DXF>(a, 1, stream) : launch_kk_cfg<192, 2, 2, EPI_DX>(a, 1, stream);
     }
     case 128: {
-      if (!epi) return launch_kk_cfg<128, 2, 2, EPI_RAW>(ka, split_k, stream);
+      if (!epi) return launch_kk_cfg<128, 2, 2, EPI_RAW>(a, split_k, stream);
       const bool fast = a.epi_vec && epi->x_dtype == EFQAT_BF16 && epi->dx_dtype == EFQAT_BF16 && (M % 128) == 0 &&
                         (N % 128) == 0 && M * N <= (int64_t)INT32_MAX;
-      return fast ? launch_kk_cfg<128, 2, 2, EPI_DXF>(ka, 1, stream) : launch_kk_cfg<128, 2, 2, EPI_DX>(ka, 1, stream);
+      return fast ? launch_kk_cfg<128, 2, 2, EPI_DXF>(a, 1, stream) : launch_kk_cfg<128, 2, 2, EPI_DX>(a, 1, stream);
     }
     default:
       return EFQAT_ERR_BAD_SHAPE;
@@ -382,10 +409,13 @@ int launch_gemm_kk(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, i
 // fills it (K a whole number of 64-channel stages, no split-K).
 int launch_gemm_kk_conv128(const GemmArgs& a, bool fast, hipStream_t stream) {
   if ((a.K % 64) != 0) return EFQAT_ERR_BAD_SHAPE;
-  GemmKkArgs ka{};
-  ka.g = a;
-  ka.g.k_per_split = a.K;
-  return fast ? launch_kk_cfg<128, 2, 2, EPI_DXF, true>(ka, 1, stream) : launch_kk_cfg<128, 2, 2, EPI_DX, true>(ka, 1, stream);
+  GemmArgs ka = a;
+  ka.k_per_split = a.K;
+  return fast ? launch_kk_cfg<128, 2, 2, EPI_DXF, 1>(ka, 1, stream) : launch_kk_cfg<128, 2, 2, EPI_DX, 1>(ka, 1, stream);
+}
+
+int launch_gemm_kk_conv128_strided(const GemmStridedArgs& a, hipStream_t stream) {
+  return launch_kk_cfg<128, 2, 2, EPI_DX, 2>(a, 1, stream);
 }
 
 }  // namespace efqat
