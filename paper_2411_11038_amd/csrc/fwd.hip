@@ -113,30 +113,6 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_fwd_skinny(
 #endif
 }
 
-// wsum[c] = sum_i w_codes[c][i]  (exact, int32).  One wavefront per output channel.
-__global__ __launch_bounds__(256) void k_row_sum_i8(const int8_t* __restrict__ w, int64_t rows, int64_t cols,
-                                                    int64_t ld, int32_t* __restrict__ wsum) {
-  const int lane = threadIdx.x & 63;
-  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  const int8_t* p = w + row * ld;
-  int acc = 0;
-  if ((ld % 4) == 0 && ((uintptr_t)w % 4) == 0) {
-    const int64_t n4 = cols >> 2;
-    for (int64_t i = lane; i < n4; i += 64) {
-      const uint32_t v = *reinterpret_cast<const uint32_t*>(p + i * 4);
-      acc += (int)(int8_t)(v & 0xFF) + (int)(int8_t)((v >> 8) & 0xFF) + (int)(int8_t)((v >> 16) & 0xFF) +
-             (int)(int8_t)(v >> 24);
-    }
-    for (int64_t i = (n4 << 2) + lane; i < cols; i += 64) acc += (int)p[i];
-  } else {
-    for (int64_t i = lane; i < cols; i += 64) acc += (int)p[i];
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, kWave);
-  if (lane == 0) wsum[row] = acc;
-}
-
 // out[r][0..ldo) = in[r][0..cols) followed by zeros (byte rows; makes K a multiple of 16 for ragged widths)
 __global__ __launch_bounds__(256) void k_pad_rows_u8(const uint8_t* __restrict__ in, int64_t rows, int64_t cols,
                                                      uint8_t* __restrict__ out, int64_t ldo) {
@@ -152,21 +128,17 @@ constexpr int64_t kSkinnyTokens = 64;
 struct FwdPlan {
   int64_t ldk;       // C_in rounded up to 16
   bool pad;          // operands copied into zero-padded rows
-  GemmPlan plan;
-  size_t b_wsum, b_xpad, b_wpad, total;
+  size_t b_xpad, b_wpad, total;
 };
 
 static FwdPlan make_fwd_plan(int64_t T, int64_t c_in, int64_t c_out) {
   FwdPlan p{};
   p.ldk = round_up(c_in, 16);
   p.pad = p.ldk != c_in;
-  // one stage of the int8 product covers twice the K of a bf16 stage in the same time
-  p.plan = gemm_plan(T, c_out, ceil_div(p.ldk, 2), false);
   WsCarver cv(nullptr);
-  p.b_wsum = (size_t)c_out * sizeof(int32_t); cv.take(p.b_wsum);
   p.b_xpad = p.pad ? (size_t)T * p.ldk : 0; cv.take(p.b_xpad);
   p.b_wpad = p.pad ? (size_t)c_out * p.ldk : 0; cv.take(p.b_wpad);
-  p.total = cv.off;
+  p.total = cv.off ? cv.off : 256;                     // 0 bytes stand for a bad shape in the size query
   return p;
 }
 
@@ -207,12 +179,8 @@ extern "C" int efqat_linear_fwd(const uint8_t* x_codes, const float* s_x, const 
     return EFQAT_OK;
   }
   WsCarver cv(ws);
-  int32_t* wsum = (int32_t*)cv.take(p.b_wsum);
   uint8_t* xpad = (uint8_t*)cv.take(p.b_xpad);
   uint8_t* wpad = (uint8_t*)cv.take(p.b_wpad);
-  hipLaunchKernelGGL(k_row_sum_i8, dim3((unsigned)ceil_div(c_out, 4)), dim3(256), 0, st, w_codes, c_out, c_in, c_in,
-                     wsum);
-  EFQAT_LAUNCH_CHECK();
   const uint8_t* xa = x_codes;
   const int8_t* wb = w_codes;
   if (p.pad) {
@@ -224,5 +192,5 @@ extern "C" int efqat_linear_fwd(const uint8_t* x_codes, const float* s_x, const 
     EFQAT_LAUNCH_CHECK();
     xa = xpad; wb = (const int8_t*)wpad;
   }
-  return launch_gemm_fwd_i8(xa, p.ldk, wb, p.ldk, T, c_out, p.ldk, p.plan, s_x, z_x, s_w, wsum, y, y_dtype, st);
+  return launch_gemm_fwd_i8(xa, p.ldk, wb, p.ldk, T, c_out, p.ldk, s_x, z_x, s_w, y, y_dtype, st);
 }

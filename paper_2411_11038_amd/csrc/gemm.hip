@@ -11,6 +11,7 @@
 // four MFMA sub-steps.  Split-K writes raw fp32 partial tiles (deterministic second-pass reduction).
 #include "common.hpp"
 
+#include <algorithm>
 #include <type_traits>
 
 #include "gemm_epilogue.hpp"
@@ -224,6 +225,7 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const typename ConvArgs<CONV>::
     for (int j = 0; j < C::TN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0;
+  int wsum[C::TN] = {};                                 // I8: this lane's share of sum_k w of its columns
 
   const int fr = lane & 31, fh = lane >> 5;
   const int a_row0 = wm * C::WM + fr, b_row0 = wn * C::WN + fr;
@@ -244,6 +246,11 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const typename ConvArgs<CONV>::
       // 128 * sum_k w back
 #pragma unroll
       for (int i = 0; i < C::TM; ++i) af[rb][i] ^= (int)0x80808080;
+      // ... for which the weight rows are summed here, from the fragments, instead of by a pass over W of its own
+#pragma unroll
+      for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) wsum[j] = __builtin_amdgcn_sdot4(bfr[rb][j][q], 0x01010101, wsum[j], false);
     }
 #pragma unroll
     for (int i = 0; i < C::TM; ++i)
@@ -373,56 +380,66 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const typename ConvArgs<CONV>::
   } else {
     // Forward epilogue: the int32 sums are over (code - 128) * w, so
     //   y[m][n] = S_x * S_w[n] * (acc + (128 - round(Z_x)) * sum_k w[n][k]).
-    // Accumulators go through LDS so that a lane owns 8 consecutive columns of a row (16/32-byte stores).
+    // A lane's accumulators belong to TN columns, whose weight sums and scales it holds itself; the products then go
+    // through the wavefront's own LDS slab, 32 rows at a time, so that a lane stores 8 consecutive columns of a row.
     constexpr int PITCH = C::WN + 8;
     constexpr int CPR = C::WN / 8;
     constexpr int RPP = 64 / CPR;
     constexpr int NPASS = (32 + RPP - 1) / RPP;
-    int* stage = reinterpret_cast<int*>(smem) + wave * 32 * PITCH;
+    float* stage = reinterpret_cast<float*>(smem) + wave * 32 * PITCH;
     const float sx = g.s_x[0];
-    const long long zc = 128 - (long long)rintf(g.z_x[0]);
+    const long long zr = (long long)rintf(g.z_x[0]);
+    // |sum_k (code - Z) w| <= 128 K max(|Z|, |255 - Z|): below 2^31 the result needs 32 bits only, and arithmetic modulo
+    // 2^32 forms it whatever the terms were.  A zero point far outside the codes' range takes the 64-bit sum.
+    const bool narrow = 128.0 * (double)g.K * (double)(zr >= 128 ? zr : 255 - zr) < 2147483648.0;
+    float scl[C::TN];
+    long long corr[C::TN];
+#pragma unroll
+    for (int j = 0; j < C::TN; ++j) {
+      const int col = n0 + wn * C::WN + j * 32 + fr;
+      scl[j] = col < g.N ? sx * g.s_w[col] : 0.0f;
+      corr[j] = (128 - zr) * (long long)(wsum[j] + __shfl_xor(wsum[j], 32, kWave));
+    }
     const int row_l0 = lane / CPR, ch = lane % CPR;
     const int gcol = n0 + wn * C::WN + ch * 8;
     const bool lane_on = row_l0 < RPP && gcol < g.N;
-    float scl[8];
-    long long corr[8];
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const bool ok = lane_on && gcol + t < g.N;
-      scl[t] = ok ? sx * g.s_w[gcol + t] : 0.0f;
-      corr[t] = ok ? zc * (long long)g.wsum[gcol + t] : 0;
-    }
+    auto wave_fence = []() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); };
 #pragma unroll
     for (int i = 0; i < C::TM; ++i) {
-      if (i > 0) __syncthreads();
+      wave_fence();
+      if (narrow) {
 #pragma unroll
-      for (int j = 0; j < C::TN; ++j)
+        for (int j = 0; j < C::TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          stage[(8 * (r >> 2) + 4 * fh + (r & 3)) * PITCH + j * 32 + fr] = acc[i][j][r];
-      __syncthreads();
+          for (int r = 0; r < 16; ++r)
+            stage[(8 * (r >> 2) + 4 * fh + (r & 3)) * PITCH + j * 32 + fr] =
+                scl[j] * (float)(int)((uint32_t)acc[i][j][r] + (uint32_t)corr[j]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            stage[(8 * (r >> 2) + 4 * fh + (r & 3)) * PITCH + j * 32 + fr] = scl[j] * (float)((long long)acc[i][j][r] + corr[j]);
+      }
+      wave_fence();
 #pragma unroll
       for (int p = 0; p < NPASS; ++p) {
         const int row_l = p * RPP + row_l0;
         const int grow = m0 + wm * C::WM + i * 32 + row_l;
         if (lane_on && row_l < 32 && grow < g.M) {
-          const int4 a0 = *reinterpret_cast<const int4*>(stage + row_l * PITCH + ch * 8);
-          const int4 a1 = *reinterpret_cast<const int4*>(stage + row_l * PITCH + ch * 8 + 4);
-          const int a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-          float o[8];
-#pragma unroll
-          for (int t = 0; t < 8; ++t) o[t] = scl[t] * (float)((long long)a[t] + corr[t]);
+          const float4 o0 = *reinterpret_cast<const float4*>(stage + row_l * PITCH + ch * 8);
+          const float4 o1 = *reinterpret_cast<const float4*>(stage + row_l * PITCH + ch * 8 + 4);
           const int64_t e = (int64_t)grow * g.N + gcol;
           if (g.epi_vec && gcol + 8 <= g.N) {
             if (g.y_dtype == EFQAT_F32) {
-              *reinterpret_cast<float4*>((float*)g.y + e) = make_float4(o[0], o[1], o[2], o[3]);
-              *reinterpret_cast<float4*>((float*)g.y + e + 4) = make_float4(o[4], o[5], o[6], o[7]);
+              *reinterpret_cast<float4*>((float*)g.y + e) = o0;
+              *reinterpret_cast<float4*>((float*)g.y + e + 4) = o1;
             } else {
-              *reinterpret_cast<uint4*>((bf16_t*)g.y + e) =
-                  make_uint4(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]), pack_bf16x2(o[4], o[5]),
-                             pack_bf16x2(o[6], o[7]));
+              *reinterpret_cast<uint4*>((bf16_t*)g.y + e) = make_uint4(pack_bf16x2(o0.x, o0.y), pack_bf16x2(o0.z, o0.w),
+                                                                       pack_bf16x2(o1.x, o1.y), pack_bf16x2(o1.z, o1.w));
             }
           } else {
+            const float o[8] = {o0.x, o0.y, o0.z, o0.w, o1.x, o1.y, o1.z, o1.w};
 #pragma unroll
             for (int t = 0; t < 8; ++t)
               if (gcol + t < g.N) {
@@ -636,24 +653,57 @@ int launch_gemm_conv_dx_strided(const bf16_t* dy_tok, int64_t ldc, const bf16_t*
   return launch_cfg<128, 128, EPI_DX, false, 2>(a, 1, stream);
 }
 
+// Tile of the int8 forward product.  `lone` / `full`: microseconds per K stage of 128 codes and per block (launch, first
+// loads, epilogue) with one block on a CU and with all `bpc` that fit (LDS); between the two by the number resident.  A
+// product is its whole rounds of 256 * bpc blocks plus what is left.  Fitted to measured launches; against the tile that
+// is fastest by measurement at 12 sizes of 128 .. 16384 tokens the choice loses 5 % at most.  T x C_in -> C_out, us with
+// tiles of 256x256 / 192x128 / 128x128 / 64x64:
+//   8192 x 4096 -> 4096    136 / 146 / 151 / 229    whole rounds of large tiles: fewest LDS bytes per operation
+//   2048 x 4096 -> 11008   138 / 105 / 120 / 161    two 192x128 blocks fill the 160 KB of LDS and overlap their epilogues
+//   12288 x 768 -> 3072     67 /  43 /  50 /  66
+//   2048 x 4096 -> 4096    few tiles: 128x128 is one round of two blocks a CU
+//   512 x 4096 -> 4096      57 /  31 /  26 /  21    less than one tile per CU: latency, the smallest tile
+struct FwdTile { int bm, bn, bpc; double lone[2], full[2]; };
+static const FwdTile kFwdTiles[] = {{256, 256, 1, {1.75, 13.5}, {1.75, 13.5}},
+                                    {192, 128, 2, {0.77, 5.9}, {1.30, 7.0}},
+                                    {128, 128, 2, {0.67, 4.3}, {1.06, 5.0}},
+                                    {64, 64, 5, {0.53, 2.4}, {1.00, 3.0}}};
+static FwdTile fwd_tile(int64_t M, int64_t N, int64_t K) {
+  const double stages = (double)ceil_div(K, 128);
+  const FwdTile* best = nullptr;
+  double best_t = 0.0;
+  for (const FwdTile& c : kFwdTiles) {
+    const int64_t tiles = ceil_div(M, c.bm) * ceil_div(N, c.bn), round = 256 * c.bpc;
+    const double lone = c.lone[0] * stages + c.lone[1], full = c.full[0] * stages + c.full[1];
+    double t = (double)(tiles / round) * full;
+    if (const int64_t rest = tiles % round) {
+      const int64_t resident = ceil_div(rest, 256);
+      t += lone + (full - lone) * (double)(resident - 1) / (double)std::max(1, c.bpc - 1);
+    }
+    if (!best || t < best_t) { best = &c; best_t = t; }
+  }
+  return *best;
+}
+
 int launch_gemm_fwd_i8(const uint8_t* x_codes, int64_t lda, const int8_t* w_codes, int64_t ldb, int64_t M, int64_t N,
-                       int64_t K, const GemmPlan& plan, const float* s_x, const float* z_x, const float* s_w,
-                       const int32_t* wsum, void* y, int y_dtype, hipStream_t stream) {
+                       int64_t K, const float* s_x, const float* z_x, const float* s_w, void* y, int y_dtype,
+                       hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0 || (K % 16) || (lda % 16) || (ldb % 16)) return EFQAT_ERR_BAD_SHAPE;
-  if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX || plan.split_k != 1) return EFQAT_ERR_BAD_SHAPE;
+  if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX) return EFQAT_ERR_BAD_SHAPE;
   GemmArgs a{};
   a.A = x_codes; a.lda = lda; a.a_rows = nullptr; a.B = w_codes; a.ldb = ldb;
   a.M = (int)M; a.N = (int)N; a.K = (int)K;
   a.k_per_split = (int)(ceil_div(K, 2 * KALIGN) * 2 * KALIGN);
-  a.s_x = s_x; a.z_x = z_x; a.s_w = s_w; a.wsum = wsum; a.y = y; a.y_dtype = y_dtype;
+  a.s_x = s_x; a.z_x = z_x; a.s_w = s_w; a.y = y; a.y_dtype = y_dtype;
   a.epi_vec = ((N % 8) == 0 && ((uintptr_t)y % 16) == 0) ? 1 : 0;
-  a.tiles_m = plan.tiles_m;
-  a.tiles_n = plan.tiles_n;
-  switch (plan.tile) {
+  const FwdTile t = fwd_tile(M, N, K);
+  a.tiles_m = (int)ceil_div(M, t.bm);
+  a.tiles_n = (int)ceil_div(N, t.bn);
+  switch (t.bm) {
     case 256: return launch_cfg<256, 256, EPI_FWD, true>(a, 1, stream);
-    case 192: return launch_cfg<192, 192, EPI_FWD, true>(a, 1, stream);
+    case 192: return launch_cfg<192, 128, EPI_FWD, true>(a, 1, stream);
     case 128: return launch_cfg<128, 128, EPI_FWD, true>(a, 1, stream);
-    default: return EFQAT_ERR_BAD_SHAPE;
+    default: return launch_cfg<64, 64, EPI_FWD, true>(a, 1, stream);
   }
 }
 

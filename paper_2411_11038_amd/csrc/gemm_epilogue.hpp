@@ -20,8 +20,8 @@ struct GemmArgs {
   const uint8_t* x_codes; const uint32_t* x_clip; const void* x; int x_dtype;
   const float* s_x; const float* z_x; void* dx; int dx_dtype; float* partial;
   int epi_vec;            // 8-wide vector accesses allowed in the fused epilogue
-  // forward epilogue (int8 product): y = s_x * s_w[n] * (acc + (128 - round(z_x)) * wsum[n])
-  const float* s_w; const int32_t* wsum; void* y; int y_dtype;
+  // forward epilogue (int8 product): y = s_x * s_w[n] * (acc + (128 - round(z_x)) * sum_k w[n][k])
+  const float* s_w; void* y; int y_dtype;
   // implicit im2col of the A operand (dX product of a stride-1 convolution): row m is the input pixel (n, h, w),
   // K runs over (tap, c_out) with cv_spt 64-channel stages per tap, and the operand element is
   // dY[n][h + pad - kh][w + pad - kw][c_out] or zero outside the output image

@@ -25,3 +25,22 @@ def test_forward_matches_integer_arithmetic(T, c_in, c_out):
     ref = sums.astype(np.float32) * (sx * sw)[None, :]            # two fp32 roundings, in this order
     # the sums are exact integers: only the roundings of the scale product and of the result are left (2^-24 each)
     assert np.abs(got.cpu().numpy() - ref).max() <= 2.0 ** -22 * np.abs(ref).max()
+
+
+# more tokens, with sizes that take each of the four tiles and end inside a tile, a 16-byte store and a K stage; the zero
+# point of 1e6 needs sums of more than 32 bits
+@pytest.mark.parametrize("z", [117.0, 1.0e6])
+@pytest.mark.parametrize("T,c_in,c_out", [(65, 100, 70), (200, 48, 129), (2000, 1003, 1900), (1100, 4112, 4088), (3000, 1536, 6000),
+                                          (8000, 4096, 4100), (16385, 64, 520)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_forward_tiles_match_integer_arithmetic(T, c_in, c_out, z, dtype):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T)
+    x = torch.randint(0, 256, (T, c_in), generator=g, device="cuda", dtype=torch.uint8)
+    w = torch.randint(-127, 128, (c_out, c_in), generator=g, device="cuda", dtype=torch.int8)
+    sx = torch.tensor([0.013], device="cuda")
+    sw = torch.rand(c_out, generator=g, device="cuda") * 0.01 + 0.001
+    got = ef.linear_fwd(x, sx, torch.tensor([z], device="cuda"), w, sw, y_dtype=dtype)
+    sums = (x.double() - z) @ w.double().t()                      # integers below 2^53: exact in any order
+    ref = sums.float() * (sx * sw)[None, :]                       # the same two roundings
+    assert torch.equal(got, ref.to(dtype))
