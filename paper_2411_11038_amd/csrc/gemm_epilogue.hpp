@@ -192,41 +192,60 @@ __device__ __forceinline__ void epilogue_dx(const GemmArgs& g, floatx16_t (&acc)
       }
     }
   } else {
-    // Element-wise path for ragged widths / unaligned pointers.
+    // Ragged widths / unaligned pointers: a lane owns one column of the slab (two when it is wider than 64), so that the
+    // loads and the store of a row touch neighbouring elements, and eight rows are loaded together.  Rows and columns past
+    // the edge read the last valid element and contribute nothing.  Eight neighbouring columns a lane with dependent
+    // single loads made the product of 2049 x 777 (K = 1008, fp32) 36 us, this one 26 us.
+    auto ragged = [&](const auto* xp) {
 #pragma unroll
-    for (int i = 0; i < C::TM; ++i) {
-      if (i > 0) __syncthreads();
+      for (int i = 0; i < C::TM; ++i) {
+        if (i > 0) __syncthreads();
 #pragma unroll
-      for (int j = 0; j < C::TN; ++j)
+        for (int j = 0; j < C::TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          stage[(8 * (r >> 2) + 4 * fh + (r & 3)) * PITCH + j * 32 + fr] = acc[i][j][r];
-      __syncthreads();
+          for (int r = 0; r < 16; ++r)
+            stage[(8 * (r >> 2) + 4 * fh + (r & 3)) * PITCH + j * 32 + fr] = acc[i][j][r];
+        __syncthreads();
 #pragma unroll
-      for (int p = 0; p < NPASS; ++p) {
-        const int row_l = p * RPP + row_l0;
-        const int grow = row_l < 32 ? row_of(wm * C::WM + i * 32 + row_l) : -1;
-        if (lane_on && grow >= 0 && grow < g.M) {
-          const int64_t e = (int64_t)grow * g.N + gcol;
+        for (int cc = 0; cc < C::WN; cc += 64) {
+          const int col = cc + lane, gc = n0 + wn * C::WN + col;
+          const bool on = col < C::WN && gc < g.N;
+          const int gl = on ? gc : 0;
+#pragma unroll 1
+          for (int r0 = 0; r0 < 32; r0 += 8) {
+            int grow[8];
+            float xv[8], q[8];
+            uint32_t clip[8];
 #pragma unroll
-          for (int t = 0; t < 8; ++t) {
-            if (gcol + t < g.N) {
-              const float av = stage[row_l * PITCH + ch * 8 + t];
-              const float q = (float)g.x_codes[e + t] - z;
-              const float xv = g.x_dtype == EFQAT_F32 ? ((const float*)g.x)[e + t]
-                                                      : bf16_to_f32(((const bf16_t*)g.x)[e + t]);
-              const bool inr = (g.x_clip[(int64_t)grow * wpr + ((gcol + t) >> 5)] >> ((gcol + t) & 31)) & 1u;
-              const float gs = inr ? fmaf(xv, ninv_s, q) : q;
-              ps = fmaf(av, gs, ps);
+            for (int u = 0; u < 8; ++u) {
+              grow[u] = row_of(wm * C::WM + i * 32 + r0 + u);
+              if (grow[u] >= g.M) grow[u] = -1;
+              const int64_t row = grow[u] < 0 ? 0 : grow[u], e = row * g.N + gl;
+              q[u] = (float)g.x_codes[e] - z;
+              clip[u] = g.x_clip[row * wpr + (gl >> 5)];
+              if constexpr (sizeof(*xp) == 4) xv[u] = xp[e]; else xv[u] = bf16_to_f32(xp[e]);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+              const bool ok = on && grow[u] >= 0;
+              const float av = ok ? stage[(r0 + u) * PITCH + col] : 0.0f;
+              const bool inr = (clip[u] >> (gl & 31)) & 1u;
+              const float gs = inr ? fmaf(xv[u], ninv_s, q[u]) : q[u];
               const float ov = inr ? av : 0.0f;
-              pz += av - ov;
-              if (g.dx_dtype == EFQAT_F32) ((float*)g.dx)[e + t] = ov;
-              else ((bf16_t*)g.dx)[e + t] = f32_to_bf16(ov);
+              if (ok) {
+                const int64_t e = (int64_t)grow[u] * g.N + gl;
+                ps = fmaf(av, gs, ps);
+                pz += av - ov;
+                if (g.dx_dtype == EFQAT_F32) ((float*)g.dx)[e] = ov;
+                else ((bf16_t*)g.dx)[e] = f32_to_bf16(ov);
+              }
             }
           }
         }
       }
-    }
+    };
+    if (g.x_dtype == EFQAT_F32) ragged((const float*)g.x);
+    else ragged((const bf16_t*)g.x);
   }
   ps = wave_sum(ps);
   pz = wave_sum(pz);
