@@ -129,21 +129,6 @@ __device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int
   }
 }
 
-// zero_page: optional by-product, 256 zero bytes
-template <typename T>
-__global__ __launch_bounds__(256) void k_transpose_bf16(const T* __restrict__ in, int64_t ld_in, int64_t R,
-                                                        int64_t Cn, const int32_t* __restrict__ colmap,
-                                                        const float* __restrict__ rowscale,
-                                                        const float* __restrict__ subz, bf16_t* __restrict__ out,
-                                                        int64_t ldo, int64_t out_off, int64_t i_pad, int vec,
-                                                        uint32_t* __restrict__ zero_page, const TransposeExtra ex) {
-  __shared__ TransposeTile tile;
-  if (zero_page && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x < 64)
-    zero_page[threadIdx.x] = 0u;
-  transpose_block<T>(tile, blockIdx.x, blockIdx.y, blockIdx.z, in, ld_in, R, Cn, colmap, rowscale, subz, out, ldo,
-                     out_off, i_pad, vec, ex);
-}
-
 // Row-wise cast/copy to bf16 with zero-padded pitch: out[m][j] = bf16(in[rm(m)][j]), j < Cn; 0 up to ldo (a multiple of
 // 8).  flat == 1: no padding, no row map and 16-byte aligned rows, i.e. one run of 8-element chunks; flat = 2 .. 64, a power
 // of two: aligned rows of whole chunks with a padded pitch, that many lanes to a row; 0: a wavefront per row, two elements
@@ -186,13 +171,6 @@ __device__ __forceinline__ void rows_block(int64_t b, int64_t nb, const T* __res
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_rows_bf16(const T* __restrict__ in, int64_t ld_in, int64_t R, int64_t Cn,
-                                                   const int32_t* __restrict__ rowmap, bf16_t* __restrict__ out,
-                                                   int64_t ldo) {
-  rows_block<T>(blockIdx.x, gridDim.x, in, ld_in, R, Cn, rowmap, out, ldo, 0);
-}
-
 // Compaction of the selected output channels of a token-major dY (the channel extraction step of Alg. 1, done
 // once per call):  out[t][m] = bf16(dY[t][idx[m]]), m < k;  0 for k <= m < kp.
 // A lane owns two neighbouring compacted channels (their source columns stay in registers); a wavefront thus
@@ -230,36 +208,68 @@ __global__ __launch_bounds__(256) void k_gather_cols(const T* __restrict__ dy, i
 }
 
 // Everything that has to be laid out ahead of the two products, in one launch: the compaction of the selected dY columns,
-// the bf16 copy of a token-major dY that cannot be used in place, the bf16 W_q^T.  They do not depend on each other, and
-// each alone is at most a few microseconds that end with the chip draining (about 4.5 us a launch, whatever it does).
-// Blocks [0, n_gather) compact, the next n_rows copy, the rest transpose; a part that is not needed has no blocks.
+// the bf16 copy of a token-major dY that cannot be used in place, the bf16 W_q^T, and for the shapes that the products
+// cannot read as they lie (ragged or few input channels, fp32 or unaligned channel-major dY) the transposed codes and
+// the selected rows of dY.  They do not depend on each other, and each alone is at most some microseconds that end with
+// the chip draining (about 4.5 us a launch, whatever it does).  2049 x 777 -> 1001, fp32: copies of
+// 12.9, 9.0 and 9.2 us in three launches, training step 107.8 us; in one launch 91.6 us.
+// The blocks of the parts follow each other; a part that is not needed has no blocks.
 struct PrepArgs {
-  const void* dy; int64_t c_out, t_out;
+  const void* dy; int64_t c_out, t_out, ldc;
   const int32_t* idx; int64_t k; bf16_t* sel; int64_t kp;          // compaction
-  bf16_t* dyn; int64_t ldc; int rows_flat;                          // copy
-  const int8_t* w_codes; const float* s_w; bf16_t* wqT;             // W_q^T
-  int64_t w_ld, c_in, w_ldo; int w_vec;
+  bf16_t* dyn; int rows_flat;                                       // copy of a token-major dY
+  int64_t c_in, w_ld, w_ldo;                                        // W_q^T
+  const int8_t* w_codes; const float* s_w; bf16_t* wqT; int w_vec;
   TransposeExtra w_ex;
-  int n_gather, gather_x, n_rows, n_w, w_x, w_y;                   // blocks of the three parts
+  uint32_t* zero_page;                                              // optional: 256 zero bytes behind it
+  const uint8_t* x_codes; const float* z_x; bf16_t* xcT;            // (codes - Z_x)^T
+  int64_t ldt; int x_vec;
+  TransposeExtra x_ex;
+  int chan, dyn_vec;                                                // dY is channel major; transposed to dyn
+  uint32_t gather_x, w_x, w_y, x_x, x_y, sel_x, dyn_x;             // blocks along the first axes of a part
+  uint32_t n_gather, n_rows, n_w, n_x, n_sel, n_dyn;
 };
 template <typename T>
 __global__ __launch_bounds__(256) void k_prep(const PrepArgs p) {
   __shared__ TransposeTile tile;
-  int b = blockIdx.x + blockIdx.y * gridDim.x;
+  const T* dy = (const T*)p.dy;
+  uint32_t b = blockIdx.x + blockIdx.y * gridDim.x;
   if (b < p.n_gather) {
-    gather_block<T>(b % p.gather_x, b / p.gather_x, p.n_gather / p.gather_x, (const T*)p.dy, p.c_out, p.t_out, p.idx, p.k,
-                    p.sel, p.kp);
+    gather_block<T>(b % p.gather_x, b / p.gather_x, p.n_gather / p.gather_x, dy, p.c_out, p.t_out, p.idx, p.k, p.sel, p.kp);
     return;
   }
   b -= p.n_gather;
   if (b < p.n_rows) {
-    rows_block<T>(b, p.n_rows, (const T*)p.dy, p.c_out, p.t_out, p.c_out, nullptr, p.dyn, p.ldc, p.rows_flat);
+    rows_block<T>(b, p.n_rows, dy, p.c_out, p.t_out, p.c_out, nullptr, p.dyn, p.ldc, p.rows_flat);
     return;
   }
   b -= p.n_rows;
-  if (b >= p.n_w) return;
-  transpose_block<int8_t>(tile, b % p.w_x, (b / p.w_x) % p.w_y, b / (p.w_x * p.w_y), p.w_codes, p.w_ld, p.c_out, p.c_in,
-                          nullptr, p.s_w, nullptr, p.wqT, p.w_ldo, 0, p.ldc, p.w_vec, p.w_ex);
+  if (b < p.n_w) {
+    if (p.zero_page && b == 0 && threadIdx.x < 64) p.zero_page[threadIdx.x] = 0u;
+    // wqT[ci][tap ldc + co] = S_w[co] code[co][tap][ci]
+    transpose_block<int8_t>(tile, b % p.w_x, (b / p.w_x) % p.w_y, b / (p.w_x * p.w_y), p.w_codes, p.w_ld, p.c_out, p.c_in,
+                            nullptr, p.s_w, nullptr, p.wqT, p.w_ldo, 0, p.ldc, p.w_vec, p.w_ex);
+    return;
+  }
+  b -= p.n_w;
+  if (b < p.n_x) {                                     // xcT[(tap, ci)][t] = code - Z_x of the input pixel
+    transpose_block<uint8_t>(tile, b % p.x_x, (b / p.x_x) % p.x_y, b / (p.x_x * p.x_y), p.x_codes, p.c_in, p.t_out, p.c_in,
+                             nullptr, nullptr, p.z_x, p.xcT, p.ldt, 0, p.ldt, p.x_vec, p.x_ex);
+    return;
+  }
+  b -= p.n_x;
+  const TransposeExtra none{};
+  if (b < p.n_sel) {                                   // sel[m][t] = dY of channel idx[m]
+    if (p.chan) rows_block<T>(b, p.n_sel, dy, p.t_out, p.k, p.t_out, p.idx, p.sel, p.ldt, 0);
+    else
+      transpose_block<T>(tile, b % p.sel_x, b / p.sel_x, 0, dy, p.c_out, p.t_out, p.k, p.idx, nullptr, nullptr, p.sel,
+                         p.ldt, 0, p.ldt, 0, none);
+    return;
+  }
+  b -= p.n_sel;
+  if (b < p.n_dyn)                                     // channel-major [c_out][t_out] -> [t_out][ldc]
+    transpose_block<T>(tile, b % p.dyn_x, b / p.dyn_x, 0, dy, p.t_out, p.c_out, p.t_out, nullptr, nullptr, nullptr, p.dyn,
+                       p.ldc, 0, p.ldc, p.dyn_vec, none);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -460,22 +470,27 @@ static inline unsigned grid1d(int64_t total, int per_block = 256) {
   return (unsigned)b;
 }
 
-template <typename T>
-static int transpose_to_bf16(const T* in, int64_t ld_in, int64_t R, int64_t Cn, const int32_t* colmap,
-                             const float* rowscale, const float* subz, bf16_t* out, int64_t ldo, int64_t out_off,
-                             int64_t i_pad, hipStream_t st, uint32_t* zero_page = nullptr, int taps = 1,
-                             const TransposeExtra* extra = nullptr) {
-  dim3 grid((unsigned)ceil_div(i_pad, 64), (unsigned)ceil_div(Cn, 64), (unsigned)taps);
-  TransposeExtra ex{};
-  if (extra) ex = *extra;
-  if (grid.y > 65535) return EFQAT_ERR_BAD_SHAPE;
-  // 16-byte stores need an 8-element aligned destination; 4-wide loads a dense, 4-element aligned source
-  if ((ldo % 8) || (out_off % 8) || (i_pad % 8) || ((uintptr_t)out % 16)) return EFQAT_ERR_ALIGNMENT;
-  const int vec = (!colmap && (ld_in % 4) == 0 && ((uintptr_t)in % (4 * sizeof(T))) == 0) ? 1 : 0;
-  hipLaunchKernelGGL((k_transpose_bf16<T>), grid, dim3(256), 0, st, in, ld_in, R, Cn, colmap, rowscale, subz, out,
-                     ldo, out_off, i_pad, vec, zero_page, ex);
+static int launch_prep(const PrepArgs& a, int dy_dtype, hipStream_t st) {
+  // a grid dimension holds less than 2^32 work items
+  const int64_t blocks = (int64_t)a.n_gather + a.n_rows + a.n_w + a.n_x + a.n_sel + a.n_dyn;
+  if (blocks == 0) return EFQAT_OK;
+  const int64_t bx = std::min<int64_t>(blocks, 1 << 22);
+  const dim3 grid((unsigned)bx, (unsigned)ceil_div(blocks, bx));
+  if (dy_dtype == EFQAT_F32) hipLaunchKernelGGL((k_prep<float>), grid, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((k_prep<bf16_t>), grid, dim3(256), 0, st, a);
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
+}
+
+// the W_q^T part: w codes [c_out][taps][c_in], rows of the result hold taps spans of ldc
+static void prep_w_operand(PrepArgs& a, const int8_t* w_codes, const float* s_w, int64_t c_in, int64_t c_out, int taps,
+                           int64_t ldc, bf16_t* wqT) {
+  a.w_codes = w_codes; a.s_w = s_w; a.wqT = wqT; a.c_in = c_in; a.c_out = c_out; a.ldc = ldc;
+  a.w_ld = (int64_t)taps * c_in; a.w_ldo = (int64_t)taps * ldc;
+  a.w_ex.z_in = c_in; a.w_ex.z_out = ldc;
+  a.w_vec = ((c_in % 4) == 0 && ((uintptr_t)w_codes % 4) == 0) ? 1 : 0;
+  a.w_x = (uint32_t)ceil_div(ldc, 64); a.w_y = (uint32_t)ceil_div(c_in, 64);
+  a.n_w = a.w_x * a.w_y * (uint32_t)taps;
 }
 
 // Plan of one backward call: sizes of every workspace slice (shared by the size query and the call).
@@ -669,49 +684,38 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   const bool copy_dy = p.need_dyn && io.dy_layout == EFQAT_DY_TOKEN_MAJOR;
   const int64_t gx = std::max<int64_t>(1, ceil_div(p.kp, 128));
   const dim3 ggrid((unsigned)gx, (unsigned)std::min(ceil_div(T_out, kGatherRows), std::max<int64_t>(1, std::min<int64_t>(65535, (1 << 24) / gx))));
-  if (own_wqT || copy_dy || (gather && !use_side)) {
-    PrepArgs a{};
-    a.dy = io.dy; a.c_out = c_out; a.t_out = T_out; a.ldc = p.ldc;
-    if (gather && !use_side) {
-      a.idx = io.idx; a.k = io.k; a.sel = sel; a.kp = p.kp;
-      a.gather_x = (int)ggrid.x; a.n_gather = (int)(ggrid.x * ggrid.y);
-    }
-    if (copy_dy) {
-      // dY as a token-major bf16 matrix [T_out][ldc] (A operand of the dX product)
-      a.dyn = dyn; a.rows_flat = p.ldc == c_out ? 1 : 0;
-      if (!a.rows_flat && (c_out % 8) == 0)
-        for (a.rows_flat = 2; a.rows_flat < 64 && a.rows_flat < p.ldc / 8;) a.rows_flat *= 2;
-      a.n_rows = (int)std::min<int64_t>(a.rows_flat ? ceil_div(T_out * p.ldc, 256 * 16) : ceil_div(T_out, 4), 4096);
-    }
-    if (own_wqT) {
-      // W_q^T in bf16:  wqT[ci][tap*ldc + co] = S_w[co] * code[co][tap][ci], zero for co in [c_out, ldc)
-      a.w_codes = io.w_codes; a.s_w = io.s_w; a.wqT = wqT; a.w_ld = (int64_t)taps * c_in; a.c_in = c_in; a.w_ldo = p.Kx;
-      a.w_ex.z_in = c_in; a.w_ex.z_out = p.ldc;
-      a.w_vec = ((a.w_ld % 4) == 0 && (c_in % 4) == 0 && ((uintptr_t)io.w_codes % 4) == 0) ? 1 : 0;
-      a.w_x = (int)ceil_div(p.ldc, 64); a.w_y = (int)ceil_div(c_in, 64);
-      a.n_w = a.w_x * a.w_y * taps;
-    }
-    // a grid dimension holds less than 2^32 work items
-    const int64_t blocks = (int64_t)a.n_gather + a.n_rows + a.n_w, bx = std::min<int64_t>(blocks, 1 << 22);
-    const dim3 grid((unsigned)bx, (unsigned)ceil_div(blocks, bx));
-    if (io.dy_dtype == EFQAT_F32) hipLaunchKernelGGL((k_prep<float>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((k_prep<bf16_t>), grid, dim3(256), 0, st, a);
-    EFQAT_LAUNCH_CHECK();
+  const bool stage_dw = io.k > 0 && !p.tn && !p.rdw;   // staged bf16 operands of the fall-back dW product
+  PrepArgs a{};
+  a.dy = io.dy; a.c_in = c_in; a.c_out = c_out; a.t_out = T_out; a.ldc = p.ldc; a.ldt = p.ldt;
+  a.idx = io.idx; a.k = io.k; a.sel = sel; a.kp = p.kp; a.dyn = dyn;
+  a.chan = io.dy_layout == EFQAT_DY_CHANNEL_MAJOR ? 1 : 0;
+  if (gather && !use_side) { a.gather_x = ggrid.x; a.n_gather = ggrid.x * ggrid.y; }
+  if (copy_dy) {
+    // dY as a token-major bf16 matrix [T_out][ldc] (A operand of the dX product)
+    a.rows_flat = p.ldc == c_out ? 1 : 0;
+    if (!a.rows_flat && (c_out % 8) == 0)
+      for (a.rows_flat = 2; a.rows_flat < 64 && a.rows_flat < p.ldc / 8;) a.rows_flat *= 2;
+    a.n_rows = (uint32_t)std::min<int64_t>(a.rows_flat ? ceil_div(T_out * p.ldc, 256 * 16) : ceil_div(T_out, 4), 4096);
+  } else if (p.need_dyn) {
+    a.dyn_vec = ((T_out % 4) == 0) ? 1 : 0;            // dY is 16-byte aligned
+    a.dyn_x = (uint32_t)ceil_div(p.ldc, 64);
+    a.n_dyn = a.dyn_x * (uint32_t)ceil_div(T_out, 64);
   }
-  const bf16_t* dy_tok = (const bf16_t*)io.dy;
-  if (p.need_dyn) {
-    if (io.dy_layout == EFQAT_DY_CHANNEL_MAJOR) {
-      // channel-major [c_out][T_out] -> [T_out][ldc]
-      if (io.dy_dtype == EFQAT_F32)
-        rc = transpose_to_bf16<float>((const float*)io.dy, T_out, c_out, T_out, nullptr, nullptr, nullptr, dyn,
-                                      p.ldc, 0, p.ldc, st);
-      else
-        rc = transpose_to_bf16<bf16_t>((const bf16_t*)io.dy, T_out, c_out, T_out, nullptr, nullptr, nullptr, dyn,
-                                       p.ldc, 0, p.ldc, st);
-      if (rc) return rc;
+  if (own_wqT) prep_w_operand(a, io.w_codes, io.s_w, c_in, c_out, taps, p.ldc, wqT);
+  if (stage_dw) {
+    a.x_codes = io.x_codes; a.z_x = io.z_x; a.xcT = xcT;
+    if (im2col) { a.x_ex.z_orow = c_in; a.x_ex.conv = 1; a.x_ex.g = *cg; }
+    a.x_vec = ((c_in % 4) == 0 && ((uintptr_t)io.x_codes % 4) == 0) ? 1 : 0;
+    a.x_x = (uint32_t)ceil_div(p.ldt, 64); a.x_y = (uint32_t)ceil_div(c_in, 64);
+    a.n_x = a.x_x * a.x_y * (uint32_t)(im2col ? taps : 1);
+    if (p.need_sel) {
+      a.sel_x = (uint32_t)ceil_div(p.ldt, 64);
+      a.n_sel = a.chan ? grid1d(io.k, 4) : a.sel_x * (uint32_t)ceil_div(io.k, 64);
     }
-    dy_tok = dyn;
   }
+  rc = launch_prep(a, io.dy_dtype, st);
+  if (rc) return rc;
+  const bf16_t* dy_tok = p.need_dyn ? dyn : (const bf16_t*)io.dy;
 
   // ---- dX product with the fused straight-through / qparam epilogue
   const bf16_t* A = dy_tok;
@@ -782,47 +786,12 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
                              T_out, p.plan_dw, part_dw, st2);
     if (rc) return rc;
   } else {
-  ProfScope stg(PROF_PREP, st);                        // staged bf16 operands of the fall-back product
-  // ---- B operand of the dW product: (codes - Z_x)^T, exact in bf16
-  if (im2col) {
-    TransposeExtra ex{};
-    ex.z_orow = c_in; ex.conv = 1; ex.g = *cg;        // xcT[(tap, ci)][(n, ho, wo)], one launch for all taps
-    rc = transpose_to_bf16<uint8_t>(io.x_codes, c_in, T_out, c_in, nullptr, nullptr, io.z_x, xcT, p.ldt, 0, p.ldt,
-                                    st, nullptr, taps, &ex);
+    // channel-major bf16 dY that is not staged: the gather is fused into the tile loads
+    const bf16_t* Aw = p.need_sel ? sel : (const bf16_t*)io.dy;
+    const int64_t ldaw = p.need_sel ? p.ldt : T_out, Kw = ldaw;
+    const int32_t* a_rows = p.need_sel ? nullptr : io.idx;
+    rc = launch_gemm_nt(Aw, ldaw, a_rows, xcT, p.ldt, io.k, p.Nw, Kw, p.plan_dw, part_dw, nullptr, st);
     if (rc) return rc;
-  } else {
-    rc = transpose_to_bf16<uint8_t>(io.x_codes, c_in, T_out, c_in, nullptr, nullptr, io.z_x, xcT, p.ldt, 0, p.ldt, st);
-    if (rc) return rc;
-  }
-
-  // ---- A operand of the dW product: the selected rows of dY^T
-  const bf16_t* Aw; int64_t ldaw; const int32_t* a_rows;
-  if (!p.need_sel) {               // channel-major bf16: gather fused into the GEMM's A-tile loads
-    Aw = (const bf16_t*)io.dy; ldaw = T_out; a_rows = io.idx;
-  } else if (io.dy_layout == EFQAT_DY_CHANNEL_MAJOR) {
-    if (io.dy_dtype == EFQAT_F32)
-      hipLaunchKernelGGL((k_rows_bf16<float>), dim3(grid1d(io.k, 4)), dim3(256), 0, st, (const float*)io.dy,
-                         T_out, io.k, T_out, io.idx, sel, p.ldt);
-    else
-      hipLaunchKernelGGL((k_rows_bf16<bf16_t>), dim3(grid1d(io.k, 4)), dim3(256), 0, st, (const bf16_t*)io.dy,
-                         T_out, io.k, T_out, io.idx, sel, p.ldt);
-    EFQAT_LAUNCH_CHECK();
-    Aw = sel; ldaw = p.ldt; a_rows = nullptr;
-  } else {
-    // token major: sel[m][t] = dY[t][idx[m]]
-    if (io.dy_dtype == EFQAT_F32)
-      rc = transpose_to_bf16<float>((const float*)io.dy, c_out, T_out, io.k, io.idx, nullptr, nullptr, sel, p.ldt, 0,
-                                    p.ldt, st);
-    else
-      rc = transpose_to_bf16<bf16_t>((const bf16_t*)io.dy, c_out, T_out, io.k, io.idx, nullptr, nullptr, sel, p.ldt,
-                                     0, p.ldt, st);
-    if (rc) return rc;
-    Aw = sel; ldaw = p.ldt; a_rows = nullptr;
-  }
-  const int64_t Kw = p.need_sel ? p.ldt : T_out;
-  stg.close();
-  rc = launch_gemm_nt(Aw, ldaw, a_rows, xcT, p.ldt, io.k, p.Nw, Kw, p.plan_dw, part_dw, nullptr, st);
-  if (rc) return rc;
   }
   if (use_side && (hipEventRecord(ev.join, st2) != hipSuccess || hipStreamWaitEvent(st, ev.join, 0) != hipSuccess))
     return EFQAT_ERR_HIP;
@@ -975,13 +944,12 @@ extern "C" int efqat_linear_bwd_weight_operand(const int8_t* w_codes, const floa
   if (((uintptr_t)operand % 256) != 0) return EFQAT_ERR_ALIGNMENT;
   if (c_in > 65535 * (int64_t)64) return EFQAT_ERR_BAD_SHAPE;
   const BwdPlan p = make_plan(T, T, c_in, c_out, 1, 0, dy_dtype, dy_layout, false, EFQAT_DX_KERNEL_AUTO);
-  TransposeExtra ex{};
-  ex.z_in = c_in; ex.z_out = p.ldc;
-  uint32_t* zero_page = (uint32_t*)((char*)operand + round_up((int64_t)p.b_wqT, 256));
+  PrepArgs a{};
+  prep_w_operand(a, w_codes, s_w, c_in, c_out, 1, p.ldc, (bf16_t*)operand);
+  a.zero_page = (uint32_t*)((char*)operand + round_up((int64_t)p.b_wqT, 256));
   hipStream_t st = (hipStream_t)stream;
   ProfScope prep(PROF_PREP, st);
-  return transpose_to_bf16<int8_t>(w_codes, c_in, c_out, c_in, nullptr, s_w, nullptr, (bf16_t*)operand, p.Kx, 0,
-                                   p.ldc, st, zero_page, 1, &ex);
+  return launch_prep(a, EFQAT_BF16, st);
 }
 
 static int conv_geom(int64_t N, int64_t H, int64_t W, int64_t c_in, int64_t c_out, int64_t KH, int64_t KW,
