@@ -143,7 +143,8 @@ int efqat_weight_quant_select(const float* w, int64_t c_out, int64_t block, int 
 
 /* EfQAT-CWPN (Table 2): one Top-K over the channels of several layers together.
  *   scores      in   double[total] = the per-layer score arrays of efqat_channel_select,
- *                    concatenated in layer order (device)
+ *                    concatenated in layer order (device); scores that function does not make (negative,
+ *                    -0.0, NaN) are ordered by their bit pattern as an unsigned number
  *   layer_off   in   int64[n_layers+1] (device), ascending prefix offsets into scores,
  *                    layer_off[0] = 0, layer_off[n_layers] = total
  *   k_total     0..total

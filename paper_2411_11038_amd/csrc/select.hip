@@ -28,7 +28,8 @@ __global__ __launch_bounds__(256) void k_row_importance(const float* __restrict_
 }
 
 // ------------------------------------------------------------------------------------------------
-// Exact Top-K.  Scores are non-negative doubles, so their bit patterns order like the values; keys are taken relative
+// Exact Top-K.  Scores are non-negative doubles, so their bit patterns order like the values (whatever else a caller
+// passes is ordered by its bit pattern as an unsigned number); keys are taken relative
 // to the smallest one (order and equality unchanged), which puts the first digit window right below the top bit of
 // (largest - smallest): the scores of a layer lie in a narrow band, and the first window of 12 bits already leaves a
 // handful of them around the threshold.  The selection under (score descending, index ascending) is a threshold pair
@@ -40,14 +41,17 @@ constexpr int64_t kTopkBlockKeys = 16384;             // one block selects from 
 constexpr int kSelRank = 64;                          // this few candidates are ranked directly by one wavefront
 
 __device__ __forceinline__ u64 score_key(double s) { return (u64)__double_as_longlong(s); }
+// v >> top == prefix; keys that differ in the sign bit need all 64 bits, and a shift by 64 is none
+__device__ __forceinline__ bool has_prefix(u64 v, int top, u64 prefix) { return top >= 64 || (v >> top) == prefix; }
 
 // Where a selected index goes.
-//   plain:      idx[pos] = c
+//   plain:      idx[pos] = c                          (pos < k: never behind the caller's k entries)
 //   layer_off:  one Top-K over the channels of several layers: idx[pos] = c - first channel of its layer, and
 //               per_layer[layer] counts (zeroed by an earlier phase);  flags (blocks are whole layers): per_layer[c] =
 //               channels of layer c if it is selected, else 0
 struct SelectOut {
   int32_t* idx;
+  int64_t k;
   const int64_t* layer_off;
   int64_t n_layers;
   int32_t* per_layer;
@@ -141,7 +145,7 @@ __device__ __forceinline__ void find_threshold(SelShared<NTH, BITS>& sh, Each ea
   const int tid = threadIdx.x;
   bool on_index = false;                              // all remaining elements have key T: the windows run over ~index
   u64 T = 0;
-  if (tid == 0) sh.ncand = 0;
+  if (tid == 0) { sh.ncand = 0; sh.T = ~0ull; sh.I = -1; }
   if (tid < kSelRank) sh.rank[tid] = 0u;
   while (count > kSelRank) {
     if (top == 0) {                                   // equal keys, more of them than are ranked directly
@@ -159,7 +163,7 @@ __device__ __forceinline__ void find_threshold(SelShared<NTH, BITS>& sh, Each ea
     } else {
       each([&](u64 key, int i) {
         const u64 v = on_index ? (u64)(unsigned int)~i : key;
-        if ((!on_index || key == T) && (v >> top) == prefix) atomicAdd(&sh.hist[(v >> shift) & mask], 1u);
+        if ((!on_index || key == T) && has_prefix(v, top, prefix)) atomicAdd(&sh.hist[(v >> shift) & mask], 1u);
       });
     }
     __syncthreads();
@@ -175,7 +179,7 @@ __device__ __forceinline__ void find_threshold(SelShared<NTH, BITS>& sh, Each ea
   __syncthreads();
   each([&](u64 key, int i) {
     const u64 v = on_index ? (u64)(unsigned int)~i : key;
-    if ((v >> top) == prefix && (!on_index || key == T)) {
+    if (has_prefix(v, top, prefix) && (!on_index || key == T)) {
       const int slot = atomicAdd(&sh.ncand, 1);
       sh.cand_key[slot] = key; sh.cand_idx[slot] = i;
     }
@@ -212,6 +216,7 @@ __device__ __forceinline__ int64_t layer_of(const int64_t* layer_off, int64_t n_
 
 // writes element c of the input: selected elements at output position pos.  Called by whole wavefronts.
 __device__ __forceinline__ void emit(const SelectOut& o, bool sel, int64_t pos, int64_t c, bool in_range) {
+  sel = sel && pos < o.k;
   if (!o.layer_off) {
     if (sel) o.idx[pos] = (int32_t)c;
     return;
@@ -568,7 +573,7 @@ static void launch_select(const double* scores, int64_t n, int64_t k, const Sele
 }
 
 void launch_topk(const double* scores, int64_t n, int64_t k, int32_t* idx, void* ws, hipStream_t st) {
-  launch_select(scores, n, k, SelectOut{idx, nullptr, 0, nullptr, 0}, ws, st);
+  launch_select(scores, n, k, SelectOut{idx, k, nullptr, 0, nullptr, 0}, ws, st);
 }
 
 int launch_topk_profiled(const double* scores, int64_t n, int64_t k, int32_t* idx, void* ws, hipStream_t st) {
@@ -702,7 +707,7 @@ extern "C" int efqat_network_select(const double* scores, const int64_t* layer_o
   if (ws_bytes < efqat_network_select_workspace_bytes(total)) return EFQAT_ERR_WORKSPACE;
   if (((uintptr_t)ws % 256) != 0) return EFQAT_ERR_ALIGNMENT;
   hipStream_t st = (hipStream_t)stream;
-  launch_select(scores, total, k_total, SelectOut{idx, layer_off, n_layers, k_per_layer, 0}, ws, st);
+  launch_select(scores, total, k_total, SelectOut{idx, k_total, layer_off, n_layers, k_per_layer, 0}, ws, st);
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
 }
@@ -753,7 +758,7 @@ extern "C" int efqat_layer_select(const double* scores, const int64_t* layer_off
   double* ls = layer_scores ? layer_scores : own;
   hipLaunchKernelGGL(k_layer_means, dim3((unsigned)n_layers), dim3(256), 0, st, scores, layer_off, ls);
   EFQAT_LAUNCH_CHECK();
-  launch_select(ls, n_layers, k_layers, SelectOut{layer_idx, layer_off, n_layers, k_per_layer, 1}, sel_ws, st);
+  launch_select(ls, n_layers, k_layers, SelectOut{layer_idx, k_layers, layer_off, n_layers, k_per_layer, 1}, sel_ws, st);
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
 }

@@ -64,3 +64,45 @@ def test_channel_selection_with_either_scratch(c_out):
     ref = orc.top_k_channels(scores.cpu().numpy(), k)
     for got in (idx, static, both["idx"]):
         assert np.array_equal(got.cpu().numpy(), ref)
+
+
+def _by_bits(s, k):
+    """The k largest by bit pattern as an unsigned number, equal ones by index; ascending index order."""
+    return np.sort(np.lexsort((np.arange(s.size), ~s.view(np.uint64)))[:k])
+
+
+# Scores with both values of the sign bit: the keys then differ in all 64 bits.  Not what channel_select makes, but the two
+# calls take any doubles, and nothing may be written behind idx[k].
+@pytest.mark.parametrize("kind", ["signs", "zeros", "nan"])
+@pytest.mark.parametrize("n", [2, 48, 64, 65, 256, 1024, 5000, 16384, 20000])
+def test_any_doubles_are_ordered_by_bit_pattern(n, kind):
+    s = synth.normal(4100 + n, 0, (n,))
+    if kind == "zeros":
+        s = np.where(np.arange(n) % 3 == 0, -0.0, 0.0)
+    elif kind == "nan":
+        s = np.abs(s)
+        s[n // 2:] = np.copysign(np.nan, -1.0)
+        s[0] = np.inf
+    off = np.arange(n + 1, dtype=np.int64)             # one score per layer: its mean is the score itself
+    L, st = ef.lib(), torch.cuda.current_stream().cuda_stream
+    flat, offd = dev(s), dev(off)
+    for k in sorted({1, n // 3, n - 1} - {0}):
+        want = _by_bits(s, k)
+        for layers in (False, True):
+            idx = torch.full((n + 64,), -7, dtype=torch.int32, device="cuda")
+            per = torch.empty(n, dtype=torch.int32, device="cuda")
+            if layers:
+                ws = torch.empty(L.efqat_layer_select_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+                mean = torch.empty(n, dtype=torch.float64, device="cuda")
+                rc = L.efqat_layer_select(flat.data_ptr(), offd.data_ptr(), n, k, mean.data_ptr(), idx.data_ptr(),
+                                          per.data_ptr(), ws.data_ptr(), ws.numel(), st)
+                torch.cuda.synchronize()
+                want = _by_bits(mean.cpu().numpy(), k)  # -0.0 / 1 may lose its sign in the sum
+            else:
+                ws = torch.empty(L.efqat_network_select_workspace_bytes(n), dtype=torch.uint8, device="cuda")
+                one = dev(np.array([0, n], dtype=np.int64))
+                rc = L.efqat_network_select(flat.data_ptr(), one.data_ptr(), 1, n, k, idx.data_ptr(), per.data_ptr(),
+                                            ws.data_ptr(), ws.numel(), st)
+                torch.cuda.synchronize()
+            got = idx.cpu().numpy()
+            assert rc == 0 and np.array_equal(got[:k], want) and np.all(got[k:] == -7)
