@@ -86,6 +86,7 @@ struct SelShared {
   int cand_idx[kSelRank];
   unsigned int rank[kSelRank];
   int ncand, bin, need, count;
+  u64 any[NTH / 64], all[NTH / 64];
   u64 T;
   int I;
 };
@@ -135,21 +136,37 @@ __device__ __forceinline__ void search_bins(SH& sh, const unsigned int (&bins)[S
 }
 
 // Threshold pair of element number `need` (from 1) under (key descending, index ascending) among the `count` elements
-// with key >> top == prefix; each(f) calls f(key, index) for every element this thread holds, at least those elements.
-// Windows of BITS bits from `top` downwards until few elements are left; equal keys are told apart by their index, the
-// last windows.
+// with key >> top == prefix; each(f) calls f(key, index) for every element this thread holds, at least those elements;
+// indices are below n.  Windows of BITS bits from `top` downwards until few elements are left; equal keys are told apart by
+// their index, the last windows.  A window that leaves every element where it was (`stuck`: so did an earlier one) is
+// followed by a look at the bits in which they differ at all: none, where scores are equal.
 template <int NTH, int BITS, class Each>
 __device__ __forceinline__ void find_threshold(SelShared<NTH, BITS>& sh, Each each, u64 prefix, int top, int need,
-                                               int count) {
-  constexpr int BINS = 1 << BITS, BPT = BINS / NTH;
+                                               int count, int64_t n, bool stuck) {
+  constexpr int BINS = 1 << BITS, BPT = BINS / NTH, NW = NTH / 64;
   const int tid = threadIdx.x;
-  bool on_index = false;                              // all remaining elements have key T: the windows run over ~index
+  bool on_index = false;                              // all remaining elements have key T: the windows run over n - 1 - index
   u64 T = 0;
   if (tid == 0) { sh.ncand = 0; sh.T = ~0ull; sh.I = -1; }
   if (tid < kSelRank) sh.rank[tid] = 0u;
   while (count > kSelRank) {
+    if (stuck) {
+      stuck = false;
+      u64 any = 0ull, all = ~0ull;
+      each([&](u64 key, int) {
+        if (has_prefix(key, top, prefix)) { any |= key; all &= key; }
+      });
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) { any |= __shfl_xor(any, o, kWave); all &= __shfl_xor(all, o, kWave); }
+      if ((tid & 63) == 0) { sh.any[tid >> 6] = any; sh.all[tid >> 6] = all; }
+      __syncthreads();
+      for (int w = 0; w < NW; ++w) { any |= sh.any[w]; all &= sh.all[w]; }
+      const u64 diff = any & ~all;                    // below top
+      if (top > 0) top = diff ? 64 - __clzll((long long)diff) : 0;
+      prefix = top >= 64 ? 0ull : any >> top;
+    }
     if (top == 0) {                                   // equal keys, more of them than are ranked directly
-      T = prefix; on_index = true; prefix = 0; top = 32;
+      T = prefix; on_index = true; prefix = 0; top = 64 - __clzll(n - 1);
     }
     const int width = top < BITS ? top : BITS, shift = top - width;
     const u64 mask = (1ull << width) - 1ull;
@@ -162,7 +179,7 @@ __device__ __forceinline__ void find_threshold(SelShared<NTH, BITS>& sh, Each ea
       });
     } else {
       each([&](u64 key, int i) {
-        const u64 v = on_index ? (u64)(unsigned int)~i : key;
+        const u64 v = on_index ? (u64)(n - 1 - i) : key;
         if ((!on_index || key == T) && has_prefix(v, top, prefix)) atomicAdd(&sh.hist[(v >> shift) & mask], 1u);
       });
     }
@@ -174,11 +191,12 @@ __device__ __forceinline__ void find_threshold(SelShared<NTH, BITS>& sh, Each ea
     prefix = (prefix << width) | (u64)sh.bin;
     need = sh.need;
     top = shift;
+    stuck = count == sh.count && !on_index;
     count = sh.count;
   }
   __syncthreads();
   each([&](u64 key, int i) {
-    const u64 v = on_index ? (u64)(unsigned int)~i : key;
+    const u64 v = on_index ? (u64)(n - 1 - i) : key;
     if (has_prefix(v, top, prefix) && (!on_index || key == T)) {
       const int slot = atomicAdd(&sh.ncand, 1);
       sh.cand_key[slot] = key; sh.cand_idx[slot] = i;
@@ -247,6 +265,8 @@ __device__ __forceinline__ void emit(const SelectOut& o, bool sel, int64_t pos, 
 // What bounds it is a chain of about ten block barriers and the load latency, not work, hence many threads with few
 // keys each and few, wide digit windows.  256 / 768 / 3072 / 11008 keys: 3.5 / 4.0 / 6.6 / 14.6 us; with four
 // wavefronts, 8-bit windows and one-wavefront ranking through LDS it was 4.7 / 7.6 / 13.5 / 29 us.
+// Equal scores, 1000 / 4000 / 16384 of them (whole call): 8 / 10 / 24 us; with windows over all the bits below the first one
+// and over 32 bits of the index 15 / 29 / 93 us.
 template <int NTH, int KPT, int BITS = kSelBits>
 __global__ __launch_bounds__(NTH) void k_topk_block(const double* __restrict__ scores, int n, int k,
                                                     const SelectOut out) {
@@ -299,7 +319,7 @@ __global__ __launch_bounds__(NTH) void k_topk_block(const double* __restrict__ s
       slots([&](int q, int i) {
         if (i < n) f(key_ref(q, i) - sub, i);
       });
-    }, 0ull, top, k, n);
+    }, 0ull, top, k, n, n, top == 32);                // 32: no key differs in its upper half
     T = sh.T + sub; I = sh.I;
   }
   // ordered output: one wavefront turns the counts of every (q, wavefront) into prefixes in index order
@@ -488,7 +508,7 @@ __global__ __launch_bounds__(256) void k_sel_write(const double* __restrict__ sc
       for (int64_t i = tid; i < n; i += 256) f(score_key(scores[i]) - kmin, (int)i);
     }
   };
-  find_threshold(sh, each, bin, shift, need, count);
+  find_threshold(sh, each, bin, shift, need, count, n, count == n);
   const u64 T = sh.T;
   const int I = sh.I;
   // ... and candidates

@@ -1,6 +1,7 @@
 """Top-K at the sizes where its kernels change or end a tile: one block with 1 / 4 / 8 / 16 keys per thread, the
 four-launch chain beyond 16384 keys (1024 keys per block, 256 blocks at most), with distinct scores, with scores of few
-values (more equal keys around the threshold than are ranked directly or kept), and with one far outlier."""
+values (more equal keys around the threshold than are ranked directly or kept), all equal, most of them zero, and with one
+far outlier."""
 import numpy as np
 import pytest
 import torch
@@ -17,6 +18,10 @@ def scores_of(kind, n):
     r = np.abs(synth.normal(777 + n, 0, (n,)))
     if kind == "distinct":
         return 0.016 * (1.0 + 0.02 * r)
+    if kind == "equal":
+        return np.full(n, 0.0625)
+    if kind == "dead":                                 # nine of ten channels are 0: the threshold lies among them, or not
+        return np.where(r < 1.6, 0.0, 0.016 * r)
     if kind == "few_values":
         return 0.5 + np.floor(r * 3.0)                 # about ten values
     s = 0.016 * (1.0 + 1e-9 * r)                       # a band far narrower than the first window next to the outlier
@@ -24,7 +29,7 @@ def scores_of(kind, n):
     return s
 
 
-@pytest.mark.parametrize("kind", ["distinct", "few_values", "outlier"])
+@pytest.mark.parametrize("kind", ["distinct", "few_values", "outlier", "equal", "dead"])
 @pytest.mark.parametrize("n", [1, 63, 256, 257, 1024, 1025, 4096, 4097, 8193, 16384, 16385, 17 * 1024, 82944, 300001])
 def test_selection_matches_the_oracle(n, kind):
     s = scores_of(kind, n)
