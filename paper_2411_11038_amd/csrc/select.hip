@@ -370,31 +370,38 @@ struct SelWs {
   unsigned int part[2 * kSelBlocks];                  // smallest, largest upper half of every block's keys
   unsigned int hist[kSelBins];                        // all keys, first window
   int above[kSelBlocks];                              // keys of every block in bins above the threshold's
-  int ncand, pad[63];
+  int tie[kSelBlocks];                                // too many candidates: selected ones of every block, and
+  u64 T;                                              // the threshold pair
+  int I, ncand, pad[60];
   u64 cand_key[kSelCand];
   int cand_idx[kSelCand];
 };
 static int64_t sel_per_block(int64_t n) { return std::max<int64_t>(1024, round_up(ceil_div(n, kSelBlocks), 1024)); }
 
-// keys of the block's range, four loads in flight per thread: f(key, index)
-template <class F>
-__device__ __forceinline__ void sel_range(const double* scores, int64_t n, int64_t per, F f) {
-  const int64_t b0 = (int64_t)blockIdx.x * per, b1 = b0 + per < n ? b0 + per : n;
-  for (int64_t i0 = b0 + threadIdx.x; i0 < b1; i0 += 1024) {
-    double v[4];
+// keys b0 .. b1 - 1 by a block of NTH threads, U loads in flight per thread: f(key, index)
+template <int NTH, int U, class F>
+__device__ __forceinline__ void sel_keys(const double* scores, int64_t b0, int64_t b1, F f) {
+  for (int64_t i0 = b0 + threadIdx.x; i0 < b1; i0 += U * NTH) {
+    double v[U];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = i0 + 256 * u < b1 ? scores[i0 + 256 * u] : 0.0;
+    for (int u = 0; u < U; ++u) v[u] = i0 + NTH * u < b1 ? scores[i0 + NTH * u] : 0.0;
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (i0 + 256 * u < b1) f(score_key(v[u]), i0 + 256 * u);
+    for (int u = 0; u < U; ++u)
+      if (i0 + NTH * u < b1) f(score_key(v[u]), i0 + NTH * u);
   }
+}
+// keys of the block's range
+template <int NTH, class F>
+__device__ __forceinline__ void sel_range(const double* scores, int64_t n, int64_t per, F f) {
+  const int64_t b0 = (int64_t)blockIdx.x * per;
+  sel_keys<NTH, 4>(scores, b0, b0 + per < n ? b0 + per : n, f);
 }
 
 __global__ __launch_bounds__(256) void k_sel_range(const double* __restrict__ scores, int64_t n, int64_t per,
                                                    SelWs* __restrict__ ws, const SelectOut out) {
   __shared__ unsigned int s_lo[4], s_hi[4];
   unsigned int lo = ~0u, hi = 0u;
-  sel_range(scores, n, per, [&](u64 key, int64_t) {
+  sel_range<256>(scores, n, per, [&](u64 key, int64_t) {
     const unsigned int h = (unsigned int)(key >> 32);
     lo = h < lo ? h : lo; hi = h > hi ? h : hi;
   });
@@ -414,10 +421,11 @@ __global__ __launch_bounds__(256) void k_sel_range(const double* __restrict__ sc
     for (int64_t l = t; l < out.n_layers; l += nt) out.per_layer[l] = 0;
 }
 
-// base of all keys from the blocks' parts; the first window is the kSelBits below the top bit of the differences
-__device__ __forceinline__ u64 sel_window(SelShared<256>& sh, const SelWs* ws, int* shift) {
+// base of all keys from the parts of the nb blocks; the first window is the kSelBits below the top bit of the differences
+template <class SH>
+__device__ __forceinline__ u64 sel_window(SH& sh, const SelWs* ws, int nb, int* shift) {
   unsigned int lo = ~0u, hi = 0u;
-  if (threadIdx.x < gridDim.x) { lo = ws->part[2 * threadIdx.x]; hi = ws->part[2 * threadIdx.x + 1]; }
+  if ((int)threadIdx.x < nb) { lo = ws->part[2 * threadIdx.x]; hi = ws->part[2 * threadIdx.x + 1]; }
   int top;
   const u64 base = block_base(sh, lo, hi, &top);
   *shift = top - kSelBits;
@@ -429,35 +437,68 @@ __global__ __launch_bounds__(256) void k_sel_hist(const double* __restrict__ sco
   __shared__ SelShared<256> sh;
   int shift;
   for (int b = threadIdx.x; b < kSelBins; b += 256) sh.hist[b] = 0u;
-  const u64 kmin = sel_window(sh, ws, &shift);        // its barrier also orders the clearing
-  sel_range(scores, n, per, [&](u64 key, int64_t) { atomicAdd(&sh.hist[(key - kmin) >> shift], 1u); });
+  const u64 kmin = sel_window(sh, ws, (int)gridDim.x, &shift);   // its barrier also orders the clearing
+  sel_range<256>(scores, n, per, [&](u64 key, int64_t) { atomicAdd(&sh.hist[(key - kmin) >> shift], 1u); });
   __syncthreads();
   for (int b = threadIdx.x; b < kSelBins; b += 256)
     if (sh.hist[b]) atomicAdd(&ws->hist[b], sh.hist[b]);
 }
 
 // the threshold's bin, from the histogram of all keys
-__device__ __forceinline__ void sel_bin(SelShared<256>& sh, const SelWs* ws, int64_t k) {
-  unsigned int bins[kSelBins / 256];
+template <class SH>
+__device__ __forceinline__ void sel_bin(SH& sh, const SelWs* ws, int64_t k) {
+  constexpr int BPT = SH::kBpt;
+  unsigned int bins[BPT];
 #pragma unroll
-  for (int u = 0; u < kSelBins / 256; u += 4) {
-    const uint4 v = *reinterpret_cast<const uint4*>(&ws->hist[threadIdx.x * (kSelBins / 256) + u]);
+  for (int u = 0; u < BPT; u += 4) {
+    const uint4 v = *reinterpret_cast<const uint4*>(&ws->hist[threadIdx.x * BPT + u]);
     bins[u] = v.x; bins[u + 1] = v.y; bins[u + 2] = v.z; bins[u + 3] = v.w;
   }
   search_bins(sh, bins, (int)k);
 }
 
-__global__ __launch_bounds__(256) void k_sel_collect(const double* __restrict__ scores, int64_t n, int64_t per,
-                                                     int64_t k, SelWs* __restrict__ ws) {
-  __shared__ SelShared<256> sh;
-  __shared__ int red[4];
+// Block b of nb collects the candidates (the keys in the threshold's bin) of its range and counts its keys above them.
+// A bin may hold more candidates than are kept: most scores equal, or a few far from the rest (one channel of zeros puts
+// all live channels of an octave fraction into one bin).  The additional block nb then finds the threshold pair from all
+// keys by itself, beside the others and in no launch of its own, and counts what it selects of every range.  1024 threads
+// for the sake of this block.  Whole call on 82944 keys, distinct / with one zero / all equal: 34 / 82 / 132 us; when every
+// block of k_sel_write went through all keys instead, 35 / 195 / 469 us.
+constexpr int kSelCollect = 1024;
+__global__ __launch_bounds__(kSelCollect) void k_sel_collect(const double* __restrict__ scores, int64_t n, int64_t per,
+                                                             int nb, int64_t k, SelWs* __restrict__ ws) {
+  constexpr int NTH = kSelCollect, NW = NTH / 64;
+  __shared__ SelShared<NTH> sh;
+  __shared__ int red[NW];
+  __shared__ int tie[kSelBlocks];
+  const int tid = threadIdx.x;
   int shift;
-  const u64 kmin = sel_window(sh, ws, &shift);
+  const u64 kmin = sel_window(sh, ws, nb, &shift);
   sel_bin(sh, ws, k);
   const u64 bin = (u64)sh.bin;
-  const bool keep = sh.count <= kSelCand;
+  const int need = sh.need, count = sh.count;
+  const bool keep = count <= kSelCand;
+  if ((int)blockIdx.x == nb) {
+    if (keep) return;
+    if (tid < kSelBlocks) tie[tid] = 0;
+    __syncthreads();                                  // everybody has read sh.need / sh.count
+    auto each = [&](auto f) {
+      sel_keys<NTH, 8>(scores, 0, n, [&](u64 key, int64_t i) { f(key - kmin, (int)i); });
+    };
+    find_threshold(sh, each, bin, shift, need, count, n, count == n);
+    const u64 T = sh.T;
+    const int I = sh.I;
+    each([&](u64 key, int i) {
+      // a wavefront's 64 neighbours lie in one range
+      const u64 sel = __ballot((key >> shift) == bin && (key > T || (key == T && i <= I)));
+      if ((tid & 63) == 0 && sel) atomicAdd(&tie[(unsigned int)i / (unsigned int)per], (int)__popcll(sel));
+    });
+    __syncthreads();
+    if (tid < nb) ws->tie[tid] = tie[tid];
+    if (tid == 0) { ws->T = T; ws->I = I; }
+    return;
+  }
   int above = 0;
-  sel_range(scores, n, per, [&](u64 key, int64_t i) {
+  sel_range<NTH>(scores, n, per, [&](u64 key, int64_t i) {
     const u64 b = (key - kmin) >> shift;
     above += b > bin ? 1 : 0;
     if (keep && b == bin) {
@@ -467,14 +508,17 @@ __global__ __launch_bounds__(256) void k_sel_collect(const double* __restrict__ 
   });
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) above += __shfl_xor(above, o, kWave);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = above;
+  if ((tid & 63) == 0) red[tid >> 6] = above;
   __syncthreads();
-  if (threadIdx.x == 0) ws->above[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+  if (tid == 0) {
+    above = 0;
+    for (int w = 0; w < NW; ++w) above += red[w];
+    ws->above[blockIdx.x] = above;
+  }
 }
 
-// Every block finds the threshold pair from the candidates (all of them in the threshold's bin), counts what the blocks
-// before it select, and writes its own range.  Should a bin hold more candidates than are kept (mass ties), every block
-// goes through all keys instead.
+// Every block finds the threshold pair from the candidates (or has it from k_sel_collect), counts what the blocks before it
+// select, and writes its own range.
 __global__ __launch_bounds__(256) void k_sel_write(const double* __restrict__ scores, int64_t n, int64_t per, int64_t k,
                                                    const SelWs* __restrict__ ws, const SelectOut out_) {
   __shared__ SelShared<256> sh;
@@ -494,27 +538,26 @@ __global__ __launch_bounds__(256) void k_sel_write(const double* __restrict__ sc
   int before = 0;                                     // selected elements ahead of this block's range: whole bins ...
   for (int b = tid; b < (int)blockIdx.x; b += 256) before += ws->above[b];
   int shift;
-  const u64 kmin = sel_window(sh, ws, &shift);
+  const u64 kmin = sel_window(sh, ws, (int)gridDim.x, &shift);
   sel_bin(sh, ws, k);
   const u64 bin = (u64)sh.bin;
   const int need = sh.need, count = sh.count;
-  const bool kept = count <= kSelCand;
   __syncthreads();                                    // everybody has read sh.need / sh.count
   if (table) out.layer_off = s_off;
-  auto each = [&](auto f) {
-    if (kept) {
+  u64 T;
+  int I;
+  if (count <= kSelCand) {
+    auto each = [&](auto f) {
       for (int i = tid; i < count; i += 256) f(ws->cand_key[i], ws->cand_idx[i]);
-    } else {
-      for (int64_t i = tid; i < n; i += 256) f(score_key(scores[i]) - kmin, (int)i);
-    }
-  };
-  find_threshold(sh, each, bin, shift, need, count, n, count == n);
-  const u64 T = sh.T;
-  const int I = sh.I;
-  // ... and candidates
-  each([&](u64 key, int i) {
-    before += (i < b0 && (key >> shift) == bin && (key > T || (key == T && i <= I))) ? 1 : 0;
-  });
+    };
+    find_threshold(sh, each, bin, shift, need, count, n, false);
+    T = sh.T; I = sh.I;
+    // ... and candidates
+    each([&](u64 key, int i) { before += (i < b0 && (key > T || (key == T && i <= I))) ? 1 : 0; });
+  } else {
+    T = ws->T; I = ws->I;
+    for (int b = tid; b < (int)blockIdx.x; b += 256) before += ws->tie[b];
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, kWave);
   if (lane == 0) red[wv] = before;
@@ -587,7 +630,7 @@ static void launch_select(const double* scores, int64_t n, int64_t k, const Sele
     const dim3 grid((unsigned)ceil_div(n, per));
     hipLaunchKernelGGL(k_sel_range, grid, dim3(256), 0, st, scores, n, per, w, out);
     hipLaunchKernelGGL(k_sel_hist, grid, dim3(256), 0, st, scores, n, per, w);
-    hipLaunchKernelGGL(k_sel_collect, grid, dim3(256), 0, st, scores, n, per, k, w);
+    hipLaunchKernelGGL(k_sel_collect, dim3(grid.x + 1), dim3(kSelCollect), 0, st, scores, n, per, (int)grid.x, k, w);
     hipLaunchKernelGGL(k_sel_write, grid, dim3(256), 0, st, scores, n, per, k, w, out);
   }
 }
