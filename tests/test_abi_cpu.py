@@ -174,6 +174,58 @@ def test_workspace_queries_are_host_only_and_monotone():
     assert L.efqat_layer_select_workspace_bytes(48) >= 48 * 8
 
 
+def test_marshalling_refuses_what_is_no_gpu_tensor():
+    """An integer is never taken for an address, nor a host or strided tensor for device memory."""
+    import torch
+    _ensure_built()
+    from paper_2411_11038_amd import binding
+    nat = binding._native()
+    host = torch.zeros(8, 8)
+    good = [None, 4, 8, 2, None, None, None, 0, None]  # channel_select with NULL pointers: refused by the library itself
+    assert nat.channel_select(*good) == -1
+
+    def call(pos, value):
+        args = list(good)
+        args[pos] = value
+        return nat.channel_select(*args)
+
+    for pos in (0, 4, 5, 6):                           # w, scores, idx, ws
+        with pytest.raises(ValueError, match="GPU"):
+            call(pos, host)
+        for wrong in (4096, ..., "x", 1.0, host.numpy()):
+            with pytest.raises(TypeError, match="tensor expected"):
+                call(pos, wrong)
+    for pos in (1, 3, 7):                              # c_out, k, ws_bytes
+        for wrong in (torch.tensor(4), 4.0, None, "4"):
+            with pytest.raises(TypeError, match="integer expected"):
+                call(pos, wrong)
+        with pytest.raises(OverflowError):
+            call(pos, 1 << 70)
+    for wrong in (host, "x", 1.0):
+        with pytest.raises(TypeError, match="stream handle expected"):
+            call(8, wrong)
+    for n in (0, 8, 10):
+        with pytest.raises(TypeError, match="9 expected"):
+            nat.channel_select(*(good + [None])[:n])
+    # through the wrappers: an address in the place of a scale, a host tensor in the place of the codes
+    with pytest.raises((TypeError, ValueError)):
+        binding.linear_fwd(torch.zeros(2, 8, dtype=torch.uint8), 4096, 4096, torch.zeros(4, 8, dtype=torch.int8), 4096,
+                           ws=torch.zeros(256, dtype=torch.uint8))
+
+
+@pytest.mark.gpu
+def test_marshalling_refuses_strided_tensors_and_addresses():
+    import torch
+    w = torch.zeros(8, 8, device="cuda")
+    with pytest.raises(ValueError, match="contiguous"):
+        ef.channel_select(w.t()[:, :4], 2)
+    x = torch.zeros(2, 16, dtype=torch.uint8, device="cuda")
+    s = torch.ones(1, device="cuda")
+    codes = torch.zeros(4, 16, dtype=torch.int8, device="cuda")
+    with pytest.raises(TypeError, match="tensor expected"):
+        ef.linear_fwd(x, s.data_ptr(), s, codes, torch.ones(4, device="cuda"))
+
+
 def test_product_path_has_no_oracle_or_cpu_fallback():
     pkg = os.path.join(ROOT, "paper_2411_11038_amd")
     for dirpath, _, files in os.walk(pkg):
