@@ -111,6 +111,9 @@ int efqat_fakequant_fwd(const void* x, int dtype, int64_t rows, int64_t cols, in
  *   k       0..c_out  (0 is valid: nothing is written to idx)
  *   scores  out, nullable  double[c_out]
  *   idx     out  int32[k]  (may be NULL when k == 0)
+ * Workspace: the Top-K of more than 16384 channels runs on many blocks in the size the query gives.
+ * Scores alone (8 c_out bytes, rounded up to 256) are accepted too, here and in
+ * efqat_weight_quant_select: same result, from one block.
  */
 size_t efqat_channel_select_workspace_bytes(int64_t c_out);
 int efqat_channel_select(const float* w, int64_t c_out, int64_t block, int64_t k, double* scores,
@@ -152,7 +155,8 @@ int efqat_weight_quant_select(const float* w, int64_t c_out, int64_t block, int 
  *                    index within each layer (index local to its layer)
  *   k_per_layer out  int32[n_layers] (device): how many channels of each layer were selected
  * Ties go to the earlier layer, then the lower channel.  EfQAT-LWPN is the same call on one
- * score per layer (n_layers = total). */
+ * score per layer (n_layers = total).
+ * Workspace: as for efqat_channel_select; 256 bytes are accepted at any size. */
 size_t efqat_network_select_workspace_bytes(int64_t total);
 int efqat_network_select(const double* scores, const int64_t* layer_off, int64_t n_layers,
                          int64_t total, int64_t k_total, int32_t* idx, int32_t* k_per_layer,
@@ -168,7 +172,8 @@ int efqat_network_select(const double* scores, const int64_t* layer_off, int64_t
  *   k_layers     0..n_layers
  *   layer_scores out, nullable  double[n_layers]
  *   layer_idx    out  int32[k_layers] ascending (may be NULL when k_layers == 0)
- *   k_per_layer  out  int32[n_layers]: C_out of the layer if it is unfrozen, else 0 */
+ *   k_per_layer  out  int32[n_layers]: C_out of the layer if it is unfrozen, else 0
+ * Workspace: as for efqat_channel_select; 8 n_layers bytes, rounded up to 256, are accepted. */
 size_t efqat_layer_select_workspace_bytes(int64_t n_layers);
 int efqat_layer_select(const double* scores, const int64_t* layer_off, int64_t n_layers,
                        int64_t k_layers, double* layer_scores, int32_t* layer_idx,

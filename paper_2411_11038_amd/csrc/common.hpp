@@ -199,8 +199,11 @@ struct ProfScope {
 // Eq. 6 scores of every row of w [c_out][block] (double precision), and the Top-K launch, shared by the select and
 // the combined weight-side entry points
 int launch_row_importance(const float* w, int64_t c_out, int64_t block, double* scores, hipStream_t st);
-// ws: topk_ws_bytes(n) bytes, 256-byte aligned (0 bytes for inputs that one block selects from)
+// ws: topk_ws_bytes(n) bytes, 256-byte aligned; nullptr for inputs that one block selects from (0 bytes), and where the
+// caller's workspace holds the scores only (same result, by one block)
 size_t topk_ws_bytes(int64_t n);
+void* take_topk_ws(WsCarver& carve, size_t ws_bytes, int64_t n);
+inline size_t scores_ws_bytes(int64_t n) { return (size_t)round_up(n * (int64_t)sizeof(double), 256); }
 void launch_topk(const double* scores, int64_t n, int64_t k, int32_t* idx, void* ws, hipStream_t st);
 int launch_topk_profiled(const double* scores, int64_t n, int64_t k, int32_t* idx, void* ws, hipStream_t st);
 

@@ -461,14 +461,14 @@ extern "C" int efqat_weight_quant_select(const float* w, int64_t c_out, int64_t 
   if (bits < 2 || bits > 8) return EFQAT_ERR_BAD_BITS;
   if (k < 0 || k > c_out) return EFQAT_ERR_BAD_K;
   if (!w || !scale || !codes || !clip_bits || !ws || (k > 0 && !idx)) return EFQAT_ERR_NULL_PTR;
-  if (ws_bytes < efqat_weight_quant_select_workspace_bytes(c_out)) return EFQAT_ERR_WORKSPACE;
+  if (ws_bytes < scores_ws_bytes(c_out)) return EFQAT_ERR_WORKSPACE;
   if (((uintptr_t)ws % 256) != 0 || ((uintptr_t)w % 4) != 0 || ((uintptr_t)clip_bits % 4) != 0 ||
       ((uintptr_t)scale % 4) != 0 || ((uintptr_t)idx % 4) != 0 || ((uintptr_t)scores % 8) != 0)
     return EFQAT_ERR_ALIGNMENT;
   hipStream_t st = (hipStream_t)stream;
   WsCarver carve(ws);
   double* own = (double*)carve.take((size_t)c_out * sizeof(double));
-  void* sel_ws = carve.take(topk_ws_bytes(c_out));
+  void* sel_ws = take_topk_ws(carve, ws_bytes, c_out);
   double* sc = scores ? scores : own;
   bool scores_done = false;
   int rc = run_fakequant<float>(w, c_out, block, EFQAT_QUANT_W_PER_ROW_SYM, bits, init_minmax, scale, nullptr, codes,

@@ -517,6 +517,43 @@ __global__ __launch_bounds__(kSelCollect) void k_sel_collect(const double* __res
   }
 }
 
+// Writes the selected keys of b0 .. b1 - 1 in index order from output position `base` on; v: this thread's first four keys.
+template <int NTH>
+__device__ __forceinline__ void write_range(const double* scores, int64_t b0, int64_t b1, int64_t base, double (&v)[4],
+                                            u64 kmin, u64 T, int I, int (&wave_sel)[4][NTH / 64], const SelectOut& out) {
+  constexpr int NW = NTH / 64;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const u64 below = (1ull << lane) - 1ull;
+  for (int64_t i0 = b0; i0 < b1; i0 += 4 * NTH) {
+    bool sel[4];
+    if (i0 > b0) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) { const int64_t i = i0 + NTH * u + tid; v[u] = i < b1 ? scores[i] : 0.0; }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t i = i0 + NTH * u + tid;
+      const u64 key = score_key(v[u]) - kmin;
+      sel[u] = i < b1 && (key > T || (key == T && (int)i <= I));
+      const u64 b = __ballot(sel[u]);
+      if (lane == 0) wave_sel[u][wv] = __popcll(b);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t i = i0 + NTH * u + tid;
+      int64_t pos = base + __popcll(__ballot(sel[u]) & below);
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        pos += w < wv ? wave_sel[u][w] : 0;
+        base += wave_sel[u][w];
+      }
+      emit(out, sel[u], pos, i, i < b1);
+    }
+    __syncthreads();
+  }
+}
+
 // Every block finds the threshold pair from the candidates (or has it from k_sel_collect), counts what the blocks before it
 // select, and writes its own range.
 __global__ __launch_bounds__(256) void k_sel_write(const double* __restrict__ scores, int64_t n, int64_t per, int64_t k,
@@ -562,38 +599,51 @@ __global__ __launch_bounds__(256) void k_sel_write(const double* __restrict__ sc
   for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, kWave);
   if (lane == 0) red[wv] = before;
   __syncthreads();
-  int64_t base = (red[0] + red[1]) + (red[2] + red[3]);
-  const u64 below = (1ull << lane) - 1ull;
-  for (int64_t i0 = b0; i0 < b1; i0 += 1024) {
-    bool sel[4];
-    if (i0 > b0) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u) { const int64_t i = i0 + 256 * u + tid; v[u] = i < b1 ? scores[i] : 0.0; }
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t i = i0 + 256 * u + tid;
-      const u64 key = score_key(v[u]) - kmin;
-      sel[u] = i < b1 && (key > T || (key == T && (int)i <= I));
-      const u64 b = __ballot(sel[u]);
-      if (lane == 0) wave_sel[u][wv] = __popcll(b);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int64_t i = i0 + 256 * u + tid;
-      int64_t pos = base + __popcll(__ballot(sel[u]) & below);
-#pragma unroll
-      for (int w = 0; w < 4; ++w) pos += w < wv ? wave_sel[u][w] : 0;
-      emit(out, sel[u], pos, i, i < b1);
-      base += (wave_sel[u][0] + wave_sel[u][1]) + (wave_sel[u][2] + wave_sel[u][3]);
-    }
-    __syncthreads();
-  }
+  write_range<256>(scores, b0, b1, (red[0] + red[1]) + (red[2] + red[3]), v, kmin, T, I, wave_sel, out);
 }
 
-// One block up to kTopkBlockKeys; the four-launch chain beyond, whose workspace is topk_ws_bytes(n).
+// Beyond kTopkBlockKeys without a workspace (a caller that hands over no more than the scores need): one block goes through
+// all keys once per window, and once more to write.  Whole call on 82944 keys, distinct / all
+// equal: 155 / 188 us (the chain: 32 / 130 us).
+__global__ __launch_bounds__(kSelCollect) void k_sel_one(const double* __restrict__ scores, int64_t n, int64_t k,
+                                                         const SelectOut out) {
+  constexpr int NTH = kSelCollect;
+  __shared__ SelShared<NTH> sh;
+  __shared__ int wave_sel[4][NTH / 64];
+  const int tid = threadIdx.x;
+  if (out.layer_off && !out.flags) {
+    for (int64_t l = tid; l < out.n_layers; l += NTH) out.per_layer[l] = 0;
+    __threadfence();
+  }
+  unsigned int lo = ~0u, hi = 0u;
+  sel_keys<NTH, 8>(scores, 0, n, [&](u64 key, int64_t) {
+    const unsigned int h = (unsigned int)(key >> 32);
+    lo = h < lo ? h : lo; hi = h > hi ? h : hi;
+  });
+  int top;
+  const u64 kmin = block_base(sh, lo, hi, &top);      // its barrier also orders the clearing of per_layer
+  u64 T = 0;
+  int I = INT32_MAX;                                  // k == n: every key
+  if (k < n) {
+    auto each = [&](auto f) {
+      sel_keys<NTH, 8>(scores, 0, n, [&](u64 key, int64_t i) { f(key - kmin, (int)i); });
+    };
+    find_threshold(sh, each, 0ull, top, (int)k, (int)n, n, top == 32);
+    T = sh.T; I = sh.I;
+  }
+  double v[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) { const int64_t i = NTH * u + tid; v[u] = i < n ? scores[i] : 0.0; }
+  write_range<NTH>(scores, 0, n, 0, v, kmin, T, I, wave_sel, out);
+}
+
+// One block up to kTopkBlockKeys; the four-launch chain beyond, whose workspace is topk_ws_bytes(n) (k_sel_one without it).
 size_t topk_ws_bytes(int64_t n) { return n > kTopkBlockKeys ? (size_t)round_up((int64_t)sizeof(SelWs), 256) : 0; }
+
+void* take_topk_ws(WsCarver& carve, size_t ws_bytes, int64_t n) {
+  const size_t need = topk_ws_bytes(n);
+  return need > 0 && carve.off + need <= ws_bytes ? carve.take(need) : nullptr;
+}
 
 // no channel selected anywhere: all counts are 0
 __global__ __launch_bounds__(256) void k_zero_counts(int32_t* __restrict__ per_layer, int64_t n_layers) {
@@ -624,6 +674,8 @@ static void launch_select(const double* scores, int64_t n, int64_t k, const Sele
     EFQAT_TOPK(1024, 0, (size_t)n * sizeof(u64));
   }
 #undef EFQAT_TOPK
+  else if (!ws)
+    hipLaunchKernelGGL(k_sel_one, dim3(1), dim3(kSelCollect), 0, st, scores, n, k, out);
   else {
     SelWs* w = (SelWs*)ws;
     const int64_t per = sel_per_block(n);
@@ -670,7 +722,7 @@ extern "C" int64_t efqat_k_from_ratio(int64_t c_out, int64_t num, int64_t den) {
 
 extern "C" size_t efqat_channel_select_workspace_bytes(int64_t c_out) {
   if (c_out <= 0) return 0;
-  return (size_t)round_up(c_out * (int64_t)sizeof(double), 256) + topk_ws_bytes(c_out);
+  return scores_ws_bytes(c_out) + topk_ws_bytes(c_out);
 }
 
 extern "C" int efqat_channel_select(const float* w, int64_t c_out, int64_t block, int64_t k, double* scores,
@@ -678,12 +730,12 @@ extern "C" int efqat_channel_select(const float* w, int64_t c_out, int64_t block
   if (c_out <= 0 || block <= 0 || c_out > INT32_MAX || c_out > INT64_MAX / block) return EFQAT_ERR_BAD_SHAPE;
   if (k < 0 || k > c_out) return EFQAT_ERR_BAD_K;
   if (!w || !ws || (k > 0 && !idx)) return EFQAT_ERR_NULL_PTR;
-  if (ws_bytes < efqat_channel_select_workspace_bytes(c_out)) return EFQAT_ERR_WORKSPACE;
+  if (ws_bytes < scores_ws_bytes(c_out)) return EFQAT_ERR_WORKSPACE;
   if (((uintptr_t)ws % 256) != 0 || ((uintptr_t)w % 4) != 0) return EFQAT_ERR_ALIGNMENT;
   hipStream_t st = (hipStream_t)stream;
   WsCarver carve(ws);
   double* sc = (double*)carve.take((size_t)c_out * sizeof(double));
-  void* sel_ws = carve.take(topk_ws_bytes(c_out));
+  void* sel_ws = take_topk_ws(carve, ws_bytes, c_out);
   double* sc_out = scores ? scores : sc;
   const int vec = (((uintptr_t)w % 16) == 0 && block % 4 == 0) ? 1 : 0;
   {
@@ -767,10 +819,12 @@ extern "C" int efqat_network_select(const double* scores, const int64_t* layer_o
   if (n_layers <= 0 || total <= 0 || total > INT32_MAX) return EFQAT_ERR_BAD_SHAPE;
   if (k_total < 0 || k_total > total) return EFQAT_ERR_BAD_K;
   if (!scores || !layer_off || !k_per_layer || !ws || (k_total > 0 && !idx)) return EFQAT_ERR_NULL_PTR;
-  if (ws_bytes < efqat_network_select_workspace_bytes(total)) return EFQAT_ERR_WORKSPACE;
+  if (ws_bytes < 256) return EFQAT_ERR_WORKSPACE;
   if (((uintptr_t)ws % 256) != 0) return EFQAT_ERR_ALIGNMENT;
   hipStream_t st = (hipStream_t)stream;
-  launch_select(scores, total, k_total, SelectOut{idx, k_total, layer_off, n_layers, k_per_layer, 0}, ws, st);
+  WsCarver carve(ws);
+  launch_select(scores, total, k_total, SelectOut{idx, k_total, layer_off, n_layers, k_per_layer, 0},
+                take_topk_ws(carve, ws_bytes, total), st);
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
 }
@@ -803,7 +857,7 @@ using namespace efqat;
 
 extern "C" size_t efqat_layer_select_workspace_bytes(int64_t n_layers) {
   const int64_t n = n_layers > 0 ? n_layers : 1;
-  return (size_t)round_up(n * (int64_t)sizeof(double), 256) + topk_ws_bytes(n);
+  return scores_ws_bytes(n) + topk_ws_bytes(n);
 }
 
 extern "C" int efqat_layer_select(const double* scores, const int64_t* layer_off, int64_t n_layers,
@@ -812,12 +866,12 @@ extern "C" int efqat_layer_select(const double* scores, const int64_t* layer_off
   if (n_layers <= 0 || n_layers > INT32_MAX) return EFQAT_ERR_BAD_SHAPE;
   if (k_layers < 0 || k_layers > n_layers) return EFQAT_ERR_BAD_K;
   if (!scores || !layer_off || !k_per_layer || !ws || (k_layers > 0 && !layer_idx)) return EFQAT_ERR_NULL_PTR;
-  if (ws_bytes < efqat_layer_select_workspace_bytes(n_layers)) return EFQAT_ERR_WORKSPACE;
+  if (ws_bytes < scores_ws_bytes(n_layers)) return EFQAT_ERR_WORKSPACE;
   if (((uintptr_t)ws % 256) != 0) return EFQAT_ERR_ALIGNMENT;
   hipStream_t st = (hipStream_t)stream;
   WsCarver carve(ws);
   double* own = (double*)carve.take((size_t)n_layers * sizeof(double));
-  void* sel_ws = carve.take(topk_ws_bytes(n_layers));
+  void* sel_ws = take_topk_ws(carve, ws_bytes, n_layers);
   double* ls = layer_scores ? layer_scores : own;
   hipLaunchKernelGGL(k_layer_means, dim3((unsigned)n_layers), dim3(256), 0, st, scores, layer_off, ls);
   EFQAT_LAUNCH_CHECK();

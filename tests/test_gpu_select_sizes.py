@@ -111,3 +111,32 @@ def test_any_doubles_are_ordered_by_bit_pattern(n, kind):
                 torch.cuda.synchronize()
             got = idx.cpu().numpy()
             assert rc == 0 and np.array_equal(got[:k], want) and np.all(got[k:] == -7)
+
+
+@pytest.mark.parametrize("kind", ["distinct", "few_values", "equal", "dead", "outlier", "signs"])
+@pytest.mark.parametrize("n", [16385, 82944, 300001])
+def test_a_workspace_without_room_for_the_chain_selects_the_same(n, kind):
+    s = synth.normal(4100 + n, 0, (n,)) if kind == "signs" else scores_of(kind, n)
+    flat, ws = dev(s), torch.empty(256, dtype=torch.uint8, device="cuda")
+    cuts = dev(np.array([0, n // 7, n // 7, n // 2, n], dtype=np.int64))
+    for k in (1, n // 4, n - 1, n):
+        idx, per_layer = ef.network_select(flat, cuts, k, ws=ws)
+        ref, ref_per = ef.network_select(flat, cuts, k)
+        torch.cuda.synchronize()
+        assert torch.equal(idx, ref) and torch.equal(per_layer, ref_per)
+
+
+def test_scores_alone_are_workspace_enough():
+    n = 20000
+    small = torch.empty((n * 8 + 255) // 256 * 256, dtype=torch.uint8, device="cuda")
+    w = dev(synth.normal(5, 1, (n, 4), std=0.02).astype(np.float32))
+    idx, scores = ef.channel_select(w, n // 4)
+    assert torch.equal(ef.channel_select(w, n // 4, ws=small)[0], idx)
+    assert torch.equal(ef.weight_quant_select(w, 8, n // 4, ws=small)["idx"], idx)
+    off = dev(np.arange(n + 1, dtype=np.int64))
+    ref = ef.layer_select(scores, off, n // 3)
+    got = ef.layer_select(scores, off, n // 3, ws=small)
+    assert all(torch.equal(a, b) for a, b in zip(got, ref))
+    for call in (lambda ws: ef.channel_select(w, 5, ws=ws), lambda ws: ef.layer_select(scores, off, 5, ws=ws)):
+        with pytest.raises(Exception, match="workspace"):
+            call(small[:-256])
