@@ -3,6 +3,7 @@
 // once per output element in the epilogue.
 #include "common.hpp"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace efqat {
@@ -31,7 +32,8 @@ __global__ __launch_bounds__(64 * kSkinnyWaves) void k_fwd_skinny(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, kg = lane >> 4;
-  const int n0 = (int)blockIdx.x * COLS;
+  const int n0 = (int)(blockIdx.y * gridDim.x + blockIdx.x) * COLS;
+  if (n0 >= c_out) return;                              // the last row of the grid
   const int steps = (K + 63) / 64, per = (steps + NW - 1) / NW;
   const int s_end = (wave + 1) * per < steps ? (wave + 1) * per : steps;
   const uint8_t* xp[MT];
@@ -167,9 +169,14 @@ extern "C" int efqat_linear_fwd(const uint8_t* x_codes, const float* s_x, const 
   hipStream_t st = (hipStream_t)stream;
   if (T <= kSkinnyTokens) {
     ProfScope prof(PROF_FWD, st);
-#define EFQAT_SKINNY(MT, NT, BATCH)                                                                                  \
-  hipLaunchKernelGGL((k_fwd_skinny<MT, NT, BATCH>), dim3((unsigned)ceil_div(c_out, 16 * NT)), dim3(64 * kSkinnyWaves), 0, \
-                     st, x_codes, w_codes, (int)T, (int)c_out, (int)c_in, s_x, z_x, s_w, y, y_dtype)
+    // a grid dimension holds less than 2^32 work items
+    auto grid = [&](int cols) {
+      const int64_t blocks = ceil_div(c_out, cols), bx = std::min<int64_t>(blocks, 1 << 22);
+      return dim3((unsigned)bx, (unsigned)ceil_div(blocks, bx));
+    };
+#define EFQAT_SKINNY(MT, NT, BATCH)                                                                                      \
+  hipLaunchKernelGGL((k_fwd_skinny<MT, NT, BATCH>), grid(16 * NT), dim3(64 * kSkinnyWaves), 0, st, x_codes, w_codes, (int)T, \
+                     (int)c_out, (int)c_in, s_x, z_x, s_w, y, y_dtype)
     if (T <= 16) EFQAT_SKINNY(1, 1, 4);
     else if (T <= 32) EFQAT_SKINNY(2, 1, 4);
     else if (c_out >= 8192) EFQAT_SKINNY(4, 4, 1);

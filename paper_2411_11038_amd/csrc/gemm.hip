@@ -674,6 +674,7 @@ static FwdTile fwd_tile(int64_t M, int64_t N, int64_t K) {
   double best_t = 0.0;
   for (const FwdTile& c : kFwdTiles) {
     const int64_t tiles = ceil_div(M, c.bm) * ceil_div(N, c.bn), round = 256 * c.bpc;
+    if (tiles >= (1 << 24) && c.bm < 256) continue;     // a grid dimension holds less than 2^32 work items
     const double lone = c.lone[0] * stages + c.lone[1], full = c.full[0] * stages + c.full[1];
     double t = (double)(tiles / round) * full;
     if (const int64_t rest = tiles % round) {

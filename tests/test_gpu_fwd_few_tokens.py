@@ -44,3 +44,14 @@ def test_forward_tiles_match_integer_arithmetic(T, c_in, c_out, z, dtype):
     sums = (x.double() - z) @ w.double().t()                      # integers below 2^53: exact in any order
     ref = sums.float() * (sx * sw)[None, :]                       # the same two roundings
     assert torch.equal(got, ref.to(dtype))
+
+
+def test_more_columns_than_one_grid_dimension_holds():
+    c_out = (1 << 27) + 5                                         # 16 columns and 512 threads a block: beyond 2^32 threads
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    x = torch.tensor([[201]], dtype=torch.uint8, device="cuda")
+    w = torch.randint(-127, 128, (c_out, 1), generator=g, device="cuda", dtype=torch.int8)
+    sx, sw = torch.tensor([0.013], device="cuda"), torch.rand(c_out, generator=g, device="cuda")
+    got = ef.linear_fwd(x, sx, torch.tensor([117.0], device="cuda"), w, sw, y_dtype=torch.float32)
+    assert torch.equal(got[0], (84.0 * w[:, 0].float()) * (sx * sw))
