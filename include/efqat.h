@@ -121,7 +121,7 @@ int efqat_channel_select(const float* w, int64_t c_out, int64_t block, int64_t k
 
 /* efqat_channel_select for callers that cannot allocate device memory or hand over a workspace (code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc): the per-channel
- * scores are kept in a device array that is part of the library image (582 KiB on every GPU the
+ * scores are kept in a device array that is part of the library image (581 KiB on every GPU the
  * library runs on, for the life of the process) and are not returned.  Same w, k, idx and result as
  * efqat_channel_select; c_out above EFQAT_STATIC_SELECT_MAX_CHANNELS is EFQAT_ERR_WORKSPACE.  The call
  * allocates and frees nothing.  All calls on one GPU share that array: calls that overlap on one GPU

@@ -3,6 +3,7 @@
 #include "common.hpp"
 
 #include <algorithm>
+#include <atomic>
 
 namespace efqat {
 
@@ -759,29 +760,28 @@ extern "C" int efqat_channel_select(const float* w, int64_t c_out, int64_t block
 namespace efqat {
 
 constexpr int64_t kStaticSelectMaxChannels = EFQAT_STATIC_SELECT_MAX_CHANNELS;
-static __device__ __align__(256) double scratch[kStaticSelectMaxChannels];   // 512 KiB per GPU, for the process' life
-static __device__ __align__(256) SelWs select_scratch;                        // and 70 KiB for the Top-K of many channels
+struct StaticScratch {
+  SelWs select;                                       // the Top-K of many channels
+  double scores[kStaticSelectMaxChannels];
+};
+static_assert(sizeof(StaticScratch) <= 581 * 1024, "the size that efqat.h states, per GPU and for the process' life");
+static __device__ __align__(256) StaticScratch scratch;
 
 // Host code must not pass `scratch` itself to a kernel: here that name is only a handle for the symbol.  The
-// array's device address differs per GPU (each holds its own copy) and is looked up once per device, with that
-// device current.
+// object's device address differs per GPU (each holds its own copy) and is looked up once per device, with that
+// device current.  One pointer for both parts, so that a thread that finds it finds all of it.
 constexpr int kMaxDevices = 64;
-static double* g_scratch_ptr[kMaxDevices];
-static void* g_select_ptr[kMaxDevices];
+static std::atomic<StaticScratch*> g_scratch_ptr[kMaxDevices];
 
-static int static_scratch(double** out, void** sel_ws) {
+static int static_scratch(StaticScratch** out) {
   int dev = -1;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return EFQAT_ERR_HIP;
-  if (!g_scratch_ptr[dev]) {
-    double* p = nullptr;
-    void* q = nullptr;
-    if (hipGetSymbolAddress(&q, HIP_SYMBOL(select_scratch)) != hipSuccess || !q) return EFQAT_ERR_HIP;
+  StaticScratch* p = g_scratch_ptr[dev].load(std::memory_order_acquire);
+  if (!p) {
     if (hipGetSymbolAddress((void**)&p, HIP_SYMBOL(scratch)) != hipSuccess || !p) return EFQAT_ERR_HIP;
-    g_select_ptr[dev] = q;
-    g_scratch_ptr[dev] = p;
+    g_scratch_ptr[dev].store(p, std::memory_order_release);
   }
-  *out = g_scratch_ptr[dev];
-  *sel_ws = g_select_ptr[dev];
+  *out = p;
   return EFQAT_OK;
 }
 
@@ -794,17 +794,17 @@ extern "C" int efqat_channel_select_static(const float* w, int64_t c_out, int64_
   if (k < 0 || k > c_out) return EFQAT_ERR_BAD_K;
   if (!w || (k > 0 && !idx)) return EFQAT_ERR_NULL_PTR;
   if (((uintptr_t)w % 4) != 0 || ((uintptr_t)idx % 4) != 0) return EFQAT_ERR_ALIGNMENT;
-  double* sc = nullptr;
-  void* sel_ws = nullptr;
-  const int rc = static_scratch(&sc, &sel_ws);
+  StaticScratch* own = nullptr;
+  const int rc = static_scratch(&own);
   if (rc) return rc;
+  double* sc = own->scores;
   hipStream_t st = (hipStream_t)stream;
   const int vec = (((uintptr_t)w % 16) == 0 && block % 4 == 0) ? 1 : 0;
   // every score that Top-K reads is written by this launch first: nothing in the scratch has to start at zero
   hipLaunchKernelGGL(k_row_importance, dim3((unsigned)ceil_div(c_out, 4)), dim3(256), 0, st, w, c_out, block, vec, sc);
   EFQAT_LAUNCH_CHECK();
   if (k == 0) return EFQAT_OK;
-  launch_topk(sc, c_out, k, idx, sel_ws, st);
+  launch_topk(sc, c_out, k, idx, &own->select, st);
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
 }
