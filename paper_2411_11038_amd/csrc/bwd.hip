@@ -522,6 +522,14 @@ static ConvDxStridedMap strided_map(const ConvGeom& g) {
   return ConvDxStridedMap{g.N, g.H, g.W, g.Ho, g.Wo, g.KH, g.KW, g.stride, g.pad};
 }
 
+// Can the dX product gather dY in its tile loads?  The pitch holds whole 64-channel K stages, and the multiplication that
+// takes a stage apart into tap and channel stage is exact: stages of a tile times stages of a tap below 2^32 (a million
+// channels and 16 taps are the first beyond).  Pixel coordinates take 16 bits each; conv_geom allows images to 2^15.
+static bool conv_stages_ok(const ConvGeom& g, int64_t ldc) {
+  const int64_t taps = ceil_div(g.KH, g.stride) * ceil_div(g.KW, g.stride), spt = ldc / 64;
+  return (ldc % 64) == 0 && taps * spt * spt < ((int64_t)1 << 32);
+}
+
 // dxk: the caller's choice of the dX kernel (EFQAT_DX_KERNEL_*); it changes workspace sizes, so the size query takes
 // it as well.  io_bf16: x and dX are both bf16 (known at the call, not at the workspace query: nothing it changes
 // may change a workspace size).
@@ -533,7 +541,8 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
   p.ldc = round_up(c_out, 8); p.ldt = round_up(T_out, 8);
   // A convolution whose channel count is no whole number of 64-channel K stages gets them by zero channels in the bf16
   // copy of dY (one copy instead of an im2col matrix of KH KW copies), unless that would more than double the product.
-  if (im2col && cg && cg->stride <= kMaxConvStride && dxk != EFQAT_DX_KERNEL_BF16_PINNED && round_up(c_out, 64) <= 2 * c_out)
+  if (im2col && cg && cg->stride <= kMaxConvStride && dxk != EFQAT_DX_KERNEL_BF16_PINNED && round_up(c_out, 64) <= 2 * c_out &&
+      conv_stages_ok(*cg, round_up(c_out, 64)))
     p.ldc = round_up(c_out, 64);
   p.Kx = (int64_t)taps * p.ldc;
   const bool direct_tok = dy_layout == EFQAT_DY_TOKEN_MAJOR && dy_dtype == EFQAT_BF16 && p.ldc == c_out;
@@ -548,11 +557,11 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
   p.kp = round_up(k, 8);
   p.need_sel = k > 0 && !direct_rows && !p.tn_direct;
   // stride-1 convolutions whose channel pitch is a multiple of the 64-element K stage gather dY in the tile loads
-  p.cdx = im2col && cg && cg->stride == 1 && (p.ldc % 64) == 0 && cg->H <= 65535 && cg->W <= 65535;
+  p.cdx = im2col && cg && cg->stride == 1 && conv_stages_ok(*cg, p.ldc);
   // Strides 2 to 4 (a 3 x 3 kernel at stride 2 forms 9 products per 4 pixels instead of 36, and no im2col matrix of 9
   // copies of dY: 32 x 28 x 28, 128 -> 256 channels, fp32: the im2col pass took 42 us, the backward call 108 -> 51 us); larger
   // strides have too many phases to sort the rows for.
-  p.cdxs = im2col && cg && cg->stride > 1 && cg->stride <= kMaxConvStride && (p.ldc % 64) == 0 && cg->H <= 65535 && cg->W <= 65535 &&
+  p.cdxs = im2col && cg && cg->stride > 1 && cg->stride <= kMaxConvStride && conv_stages_ok(*cg, p.ldc) &&
            dxk != EFQAT_DX_KERNEL_BF16_PINNED;
   p.plan_dx = gemm_plan(p.Mx, c_in, p.Kx, false, true, !p.cdx);
   if (p.cdxs) {

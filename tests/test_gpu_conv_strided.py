@@ -3,6 +3,7 @@ stages, against the oracle: phases with different tap counts and without taps, i
 tiles of a phase, one and several column tiles, both block shapes (up to 256 tiles and more), both dY layouts."""
 import numpy as np
 import pytest
+import torch
 
 import paper_2411_11038_amd as ef
 from tests.test_gpu_parity import _conv_case
@@ -49,3 +50,29 @@ def _draw(seed):
 @pytest.mark.parametrize("seed", range(20))
 def test_conv_bwd_gathered_dx_drawn(seed):
     _conv_case(_draw(seed))
+
+
+# K stages beyond what the tile loads take apart exactly: 2^14 channel stages times 4 x 5 taps go through the im2col matrix.
+# fp32 dX against a product in 64 bits of the same quantised operands; each operand is rounded to bf16 once (2^-8), the
+# terms are independent, so the error of a sum stays within a few times that of its 2-norm.
+def test_a_million_channels():
+    c_out, c_in, KH, KW, H, W, pad = 1 << 20, 8, 4, 5, 4, 5, 1
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9)
+    Ho, Wo = H + 2 * pad - KH + 1, W + 2 * pad - KW + 1
+    dy = torch.randn((1, Ho, Wo, c_out), generator=g, device="cuda")
+    w = torch.randint(-127, 128, (c_out, KH, KW, c_in), generator=g, device="cuda", dtype=torch.int8)
+    sw = torch.rand(c_out, generator=g, device="cuda") + 0.5
+    x = torch.zeros((1, H, W, c_in), device="cuda")
+    fx = ef.fakequant_fwd(x.view(H * W, c_in), ef.ACT_PER_TENSOR_ASYM, 8, init_minmax=False,
+                          scale=torch.ones(1, device="cuda"), zero_point=torch.full((1,), 128.0, device="cuda"))
+    out = ef.conv_bwd(dy, fx["codes"].view(1, H, W, c_in), fx["clip_bits"], x, fx["scale"], fx["zero_point"], w, None,
+                      torch.empty(1, device="cuda"), sw, None, stride=1, pad=pad)
+    ref = torch.zeros((H + 2 * pad, W + 2 * pad, c_in), dtype=torch.float64, device="cuda")
+    rows = dy.double().view(Ho * Wo, c_out)
+    for kh in range(KH):
+        for kw in range(KW):
+            part = rows @ (w[:, kh, kw].double() * sw.double()[:, None])
+            ref[kh:kh + Ho, kw:kw + Wo] += part.view(Ho, Wo, c_in)
+    ref = ref[pad:pad + H, pad:pad + W]
+    assert (out["dx"][0].double() - ref).norm() <= 2.0 ** -7 * ref.norm()
