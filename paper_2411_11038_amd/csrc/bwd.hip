@@ -129,14 +129,19 @@ __device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int
   }
 }
 
+// A row in segments, one wavefront each: of 2048 columns, or of 512 where that leaves few wavefronts (the selected rows of
+// a channel-major dY are few and long).  2 of 40 channels, 25088 tokens, fp32: backward call 73 us, with a wavefront per
+// row 124 us; 2049 x 1001, 1001 rows: segments of 512 are 1 us slower than of 2048.
+struct RowCut { uint32_t segs, cols; };
+
 // Row-wise cast/copy to bf16 with zero-padded pitch: out[m][j] = bf16(in[rm(m)][j]), j < Cn; 0 up to ldo (a multiple of
 // 8).  flat == 1: no padding, no row map and 16-byte aligned rows, i.e. one run of 8-element chunks; flat = 2 .. 64, a power
-// of two: aligned rows of whole chunks with a padded pitch, that many lanes to a row; 0: a wavefront per row, two elements
-// per lane and step.  block b of nb.
+// of two: aligned rows of whole chunks with a padded pitch, that many lanes to a row; 0: a wavefront per row segment, two
+// elements per lane and step.  block b of nb.
 template <typename T>
 __device__ __forceinline__ void rows_block(int64_t b, int64_t nb, const T* __restrict__ in, int64_t ld_in, int64_t R,
                                            int64_t Cn, const int32_t* __restrict__ rowmap, bf16_t* __restrict__ out,
-                                           int64_t ldo, int flat) {
+                                           int64_t ldo, int flat, const RowCut& cut) {
   auto chunk = [](const T* src, bf16_t* dst) {
     if constexpr (sizeof(T) == 4) {
       const float4 p = *reinterpret_cast<const float4*>(src), q = *reinterpret_cast<const float4*>(src + 4);
@@ -161,10 +166,13 @@ __device__ __forceinline__ void rows_block(int64_t b, int64_t nb, const T* __res
     return;
   }
   const int lane = threadIdx.x & 63;
-  for (int64_t m = b * 4 + (threadIdx.x >> 6); m < R; m += nb * 4) {
+  for (int64_t u = b * 4 + (threadIdx.x >> 6); u < R * cut.segs; u += nb * 4) {
+    // several segments a row: fewer than 2^32 in all (each is 512 or more elements in memory)
+    const int64_t m = cut.segs == 1 ? u : (int64_t)((uint32_t)u / cut.segs), s0 = (u - m * cut.segs) * cut.cols;
+    const int64_t s1 = s0 + cut.cols < ldo ? s0 + cut.cols : ldo;
     const T* src = in + (rowmap ? (int64_t)rowmap[m] : m) * ld_in;
 #pragma unroll 4
-    for (int64_t j = 2 * lane; j < ldo; j += 128) {
+    for (int64_t j = s0 + 2 * lane; j < s1; j += 128) {
       const float v0 = j < Cn ? rd<T>(src, j) : 0.0f, v1 = j + 1 < Cn ? rd<T>(src, j + 1) : 0.0f;
       *reinterpret_cast<uint32_t*>(out + m * ldo + j) = pack_bf16x2(v0, v1);
     }
@@ -218,6 +226,7 @@ struct PrepArgs {
   const void* dy; int64_t c_out, t_out, ldc;
   const int32_t* idx; int64_t k; bf16_t* sel; int64_t kp;          // compaction
   bf16_t* dyn; int rows_flat;                                       // copy of a token-major dY
+  RowCut rows_cut, sel_cut;                                         // of that copy, and of the selected rows
   int64_t c_in, w_ld, w_ldo;                                        // W_q^T
   const int8_t* w_codes; const float* s_w; bf16_t* wqT; int w_vec;
   TransposeExtra w_ex;
@@ -240,7 +249,7 @@ __global__ __launch_bounds__(256) void k_prep(const PrepArgs p) {
   }
   b -= p.n_gather;
   if (b < p.n_rows) {
-    rows_block<T>(b, p.n_rows, dy, p.c_out, p.t_out, p.c_out, nullptr, p.dyn, p.ldc, p.rows_flat);
+    rows_block<T>(b, p.n_rows, dy, p.c_out, p.t_out, p.c_out, nullptr, p.dyn, p.ldc, p.rows_flat, p.rows_cut);
     return;
   }
   b -= p.n_rows;
@@ -260,7 +269,7 @@ __global__ __launch_bounds__(256) void k_prep(const PrepArgs p) {
   b -= p.n_x;
   const TransposeExtra none{};
   if (b < p.n_sel) {                                   // sel[m][t] = dY of channel idx[m]
-    if (p.chan) rows_block<T>(b, p.n_sel, dy, p.t_out, p.k, p.t_out, p.idx, p.sel, p.ldt, 0);
+    if (p.chan) rows_block<T>(b, p.n_sel, dy, p.t_out, p.k, p.t_out, p.idx, p.sel, p.ldt, 0, p.sel_cut);
     else
       transpose_block<T>(tile, b % p.sel_x, b / p.sel_x, 0, dy, p.c_out, p.t_out, p.k, p.idx, nullptr, nullptr, p.sel,
                          p.ldt, 0, p.ldt, 0, none);
@@ -463,11 +472,17 @@ __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ par
 }
 
 // ------------------------------------------------------------------------------------------------
-static inline unsigned grid1d(int64_t total, int per_block = 256) {
-  int64_t b = ceil_div(total, per_block);
+static inline unsigned grid1d(int64_t total) {
+  int64_t b = ceil_div(total, 256);
   if (b > 256 * 64) b = 256 * 64;
   if (b < 1) b = 1;
   return (unsigned)b;
+}
+
+static uint32_t cut_rows(int64_t rows, int64_t ldo, RowCut* cut) {   // returns the blocks
+  cut->cols = rows * ceil_div(ldo, 512) > 4096 ? 2048 : 512;
+  cut->segs = (uint32_t)ceil_div(ldo, cut->cols);
+  return (uint32_t)std::min<int64_t>(ceil_div(rows * cut->segs, 4), 16384);
 }
 
 static int launch_prep(const PrepArgs& a, int dy_dtype, hipStream_t st) {
@@ -704,7 +719,7 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
     a.rows_flat = p.ldc == c_out ? 1 : 0;
     if (!a.rows_flat && (c_out % 8) == 0)
       for (a.rows_flat = 2; a.rows_flat < 64 && a.rows_flat < p.ldc / 8;) a.rows_flat *= 2;
-    a.n_rows = (uint32_t)std::min<int64_t>(a.rows_flat ? ceil_div(T_out * p.ldc, 256 * 16) : ceil_div(T_out, 4), 4096);
+    a.n_rows = (uint32_t)std::min<int64_t>(a.rows_flat ? ceil_div(T_out * p.ldc, 256 * 16) : cut_rows(T_out, p.ldc, &a.rows_cut), 4096);
   } else if (p.need_dyn) {
     a.dyn_vec = ((T_out % 4) == 0) ? 1 : 0;            // dY is 16-byte aligned
     a.dyn_x = (uint32_t)ceil_div(p.ldc, 64);
@@ -719,7 +734,7 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
     a.n_x = a.x_x * a.x_y * (uint32_t)(im2col ? taps : 1);
     if (p.need_sel) {
       a.sel_x = (uint32_t)ceil_div(p.ldt, 64);
-      a.n_sel = a.chan ? grid1d(io.k, 4) : a.sel_x * (uint32_t)ceil_div(io.k, 64);
+      a.n_sel = a.chan ? cut_rows(io.k, p.ldt, &a.sel_cut) : a.sel_x * (uint32_t)ceil_div(io.k, 64);
     }
   }
   rc = launch_prep(a, io.dy_dtype, st);

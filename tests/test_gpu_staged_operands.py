@@ -18,6 +18,10 @@ LINEAR = [
     (66, 63, 64, "bf16", (1, 2), 1),       # rows of dY not 16-byte aligned
     (64, 66, 72, "bf16", (1, 4), 1),       # rows of dY in place for dW, transposed for dX
     (65, 63, 64, "f32", (0, 1), 1),        # nothing selected
+    (1031, 40, 24, "f32", (1, 4), 1),      # few selected rows of several 512-column segments, the last one ragged
+    (512, 16, 33, "f32", (1, 1), 1),       # rows of one whole segment
+    (65, 24, 515, "bf16", (1, 4), 0),      # copy of dY: two segments a row
+    (16500, 9, 9, "f32", (1, 3), 0),       # more rows than blocks
 ]
 
 
