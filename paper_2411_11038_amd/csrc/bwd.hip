@@ -479,6 +479,20 @@ static inline unsigned grid1d(int64_t total) {
   return (unsigned)b;
 }
 
+// W_q^T alone (dY is used in place and no column of it is compacted), one block per tile and tap.  With the other parts'
+// code and arguments around it the launch is up to 1 us longer: 3 x 3 convolution of 8 x 14 x 14, 128 -> 64 channels, bf16,
+// all selected: backward call 34.8 us, by k_prep 35.9 us; 4096 x 1024 -> 1024, nothing selected: 20.6, 21.3 us.
+__global__ __launch_bounds__(256) void k_prep_w(const int8_t* __restrict__ w_codes, int64_t w_ld, int64_t c_out, int64_t c_in,
+                                                const float* __restrict__ s_w, bf16_t* __restrict__ wqT, int64_t w_ldo,
+                                                int64_t ldc, int w_vec, uint32_t* __restrict__ zero_page) {
+  __shared__ TransposeTile tile;
+  if (zero_page && (blockIdx.x | blockIdx.y | blockIdx.z) == 0 && threadIdx.x < 64) zero_page[threadIdx.x] = 0u;
+  TransposeExtra ex{};
+  ex.z_in = c_in; ex.z_out = ldc;
+  transpose_block<int8_t>(tile, blockIdx.x, blockIdx.y, blockIdx.z, w_codes, w_ld, c_out, c_in, nullptr, s_w, nullptr, wqT,
+                          w_ldo, 0, ldc, w_vec, ex);
+}
+
 static uint32_t cut_rows(int64_t rows, int64_t ldo, RowCut* cut) {   // returns the blocks
   cut->cols = rows * ceil_div(ldo, 512) > 4096 ? 2048 : 512;
   cut->segs = (uint32_t)ceil_div(ldo, cut->cols);
@@ -489,6 +503,12 @@ static int launch_prep(const PrepArgs& a, int dy_dtype, hipStream_t st) {
   // a grid dimension holds less than 2^32 work items
   const int64_t blocks = (int64_t)a.n_gather + a.n_rows + a.n_w + a.n_x + a.n_sel + a.n_dyn;
   if (blocks == 0) return EFQAT_OK;
+  if (blocks == a.n_w && a.w_y <= 65535) {
+    hipLaunchKernelGGL(k_prep_w, dim3(a.w_x, a.w_y, a.n_w / (a.w_x * a.w_y)), dim3(256), 0, st, a.w_codes, a.w_ld, a.c_out,
+                       a.c_in, a.s_w, a.wqT, a.w_ldo, a.ldc, a.w_vec, a.zero_page);
+    EFQAT_LAUNCH_CHECK();
+    return EFQAT_OK;
+  }
   const int64_t bx = std::min<int64_t>(blocks, 1 << 22);
   const dim3 grid((unsigned)bx, (unsigned)ceil_div(blocks, bx));
   if (dy_dtype == EFQAT_F32) hipLaunchKernelGGL((k_prep<float>), grid, dim3(256), 0, st, a);
