@@ -372,7 +372,7 @@ int efqat_conv_bwd_ex(const void* dy, int dy_dtype, int dy_layout, int64_t N, in
  *   x_codes  in  uint8 [T][c_in];  w_codes  in  int8 [c_out][c_in];  s_x, z_x float[1];  s_w float[c_out]
  *   y        out [T][c_out], dtype y_dtype (F32 or BF16)
  *   c_in <= 131072.  Codes must be 16-byte aligned unless c_in is not a multiple of 16 (then they
- *   are copied into zero-padded rows in the workspace). */
+ *   are copied into zero-padded rows in the workspace, at more than 64 tokens). */
 size_t efqat_linear_fwd_workspace_bytes(int64_t T, int64_t c_in, int64_t c_out);
 int efqat_linear_fwd(const uint8_t* x_codes, const float* s_x, const float* z_x, const int8_t* w_codes,
                      const float* s_w, int64_t T, int64_t c_in, int64_t c_out, void* y, int y_dtype,

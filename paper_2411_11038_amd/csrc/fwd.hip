@@ -17,9 +17,15 @@ typedef int intx4_t __attribute__((ext_vector_type(4)));
 // sum_k w, which the zero point needs, is taken from the same fragments.  Rows of any length and alignment.
 // One launch of 1 / 16 / 32 / 64 tokens, 4096 -> 11008 (45 MB of weight codes): 10 / 14 / 19 / 21 us; with 128 x 128
 // tiles on 86 CUs after a pass for the row sums it was 40 - 42 us.  NT = 1 spreads the rows over most blocks and wins at
-// up to 32 tokens (11008 -> 4096, 16 tokens: 13 us, NT = 2 18 us, NT = 4 28 us); at 64 tokens the token fragments are the
-// larger part of the loads, so NT = 4 shares them among more rows where that still leaves a block for most CUs (21 us,
-// NT = 1 30 us; 11008 -> 4096, too few rows for that: 44 us, NT = 1 28 us).
+// up to 32 tokens (11008 -> 4096, 16 tokens: 13 us, NT = 2 18 us, NT = 4 28 us); at 33 to 64 tokens the token fragments are
+// the larger part of the loads, so NT = 4 shares them among more rows where that still leaves a block for half of the CUs,
+// 8192 columns on.  NT = 1 / NT = 4 at 64 tokens, us:
+//   C_in      -> 4096       8192         9000         16384       32768
+//   512        4.8 /  7.8   6.2 /  8.3   7.6 /  8.4   9.5 /  8.6   17 /  16
+//   2048       8.2 / 13     13 /  14     17 /  14     23 /  16     44 /  31
+//   4096       13 /  20     23 /  22     33 /  23     44 /  28     85 /  51
+//   11008      32 /  51     62 /  56     89 /  57    116 /  61    230 / 116
+// (short rows: the line lies higher, by at most 2 us)
 constexpr int kSkinnyWaves = 8;
 template <int MT, int NT, int BATCH>
 __global__ __launch_bounds__(64 * kSkinnyWaves) void k_fwd_skinny(
@@ -136,7 +142,7 @@ struct FwdPlan {
 static FwdPlan make_fwd_plan(int64_t T, int64_t c_in, int64_t c_out) {
   FwdPlan p{};
   p.ldk = round_up(c_in, 16);
-  p.pad = p.ldk != c_in;
+  p.pad = p.ldk != c_in && T > kSkinnyTokens;         // k_fwd_skinny reads rows of any length
   WsCarver cv(nullptr);
   p.b_xpad = p.pad ? (size_t)T * p.ldk : 0; cv.take(p.b_xpad);
   p.b_wpad = p.pad ? (size_t)c_out * p.ldk : 0; cv.take(p.b_wpad);
@@ -165,7 +171,7 @@ extern "C" int efqat_linear_fwd(const uint8_t* x_codes, const float* s_x, const 
   const FwdPlan p = make_fwd_plan(T, c_in, c_out);
   if (ws_bytes < p.total) return EFQAT_ERR_WORKSPACE;
   // the tile loads are 16-byte vectors when the codes are used in place
-  if (!p.pad && ((((uintptr_t)x_codes) % 16) != 0 || (((uintptr_t)w_codes) % 16) != 0)) return EFQAT_ERR_ALIGNMENT;
+  if (p.ldk == c_in && ((((uintptr_t)x_codes) % 16) != 0 || (((uintptr_t)w_codes) % 16) != 0)) return EFQAT_ERR_ALIGNMENT;
   hipStream_t st = (hipStream_t)stream;
   if (T <= kSkinnyTokens) {
     ProfScope prof(PROF_FWD, st);
@@ -179,7 +185,7 @@ extern "C" int efqat_linear_fwd(const uint8_t* x_codes, const float* s_x, const 
                      (int)c_out, (int)c_in, s_x, z_x, s_w, y, y_dtype)
     if (T <= 16) EFQAT_SKINNY(1, 1, 4);
     else if (T <= 32) EFQAT_SKINNY(2, 1, 4);
-    else if (c_out >= 8192) EFQAT_SKINNY(4, 4, 1);
+    else if (c_out >= 8192) EFQAT_SKINNY(4, 4, 1);      // see k_fwd_skinny for both sides of this line
     else EFQAT_SKINNY(4, 1, 2);
 #undef EFQAT_SKINNY
     EFQAT_LAUNCH_CHECK();

@@ -226,6 +226,13 @@ def test_marshalling_refuses_strided_tensors_and_addresses():
         ef.linear_fwd(x, s.data_ptr(), s, codes, torch.ones(4, device="cuda"))
 
 
+def test_forward_of_few_tokens_needs_no_padded_copies():
+    _ensure_built()
+    need = ef.lib().efqat_linear_fwd_workspace_bytes
+    assert need(1, 1003, 515) == need(64, 1003, 515) == need(64, 1024, 515) == 256
+    assert need(65, 1003, 515) >= 65 * 1008 + 515 * 1008
+
+
 def test_product_path_has_no_oracle_or_cpu_fallback():
     pkg = os.path.join(ROOT, "paper_2411_11038_amd")
     for dirpath, _, files in os.walk(pkg):
