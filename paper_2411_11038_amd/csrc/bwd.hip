@@ -232,7 +232,7 @@ struct PrepArgs {
   int64_t c_in, w_ld, w_ldo;                                        // W_q^T
   const int8_t* w_codes; const float* s_w; bf16_t* wqT; int w_vec;
   TransposeExtra w_ex;
-  uint32_t* zero_page;                                              // optional: 256 zero bytes behind it
+  uint32_t* zero_page;                                              // optional: the 256 zero bytes a made operand ends in
   const uint8_t* x_codes; const float* z_x; bf16_t* xcT;            // (codes - Z_x)^T
   int64_t ldt; int x_vec;
   TransposeExtra x_ex;
@@ -578,6 +578,9 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
   p.ldc = round_up(c_out, 8); p.ldt = round_up(T_out, 8);
   // A convolution whose channel count is no whole number of 64-channel K stages gets them by zero channels in the bf16
   // copy of dY (one copy instead of an im2col matrix of KH KW copies), unless that would more than double the product.
+  // 3 x 3, c_in 128, bf16 token-major, r = 5 %, backward call padded / by im2col, us: 32 images of 28 x 28 at stride 1 with
+  // 40, 72, 136, 520 channels: 52 / 67, 61 / 73, 67 / 88, 104 / 188; at stride 2: 39 / 57, 45 / 64, 50 / 76, 66 / 162; 8 of
+  // 14 x 14 at stride 1: 36 / 37, 41 / 40, 46 / 47, 78 / 90 (72 channels, all selected: 41.3 / 39.9, the worst found).
   if (im2col && cg && cg->stride <= kMaxConvStride && dxk != EFQAT_DX_KERNEL_BF16_PINNED && round_up(c_out, 64) <= 2 * c_out &&
       conv_stages_ok(*cg, round_up(c_out, 64)))
     p.ldc = round_up(c_out, 64);
@@ -652,7 +655,7 @@ struct BwdIo {
   const int8_t* w_codes; const uint32_t* w_clip; const float* w; const float* s_w; const int32_t* idx; int64_t k;
   void* dx; int dx_dtype; float* dw; int scatter; float* ds_w; float* ds_x; float* dz_x;
   StepArgs sgd;    // fused optimizer step (sgd.w == nullptr: none)
-  const void* w_operand = nullptr;   // optional: the bf16 W_q^T matrix (then 256 zero bytes) made beforehand
+  const void* w_operand = nullptr;   // optional: the bf16 W_q^T matrix made beforehand
   hipStream_t side = nullptr;        // optional: second stream for the weight-gradient branch
 };
 
@@ -676,18 +679,18 @@ static int side_events(SideEvents* out) {
 }
 
 // Everything that can still fail once the plan is known, checked before the first launch: pointer alignment of the
-// operands that the chosen kernels copy 16 bytes at a time, and the grid limits of the staging kernels.
-static int check_plan(const BwdPlan& p, const BwdIo& io, int64_t T_out, int64_t c_in, int64_t c_out, bool im2col) {
+// operands that the chosen kernels copy 16 bytes at a time, and the size limits of the staged copies (65535 tiles of 64
+// columns: a limit of the interface, no longer of a grid).
+constexpr int64_t kMaxStagedColumns = 65535 * (int64_t)64;
+static int check_plan(const BwdPlan& p, const BwdIo& io, int64_t T_out, int64_t c_in, int64_t c_out) {
   if (p.dx8 && ((uintptr_t)io.w_codes % 16) != 0) return EFQAT_ERR_ALIGNMENT;
   if ((p.tn || p.rdw) && ((uintptr_t)io.x_codes % 16) != 0) return EFQAT_ERR_ALIGNMENT;
-  const int64_t ymax = 65535 * (int64_t)64;           // the transposing copies put 64 source columns on grid.y
-  if (!p.dx8 && !io.w_operand && c_in > ymax) return EFQAT_ERR_BAD_SHAPE;
-  if (p.need_dyn && io.dy_layout == EFQAT_DY_CHANNEL_MAJOR && T_out > ymax) return EFQAT_ERR_BAD_SHAPE;
-  if (io.k > 0 && !p.tn && !p.rdw && (c_in > ymax || io.k > ymax)) return EFQAT_ERR_BAD_SHAPE;
+  if (!p.dx8 && !io.w_operand && c_in > kMaxStagedColumns) return EFQAT_ERR_BAD_SHAPE;
+  if (p.need_dyn && io.dy_layout == EFQAT_DY_CHANNEL_MAJOR && T_out > kMaxStagedColumns) return EFQAT_ERR_BAD_SHAPE;
+  if (io.k > 0 && !p.tn && !p.rdw && (c_in > kMaxStagedColumns || io.k > kMaxStagedColumns)) return EFQAT_ERR_BAD_SHAPE;
   // 32-bit per-stage pointer steps of the kernels that read operands as they lie
   if ((p.dx8 || p.tn || p.rdw) && (c_in >= (1 << 24) || c_out >= (1 << 24))) return EFQAT_ERR_BAD_SHAPE;
   if ((p.cmx || p.rdw) && T_out >= (1 << 24)) return EFQAT_ERR_BAD_SHAPE;
-  (void)im2col;
   return EFQAT_OK;
 }
 
@@ -729,7 +732,8 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   const bool gather = p.tn && !p.tn_direct;
   const bool copy_dy = p.need_dyn && io.dy_layout == EFQAT_DY_TOKEN_MAJOR;
   const int64_t gx = std::max<int64_t>(1, ceil_div(p.kp, 128));
-  const dim3 ggrid((unsigned)gx, (unsigned)std::min(ceil_div(T_out, kGatherRows), std::max<int64_t>(1, std::min<int64_t>(65535, (1 << 24) / gx))));
+  const int64_t gy = std::max<int64_t>(1, std::min<int64_t>(65535, (1 << 24) / gx));
+  const dim3 ggrid((unsigned)gx, (unsigned)std::min(ceil_div(T_out, kGatherRows), gy));
   const bool stage_dw = io.k > 0 && !p.tn && !p.rdw;   // staged bf16 operands of the fall-back dW product
   PrepArgs a{};
   a.dy = io.dy; a.c_in = c_in; a.c_out = c_out; a.t_out = T_out; a.ldc = p.ldc; a.ldt = p.ldt;
@@ -741,7 +745,8 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
     a.rows_flat = p.ldc == c_out ? 1 : 0;
     if (!a.rows_flat && (c_out % 8) == 0)
       for (a.rows_flat = 2; a.rows_flat < 64 && a.rows_flat < p.ldc / 8;) a.rows_flat *= 2;
-    a.n_rows = (uint32_t)std::min<int64_t>(a.rows_flat ? ceil_div(T_out * p.ldc, 256 * 16) : cut_rows(T_out, p.ldc, &a.rows_cut), 4096);
+    const int64_t nb = a.rows_flat ? ceil_div(T_out * p.ldc, 256 * 16) : cut_rows(T_out, p.ldc, &a.rows_cut);
+    a.n_rows = (uint32_t)std::min<int64_t>(nb, 4096);
   } else if (p.need_dyn) {
     a.dyn_vec = ((T_out % 4) == 0) ? 1 : 0;            // dY is 16-byte aligned
     a.dyn_x = (uint32_t)ceil_div(p.ldc, 64);
@@ -924,7 +929,7 @@ static int linear_bwd_entry(BwdIo& io, int64_t T, int64_t c_in, int64_t c_out, c
   const BwdPlan p = make_plan(T, T, c_in, c_out, 1, io.k, io.dy_dtype, io.dy_layout, false, dxk, nullptr,
                               io.x_dtype == EFQAT_BF16 && io.dx_dtype == EFQAT_BF16);
   if (ws_bytes < p.total) return EFQAT_ERR_WORKSPACE;
-  rc = check_plan(p, io, T, c_in, c_out, false);
+  rc = check_plan(p, io, T, c_in, c_out);
   if (rc) return rc;
   return run_bwd(io, p, T, T, c_in, c_out, nullptr, ws, (hipStream_t)stream);
 }
@@ -974,7 +979,7 @@ extern "C" size_t efqat_linear_bwd_weight_operand_bytes(int64_t T, int64_t c_in,
                                                         int dy_layout) {
   if (!linear_shape_ok(T, c_in, c_out)) return 0;
   const BwdPlan p = make_plan(T, T, c_in, c_out, 1, 0, dy_dtype, dy_layout, false, EFQAT_DX_KERNEL_AUTO);
-  return p.dx8 ? 0 : (size_t)round_up((int64_t)p.b_wqT, 256) + 256;
+  return p.dx8 ? 0 : (size_t)round_up((int64_t)p.b_wqT, 256) + 256;   // W_q^T and 256 zero bytes (part of its format)
 }
 
 extern "C" int efqat_linear_bwd_weight_operand(const int8_t* w_codes, const float* s_w, int64_t T, int64_t c_in,
@@ -988,7 +993,7 @@ extern "C" int efqat_linear_bwd_weight_operand(const int8_t* w_codes, const floa
   if (!w_codes || !s_w || !operand) return EFQAT_ERR_NULL_PTR;
   if (operand_bytes < need) return EFQAT_ERR_WORKSPACE;
   if (((uintptr_t)operand % 256) != 0) return EFQAT_ERR_ALIGNMENT;
-  if (c_in > 65535 * (int64_t)64) return EFQAT_ERR_BAD_SHAPE;
+  if (c_in > kMaxStagedColumns) return EFQAT_ERR_BAD_SHAPE;
   const BwdPlan p = make_plan(T, T, c_in, c_out, 1, 0, dy_dtype, dy_layout, false, EFQAT_DX_KERNEL_AUTO);
   PrepArgs a{};
   prep_w_operand(a, w_codes, s_w, c_in, c_out, 1, p.ldc, (bf16_t*)operand);
@@ -1051,7 +1056,7 @@ static int conv_bwd_entry(BwdIo& io, int64_t N, int64_t H, int64_t W, int64_t c_
   const BwdPlan p = conv_plan(g, io.k, io.dy_dtype, io.dy_layout, dxk, io.x_dtype == EFQAT_BF16 && io.dx_dtype == EFQAT_BF16);
   if (ws_bytes < p.total) return EFQAT_ERR_WORKSPACE;
   const int64_t T_in = (int64_t)N * H * W, T_out = (int64_t)N * g.Ho * g.Wo;
-  rc = check_plan(p, io, T_out, c_in, c_out, true);
+  rc = check_plan(p, io, T_out, c_in, c_out);
   if (rc) return rc;
   return run_bwd(io, p, T_in, T_out, c_in, c_out, &g, ws, (hipStream_t)stream);
 }

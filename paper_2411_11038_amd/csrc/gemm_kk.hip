@@ -114,13 +114,13 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const typename ConvArgs<CONV>::
       const int64_t pix = (int64_t)cv_q0[j] + ho * g.cv_Wo + wo;
       return ok ? (const char*)g.A + (pix * g.lda + cst * 64) * 2 + c_lch * 16 : zero;
     } else {
-    const int sidx = k_begin / 64 + kt;                // 64-channel stage index along K = (tap, channel)
-    const int tap = (int)(((uint64_t)(uint32_t)sidx * g.cv_m_spt) >> 32), cst = sidx - tap * g.cv_spt;
-    const int kh = (int)(((uint64_t)(uint32_t)tap * g.cv_m_kw) >> 32), kw = tap - kh * g.cv_KW;
-    const int ho = (cv_hw[j] >> 16) + g.cv_pad - kh, wo = (cv_hw[j] & 0xFFFF) + g.cv_pad - kw;
-    const bool ok = (unsigned)ho < (unsigned)g.cv_Ho && (unsigned)wo < (unsigned)g.cv_Wo;
-    const int64_t pix = (int64_t)cv_q0[j] + ho * g.cv_Wo + wo;
-    return ok ? (const char*)g.A + (pix * g.lda + cst * 64) * 2 + c_lch * 16 : zero;
+      const int sidx = k_begin / 64 + kt;                // 64-channel stage index along K = (tap, channel)
+      const int tap = (int)(((uint64_t)(uint32_t)sidx * g.cv_m_spt) >> 32), cst = sidx - tap * g.cv_spt;
+      const int kh = (int)(((uint64_t)(uint32_t)tap * g.cv_m_kw) >> 32), kw = tap - kh * g.cv_KW;
+      const int ho = (cv_hw[j] >> 16) + g.cv_pad - kh, wo = (cv_hw[j] & 0xFFFF) + g.cv_pad - kw;
+      const bool ok = (unsigned)ho < (unsigned)g.cv_Ho && (unsigned)wo < (unsigned)g.cv_Wo;
+      const int64_t pix = (int64_t)cv_q0[j] + ho * g.cv_Wo + wo;
+      return ok ? (const char*)g.A + (pix * g.lda + cst * 64) * 2 + c_lch * 16 : zero;
     }
   };
 #pragma unroll

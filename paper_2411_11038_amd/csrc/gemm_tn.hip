@@ -781,8 +781,9 @@ static int launch_tn_cfg(const GemmTnArgs& a, int split_k, hipStream_t st) {
   return EFQAT_OK;
 }
 
-int launch_gemm_tn(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* B, int64_t ldb, int64_t b_cols, const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
-                   float* out_partial, hipStream_t stream) {
+int launch_gemm_tn(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* B, int64_t ldb, int64_t b_cols,
+                   const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan, float* out_partial,
+                   hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0 || (lda % 8) || (ldb % 16) || (a_cols % 8) || (b_cols % 16)) return EFQAT_ERR_BAD_SHAPE;
   if (lda >= (1 << 24) || ldb >= (1 << 24)) return EFQAT_ERR_BAD_SHAPE;   // 32-bit per-stage pointer strides
   if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX || a_cols > lda || b_cols > ldb) return EFQAT_ERR_BAD_SHAPE;
@@ -823,8 +824,8 @@ static bool dx8_epilogue_fast(const GemmArgs& g, const GemmEpilogueDx& epi, int 
          (g.N % tile) == 0 && (int64_t)g.M * g.N <= (int64_t)INT32_MAX;
 }
 
-int launch_gemm_dx8_cm(const bf16_t* dy_cm, int64_t lda, const int8_t* w_codes, int64_t ldb, const float* s_w, int64_t M, int64_t N, int64_t K, int tile, const GemmEpilogueDx& epi,
-                       hipStream_t stream) {
+int launch_gemm_dx8_cm(const bf16_t* dy_cm, int64_t lda, const int8_t* w_codes, int64_t ldb, const float* s_w,
+                       int64_t M, int64_t N, int64_t K, int tile, const GemmEpilogueDx& epi, hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0 || (M % 8) || (lda % 8) || (ldb % 16) || (N % 16)) return EFQAT_ERR_BAD_SHAPE;
   if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX || ldb >= (1 << 24) || lda >= (1 << 24)) return EFQAT_ERR_BAD_SHAPE;
   if (((uintptr_t)dy_cm % 16) || ((uintptr_t)w_codes % 16) || ((uintptr_t)s_w % 4))
@@ -847,8 +848,9 @@ int launch_gemm_dx8_cm(const bf16_t* dy_cm, int64_t lda, const int8_t* w_codes, 
   }
 }
 
-int launch_gemm_dw_rows(const bf16_t* dy_cm, int64_t lda, const int32_t* idx, const uint8_t* x_codes, int64_t ldb, const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
-                        float* out_partial, hipStream_t stream) {
+int launch_gemm_dw_rows(const bf16_t* dy_cm, int64_t lda, const int32_t* idx, const uint8_t* x_codes, int64_t ldb,
+                        const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan, float* out_partial,
+                        hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0 || (K % 8) || (lda % 8) || (ldb % 16) || (N % 16)) return EFQAT_ERR_BAD_SHAPE;
   if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX || ldb >= (1 << 24)) return EFQAT_ERR_BAD_SHAPE;
   if (((uintptr_t)dy_cm % 16) || ((uintptr_t)x_codes % 16)) return EFQAT_ERR_ALIGNMENT;
@@ -866,8 +868,9 @@ int launch_gemm_dw_rows(const bf16_t* dy_cm, int64_t lda, const int32_t* idx, co
   }
 }
 
-int launch_gemm_tn_conv(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* x_codes, const ConvDwMap& cm, const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
-                        float* out_partial, hipStream_t stream) {
+int launch_gemm_tn_conv(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* x_codes, const ConvDwMap& cm,
+                        const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan, float* out_partial,
+                        hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0 || (lda % 8) || (a_cols % 8) || a_cols > lda || lda >= (1 << 24)) return EFQAT_ERR_BAD_SHAPE;
   if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX || plan.tile != 128 || (cm.c_in % 128) != 0)
     return EFQAT_ERR_BAD_SHAPE;
@@ -886,8 +889,8 @@ int launch_gemm_tn_conv(const bf16_t* A, int64_t lda, int64_t a_cols, const uint
   return launch_tn_cfg<128, true>(a, plan.split_k, stream);
 }
 
-int launch_gemm_dx8(const bf16_t* dy, int64_t lda, const int8_t* w_codes, int64_t ldb, const float* s_w, int64_t M, int64_t N, int64_t K, int tile, const GemmEpilogueDx& epi,
-                    hipStream_t stream) {
+int launch_gemm_dx8(const bf16_t* dy, int64_t lda, const int8_t* w_codes, int64_t ldb, const float* s_w, int64_t M,
+                    int64_t N, int64_t K, int tile, const GemmEpilogueDx& epi, hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0 || (K % 8) || (lda % 8) || (ldb % 16) || (N % 16)) return EFQAT_ERR_BAD_SHAPE;
   if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX || ldb >= (1 << 24)) return EFQAT_ERR_BAD_SHAPE;
   if (((uintptr_t)dy % 16) || ((uintptr_t)w_codes % 16) || ((uintptr_t)s_w % 4))
