@@ -26,7 +26,8 @@ struct BadArgument {};
 }
 
 long long integer(PyObject* o, const char* what) {
-  if (!PyLong_Check(o)) refuse(PyExc_TypeError, what, o);
+  // other integer types (numpy's) by their __index__; a tensor's would wait for the GPU
+  if (!PyLong_Check(o) && (!PyIndex_Check(o) || THPVariable_Check(o))) refuse(PyExc_TypeError, what, o);
   const long long v = PyLong_AsLongLong(o);
   if (v == -1 && PyErr_Occurred()) throw BadArgument();
   return v;

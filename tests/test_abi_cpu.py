@@ -4,6 +4,7 @@ import ctypes as C
 import os
 import re
 
+import numpy as np
 import pytest
 
 import paper_2411_11038_amd as ef
@@ -183,6 +184,7 @@ def test_marshalling_refuses_what_is_no_gpu_tensor():
     host = torch.zeros(8, 8)
     good = [None, 4, 8, 2, None, None, None, 0, None]  # channel_select with NULL pointers: refused by the library itself
     assert nat.channel_select(*good) == -1
+    assert nat.channel_select(None, np.int64(4), np.int32(8), 9, None, None, None, 0, None) == -4
 
     def call(pos, value):
         args = list(good)
