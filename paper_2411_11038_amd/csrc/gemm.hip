@@ -31,8 +31,9 @@ constexpr int KALIGN = 64;  // split-K slices start on multiples of this many K 
 
 // BM x BN output tile per 256-thread block; one LDS stage holds 128 bytes of K per tile row (64 bf16 or 128 int8),
 // S stages.
-template <int BM, int BN, int S>
+template <int BM_, int BN_, int S>
 struct TileCfg {
+  static constexpr int BM = BM_, BN = BN_;
   static constexpr int BKT = 64;                        // K in units of 2 bytes
   static constexpr int WM = BM / 2, WN = BN / 2;        // per-wave tile (2 x 2 wavefronts)
   static constexpr int TM = WM / 32, TN = WN / 32;      // MFMA tiles per wave
@@ -46,7 +47,11 @@ struct TileCfg {
   static constexpr int LDS_STAGE = LDS_A + LDS_B;
   static constexpr int LDS_LOOP = S * LDS_STAGE;
   static constexpr int LDS_EPI = 4 * 32 * (WN + 8) * 4;  // staging of the fused dX epilogue
-  static constexpr int LDS_BYTES = LDS_LOOP > LDS_EPI ? LDS_LOOP : LDS_EPI;
+  template <int EPI>
+  static constexpr int lds_bytes() {
+    constexpr int e = EPI == EPI_DX ? EpiDxAny<TileCfg, float>::LDS : LDS_EPI;
+    return LDS_LOOP > e ? LDS_LOOP : e;
+  }
   // XOR swizzle: 16 consecutive rows read the same logical chunk in one ds_read_b128 quarter-wave; with
   // f(row) = (row / R256) mod CPRW the 16 physical chunks are distinct modulo 256 bytes (64 banks).
   __device__ static __forceinline__ int swz(int row, int chunk) {
@@ -80,8 +85,9 @@ __device__ __forceinline__ void wait_vmcnt() {
 // I8: operands are int8 codes (A unsigned, re-biased by 128 in registers) on v_mfma_i32_32x32x32_i8; else bf16.
 // CONV = 1: the A operand is gathered from a token-major dY with the im2col map of a stride-1 convolution (see GemmArgs);
 // CONV = 2: of a convolution with a stride, rows sorted by phase (see ConvPhase).
+// two blocks of up to 128 x 128 share a CU (by LDS): the epilogue must not take more than half of the registers
 template <int BM, int BN, int EPI, bool I8, int CONV = 0>
-__global__ __launch_bounds__(256) void k_gemm_nt(const typename ConvArgs<CONV>::type g) {
+__global__ __launch_bounds__(256, BM * BN <= 128 * 128 ? 2 : 1) void k_gemm_nt(const typename ConvArgs<CONV>::type g) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the body uses gfx950-only builtins; the host pass needs only the launch stub
   constexpr int S = 2;
   constexpr int ESZ = I8 ? 1 : 2;                       // bytes per K element
@@ -297,7 +303,7 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const typename ConvArgs<CONV>::
   };
 
   // CONV = 2: the matrix row of every tile row, behind the stages in LDS
-  int* rowmap = reinterpret_cast<int*>(smem + C::LDS_BYTES);
+  int* rowmap = reinterpret_cast<int*>(smem + C::template lds_bytes<EPI>());
   if constexpr (CONV == 2) {
     if (tid < BM) {
       int q0, hw;
@@ -374,7 +380,7 @@ __global__ __launch_bounds__(256) void k_gemm_nt(const typename ConvArgs<CONV>::
         }
       }
   } else if constexpr (EPI == EPI_DX) {
-    epilogue_dx<C, CONV == 2>(g, acc, smem, m0, n0, wm, wn, rowmap);
+    epilogue_dx<C, CONV == 2>(g, acc, smem, m0, n0, wm, wn, CONV == 2 ? ph.rows : g.M, rowmap);
   } else if constexpr (EPI == EPI_DXF) {
     epilogue_dx_fast<C>(g, acc, smem, m0, n0, wm, wn);
   } else {
@@ -505,7 +511,7 @@ bool gemm_epilogue_vec_ok(const GemmEpilogueDx& e, int64_t N) {
 template <int BM, int BN, int EPI, bool I8, int CONV = 0>
 static int launch_cfg(const typename ConvArgs<CONV>::type& a, int split_k, hipStream_t st) {
   using C = TileCfg<BM, BN, 2>;
-  constexpr int kLds = C::LDS_BYTES + (CONV == 2 ? BM * (int)sizeof(int) : 0);
+  constexpr int kLds = C::template lds_bytes<EPI>() + (CONV == 2 ? BM * (int)sizeof(int) : 0);
   // set once per process (initialisation of a function-local static is thread-safe)
   static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_nt<BM, BN, EPI, I8, CONV>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return EFQAT_ERR_HIP;

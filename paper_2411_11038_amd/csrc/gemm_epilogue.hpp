@@ -2,11 +2,14 @@
 #pragma once
 #include "common.hpp"
 
+#include <type_traits>
+
 namespace efqat {
 
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
 
-enum { EPI_RAW = 0, EPI_DX = 1, EPI_FWD = 2, EPI_DXF = 3 };   // DXF: epilogue_dx_fast
+// the dX epilogue for any matrix with x in bf16 (DX) or fp32 (DXS), and for whole bf16 tiles (DXF)
+enum { EPI_RAW = 0, EPI_DX = 1, EPI_FWD = 2, EPI_DXF = 3, EPI_DXS = 4 };
 
 struct GemmArgs {
   const void* A; int64_t lda; const int32_t* a_rows;   // lda / ldb / K in elements (bf16 or int8)
@@ -83,179 +86,245 @@ __device__ __forceinline__ void lds_barrier() {
 
 // Fused epilogue of the dX product for a 256-thread block whose wavefront (wm, wn) holds the C::WM x C::WN
 // sub-tile at (m0 + wm * C::WM, n0 + wn * C::WN) of an M x N output in C::TM x C::TN 32x32 MFMA accumulators.
-// smem: at least 4 * 32 * (C::WN + 8) floats, no longer used by the main loop (the caller has synchronised).
-// MAP: the matrix row of the block's row r is rowmap[r] (LDS, -1 past the last row) instead of m0 + r.
-template <class C, bool MAP = false>
-__device__ __forceinline__ void epilogue_dx(const GemmArgs& g, floatx16_t (&acc)[C::TM][C::TN], char* smem, int m0,
-                                            int n0, int wm, int wn, const int* rowmap = nullptr) {
-  auto row_of = [&](int r) -> int { if constexpr (MAP) return rowmap[r]; else return m0 + r; };
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int fr = lane & 31, fh = lane >> 5;
-  // dX = dX_q where the activation was not clipped (straight-through), 0 elsewhere; block partial sums
-  // of dS_x = sum dX_q * (in range ? (code - Z) - x/S : code - Z) and dZ_x = sum dX_q * (in range ? 0 : -S).
-  // The accumulators go through LDS (32 rows of the wave's tile at a time) so that every lane then owns
-  // 8 consecutive columns of one row: 8-byte code loads, 16-byte x loads and 16-byte dX stores.
-  constexpr int PITCH = C::WN + 8;                   // floats; 4*PITCH = 32 (mod 64) banks
-  constexpr int CPR = C::WN / 8;                     // 8-column chunks per row
-  constexpr int RPP = 64 / CPR;                      // rows per pass of the wavefront (lanes beyond RPP*CPR idle)
-  constexpr int NPASS = (32 + RPP - 1) / RPP;
-  float* stage = reinterpret_cast<float*>(smem) + wave * 32 * PITCH;
-  const float s = g.s_x[0];
-  const float z = rintf(g.z_x[0]);
-  const float ninv_s = -1.0f / s;
-  const int64_t wpr = (g.N + 31) >> 5;
-  const int row_l0 = lane / CPR, ch = lane % CPR;
-  const int gcol = n0 + wn * C::WN + ch * 8;
-  float ps = 0.0f, pz = 0.0f;
-  const bool lane_on = row_l0 < RPP && gcol < g.N;
-  if (g.epi_vec) {
-    // Vector path (N % 8 == 0, aligned pointers): a lane's 8-column chunk is entirely inside the matrix.
-    // The global inputs of 32-row slab i+1 are fetched while slab i is computed, so their latency is hidden
-    // even with a single resident block per CU.
-    struct Inputs { uint2 cw; uint4 xa, xb; uint32_t mb; };
-    Inputs in[2][NPASS];
-    auto fetch = [&](int i, int b) {
-#pragma unroll
-      for (int p = 0; p < NPASS; ++p) {
-        const int row_l = p * RPP + row_l0;
-        const int grow = row_l < 32 ? row_of(wm * C::WM + i * 32 + row_l) : -1;
-        if (lane_on && grow >= 0 && grow < g.M) {
-          const int64_t e = (int64_t)grow * g.N + gcol;
-          in[b][p].mb = g.x_clip[(int64_t)grow * wpr + (gcol >> 5)] >> (gcol & 31);
-          in[b][p].cw = *reinterpret_cast<const uint2*>(g.x_codes + e);
-          if (g.x_dtype == EFQAT_F32) {
-            in[b][p].xa = *reinterpret_cast<const uint4*>((const float*)g.x + e);
-            in[b][p].xb = *reinterpret_cast<const uint4*>((const float*)g.x + e + 4);
-          } else {
-            in[b][p].xa = *reinterpret_cast<const uint4*>((const bf16_t*)g.x + e);
-          }
-        }
-      }
-    };
-    fetch(0, 0);
-#pragma unroll
-    for (int i = 0; i < C::TM; ++i) {
-      const int b = i & 1;
-      if (i > 0) __syncthreads();
-#pragma unroll
-      for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          stage[(8 * (r >> 2) + 4 * fh + (r & 3)) * PITCH + j * 32 + fr] = acc[i][j][r];
-      __syncthreads();
-      if (i + 1 < C::TM) fetch(i + 1, b ^ 1);
-#pragma unroll
-      for (int p = 0; p < NPASS; ++p) {
-        const int row_l = p * RPP + row_l0;
-        const int grow = row_l < 32 ? row_of(wm * C::WM + i * 32 + row_l) : -1;
-        if (lane_on && grow >= 0 && grow < g.M) {
-          const float4 a0 = *reinterpret_cast<const float4*>(stage + row_l * PITCH + ch * 8);
-          const float4 a1 = *reinterpret_cast<const float4*>(stage + row_l * PITCH + ch * 8 + 4);
-          const float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-          const int64_t e = (int64_t)grow * g.N + gcol;
-          const Inputs& q8 = in[b][p];
-          float xv[8];
-          if (g.x_dtype == EFQAT_F32) {
-            xv[0] = __uint_as_float(q8.xa.x); xv[1] = __uint_as_float(q8.xa.y);
-            xv[2] = __uint_as_float(q8.xa.z); xv[3] = __uint_as_float(q8.xa.w);
-            xv[4] = __uint_as_float(q8.xb.x); xv[5] = __uint_as_float(q8.xb.y);
-            xv[6] = __uint_as_float(q8.xb.z); xv[7] = __uint_as_float(q8.xb.w);
-          } else {
-            const uint32_t xw[4] = {q8.xa.x, q8.xa.y, q8.xa.z, q8.xa.w};
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              xv[2 * t] = __uint_as_float(xw[t] << 16);
-              xv[2 * t + 1] = __uint_as_float(xw[t] & 0xFFFF0000u);
-            }
-          }
-          float o[8];
-#pragma unroll
-          for (int t = 0; t < 8; ++t) {
-            const uint32_t byte = ((t < 4 ? q8.cw.x : q8.cw.y) >> (8 * (t & 3))) & 0xFFu;
-            const float q = (float)byte - z;
-            const bool inr = (q8.mb >> t) & 1u;
-            const float gs = inr ? fmaf(xv[t], ninv_s, q) : q;
-            ps = fmaf(a[t], gs, ps);
-            o[t] = inr ? a[t] : 0.0f;
-            pz += a[t] - o[t];
-          }
-          if (g.dx_dtype == EFQAT_F32) {
-            *reinterpret_cast<float4*>((float*)g.dx + e) = make_float4(o[0], o[1], o[2], o[3]);
-            *reinterpret_cast<float4*>((float*)g.dx + e + 4) = make_float4(o[4], o[5], o[6], o[7]);
-          } else {
-            *reinterpret_cast<uint4*>((bf16_t*)g.dx + e) =
-                make_uint4(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]), pack_bf16x2(o[4], o[5]),
-                           pack_bf16x2(o[6], o[7]));
-          }
+//   dX = dX_q where the activation was not clipped (straight-through), 0 elsewhere; block partial sums of
+//   dS_x = sum dX_q * (in range ? (code - Z) - x/S : code - Z) and dZ_x = sum dX_q * (in range ? 0 : -S).
+// Any M, N, type and alignment of x (XT) and dX; EpiDxFast below is the case without edges.  The accumulators go to the
+// wavefront's own part of LDS, GS slabs of 32 rows at a time, so that a lane then owns chunks of 8 consecutive columns of a
+// row: LPR lanes share a row, a pass covers 64 / LPR rows.  Rows of any width and alignment are read and written in whole
+// chunks (the hardware takes vector accesses at element alignment; a chunk that runs over the end of its row reads into the
+// next one, the last ones of the matrix start earlier and are shifted), so every lane has one load of codes and one or two
+// of x per chunk, and U passes of them are in flight: what bounds it is the chain of these loads behind the main loop, a
+// lone block has nothing else to run meanwhile.  On 128 x 128 fp32 tiles of a lone block it takes 3.6 us, 4.2 us where the
+// width is odd; with branches on type and edge around each element and one 32-row slab of loads in flight (one column a
+// lane for odd widths) it took 6.5 and 12.6 us.
+template <class C, typename XT, bool MAP = false>
+struct EpiDxAny {
+  static constexpr int PITCH = C::WN + 8;            // floats; 4*PITCH = 32 (mod 64) banks
+  static constexpr int CPR = C::WN / 8;              // 8-column chunks per row
+  static constexpr int LPR = (CPR % 8 == 0) ? 8 : 4;
+  static_assert(CPR % LPR == 0, "chunks per row");
+  static constexpr int KC = CPR / LPR, RP = 64 / LPR, NP = 32 / RP * KC;   // NP: passes per slab
+  static constexpr int GS = C::TM * 512 * PITCH <= 160 * 1024 ? C::TM : C::TM / 2;
+  static constexpr int LDS = GS * 512 * PITCH;       // 4 wavefronts x 32 rows x 4 bytes
+  static_assert(LDS <= 160 * 1024 && C::TM % GS == 0, "staging");
+  static constexpr int U = KC == 1 ? (NP * GS < 4 ? NP * GS : 4) : 2 * KC;
+  static_assert(NP * GS % U == 0 && U % KC == 0, "passes");
+  static constexpr int XW = sizeof(XT) / 2;          // 16-byte words of x per chunk
+  struct Inputs { uint2 cw; uint4 xa[XW]; uint32_t mb; };
+  Inputs in[U];
+  int row_b, col_b, first_row, rows;                 // rows: of this wavefront's sub-tile that lie inside the matrix
+  const int* rowmap;
+  int64_t last;                                      // the last element a chunk may start at
+
+  // matrix row of the lane's row in the pass from row r of the sub-tile on, -1 past the end; first column of its chunk
+  template <bool EDGE>
+  __device__ __forceinline__ int row_of(int r) const {
+    if (EDGE && r + (int)(threadIdx.x & 63) / LPR >= rows) return -1;
+    if constexpr (MAP) return rowmap[row_b + r];
+    else return first_row + row_b + r;
+  }
+  __device__ __forceinline__ int col_of(int u) const { return col_b + 8 * LPR * (u % KC); }
+  // EDGE: the tile reaches over the end of the rows or columns.  Chunks outside the matrix stand at its first row or column.
+  template <bool EDGE>
+  __device__ __forceinline__ int64_t elem(const GemmArgs& g, int row, int col) const {
+    if constexpr (EDGE) return (int64_t)(row < 0 ? 0 : row) * g.N + (col < g.N ? col : 0);
+    else return (int64_t)row * g.N + col;
+  }
+  // requests the inputs of the pass from row r of the sub-tile on, set u
+  template <bool EDGE>
+  __device__ __forceinline__ void fetch(const GemmArgs& g, int r, int u) {
+    const int row = row_of<EDGE>(r), col = col_of(u);
+    const int64_t e = elem<EDGE>(g, row, col), a = EDGE && e > last ? last : e;
+    const int64_t wpr = (g.N + 31) >> 5;
+    in[u].mb = g.x_clip[(EDGE && row < 0 ? 0 : row) * wpr + ((EDGE && col >= g.N ? 0 : col) >> 5)];
+    if (!EDGE || last >= 0) {
+      __builtin_memcpy(&in[u].cw, g.x_codes + a, 8);
+      __builtin_memcpy(in[u].xa, (const XT*)g.x + a, 8 * sizeof(XT));
+    } else {                                         // a matrix of fewer than 8 elements, from its last one downwards
+#pragma unroll 1
+      for (int64_t t = (int64_t)g.M * g.N - 1; t >= e; --t) {
+        in[u].cw.y = (in[u].cw.y << 8) | (in[u].cw.x >> 24); in[u].cw.x = (in[u].cw.x << 8) | g.x_codes[t];
+        uint4& x0 = in[u].xa[0];
+        uint4& x1 = in[u].xa[XW - 1];
+        if constexpr (XW == 1) {
+          x0.w = (x0.w << 16) | (x0.z >> 16); x0.z = (x0.z << 16) | (x0.y >> 16); x0.y = (x0.y << 16) | (x0.x >> 16);
+          x0.x = (x0.x << 16) | ((const bf16_t*)g.x)[t];
+        } else {
+          x1.w = x1.z; x1.z = x1.y; x1.y = x1.x; x1.x = x0.w; x0.w = x0.z; x0.z = x0.y; x0.y = x0.x;
+          x0.x = ((const uint32_t*)g.x)[t];
         }
       }
     }
-  } else {
-    // Ragged widths / unaligned pointers: a lane owns one column of the slab (two when it is wider than 64), so that the
-    // loads and the store of a row touch neighbouring elements, and eight rows are loaded together.  Rows past the edge
-    // read row 0, columns past it column 0, and contribute nothing.  Eight neighbouring columns a lane with dependent
-    // single loads made the product of 2049 x 777 (K = 1008, fp32) 36 us, this one 26 us.
-    auto ragged = [&](const auto* xp) {
+  }
+  // Addresses of this wavefront's sub-tile, and the requests for its first U passes.  A kernel may call this
+  // before its main loop has ended, provided none of its own global -> LDS copies is still outstanding or issued later
+  // (a wavefront's loads complete in order).  m_end: end of the rows that m0 counts in.  map: the matrix row of every row
+  // of the tile (MAP).
+  template <bool EDGE>
+  __device__ __forceinline__ void prefetch_tile(const GemmArgs& g, int m0, int n0, int wm, int wn, int m_end,
+                                                const int* map) {
+    const int lane = threadIdx.x & 63;
+    row_b = wm * C::WM + lane / LPR;
+    col_b = n0 + wn * C::WN + (lane % LPR) * 8;
+    first_row = m0; rowmap = map;
+    rows = n0 + wn * C::WN >= g.N ? 0 : m_end - m0 - wm * C::WM < C::WM ? m_end - m0 - wm * C::WM : C::WM;
+    last = (int64_t)g.M * g.N - 8;
 #pragma unroll
-      for (int i = 0; i < C::TM; ++i) {
-        if (i > 0) __syncthreads();
+    for (int u = 0; u < U; ++u) {
+      if (EDGE) in[u] = Inputs{};
+      if (!EDGE || RP * (u / KC) < rows) fetch<EDGE>(g, RP * (u / KC), u);
+    }
+  }
+  __device__ __forceinline__ void prefetch(const GemmArgs& g, int m0, int n0, int wm, int wn, int m_end, bool edge,
+                                           const int* map) {
+    if (edge) prefetch_tile<true>(g, m0, n0, wm, wn, m_end, map);
+    else prefetch_tile<false>(g, m0, n0, wm, wn, m_end, map);
+  }
+  // The epilogue proper; prefetch() has been called with the same `edge`.  smem: LDS bytes, no longer used by the main loop
+  // (the caller has synchronised).  part_idx: the tile's slot in g.partial.
+  __device__ __forceinline__ void run(const GemmArgs& g, floatx16_t (&acc)[C::TM][C::TN], char* smem, bool edge,
+                                      int part_idx) {
+    float s1 = 0.0f, sd = 0.0f;
+    if (edge) sum_tile<true>(g, acc, smem, s1, sd);
+    else sum_tile<false>(g, acc, smem, s1, sd);
+    finish(g, smem, s1, sd, part_idx);
+  }
+  __device__ __forceinline__ void finish(const GemmArgs& g, char* smem, float s1, float sd, int part_idx) {
+    const float ps = wave_sum(s1);
+    const float pz = wave_sum(sd);
+    lds_barrier();                                   // staging area is dead: reuse for the block sum
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    float* red = reinterpret_cast<float*>(smem);
+    if ((threadIdx.x & 63) == 0) { red[2 * wave] = ps; red[2 * wave + 1] = pz; }
+    lds_barrier();
+    if (threadIdx.x == 0) {
+      g.partial[2 * part_idx] = (red[0] + red[2]) + (red[4] + red[6]);
+      g.partial[2 * part_idx + 1] = -g.s_x[0] * ((red[1] + red[3]) + (red[5] + red[7]));
+    }
+  }
+  // the tile's dX; s1, sd: this lane's share of the sums (see EpiDxFast)
+  template <bool EDGE>
+  __device__ __forceinline__ void sum_tile(const GemmArgs& g, floatx16_t (&acc)[C::TM][C::TN], char* smem, float& s1,
+                                           float& sd) {
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int fr = lane & 31, fh = lane >> 5;
+    float* stage = reinterpret_cast<float*>(smem) + wave * GS * 32 * PITCH;
+    const float z = rintf(g.z_x[0]);
+    const float ninv_s = -1.0f / g.s_x[0];
+    const float* st_b = stage + (lane / LPR) * PITCH + (lane % LPR) * 8;
+#pragma unroll
+    for (int i0 = 0; i0 < C::TM; i0 += GS) {
+      // a wavefront reads what it wrote itself: no barrier, its own LDS accesses have to be done
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+      for (int i = 0; i < GS; ++i)
 #pragma unroll
         for (int j = 0; j < C::TN; ++j)
 #pragma unroll
           for (int r = 0; r < 16; ++r)
-            stage[(8 * (r >> 2) + 4 * fh + (r & 3)) * PITCH + j * 32 + fr] = acc[i][j][r];
-        __syncthreads();
-#pragma unroll
-        for (int cc = 0; cc < C::WN; cc += 64) {
-          const int col = cc + lane, gc = n0 + wn * C::WN + col;
-          const bool on = col < C::WN && gc < g.N;
-          const int gl = on ? gc : 0;
+            stage[(32 * i + 8 * (r >> 2) + 4 * fh + (r & 3)) * PITCH + j * 32 + fr] = acc[i0 + i][j][r];
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll 1
-          for (int r0 = 0; r0 < 32; r0 += 8) {
-            int grow[8];
-            float xv[8], q[8];
-            uint32_t clip[8];
+      for (int r0 = 0; r0 < 32 * GS; r0 += RP * U / KC) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              grow[u] = row_of(wm * C::WM + i * 32 + r0 + u);
-              if (grow[u] >= g.M) grow[u] = -1;
-              const int64_t row = grow[u] < 0 ? 0 : grow[u], e = row * g.N + gl;
-              q[u] = (float)g.x_codes[e] - z;
-              clip[u] = g.x_clip[row * wpr + (gl >> 5)];
-              if constexpr (sizeof(*xp) == 4) xv[u] = xp[e]; else xv[u] = bf16_to_f32(xp[e]);
-            }
+        for (int u = 0; u < U; ++u) {
+          const int r = r0 + RP * (u / KC);
+          if (EDGE && 32 * i0 + r >= rows) continue;
+          const float4 n0v = *reinterpret_cast<const float4*>(st_b + r * PITCH + 8 * LPR * (u % KC));
+          const float4 n1v = *reinterpret_cast<const float4*>(st_b + r * PITCH + 8 * LPR * (u % KC) + 4);
+          float a[8] = {n0v.x, n0v.y, n0v.z, n0v.w, n1v.x, n1v.y, n1v.z, n1v.w};
+          Inputs q8 = in[u];
+          if (32 * i0 + r + RP * U / KC < (EDGE ? rows : C::WM)) fetch<EDGE>(g, 32 * i0 + r + RP * U / KC, u);
+          const int row = row_of<EDGE>(32 * i0 + r), col = col_of(u);
+          const int64_t e = elem<EDGE>(g, row, col);
+          uint32_t mb = q8.mb >> (col & 31);          // mask bits of the chunk
+          int n = 8;                                  // its elements inside the matrix
+          if constexpr (EDGE) {
+            n = row < 0 ? 0 : g.N - col;
+            mb &= n >= 8 ? 0xFFu : n > 0 ? (1u << n) - 1u : 0u;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-              const bool ok = on && grow[u] >= 0;
-              const float av = ok ? stage[(r0 + u) * PITCH + col] : 0.0f;
-              const bool inr = (clip[u] >> (gl & 31)) & 1u;
-              const float gs = inr ? fmaf(xv[u], ninv_s, q[u]) : q[u];
-              const float ov = inr ? av : 0.0f;
-              if (ok) {
-                const int64_t e = (int64_t)grow[u] * g.N + gl;
-                ps = fmaf(av, gs, ps);
-                pz += av - ov;
-                if (g.dx_dtype == EFQAT_F32) ((float*)g.dx)[e] = ov;
-                else ((bf16_t*)g.dx)[e] = f32_to_bf16(ov);
+            for (int t = 0; t < 8; ++t) a[t] = t < n ? a[t] : 0.0f;
+            if (last >= 0)
+#pragma unroll 1
+              for (int64_t sh = e - last; sh > 0; --sh) {  // the chunk was read from `last` on: move it down
+                q8.cw.x = (q8.cw.x >> 8) | (q8.cw.y << 24); q8.cw.y >>= 8;
+                uint4& x0 = q8.xa[0];
+                uint4& x1 = q8.xa[XW - 1];
+                if constexpr (XW == 1) {
+                  x0.x = (x0.x >> 16) | (x0.y << 16); x0.y = (x0.y >> 16) | (x0.z << 16);
+                  x0.z = (x0.z >> 16) | (x0.w << 16); x0.w >>= 16;
+                } else {
+                  x0.x = x0.y; x0.y = x0.z; x0.z = x0.w; x0.w = x1.x; x1.x = x1.y; x1.y = x1.z; x1.z = x1.w;
+                }
               }
-            }
           }
+          const uint32_t xw[8] = {q8.xa[0].x,      q8.xa[0].y,      q8.xa[0].z,      q8.xa[0].w,
+                                  q8.xa[XW - 1].x, q8.xa[XW - 1].y, q8.xa[XW - 1].z, q8.xa[XW - 1].w};
+          float o[8];
+#pragma unroll
+          for (int t = 0; t < 8; ++t) {
+            const float xv = XW == 2 ? __uint_as_float(xw[t])
+                                     : __uint_as_float((t & 1) ? xw[t >> 1] & 0xFFFF0000u : xw[t >> 1] << 16);
+            const uint32_t byte = ((t < 4 ? q8.cw.x : q8.cw.y) >> (8 * (t & 3))) & 0xFFu;
+            const bool inr = (mb >> t) & 1u;
+            const float q = (float)byte - z;
+            const float gs = inr ? fmaf(xv, ninv_s, q) : q;
+            s1 = fmaf(a[t], gs, s1);
+            o[t] = inr ? a[t] : 0.0f;
+            sd += a[t] - o[t];
+          }
+          if (g.dx_dtype == EFQAT_F32) {
+            float* d = (float*)g.dx + e;
+            if (!EDGE || n >= 8) __builtin_memcpy(d, o, 32);
+            else
+#pragma unroll 1
+              for (int t = 0; t < n; ++t) {
+                d[t] = o[0];
+#pragma unroll
+                for (int v = 0; v < 6; ++v) o[v] = o[v + 1];
+              }
+          } else {
+            bf16_t* d = (bf16_t*)g.dx + e;
+            uint32_t w[4] = {pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]), pack_bf16x2(o[4], o[5]),
+                             pack_bf16x2(o[6], o[7])};
+            if (!EDGE || n >= 8) __builtin_memcpy(d, w, 16);
+            else
+#pragma unroll 1
+              for (int t = 0; t < n; ++t) {
+                d[t] = (bf16_t)w[0];
+#pragma unroll
+                for (int v = 0; v < 3; ++v) w[v] = (w[v] >> 16) | (w[v + 1] << 16);
+                w[3] >>= 16;
+              }
+          }
+          __builtin_amdgcn_sched_barrier(0);          // keeps the passes from piling up in registers
         }
       }
-    };
-    if (g.x_dtype == EFQAT_F32) ragged((const float*)g.x);
-    else ragged((const bf16_t*)g.x);
+    }
   }
-  ps = wave_sum(ps);
-  pz = wave_sum(pz);
-  __syncthreads();                                   // staging area is dead: reuse for the block sum
-  float* red = reinterpret_cast<float*>(smem);
-  if (lane == 0) { red[2 * wave] = ps; red[2 * wave + 1] = pz; }
-  __syncthreads();
-  if (tid == 0) {
-    g.partial[2 * blockIdx.x] = (red[0] + red[2]) + (red[4] + red[6]);
-    g.partial[2 * blockIdx.x + 1] = -s * ((red[1] + red[3]) + (red[5] + red[7]));
+};
+
+// ... with the type of x decided at run time, all requests behind the main loop
+template <class C, bool MAP = false>
+__device__ __forceinline__ void epilogue_dx(const GemmArgs& g, floatx16_t (&acc)[C::TM][C::TN], char* smem, int m0,
+                                            int n0, int wm, int wn, int m_end, const int* rowmap = nullptr) {
+  const bool edge = m0 + C::BM > m_end || n0 + C::BN > g.N;
+  auto all = [&](auto e, auto edgec) {
+    constexpr bool EDGE = decltype(edgec)::value;
+    e.template prefetch_tile<EDGE>(g, m0, n0, wm, wn, m_end, rowmap);
+    float s1 = 0.0f, sd = 0.0f;
+    e.template sum_tile<EDGE>(g, acc, smem, s1, sd);
+    e.finish(g, smem, s1, sd, blockIdx.x);
+  };
+  using Yes = std::integral_constant<bool, true>;
+  using No = std::integral_constant<bool, false>;
+  if (g.x_dtype == EFQAT_F32) {
+    if (edge) all(EpiDxAny<C, float, MAP>(), Yes{});
+    else all(EpiDxAny<C, float, MAP>(), No{});
+  } else {
+    if (edge) all(EpiDxAny<C, bf16_t, MAP>(), Yes{});
+    else all(EpiDxAny<C, bf16_t, MAP>(), No{});
   }
 }
 
@@ -268,7 +337,7 @@ __device__ __forceinline__ void epilogue_dx(const GemmArgs& g, floatx16_t (&acc)
 // of pass p of the next slab are requested as soon as pass p of this slab has consumed its own (one register set, a
 // whole slab of prefetch distance).  With a single resident block per CU the predicated, branching formulation
 // above runs at about half this speed.
-// Per lane: s1 = sum a gs with gs = in range ? (code - Z) - x / S : code - Z, formed term by term as in epilogue_dx
+// Per lane: s1 = sum a gs with gs = in range ? (code - Z) - x / S : code - Z, formed term by term as in EpiDxAny
 // (in range |gs| <= 1/2, whereas sum a (code - Z) and sum a x / S taken apart would each be some hundred times larger
 // and cancel); sd = sum (a - o) with o = in range ? a : 0.
 template <class C>

@@ -37,7 +37,11 @@ struct KkCfg {
   static constexpr int NST = 3;                                  // LDS stages in the ring
   static constexpr int LDS_LOOP = NST * LDS_STAGE;
   static constexpr int LDS_EPI = 4 * 32 * (WN + 8) * 4;
-  static constexpr int LDS_BYTES = LDS_LOOP > LDS_EPI ? LDS_LOOP : LDS_EPI;
+  template <int EPI>
+  static constexpr int lds_bytes() {
+    constexpr int e = EPI == EPI_DX || EPI == EPI_DXS ? EpiDxAny<KkCfg, float>::LDS : LDS_EPI;
+    return LDS_LOOP > e ? LDS_LOOP : e;
+  }
   static_assert(WGM * WGN == 4 && WM % 32 == 0 && WN % 32 == 0 && BM % 32 == 0, "tile / wavefront grid");
 };
 
@@ -252,7 +256,12 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const typename ConvArgs<CONV>::
     }
   };
 
-  EpiDxFast<C> epi;                                   // used by EPI_DXF only
+  // the fused dX epilogue (dead code for EPI_RAW)
+  typename std::conditional<EPI == EPI_DXF, EpiDxFast<C>,
+                            EpiDxAny<C, typename std::conditional<EPI == EPI_DXS, float, bf16_t>::type, CONV == 2>>::type epi;
+  const int m_end = CONV == 2 ? ph.rows : g.M;
+  const bool edge = m0 + C::BM > m_end || n0 + C::BN > g.N;
+  int* rowmap = reinterpret_cast<int*>(smem + C::template lds_bytes<EPI>());   // CONV = 2: the matrix row of every tile row
   const int kt_epi = nk >= 2 ? nk - 2 : 0;            // the first of the last two stages
 
   // ---- main loop.  Stage kt lives in buffer kt % 3.  On entry to stage kt the first P0 copies of stage kt + 2 have
@@ -276,8 +285,9 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const typename ConvArgs<CONV>::
       const bool tail = kt + 2 >= nk;
       if (kt + 2 < nfull) issue_range(Unchecked{}, kt + 2, nn, P0, LPS);
       else if (kt + 2 < nk) issue_range(Checked{}, kt + 2, nn, 0, LPS);
-      if constexpr (EPI == EPI_DXF) {
-        if (kt == kt_epi) epi.prefetch(g, m0, n0, wm, wn);
+      if (EPI != EPI_RAW && kt == kt_epi) {
+        if constexpr (EPI == EPI_DXF) epi.prefetch(g, m0, n0, wm, wn);
+        else epi.prefetch(g, m0, n0, wm, wn, m_end, edge, rowmap);
       }
       __builtin_amdgcn_sched_barrier(0);
       load_frags(bufc, 1, 1);
@@ -301,8 +311,6 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const typename ConvArgs<CONV>::
   using Steady = std::integral_constant<bool, true>;
   using Drain = std::integral_constant<bool, false>;
 
-  // CONV = 2: the matrix row of every tile row, behind the stages in LDS
-  int* rowmap = reinterpret_cast<int*>(smem + C::LDS_BYTES);
   if constexpr (CONV == 2) {
     if (tid < C::BM) {
       int q0, hw;
@@ -329,10 +337,11 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const typename ConvArgs<CONV>::
   }
   __syncthreads();
 
-  if constexpr (EPI == EPI_DX) {
-    epilogue_dx<C, CONV == 2>(g, acc, smem, m0, n0, wm, wn, rowmap);
-  } else if constexpr (EPI == EPI_DXF) {
+  if constexpr (EPI == EPI_DXF) {
     epi.run(g, acc, smem, blockIdx.x);
+  } else if constexpr (EPI != EPI_RAW) {
+    if (CONV == 2 && nk == 0) epi.prefetch(g, m0, n0, wm, wn, m_end, edge, rowmap);   // a phase without taps
+    epi.run(g, acc, smem, edge, blockIdx.x);
   } else {
     float* out = g.out + (int64_t)split * g.M * g.N;
 #pragma unroll
@@ -354,7 +363,7 @@ template <int T, int WGM, int WGN, int EPI, int CONV = 0>
 static int launch_kk_cfg(const typename ConvArgs<CONV>::type& a, int split_k, hipStream_t st) {
   using C = KkCfg<T, WGM, WGN>;
   // set once per process (initialisation of a function-local static is thread-safe)
-  constexpr int kLds = C::LDS_BYTES + (CONV == 2 ? C::BM * (int)sizeof(int) : 0);
+  constexpr int kLds = C::template lds_bytes<EPI>() + (CONV == 2 ? C::BM * (int)sizeof(int) : 0);
   static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_kk<T, WGM, WGN, EPI, CONV>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return EFQAT_ERR_HIP;
   dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)split_k);
@@ -392,13 +401,15 @@ int launch_gemm_kk(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, i
       // nothing to decide at run time: the straight-line epilogue
       const bool fast = a.epi_vec && epi->x_dtype == EFQAT_BF16 && epi->dx_dtype == EFQAT_BF16 && (M % 192) == 0 &&
                         (N % 192) == 0 && M * N <= (int64_t)INT32_MAX;
-      return fast ? launch_kk_cfg<192, 2, 2, EPI_DXF>(a, 1, stream) : launch_kk_cfg<192, 2, 2, EPI_DX>(a, 1, stream);
+      if (fast) return launch_kk_cfg<192, 2, 2, EPI_DXF>(a, 1, stream);
+      return epi->x_dtype == EFQAT_F32 ? launch_kk_cfg<192, 2, 2, EPI_DXS>(a, 1, stream) : launch_kk_cfg<192, 2, 2, EPI_DX>(a, 1, stream);
     }
     case 128: {
       if (!epi) return launch_kk_cfg<128, 2, 2, EPI_RAW>(a, split_k, stream);
       const bool fast = a.epi_vec && epi->x_dtype == EFQAT_BF16 && epi->dx_dtype == EFQAT_BF16 && (M % 128) == 0 &&
                         (N % 128) == 0 && M * N <= (int64_t)INT32_MAX;
-      return fast ? launch_kk_cfg<128, 2, 2, EPI_DXF>(a, 1, stream) : launch_kk_cfg<128, 2, 2, EPI_DX>(a, 1, stream);
+      if (fast) return launch_kk_cfg<128, 2, 2, EPI_DXF>(a, 1, stream);
+      return epi->x_dtype == EFQAT_F32 ? launch_kk_cfg<128, 2, 2, EPI_DXS>(a, 1, stream) : launch_kk_cfg<128, 2, 2, EPI_DX>(a, 1, stream);
     }
     default:
       return EFQAT_ERR_BAD_SHAPE;
@@ -411,11 +422,12 @@ int launch_gemm_kk_conv128(const GemmArgs& a, bool fast, hipStream_t stream) {
   if ((a.K % 64) != 0) return EFQAT_ERR_BAD_SHAPE;
   GemmArgs ka = a;
   ka.k_per_split = a.K;
-  return fast ? launch_kk_cfg<128, 2, 2, EPI_DXF, 1>(ka, 1, stream) : launch_kk_cfg<128, 2, 2, EPI_DX, 1>(ka, 1, stream);
+  if (fast) return launch_kk_cfg<128, 2, 2, EPI_DXF, 1>(ka, 1, stream);
+  return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<128, 2, 2, EPI_DXS, 1>(ka, 1, stream) : launch_kk_cfg<128, 2, 2, EPI_DX, 1>(ka, 1, stream);
 }
 
 int launch_gemm_kk_conv128_strided(const GemmStridedArgs& a, hipStream_t stream) {
-  return launch_kk_cfg<128, 2, 2, EPI_DX, 2>(a, 1, stream);
+  return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<128, 2, 2, EPI_DXS, 2>(a, 1, stream) : launch_kk_cfg<128, 2, 2, EPI_DX, 2>(a, 1, stream);
 }
 
 }  // namespace efqat

@@ -420,7 +420,11 @@ struct Dx8Cfg {
   static constexpr int LDS_STAGE = LDS_A + LDS_B + LDS_S;
   static constexpr int LDS_LOOP = 2 * LDS_STAGE;
   static constexpr int LDS_EPI = 4 * 32 * (WN + 8) * 4;
-  static constexpr int LDS_BYTES = LDS_LOOP > LDS_EPI ? LDS_LOOP : LDS_EPI;
+  template <bool ANY>                                        // with EpiDxAny
+  static constexpr int lds_bytes() {
+    constexpr int e = ANY ? EpiDxAny<Dx8Cfg, float>::LDS : LDS_EPI;
+    return LDS_LOOP > e ? LDS_LOOP : e;
+  }
   static constexpr int KSH = RB == 256 ? 0 : 1;
   __device__ static __forceinline__ int swz_a(int row, int chunk) { return row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4); }
   __device__ static __forceinline__ int swz_atn(int c, int k) { return c ^ (4 * (k & 3)); }
@@ -436,7 +440,7 @@ struct GemmDx8Args {
 
 // FAST (dX only): the straight-line epilogue for bf16 x / dX and whole tiles (epilogue_dx_fast).
 template <int T, bool DW = false, bool ATN = false, bool FAST = false>
-__global__ __launch_bounds__(256) void k_gemm_dx8(const GemmDx8Args ga) {
+__global__ __launch_bounds__(256, T == 128 ? 2 : 1) void k_gemm_dx8(const GemmDx8Args ga) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using C = Dx8Cfg<T, ATN>;
   const GemmArgs& g = ga.g;
@@ -755,7 +759,7 @@ __global__ __launch_bounds__(256) void k_gemm_dx8(const GemmDx8Args ga) {
   } else if constexpr (FAST) {
     epilogue_dx_fast<C>(g, acc, smem, m0, n0, wm, wn);
   } else {
-    epilogue_dx<C>(g, acc, smem, m0, n0, wm, wn);
+    epilogue_dx<C>(g, acc, smem, m0, n0, wm, wn, g.M);
   }
 #endif
 }
@@ -805,14 +809,14 @@ int launch_gemm_tn(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* 
 
 template <int T, bool DW = false, bool ATN = false, bool FAST = false>
 static int launch_dx8_cfg(const GemmDx8Args& a, int split_k, hipStream_t st) {
-  using C = Dx8Cfg<T, ATN>;
+  constexpr int kLds = Dx8Cfg<T, ATN>::template lds_bytes<!DW && !FAST>();
   // set once per process (initialisation of a function-local static is thread-safe)
-  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_dx8<T, DW, ATN, FAST>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
+  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_dx8<T, DW, ATN, FAST>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return EFQAT_ERR_HIP;
   dim3 grid((unsigned)(a.g.tiles_m * a.g.tiles_n), (unsigned)split_k);
   {
     ProfScope prof(DW ? PROF_DW : PROF_DX, st);
-    hipLaunchKernelGGL((k_gemm_dx8<T, DW, ATN, FAST>), grid, dim3(256), C::LDS_BYTES, st, a);
+    hipLaunchKernelGGL((k_gemm_dx8<T, DW, ATN, FAST>), grid, dim3(256), kLds, st, a);
   }
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
