@@ -530,6 +530,9 @@ static void prep_w_operand(PrepArgs& a, const int8_t* w_codes, const float* s_w,
   a.n_w = a.w_x * a.w_y * (uint32_t)taps;
 }
 
+// widest staged copy, 65535 tiles of 64 columns: a limit of the interface, no longer of a grid
+constexpr int64_t kMaxStagedColumns = 65535 * (int64_t)64;
+
 // Plan of one backward call: sizes of every workspace slice (shared by the size query and the call).
 struct BwdPlan {
   int64_t Mx;      // rows of dX as a matrix (T, or N*H*W)
@@ -568,11 +571,11 @@ static bool conv_stages_ok(const ConvGeom& g, int64_t ldc) {
 }
 
 // dxk: the caller's choice of the dX kernel (EFQAT_DX_KERNEL_*); it changes workspace sizes, so the size query takes
-// it as well.  io_bf16: x and dX are both bf16 (known at the call, not at the workspace query: nothing it changes
-// may change a workspace size).
+// it as well.  wide: dX tiles of 128 and more by gemm_plan's rule, for callers whose workspace or weight codes do not fit
+// the plan by kDxTiles (see choose_plan).
 static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_out, int taps, int64_t k,
                          int dy_dtype, int dy_layout, bool im2col, int dxk, const ConvGeom* cg = nullptr,
-                         bool io_bf16 = false) {
+                         bool wide = false) {
   BwdPlan p{};
   p.Mx = T_in; p.Tw = T_out; p.Nw = (int64_t)taps * c_in;
   p.ldc = round_up(c_out, 8); p.ldt = round_up(T_out, 8);
@@ -603,36 +606,30 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
   // strides have too many phases to sort the rows for.
   p.cdxs = im2col && cg && cg->stride > 1 && cg->stride <= kMaxConvStride && conv_stages_ok(*cg, p.ldc) &&
            dxk != EFQAT_DX_KERNEL_BF16_PINNED;
-  p.plan_dx = gemm_plan(p.Mx, c_in, p.Kx, false, true, !p.cdx);
-  if (p.cdxs) {
-    p.cdx = true;
-    p.plan_dx = GemmPlan{128, 1, (int)conv_dx_strided_row_tiles(strided_map(*cg), 128), (int)ceil_div(c_in, 128)};
+  const ConvDxStridedMap sm = p.cdxs ? strided_map(*cg) : ConvDxStridedMap{};
+  const bool int8_ok = taps == 1 && !im2col && direct_tok && (c_in % 16) == 0 && dxk != EFQAT_DX_KERNEL_BF16;
+  if (wide) {
+    p.plan_dx = gemm_plan(p.Mx, c_in, p.Kx, false, true, !p.cdx);
+    if (p.cdxs) p.plan_dx = GemmPlan{128, 1, (int)conv_dx_strided_row_tiles(sm, 128), (int)ceil_div(c_in, 128)};
+    p.plan_dx.ring = (p.plan_dx.tile == 192 && !p.cdx) ||
+                     (p.plan_dx.tile == 128 && (int64_t)p.plan_dx.tiles_m * p.plan_dx.tiles_n <= 256);
+  } else {
+    p.plan_dx = dx_plan(p.Mx, c_in, p.Kx, dy_dtype == EFQAT_F32, p.cdx || p.cdxs, p.cdxs ? &sm : nullptr, int8_ok);
   }
+  if (p.cdxs) p.cdx = true;
   p.dx8 = false; p.dx8_tile = 0;
-  // Large products (the planner's 256 x 256 case) with a bf16 token-major dY read the weight operand straight
-  // from the int8 codes: same speed as the bf16 kernel on these shapes, and no transposed bf16 copy of W_q.
+  // Products on 256 x 256 tiles with a bf16 token-major dY read the weight operand straight from the int8 codes: same speed
+  // as the bf16 kernel on these shapes, and no transposed bf16 copy of W_q.
   if (p.cmx) {
     p.plan_dx = gemm_plan(p.Mx, c_in, p.Kx, false, false);
     p.dx8 = true; p.dx8_tile = p.plan_dx.tile;
   } else if (dxk == EFQAT_DX_KERNEL_BF16_PINNED) {
-    if (!p.cdx) {
-      p.plan_dx.tile = 192; p.plan_dx.split_k = 1;
-      p.plan_dx.tiles_m = (int)ceil_div(p.Mx, 192); p.plan_dx.tiles_n = (int)ceil_div(c_in, 192);
-    }
-  } else if (taps == 1 && !im2col && direct_tok && (c_in % 16) == 0 && dxk != EFQAT_DX_KERNEL_BF16 &&
-      (p.plan_dx.tile == 256 || dxk == EFQAT_DX_KERNEL_INT8)) {
+    if (!p.cdx) p.plan_dx = GemmPlan{192, 1, (int)ceil_div(p.Mx, 192), (int)ceil_div(c_in, 192), true};
+  } else if (int8_ok && (p.plan_dx.tile == 256 || dxk == EFQAT_DX_KERNEL_INT8)) {
     p.dx8 = true; p.dx8_tile = (p.plan_dx.tile == 256 || (p.Mx >= 1024 && c_in >= 512)) ? 256 : 128;
     p.plan_dx.tiles_m = (int)ceil_div(p.Mx, p.dx8_tile); p.plan_dx.tiles_n = (int)ceil_div(c_in, p.dx8_tile);
   }
-  // bf16 in and out, whole 192 x 192 tiles: the pinned kernel with its straight-line epilogue changes the ranking of
-  // the tiles below 256 (the workspace slices do not depend on the outcome)
-  if (!p.dx8 && !p.cdx && io_bf16 && p.plan_dx.tile != 256 && (p.Mx % 192) == 0 && (c_in % 192) == 0 &&
-      p.Mx * c_in <= (int64_t)INT32_MAX && dxk != EFQAT_DX_KERNEL_BF16_PINNED)
-    p.plan_dx = gemm_plan(p.Mx, c_in, p.Kx, false, true, false, true);
-  // 128 x 128 tiles that leave at most one block per compute unit anyway (<= 256 tiles) also take the three-stage
-  // ring: a lone block has nothing else to cover the load latency with (1 x 1 convolution of cfg4: 18 -> 14 us)
-  p.kk = !p.dx8 && !p.cdx &&
-         (p.plan_dx.tile == 192 || (p.plan_dx.tile == 128 && (int64_t)p.plan_dx.tiles_m * p.plan_dx.tiles_n <= 256));
+  p.kk = !p.dx8 && !p.cdx && p.plan_dx.ring;
   p.plan_dw = k > 0 ? gemm_plan(k, p.Nw, p.ldt, true, !(p.tn || p.rdw), !p.cdw) : GemmPlan{128, 1, 0, 0};
   WsCarver cv(nullptr);
   p.b_wqT = p.dx8 ? 0 : (size_t)c_in * p.Kx * 2; cv.take(p.b_wqT);
@@ -648,6 +645,21 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
   p.total = cv.off;
   return p;
 }
+
+// The plan of a call: by kDxTiles, or the wide one where that needs less workspace than the call brings, or 16-byte aligned
+// weight codes that it does not.  A workspace of either size is taken, and the query returns the larger.
+// c_in beyond what the bf16 W_q^T may have (check_plan) also leaves the choice to gemm_plan's rule.
+template <class Plan>
+static BwdPlan choose_plan(const Plan& plan, int64_t c_in, const int8_t* w_codes, size_t ws_bytes) {
+  BwdPlan p = plan(c_in > kMaxStagedColumns);
+  if (ws_bytes < p.total || (p.dx8 && ((uintptr_t)w_codes % 16) != 0)) {
+    const BwdPlan w = plan(true);
+    if (ws_bytes >= w.total) p = w;
+  }
+  return p;
+}
+template <class Plan>
+static size_t query_plan(const Plan& plan) { return std::max(plan(false).total, plan(true).total); }
 
 struct BwdIo {
   const void* dy; int dy_dtype; int dy_layout;
@@ -679,9 +691,7 @@ static int side_events(SideEvents* out) {
 }
 
 // Everything that can still fail once the plan is known, checked before the first launch: pointer alignment of the
-// operands that the chosen kernels copy 16 bytes at a time, and the size limits of the staged copies (65535 tiles of 64
-// columns: a limit of the interface, no longer of a grid).
-constexpr int64_t kMaxStagedColumns = 65535 * (int64_t)64;
+// operands that the chosen kernels copy 16 bytes at a time, and the size limits of the staged copies.
 static int check_plan(const BwdPlan& p, const BwdIo& io, int64_t T_out, int64_t c_in, int64_t c_out) {
   if (p.dx8 && ((uintptr_t)io.w_codes % 16) != 0) return EFQAT_ERR_ALIGNMENT;
   if ((p.tn || p.rdw) && ((uintptr_t)io.x_codes % 16) != 0) return EFQAT_ERR_ALIGNMENT;
@@ -926,8 +936,9 @@ static int linear_bwd_entry(BwdIo& io, int64_t T, int64_t c_in, int64_t c_out, c
   if (rc) return rc;
   if (io.w_operand && dxk != EFQAT_DX_KERNEL_AUTO) return EFQAT_ERR_BAD_LAYOUT;   // the operand belongs to the default plan
   if (io.w_operand && ((uintptr_t)io.w_operand % 256) != 0) return EFQAT_ERR_ALIGNMENT;
-  const BwdPlan p = make_plan(T, T, c_in, c_out, 1, io.k, io.dy_dtype, io.dy_layout, false, dxk, nullptr,
-                              io.x_dtype == EFQAT_BF16 && io.dx_dtype == EFQAT_BF16);
+  const BwdPlan p = choose_plan([&](bool wide) {
+    return make_plan(T, T, c_in, c_out, 1, io.k, io.dy_dtype, io.dy_layout, false, dxk, nullptr, wide);
+  }, c_in, io.w_codes, ws_bytes);
   if (ws_bytes < p.total) return EFQAT_ERR_WORKSPACE;
   rc = check_plan(p, io, T, c_in, c_out);
   if (rc) return rc;
@@ -942,7 +953,9 @@ extern "C" size_t efqat_linear_bwd_workspace_bytes_ex(int64_t T, int64_t c_in, i
                                                       int dy_layout, int dx_kernel) {
   if (!linear_shape_ok(T, c_in, c_out) || k < 0 || k > c_out) return 0;
   if (dx_kernel < EFQAT_DX_KERNEL_AUTO || dx_kernel > EFQAT_DX_KERNEL_BF16_PINNED) return 0;
-  return make_plan(T, T, c_in, c_out, 1, k, dy_dtype, dy_layout, false, dx_kernel).total;
+  return query_plan([&](bool wide) {
+    return make_plan(T, T, c_in, c_out, 1, k, dy_dtype, dy_layout, false, dx_kernel, nullptr, wide);
+  });
 }
 
 extern "C" size_t efqat_linear_bwd_workspace_bytes(int64_t T, int64_t c_in, int64_t c_out, int64_t k, int dy_dtype,
@@ -978,7 +991,8 @@ extern "C" int efqat_linear_bwd_ex(const void* dy, int dy_dtype, int dy_layout, 
 extern "C" size_t efqat_linear_bwd_weight_operand_bytes(int64_t T, int64_t c_in, int64_t c_out, int dy_dtype,
                                                         int dy_layout) {
   if (!linear_shape_ok(T, c_in, c_out)) return 0;
-  const BwdPlan p = make_plan(T, T, c_in, c_out, 1, 0, dy_dtype, dy_layout, false, EFQAT_DX_KERNEL_AUTO);
+  const BwdPlan p = make_plan(T, T, c_in, c_out, 1, 0, dy_dtype, dy_layout, false, EFQAT_DX_KERNEL_AUTO, nullptr,
+                              c_in > kMaxStagedColumns);
   return p.dx8 ? 0 : (size_t)round_up((int64_t)p.b_wqT, 256) + 256;   // W_q^T and 256 zero bytes (part of its format)
 }
 
@@ -994,7 +1008,8 @@ extern "C" int efqat_linear_bwd_weight_operand(const int8_t* w_codes, const floa
   if (operand_bytes < need) return EFQAT_ERR_WORKSPACE;
   if (((uintptr_t)operand % 256) != 0) return EFQAT_ERR_ALIGNMENT;
   if (c_in > kMaxStagedColumns) return EFQAT_ERR_BAD_SHAPE;
-  const BwdPlan p = make_plan(T, T, c_in, c_out, 1, 0, dy_dtype, dy_layout, false, EFQAT_DX_KERNEL_AUTO);
+  const BwdPlan p = make_plan(T, T, c_in, c_out, 1, 0, dy_dtype, dy_layout, false, EFQAT_DX_KERNEL_AUTO, nullptr,
+                              c_in > kMaxStagedColumns);
   PrepArgs a{};
   prep_w_operand(a, w_codes, s_w, c_in, c_out, 1, p.ldc, (bf16_t*)operand);
   a.zero_page = (uint32_t*)((char*)operand + round_up((int64_t)p.b_wqT, 256));
@@ -1019,10 +1034,10 @@ static int conv_geom(int64_t N, int64_t H, int64_t W, int64_t c_in, int64_t c_ou
   return EFQAT_OK;
 }
 
-static BwdPlan conv_plan(const ConvGeom& g, int64_t k, int dy_dtype, int dy_layout, int dxk, bool io_bf16) {
+static BwdPlan conv_plan(const ConvGeom& g, int64_t k, int dy_dtype, int dy_layout, int dxk, bool wide) {
   const bool im2col = !(g.KH * g.KW == 1 && g.stride == 1 && g.pad == 0);
   return make_plan((int64_t)g.N * g.H * g.W, (int64_t)g.N * g.Ho * g.Wo, g.c_in, g.c_out, g.KH * g.KW, k, dy_dtype,
-                   dy_layout, im2col, dxk, &g, io_bf16);
+                   dy_layout, im2col, dxk, &g, wide);
 }
 
 extern "C" size_t efqat_conv_bwd_workspace_bytes_ex(int64_t N, int64_t H, int64_t W, int64_t c_in, int64_t c_out,
@@ -1031,7 +1046,7 @@ extern "C" size_t efqat_conv_bwd_workspace_bytes_ex(int64_t N, int64_t H, int64_
   ConvGeom g;
   if (conv_geom(N, H, W, c_in, c_out, KH, KW, stride, pad, &g) || k < 0 || k > c_out) return 0;
   if (dx_kernel < EFQAT_DX_KERNEL_AUTO || dx_kernel > EFQAT_DX_KERNEL_BF16_PINNED) return 0;
-  return conv_plan(g, k, dy_dtype, dy_layout, dx_kernel, false).total;
+  return query_plan([&](bool wide) { return conv_plan(g, k, dy_dtype, dy_layout, dx_kernel, wide); });
 }
 
 extern "C" size_t efqat_conv_bwd_workspace_bytes(int64_t N, int64_t H, int64_t W, int64_t c_in, int64_t c_out,
@@ -1053,7 +1068,9 @@ static int conv_bwd_entry(BwdIo& io, int64_t N, int64_t H, int64_t W, int64_t c_
   }
   rc = check_common(io, c_out, ws, dxk);
   if (rc) return rc;
-  const BwdPlan p = conv_plan(g, io.k, io.dy_dtype, io.dy_layout, dxk, io.x_dtype == EFQAT_BF16 && io.dx_dtype == EFQAT_BF16);
+  const BwdPlan p = choose_plan([&](bool wide) {
+    return conv_plan(g, io.k, io.dy_dtype, io.dy_layout, dxk, wide);
+  }, c_in, io.w_codes, ws_bytes);
   if (ws_bytes < p.total) return EFQAT_ERR_WORKSPACE;
   const int64_t T_in = (int64_t)N * H * W, T_out = (int64_t)N * g.Ho * g.Wo;
   rc = check_plan(p, io, T_out, c_in, c_out);

@@ -105,16 +105,21 @@ struct GemmEpilogueDx {   // fused STE + activation-qparam partial sums (Eq. 5 l
 // true when the fused epilogue may use 8-element vector accesses on x_codes / x / dx
 bool gemm_epilogue_vec_ok(const GemmEpilogueDx& e, int64_t N);
 
-// Launch shape of one product: square block tile (256, 192 or 128), split-K factor, tile grid.
+// Launch shape of one product: square block tile (256, 192, 128 or 64), split-K factor, tile grid; dX products: whether
+// the kernel with the ring of three LDS stages (k_gemm_kk) runs them.
 struct GemmPlan {
   int tile;
   int split_k;
   int tiles_m, tiles_n;
+  bool ring;
 };
-// Pure host function of the problem size (so the workspace query and the call agree).  allow_split = false
-// for the product with the fused dX epilogue.
-GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool allow_split, bool allow_192 = true, bool allow_256 = true,
-                   bool fast192 = false);   // fast192: price the 192 tile as k_gemm_kk with its straight-line epilogue
+// Pure host functions of the problem size (so the workspace query and the call agree).  allow_split = false: a product
+// with the fused dX epilogue.
+GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool allow_split, bool allow_192 = true, bool allow_256 = true);
+// Kernel and tile of a dX product (see kDxTiles).  conv: dY is gathered in the tile loads, by phase when `strided` is given;
+// int8_ok: tiles of 256 are run by k_gemm_dx8, which needs no bf16 W_q^T.
+struct ConvDxStridedMap;
+GemmPlan dx_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const ConvDxStridedMap* strided, bool int8_ok);
 
 // C[M][N] = sum_k A[row(m)][k] * B[n][k]; both operands bf16 with K contiguous.
 //   a_rows: optional gather, row(m) = a_rows[m]; lda/ldb in elements (multiples of 8), K multiple of 8.
@@ -126,7 +131,7 @@ int launch_gemm_nt(const bf16_t* A, int64_t lda, const int32_t* a_rows, const bf
                    const GemmEpilogueDx* epi, hipStream_t stream);
 
 // The same product as launch_gemm_nt (no row gather) by the kernel with a hand-pinned instruction order:
-// plan.tile 192 or 128; A and B 16-byte aligned.
+// plan.tile 192, 128 or 64; A and B 16-byte aligned.
 int launch_gemm_kk(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M,
                    int64_t N, int64_t K, const GemmPlan& plan, float* out_partial, const GemmEpilogueDx* epi,
                    hipStream_t stream);
@@ -146,13 +151,13 @@ int launch_gemm_tn_conv(const bf16_t* A, int64_t lda, int64_t a_cols, const uint
                         float* out_partial, hipStream_t stream);
 // dX product of a stride-1 convolution without a materialised im2col matrix: row m of the A operand is the input
 // pixel (n, h, w); its K = (tap, c_out) elements are gathered from the token-major dY [N*Ho*Wo][ldc] inside the
-// tile loads (zeros for taps that fall outside the output image).  ldc % 64 == 0, K = KH*KW*ldc, plan.tile 192 or
-// 128, no split-K.
+// tile loads (zeros for taps that fall outside the output image).  ldc % 64 == 0, K = KH*KW*ldc, plan.tile 192, 128 or
+// 64, no split-K.
 struct ConvDxMap { int H, W, Ho, Wo, KW, pad; };
 int launch_gemm_nt_conv_dx(const bf16_t* dy_tok, int64_t ldc, const bf16_t* wqT, int64_t ldb, int64_t M, int64_t N,
                            int64_t K, const ConvDxMap& cm, const GemmPlan& plan, const GemmEpilogueDx& epi,
                            hipStream_t stream);
-// The same for a stride of 2 to 4: rows sorted by (h mod stride, w mod stride), plan.tile 128, plan.tiles_m =
+// The same for a stride of 2 to 4: rows sorted by (h mod stride, w mod stride), plan.tile 128 or 64, plan.tiles_m =
 // conv_dx_strided_row_tiles (whole tiles per phase).
 constexpr int kMaxConvStride = 4;
 struct ConvDxStridedMap { int N, H, W, Ho, Wo, KH, KW, stride, pad; };

@@ -85,9 +85,9 @@ __device__ __forceinline__ void wait_vmcnt() {
 // I8: operands are int8 codes (A unsigned, re-biased by 128 in registers) on v_mfma_i32_32x32x32_i8; else bf16.
 // CONV = 1: the A operand is gathered from a token-major dY with the im2col map of a stride-1 convolution (see GemmArgs);
 // CONV = 2: of a convolution with a stride, rows sorted by phase (see ConvPhase).
-// two blocks of up to 128 x 128 share a CU (by LDS): the epilogue must not take more than half of the registers
+// two blocks of up to 128 x 128, or four of 64 x 64, share a CU (by LDS): the epilogue must leave them the registers
 template <int BM, int BN, int EPI, bool I8, int CONV = 0>
-__global__ __launch_bounds__(256, BM * BN <= 128 * 128 ? 2 : 1) void k_gemm_nt(const typename ConvArgs<CONV>::type g) {
+__global__ __launch_bounds__(256, BM * BN <= 64 * 64 ? 4 : BM * BN <= 128 * 128 ? 2 : 1) void k_gemm_nt(const typename ConvArgs<CONV>::type g) {
 #if defined(__HIP_DEVICE_COMPILE__)   // the body uses gfx950-only builtins; the host pass needs only the launch stub
   constexpr int S = 2;
   constexpr int ESZ = I8 ? 1 : 2;                       // bytes per K element
@@ -472,15 +472,12 @@ __global__ __launch_bounds__(256, BM * BN <= 128 * 128 ? 2 : 1) void k_gemm_nt(c
 //   - blocks run in rounds of 256 CUs x blocks-per-CU;  split-K adds its fp32 partial tiles, written and read once.
 struct TileModel { int t; int bpc; double rate; double epi_dx; };
 static const TileModel kTiles[3] = {{256, 1, 2500.0, 0.75}, {192, 1, 2100.0, 0.75}, {128, 2, 1000.0, 0.6}};
-// the 192 x 192 kernel with the three-stage ring and the straight-line epilogue (k_gemm_kk, EPI_DXF)
-static const TileModel kTileFast192 = {192, 1, 2545.0, 0.45};
 
-GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool allow_split, bool allow_192, bool allow_256, bool fast192) {
+GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool allow_split, bool allow_192, bool allow_256) {
   GemmPlan best{};
   double best_t = 1e300;
   const int64_t ksteps = ceil_div(K, KALIGN);
-  for (const TileModel& tm0 : kTiles) {
-    const TileModel& tm = (tm0.t == 192 && fast192) ? kTileFast192 : tm0;
+  for (const TileModel& tm : kTiles) {
     if (tm.t == 192 && !allow_192) continue;
     if (tm.t == 256 && !allow_256) continue;
     const int64_t tiles = ceil_div(M, tm.t) * ceil_div(N, tm.t);
@@ -501,6 +498,67 @@ GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool allow_split, bool allow
       }
     }
   }
+  return best;
+}
+
+// Kernel and tile of a dX product.  Microseconds per K stage of 64 and per block (launch, first loads, epilogue) with one
+// block on a CU (lone) and with all `bpc` that fit by LDS and registers (full), between the two by the number resident; what
+// x and dX in fp32 add and what the straight-line epilogue of whole bf16 tiles saves.  A product is its whole rounds of
+// 256 * bpc blocks plus what is left.  Fitted to measured launches of 240 linear layers (each dimension 64 .. 16384) and 28
+// convolutions; the choice is 1.1 % from the fastest of the seven in the mean, the linear layers 1.33 x and the convolutions
+// 1.6 x as fast as with tiles of 128 and more only.  T x C_out -> C_in in us by k_gemm_kk 64 / nt 64 / kk 128 / nt 128 / kk 192 /
+// dx8 256, bf16:
+//   256 x 256 -> 256         6.6 / 5.8 / 8.4 /  - /  18 / -      few tiles: the smallest, with the shortest epilogue
+//   64 x 4096 -> 4096         21 /  33 /  30 /  46 /  51 /  -    ... and the ring, where K is long
+//   2048 x 768 -> 3072        28 /  28 /  26 /  26 /  30 /  30   (C_out 320)
+//   4224 x 112 -> 6144        46 /  37 /  46 /  34 /  38 /  44   two blocks a CU hide each other's epilogues
+//   12288 x 3072 -> 768       89 /  99 /  87 /  85 /  54 /  -    one round of 192 x 192
+//   13824 x 2504 -> 768      135 / 132 /  93 /  93 /  95 /  65   long K and whole rounds: 256 x 256 (without int8 operand:
+//                                                               k_gemm_nt, priced the same)
+// Convolutions pay for the gather in every stage.
+struct DxTile { int t; bool ring; int bpc; double lone[2], full[2], f32[2], fast[2]; };
+static const DxTile kDxTiles[] = {{64, true, 3, {0.28, 5.6}, {0.73, 4.5}, {0.1, 1.0}, {0.0, 0.0}},
+                                  {64, false, 4, {0.465, 4.4}, {0.97, 4.5}, {0.1, 2.1}, {0.0, 0.0}},
+                                  {128, true, 1, {0.535, 8.9}, {0.535, 8.9}, {0.2, 0.2}, {-2.0, -2.0}},
+                                  {128, false, 2, {0.735, 8.0}, {1.08, 10.0}, {0.6, 2.3}, {-1.7, -2.4}},
+                                  {192, true, 1, {0.77, 15.8}, {0.77, 15.8}, {0.2, 0.2}, {-4.0, -4.0}},
+                                  {256, false, 1, {1.125, 20.0}, {1.125, 20.0}, {0.5, 0.5}, {-3.5, -3.5}}};
+static const DxTile kDxConvTiles[] = {{64, true, 3, {0.30, 6.3}, {0.575, 6.6}, {0.0, 0.0}, {0.0, 0.0}},
+                                      {64, false, 4, {0.54, 5.2}, {0.71, 5.4}, {0.0, 0.1}, {0.0, 0.0}},
+                                      {128, true, 1, {0.56, 10.0}, {0.56, 10.0}, {0.5, 0.5}, {-1.0, -1.0}},
+                                      {128, false, 2, {0.79, 9.4}, {0.94, 11.2}, {0.0, 0.6}, {-1.0, -1.0}},
+                                      {192, false, 1, {1.12, 15.6}, {1.12, 15.6}, {0.2, 0.2}, {-1.0, -1.0}}};
+static int64_t conv_phases(const ConvDxStridedMap& cm, int tile, ConvPhase* out, int* nphase);
+
+GemmPlan dx_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const ConvDxStridedMap* strided, bool int8_ok) {
+  GemmPlan best{};
+  double best_t = 0.0;
+  auto price = [&](const DxTile& c) {
+    if (c.t == 192 && strided) return;
+    int64_t tm = ceil_div(M, c.t);
+    double stages = (double)ceil_div(K, KALIGN);
+    if (strided) {                                     // mean stages of a tile
+      ConvPhase ph[kMaxConvStride * kMaxConvStride];
+      int n = 0;
+      tm = conv_phases(*strided, c.t, ph, &n);
+      double sum = 0.0;
+      for (int i = 0; i < n; ++i) sum += (double)ph[i].tiles * ph[i].ntap;
+      stages *= sum / ((double)tm * strided->KH * strided->KW);
+    }
+    const int64_t tn = ceil_div(N, c.t), tiles = tm * tn, round = 256 * c.bpc;
+    if (tiles >= (1 << 24) && c.t < 128) return;        // a grid dimension holds less than 2^32 work items
+    const bool fast = !f32 && !strided && (M % c.t) == 0 && (N % c.t) == 0;
+    const double add[2] = {(f32 ? c.f32[0] : 0.0) + (fast ? c.fast[0] : 0.0), (f32 ? c.f32[1] : 0.0) + (fast ? c.fast[1] : 0.0)};
+    const double lone = c.lone[0] * stages + c.lone[1] + add[0], full = c.full[0] * stages + c.full[1] + add[1];
+    double t = (double)(tiles / round) * full;
+    if (const int64_t rest = tiles % round)
+      t += lone + (full - lone) * (double)(ceil_div(rest, 256) - 1) / (double)std::max(1, c.bpc - 1);
+    // the others need W_q^T in bf16: the codes read, twice as many bytes written, at 4 TB/s
+    if (int8_ok && c.t != 256) t += 3.0 * (double)N * (double)K / 4e6;
+    if (best.tile == 0 || t < best_t) { best_t = t; best = GemmPlan{c.t, 1, (int)tm, (int)tn, c.ring}; }
+  };
+  if (conv) for (const DxTile& c : kDxConvTiles) price(c);
+  else for (const DxTile& c : kDxTiles) price(c);
   return best;
 }
 
@@ -557,6 +615,7 @@ int launch_gemm_nt(const bf16_t* A, int64_t lda, const int32_t* a_rows, const bf
     case 192:
       return epi ? launch_cfg<192, 192, EPI_DX, false>(a, 1, stream)
                  : launch_cfg<192, 192, EPI_RAW, false>(a, split_k, stream);
+    case 64: return launch_cfg<64, 64, EPI_DX, false>(a, 1, stream);
     case 128:
       if (epi && nt_epilogue_fast(a, *epi, 128)) return launch_cfg<128, 128, EPI_DXF, false>(a, 1, stream);
       return epi ? launch_cfg<128, 128, EPI_DX, false>(a, 1, stream)
@@ -586,9 +645,11 @@ int launch_gemm_nt_conv_dx(const bf16_t* dy_tok, int64_t ldc, const bf16_t* wqT,
   switch (plan.tile) {
     case 192: return nt_epilogue_fast(a, epi, 192) ? launch_cfg<192, 192, EPI_DXF, false, 1>(a, 1, stream)
                                                    : launch_cfg<192, 192, EPI_DX, false, 1>(a, 1, stream);
+    case 64:
+      if (plan.ring) return launch_gemm_kk_conv(a, 64, false, stream);
+      return launch_cfg<64, 64, EPI_DX, false, 1>(a, 1, stream);
     case 128:
-      // at most one block per compute unit anyway: the three-stage ring hides the load latency a lone block sees
-      if ((int64_t)a.tiles_m * a.tiles_n <= 256) return launch_gemm_kk_conv128(a, nt_epilogue_fast(a, epi, 128), stream);
+      if (plan.ring) return launch_gemm_kk_conv(a, 128, nt_epilogue_fast(a, epi, 128), stream);
       return nt_epilogue_fast(a, epi, 128) ? launch_cfg<128, 128, EPI_DXF, false, 1>(a, 1, stream)
                                            : launch_cfg<128, 128, EPI_DX, false, 1>(a, 1, stream);
     default: return EFQAT_ERR_BAD_SHAPE;
@@ -639,7 +700,7 @@ int launch_gemm_conv_dx_strided(const bf16_t* dy_tok, int64_t ldc, const bf16_t*
                                 const ConvDxStridedMap& cm, const GemmPlan& plan, const GemmEpilogueDx& epi,
                                 hipStream_t stream) {
   if (M <= 0 || N <= 0 || (ldc % 64) || (ldb % 8) || cm.H > 65535 || cm.W > 65535 || cm.stride < 2 ||
-      cm.stride > kMaxConvStride || plan.tile != 128 || plan.split_k != 1 || M > INT32_MAX || N > INT32_MAX)
+      cm.stride > kMaxConvStride || (plan.tile != 128 && plan.tile != 64) || plan.split_k != 1 || M > INT32_MAX || N > INT32_MAX)
     return EFQAT_ERR_BAD_SHAPE;
   GemmStridedArgs a{};
   a.A = dy_tok; a.lda = ldc; a.B = wqT; a.ldb = ldb;
@@ -654,8 +715,8 @@ int launch_gemm_conv_dx_strided(const bf16_t* dy_tok, int64_t ldc, const bf16_t*
   a.tiles_n = plan.tiles_n;
   a.tiles_m = (int)conv_phases(cm, plan.tile, a.phase, &a.nphase);
   if (a.tiles_m != plan.tiles_m) return EFQAT_ERR_BAD_SHAPE;
-  // as at stride 1: a lone block per compute unit takes the three-stage ring, more share a unit in pairs
-  if ((int64_t)a.tiles_m * a.tiles_n <= 256) return launch_gemm_kk_conv128_strided(a, stream);
+  if (plan.ring) return launch_gemm_kk_conv_strided(a, plan.tile, stream);
+  if (plan.tile == 64) return launch_cfg<64, 64, EPI_DX, false, 2>(a, 1, stream);
   return launch_cfg<128, 128, EPI_DX, false, 2>(a, 1, stream);
 }
 

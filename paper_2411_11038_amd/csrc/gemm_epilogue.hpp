@@ -45,8 +45,8 @@ template <int CONV> struct ConvArgs { typedef GemmArgs type; };
 template <> struct ConvArgs<2> { typedef GemmStridedArgs type; };
 
 // dX product of a convolution on 128 x 128 tiles by the kernel with the three-stage ring (gemm_kk.hip)
-int launch_gemm_kk_conv128(const GemmArgs& a, bool fast, hipStream_t stream);
-int launch_gemm_kk_conv128_strided(const GemmStridedArgs& a, hipStream_t stream);
+int launch_gemm_kk_conv(const GemmArgs& a, int tile, bool fast, hipStream_t stream);
+int launch_gemm_kk_conv_strided(const GemmStridedArgs& a, int tile, hipStream_t stream);
 
 // phase and phase-local row tile / column tile of a block: each XCD gets a contiguous range of every phase's tiles
 __device__ __forceinline__ void strided_tile(const GemmStridedArgs& g, int block, ConvPhase* ph, int* tm, int* tn) {

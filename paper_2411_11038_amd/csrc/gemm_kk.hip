@@ -25,10 +25,10 @@
 
 namespace efqat {
 
-template <int T, int WGM_, int WGN_>
+template <int BM_, int BN_>
 struct KkCfg {
-  static constexpr int BM = T, BN = T;
-  static constexpr int WGM = WGM_, WGN = WGN_;
+  static constexpr int BM = BM_, BN = BN_;
+  static constexpr int WGM = 2, WGN = 2;
   static constexpr int WM = BM / WGM, WN = BN / WGN;
   static constexpr int TM = WM / 32, TN = WN / 32;
   static constexpr int A_G = BM / 8 / 4, B_G = BN / 8 / 4;       // 1-KiB copies (8 rows) per wavefront and stage
@@ -49,10 +49,10 @@ struct KkCfg {
 // k_gemm_nt (see GemmArgs): every copy slot keeps (n, h, w) of its input pixel and forms its source address per stage
 // from the stage's tap; K = taps * ldc is a whole number of stages.  CONV = 2: a convolution with a stride, rows sorted
 // by phase (see ConvPhase); W_q^T is read at the stage's tap as well.
-template <int T, int WGM, int WGN, int EPI, int CONV = 0>
+template <int BM, int BN, int EPI, int CONV = 0>
 __global__ __launch_bounds__(256) void k_gemm_kk(const typename ConvArgs<CONV>::type g) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  using C = KkCfg<T, WGM, WGN>;
+  using C = KkCfg<BM, BN>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -320,7 +320,9 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const typename ConvArgs<CONV>::
 
   if (nk > 0) issue_range(Checked{}, 0, 0, 0, LPS);
   if (nk > 1) issue_range(Checked{}, 1, 1, 0, LPS);
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  // stage 0 has to be there; the tail stages (see stage_sync) count on everything having landed
+  if (nk > 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS) : "memory");
+  else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (2 < nfull) issue_range(Unchecked{}, 2, 2, 0, P0);
   if (nk > 0) load_frags(B0{}, 0, 0);
@@ -359,17 +361,17 @@ __global__ __launch_bounds__(256) void k_gemm_kk(const typename ConvArgs<CONV>::
 #endif
 }
 
-template <int T, int WGM, int WGN, int EPI, int CONV = 0>
+template <int BM, int BN, int EPI, int CONV = 0>
 static int launch_kk_cfg(const typename ConvArgs<CONV>::type& a, int split_k, hipStream_t st) {
-  using C = KkCfg<T, WGM, WGN>;
+  using C = KkCfg<BM, BN>;
   // set once per process (initialisation of a function-local static is thread-safe)
   constexpr int kLds = C::template lds_bytes<EPI>() + (CONV == 2 ? C::BM * (int)sizeof(int) : 0);
-  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_kk<T, WGM, WGN, EPI, CONV>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_kk<BM, BN, EPI, CONV>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return EFQAT_ERR_HIP;
   dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)split_k);
   {
     ProfScope prof(EPI == EPI_RAW ? PROF_DW : PROF_DX, st);
-    hipLaunchKernelGGL((k_gemm_kk<T, WGM, WGN, EPI, CONV>), grid, dim3(256), kLds, st, a);
+    hipLaunchKernelGGL((k_gemm_kk<BM, BN, EPI, CONV>), grid, dim3(256), kLds, st, a);
   }
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
@@ -397,20 +399,22 @@ int launch_gemm_kk(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, i
   a.tiles_n = plan.tiles_n;
   switch (plan.tile) {
     case 192: {
-      if (!epi) return launch_kk_cfg<192, 2, 2, EPI_RAW>(a, split_k, stream);
+      if (!epi) return launch_kk_cfg<192, 192, EPI_RAW>(a, split_k, stream);
       // nothing to decide at run time: the straight-line epilogue
       const bool fast = a.epi_vec && epi->x_dtype == EFQAT_BF16 && epi->dx_dtype == EFQAT_BF16 && (M % 192) == 0 &&
                         (N % 192) == 0 && M * N <= (int64_t)INT32_MAX;
-      if (fast) return launch_kk_cfg<192, 2, 2, EPI_DXF>(a, 1, stream);
-      return epi->x_dtype == EFQAT_F32 ? launch_kk_cfg<192, 2, 2, EPI_DXS>(a, 1, stream) : launch_kk_cfg<192, 2, 2, EPI_DX>(a, 1, stream);
+      if (fast) return launch_kk_cfg<192, 192, EPI_DXF>(a, 1, stream);
+      return epi->x_dtype == EFQAT_F32 ? launch_kk_cfg<192, 192, EPI_DXS>(a, 1, stream) : launch_kk_cfg<192, 192, EPI_DX>(a, 1, stream);
     }
     case 128: {
-      if (!epi) return launch_kk_cfg<128, 2, 2, EPI_RAW>(a, split_k, stream);
+      if (!epi) return launch_kk_cfg<128, 128, EPI_RAW>(a, split_k, stream);
       const bool fast = a.epi_vec && epi->x_dtype == EFQAT_BF16 && epi->dx_dtype == EFQAT_BF16 && (M % 128) == 0 &&
                         (N % 128) == 0 && M * N <= (int64_t)INT32_MAX;
-      if (fast) return launch_kk_cfg<128, 2, 2, EPI_DXF>(a, 1, stream);
-      return epi->x_dtype == EFQAT_F32 ? launch_kk_cfg<128, 2, 2, EPI_DXS>(a, 1, stream) : launch_kk_cfg<128, 2, 2, EPI_DX>(a, 1, stream);
+      if (fast) return launch_kk_cfg<128, 128, EPI_DXF>(a, 1, stream);
+      return epi->x_dtype == EFQAT_F32 ? launch_kk_cfg<128, 128, EPI_DXS>(a, 1, stream) : launch_kk_cfg<128, 128, EPI_DX>(a, 1, stream);
     }
+    case 64:
+      return epi->x_dtype == EFQAT_F32 ? launch_kk_cfg<64, 64, EPI_DXS>(a, 1, stream) : launch_kk_cfg<64, 64, EPI_DX>(a, 1, stream);
     default:
       return EFQAT_ERR_BAD_SHAPE;
   }
@@ -418,16 +422,20 @@ int launch_gemm_kk(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, i
 
 // dX product of a stride-1 convolution on 128 x 128 tiles with the three-stage ring; `a` as launch_gemm_nt_conv_dx
 // fills it (K a whole number of 64-channel stages, no split-K).
-int launch_gemm_kk_conv128(const GemmArgs& a, bool fast, hipStream_t stream) {
+int launch_gemm_kk_conv(const GemmArgs& a, int tile, bool fast, hipStream_t stream) {
   if ((a.K % 64) != 0) return EFQAT_ERR_BAD_SHAPE;
   GemmArgs ka = a;
   ka.k_per_split = a.K;
-  if (fast) return launch_kk_cfg<128, 2, 2, EPI_DXF, 1>(ka, 1, stream);
-  return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<128, 2, 2, EPI_DXS, 1>(ka, 1, stream) : launch_kk_cfg<128, 2, 2, EPI_DX, 1>(ka, 1, stream);
+  if (tile == 64)
+    return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<64, 64, EPI_DXS, 1>(ka, 1, stream) : launch_kk_cfg<64, 64, EPI_DX, 1>(ka, 1, stream);
+  if (fast) return launch_kk_cfg<128, 128, EPI_DXF, 1>(ka, 1, stream);
+  return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<128, 128, EPI_DXS, 1>(ka, 1, stream) : launch_kk_cfg<128, 128, EPI_DX, 1>(ka, 1, stream);
 }
 
-int launch_gemm_kk_conv128_strided(const GemmStridedArgs& a, hipStream_t stream) {
-  return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<128, 2, 2, EPI_DXS, 2>(a, 1, stream) : launch_kk_cfg<128, 2, 2, EPI_DX, 2>(a, 1, stream);
+int launch_gemm_kk_conv_strided(const GemmStridedArgs& a, int tile, hipStream_t stream) {
+  if (tile == 64)
+    return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<64, 64, EPI_DXS, 2>(a, 1, stream) : launch_kk_cfg<64, 64, EPI_DX, 2>(a, 1, stream);
+  return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<128, 128, EPI_DXS, 2>(a, 1, stream) : launch_kk_cfg<128, 128, EPI_DX, 2>(a, 1, stream);
 }
 
 }  // namespace efqat
