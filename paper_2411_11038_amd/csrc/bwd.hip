@@ -385,7 +385,14 @@ __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ par
       const float* p = part + m * ncols + j;
       float4 a = *reinterpret_cast<const float4*>(p);
       int s = 1;
-      for (; s + 3 < S; s += 4) {                     // four slices in flight; summed in slice order as below
+      for (; s + 7 < S; s += 8) {                     // eight slices in flight; summed in slice order as below
+        float4 b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) b[u] = *reinterpret_cast<const float4*>(p + (int64_t)(s + u) * slice);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) { a.x += b[u].x; a.y += b[u].y; a.z += b[u].z; a.w += b[u].w; }
+      }
+      for (; s + 3 < S; s += 4) {
         float4 b[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) b[u] = *reinterpret_cast<const float4*>(p + (int64_t)(s + u) * slice);
@@ -430,7 +437,15 @@ __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ par
   } else {
     for (int64_t j = threadIdx.x; j < ncols; j += NTH) {
       float a = 0.0f;
-      for (int s = 0; s < S; ++s) a += part[(int64_t)s * slice + m * ncols + j];
+      int s = 0;
+      for (; s + 3 < S; s += 4) {                     // four slices in flight
+        float b[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) b[u] = part[(int64_t)(s + u) * slice + m * ncols + j];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a += b[u];
+      }
+      for (; s < S; ++s) a += part[(int64_t)s * slice + m * ncols + j];
       const float dwq = sx * a;
       const bool inr = (w_clip[c * wpr + (j >> 5)] >> (j & 31)) & 1u;
       const float code = (float)w_codes[c * ncols + j];
@@ -571,8 +586,8 @@ static bool conv_stages_ok(const ConvGeom& g, int64_t ldc) {
 }
 
 // dxk: the caller's choice of the dX kernel (EFQAT_DX_KERNEL_*); it changes workspace sizes, so the size query takes
-// it as well.  wide: dX tiles of 128 and more by gemm_plan's rule, for callers whose workspace or weight codes do not fit
-// the plan by kDxTiles (see choose_plan).
+// it as well.  wide: tiles of 128 and more by gemm_plan's rule, for callers whose workspace or weight codes do not fit
+// the plan by kDxTiles and kDwTiles (see choose_plan).
 static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_out, int taps, int64_t k,
                          int dy_dtype, int dy_layout, bool im2col, int dxk, const ConvGeom* cg = nullptr,
                          bool wide = false) {
@@ -630,7 +645,9 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
     p.plan_dx.tiles_m = (int)ceil_div(p.Mx, p.dx8_tile); p.plan_dx.tiles_n = (int)ceil_div(c_in, p.dx8_tile);
   }
   p.kk = !p.dx8 && !p.cdx && p.plan_dx.ring;
-  p.plan_dw = k > 0 ? gemm_plan(k, p.Nw, p.ldt, true, !(p.tn || p.rdw), !p.cdw) : GemmPlan{128, 1, 0, 0};
+  if (k == 0) p.plan_dw = GemmPlan{128, 1, 0, 0, false};
+  else if (wide || p.rdw) p.plan_dw = gemm_plan(k, p.Nw, p.ldt, true, !(p.tn || p.rdw), !p.cdw);
+  else p.plan_dw = dw_plan(p.cdw ? DW_CONV : p.tn ? DW_TOKENS : DW_STAGED, k, p.Nw, p.ldt);
   WsCarver cv(nullptr);
   p.b_wqT = p.dx8 ? 0 : (size_t)c_in * p.Kx * 2; cv.take(p.b_wqT);
   p.b_dyn = p.need_dyn ? (size_t)T_out * p.ldc * 2 : 0; cv.take(p.b_dyn);
@@ -646,7 +663,7 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
   return p;
 }
 
-// The plan of a call: by kDxTiles, or the wide one where that needs less workspace than the call brings, or 16-byte aligned
+// The plan of a call: by kDxTiles and kDwTiles, or the wide one where that needs less workspace than the call brings, or 16-byte aligned
 // weight codes that it does not.  A workspace of either size is taken, and the query returns the larger.
 // c_in beyond what the bf16 W_q^T may have (check_plan) also leaves the choice to gemm_plan's rule.
 template <class Plan>

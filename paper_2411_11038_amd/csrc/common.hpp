@@ -120,6 +120,10 @@ GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool allow_split, bool allow
 // int8_ok: tiles of 256 are run by k_gemm_dx8, which needs no bf16 W_q^T.
 struct ConvDxStridedMap;
 GemmPlan dx_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const ConvDxStridedMap* strided, bool int8_ok);
+// Tile and split of a dW product [M][N] over K tokens (see kDwTiles): by k_gemm_tn (tiles 64 x 128, 128 and 256), by it with the
+// gather of a convolution (64 x 128, 128), or from the staged operands by k_gemm_nt (64, 128, 192, 256).
+enum DwKind { DW_TOKENS = 0, DW_CONV = 1, DW_STAGED = 2 };
+GemmPlan dw_plan(DwKind kind, int64_t M, int64_t N, int64_t K);
 
 // C[M][N] = sum_k A[row(m)][k] * B[n][k]; both operands bf16 with K contiguous.
 //   a_rows: optional gather, row(m) = a_rows[m]; lda/ldb in elements (multiples of 8), K multiple of 8.
@@ -138,13 +142,13 @@ int launch_gemm_kk(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, i
 
 // Weight-gradient product from token-major operands (no transposed copies):
 //   out[s][m][n] = sum over the K-slice s of A[t][m] * (B[t][n] - round(z_x)),  A bf16 [K][lda], B uint8 [K][ldb].
-// Columns >= a_cols / b_cols and rows >= K are taken as zero.  plan.tile must be 256 or 128.
+// Columns >= a_cols / b_cols and rows >= K are taken as zero.  plan.tile 256, 128 or 64 (64 x 128).
 int launch_gemm_tn(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* B, int64_t ldb, int64_t b_cols,
                    const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
                    float* out_partial, hipStream_t stream);
 // dW product of a convolution without a materialised im2col matrix: A = compacted dY columns [N*Ho*Wo][lda] as in
 // launch_gemm_tn, B = the activation codes x_codes NHWC gathered with the tap map inside the tile loads.
-// N = KH*KW*c_in, c_in % 128 == 0 (a 128-wide column tile lies inside one tap), plan.tile == 128.
+// N = KH*KW*c_in, c_in % 128 == 0 (a 128-wide column tile lies inside one tap), plan.tile 128 or 64 (64 x 128).
 struct ConvDwMap { int H, W, Ho, Wo, KW, stride, pad, c_in; };
 int launch_gemm_tn_conv(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* x_codes, const ConvDwMap& cm,
                         const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,

@@ -562,6 +562,41 @@ GemmPlan dx_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const Con
   return best;
 }
 
+// Tile and split-K of a dW product.  Costs as in kDxTiles; to them comes the second pass (k_dw_finish), which reads every
+// slice: 3.7 us, 0.07 us a slice, and 0.119 us per 2^20 values and 4 bytes.  Slices of two K stages and more, where
+// eight stages and fewer, larger tiles were the rule before.  Fitted to 100 layers and convolutions by k_gemm_tn and 55 from
+// staged operands, dW product and second pass together: 1.02 x (staged 1.06 x) the fastest of all tiles and splits, 1.21 x
+// (convolutions 1.25 x, staged 1.29 x) as fast as before.  T x C_in, k rows, us with the best split on 64 / 128 rows (slices):
+//   480 x 512, 172        7.8 (4) / 10.1 (4), before 13.4 (1)     few tiles: as many short slices as fill the chip
+//   12144 x 688, 40      13.9 (32) / 15.5 (32), before 16.7 (22)  half of a 128-row tile would be padding
+//   6848 x 1776, 1500    63 (3) / 54 (3)                          many tiles: fewer LDS bytes per product
+// The 256 x 256 and 192 x 192 tiles stay where gemm_plan prices them lowest: large products.
+struct DwTile { int bm, bn, bpc; double lone[2], full[2]; };
+static const DwTile kDwTiles[3][2] = {{{64, 128, 4, {0.515, 4.4}, {1.10, 6.2}}, {128, 128, 3, {0.575, 5.8}, {1.305, 8.3}}},
+                                      {{64, 128, 4, {0.785, 5.0}, {1.51, 7.6}}, {128, 128, 3, {0.955, 6.6}, {1.68, 11.2}}},
+                                      {{64, 64, 4, {0.453, 3.0}, {0.95, 3.5}}, {128, 128, 2, {0.71, 4.5}, {0.88, 7.0}}}};
+GemmPlan dw_plan(DwKind kind, int64_t M, int64_t N, int64_t K) {
+  GemmPlan best = gemm_plan(M, N, K, true, kind == DW_STAGED, kind != DW_CONV);
+  if (best.tile > 128) return best;
+  const int64_t stages = ceil_div(K, KALIGN);
+  double best_t = 0.0;
+  bool have = false;
+  for (const DwTile& c : kDwTiles[kind]) {
+    const int64_t tm = ceil_div(M, c.bm), tn = ceil_div(N, c.bn), round = 256 * c.bpc;
+    if (tm * tn >= (1 << 24)) continue;                 // a grid dimension holds less than 2^32 work items
+    for (int64_t s = 1; s <= 64 && (s == 1 || 2 * s <= stages); ++s) {
+      const int64_t per = ceil_div(stages, s);
+      if (ceil_div(stages, per) != s) continue;         // slices without a stage
+      const double lone = c.lone[0] * (double)per + c.lone[1], full = c.full[0] * (double)per + c.full[1];
+      double t = (double)(tm * tn * s / round) * full + 3.7 + 0.07 * (double)s + 0.119e-6 * (double)M * (double)N * (double)(4 * s + 9);
+      if (const int64_t rest = tm * tn * s % round)
+        t += lone + (full - lone) * (double)(ceil_div(rest, 256) - 1) / (double)(c.bpc - 1);
+      if (!have || t < best_t) { best_t = t; best = GemmPlan{c.bm, (int)s, (int)tm, (int)tn, false}; have = true; }
+    }
+  }
+  return best;
+}
+
 bool gemm_epilogue_vec_ok(const GemmEpilogueDx& e, int64_t N) {
   return (N % 8) == 0 && ((uintptr_t)e.x_codes % 8) == 0 && ((uintptr_t)e.x % 16) == 0 && ((uintptr_t)e.dx % 16) == 0;
 }
@@ -615,7 +650,8 @@ int launch_gemm_nt(const bf16_t* A, int64_t lda, const int32_t* a_rows, const bf
     case 192:
       return epi ? launch_cfg<192, 192, EPI_DX, false>(a, 1, stream)
                  : launch_cfg<192, 192, EPI_RAW, false>(a, split_k, stream);
-    case 64: return launch_cfg<64, 64, EPI_DX, false>(a, 1, stream);
+    case 64:
+      return epi ? launch_cfg<64, 64, EPI_DX, false>(a, 1, stream) : launch_cfg<64, 64, EPI_RAW, false>(a, split_k, stream);
     case 128:
       if (epi && nt_epilogue_fast(a, *epi, 128)) return launch_cfg<128, 128, EPI_DXF, false>(a, 1, stream);
       return epi ? launch_cfg<128, 128, EPI_DX, false>(a, 1, stream)

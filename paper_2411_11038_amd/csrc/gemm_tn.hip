@@ -39,9 +39,9 @@ struct GemmTnArgs {
   int cv_H, cv_W, cv_Ho, cv_Wo, cv_KW, cv_stride, cv_pad, cv_cin, cv_dn, cv_dh, cv_dw;
 };
 
-template <int T>
+template <int BM_, int BN_>
 struct TnCfg {
-  static constexpr int BM = T, BN = T;
+  static constexpr int BM = BM_, BN = BN_;
   // wavefront grid 1 x 4: every wavefront spans all rows of the tile, so each uint8 fragment of B is converted to
   // bf16 by exactly one wavefront
   static constexpr int WGM = 1, WGN = 4;
@@ -55,19 +55,21 @@ struct TnCfg {
   static constexpr int LDS_BYTES = 2 * LDS_STAGE;
   static constexpr int KSH = RB == 256 ? 0 : 1;              // B swizzle: rows per 256 bytes = 1 << KSH
   // physical 16-byte chunk of logical chunk c in token row k.  A: a 16-lane transpose read touches 4 rows x 32
-  // bytes, B: 8 rows x 16 bytes; these XORs spread each half-wave's 256 bytes over all 64 banks.
-  __device__ static __forceinline__ int swz_a(int c, int k) { return c ^ (4 * (k & 3)); }
+  // bytes, B: 8 rows x 16 bytes; these XORs spread each half-wave's 256 bytes over all 64 banks (A rows of 128 bytes: two
+  // rows lie beside each other in the banks already).
+  __device__ static __forceinline__ int swz_a_row(int k) { return BM == 64 ? (k >> 1) & 1 : k & 3; }
+  __device__ static __forceinline__ int swz_a(int c, int k) { return c ^ (4 * swz_a_row(k)); }
   __device__ static __forceinline__ int swz_b(int c, int k) { return c ^ (2 * ((k >> KSH) & (CB / 2 - 1))); }
 };
 
-template <int T, bool CONV = false>
+template <int BM, int BN, bool CONV = false>
 __global__ __launch_bounds__(256) void k_gemm_tn(const GemmTnArgs g) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  using C = TnCfg<T>;
+  using C = TnCfg<BM, BN>;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave / C::WGN, wn = wave % C::WGN;
+  const int wn = wave;
 
   // (tile, split-K slice) of this block: slice-major logical order, one contiguous range per XCD
   const int ntile = gridDim.x;
@@ -205,16 +207,17 @@ __global__ __launch_bounds__(256) void k_gemm_tn(const GemmTnArgs g) {
   //      addresses per LDS buffer (one per i % 4) and compile-time offsets for i / 4, r and the sub-step.
   //   B: lane addresses 8 bytes = 8 n at token 16*sub + 8h + s/2, n = wave_n + 32 j + mb + 8 (s % 2);
   //      result: lane owns n = ... + mb + s, tokens 8h + 0..7.
-  static_assert(C::WGM == 1 || C::TM <= 4, "A fragment addressing");
+  static_assert(C::WGM == 1, "A fragment addressing");
+  constexpr int UA = C::TM < 4 ? C::TM : 4;
   const int s16 = lane & 15, q = lane >> 4;
   const int mb = 16 * (q & 1), h = q >> 1;
-  int a_base[2][4], b_base[2][C::TN];           // LDS byte offsets of sub-step 0, per buffer
+  int a_base[2][UA], b_base[2][C::TN];          // LDS byte offsets of sub-step 0, per buffer
   {
-    const int k = 8 * h + (s16 >> 2), kk = (s16 >> 2) & 3;
+    const int k = 8 * h + (s16 >> 2), kk = C::swz_a_row(s16 >> 2);
     const int c0 = (mb >> 3) + ((s16 & 3) >> 1);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      a_base[0][u] = k * C::RA + ((4 * ((u + wm * (C::WM / 32)) ^ kk) + c0) << 4) + 8 * (s16 & 1);
+    for (int u = 0; u < UA; ++u) {
+      a_base[0][u] = k * C::RA + ((4 * (u ^ kk) + c0) << 4) + 8 * (s16 & 1);
       a_base[1][u] = a_base[0][u] + C::LDS_STAGE;
     }
   }
@@ -239,7 +242,7 @@ __global__ __launch_bounds__(256) void k_gemm_tn(const GemmTnArgs g) {
     } else {
       const int i = (r - C::TN) >> 1, hh = (r - C::TN) & 1;
       af[rb][i][hh] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4_t*)(
-          smem + a_base[buf][i & 3] + (i >> 2) * 256 + hh * 4 * C::RA + sub * 16 * C::RA));
+          smem + a_base[buf][i % UA] + (i / UA) * 256 + hh * 4 * C::RA + sub * 16 * C::RA));
     }
   };
   auto load_frags = [&](auto bufc, int sub, int rb) {
@@ -379,7 +382,7 @@ __global__ __launch_bounds__(256) void k_gemm_tn(const GemmTnArgs g) {
       const int col = n0 + wn * C::WN + j * 32 + fr;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int row = m0 + wm * C::WM + i * 32 + 8 * (r >> 2) + 4 * fh + (r & 3);
+        const int row = m0 + i * 32 + 8 * (r >> 2) + 4 * fh + (r & 3);
         if (row < g.M && col < g.N) out[(int64_t)row * g.N + col] = acc[i][j][r];
       }
     }
@@ -770,16 +773,16 @@ __global__ __launch_bounds__(256, T == 128 ? 2 : 1) void k_gemm_dx8(const GemmDx
 // smaller tiles, which stay at 8.
 static int tile_group_m(int tile) { return tile == 256 ? 2 : 8; }
 
-template <int T, bool CONV = false>
+template <int BM, int BN, bool CONV = false>
 static int launch_tn_cfg(const GemmTnArgs& a, int split_k, hipStream_t st) {
-  using C = TnCfg<T>;
+  using C = TnCfg<BM, BN>;
   // set once per process (initialisation of a function-local static is thread-safe)
-  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_tn<T, CONV>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
+  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_tn<BM, BN, CONV>, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
   if (attr != hipSuccess) return EFQAT_ERR_HIP;
   dim3 grid((unsigned)(a.tiles_m * a.tiles_n), (unsigned)split_k);
   {
     ProfScope prof(PROF_DW, st);
-    hipLaunchKernelGGL((k_gemm_tn<T, CONV>), grid, dim3(256), C::LDS_BYTES, st, a);
+    hipLaunchKernelGGL((k_gemm_tn<BM, BN, CONV>), grid, dim3(256), C::LDS_BYTES, st, a);
   }
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
@@ -800,8 +803,9 @@ int launch_gemm_tn(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* 
   a.tiles_m = plan.tiles_m; a.tiles_n = plan.tiles_n; a.group_m = tile_group_m(plan.tile);
   a.out = out_partial;
   switch (plan.tile) {
-    case 256: return launch_tn_cfg<256>(a, plan.split_k, stream);
-    case 128: return launch_tn_cfg<128>(a, plan.split_k, stream);
+    case 256: return launch_tn_cfg<256, 256>(a, plan.split_k, stream);
+    case 128: return launch_tn_cfg<128, 128>(a, plan.split_k, stream);
+    case 64: return launch_tn_cfg<64, 128>(a, plan.split_k, stream);
     default: return EFQAT_ERR_BAD_SHAPE;
   }
 }
@@ -876,7 +880,7 @@ int launch_gemm_tn_conv(const bf16_t* A, int64_t lda, int64_t a_cols, const uint
                         const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan, float* out_partial,
                         hipStream_t stream) {
   if (M <= 0 || N <= 0 || K <= 0 || (lda % 8) || (a_cols % 8) || a_cols > lda || lda >= (1 << 24)) return EFQAT_ERR_BAD_SHAPE;
-  if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX || plan.tile != 128 || (cm.c_in % 128) != 0)
+  if (M > INT32_MAX || N > INT32_MAX || K > INT32_MAX || (plan.tile != 128 && plan.tile != 64) || (cm.c_in % 128) != 0)
     return EFQAT_ERR_BAD_SHAPE;
   if (((uintptr_t)A % 16) || ((uintptr_t)x_codes % 16)) return EFQAT_ERR_ALIGNMENT;
   GemmTnArgs a{};
@@ -890,7 +894,7 @@ int launch_gemm_tn_conv(const bf16_t* A, int64_t lda, int64_t a_cols, const uint
   a.cv_pad = cm.pad; a.cv_cin = cm.c_in;
   const int hw = cm.Ho * cm.Wo, rem = 64 % hw;
   a.cv_dn = 64 / hw; a.cv_dh = rem / cm.Wo; a.cv_dw = rem % cm.Wo;
-  return launch_tn_cfg<128, true>(a, plan.split_k, stream);
+  return plan.tile == 64 ? launch_tn_cfg<64, 128, true>(a, plan.split_k, stream) : launch_tn_cfg<128, 128, true>(a, plan.split_k, stream);
 }
 
 int launch_gemm_dx8(const bf16_t* dy, int64_t lda, const int8_t* w_codes, int64_t ldb, const float* s_w, int64_t M,
