@@ -502,10 +502,11 @@ GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool allow_split, bool allow
 }
 
 // Kernel and tile of a dX product.  Microseconds per K stage of 64 and per block (launch, first loads, epilogue) with one
-// block on a CU (lone) and with all `bpc` that fit by LDS and registers (full), between the two by the number resident; what
+// block on a CU (lone; of a tile that fits once: on few of the CUs, where clock and memory are its own) and with all `bpc`
+// that fit by LDS and registers (full), between the two by the number resident; what
 // x and dX in fp32 add and what the straight-line epilogue of whole bf16 tiles saves.  A product is its whole rounds of
-// 256 * bpc blocks plus what is left.  Fitted to measured launches of 240 linear layers (each dimension 64 .. 16384) and 28
-// convolutions; the choice is 1.1 % from the fastest of the seven in the mean, the linear layers 1.33 x and the convolutions
+// 256 * bpc blocks plus what is left.  Fitted to measured launches of 300 linear layers (each dimension 64 .. 16384) and 28
+// convolutions; the choice is 0.9 % from the fastest of the six in the mean, the linear layers 1.33 x and the convolutions
 // 1.6 x as fast as with tiles of 128 and more only.  T x C_out -> C_in in us by k_gemm_kk 64 / nt 64 / kk 128 / nt 128 / kk 192 /
 // dx8 256, bf16:
 //   256 x 256 -> 256         6.6 / 5.8 / 8.4 /  - /  18 / -      few tiles: the smallest, with the shortest epilogue
@@ -518,11 +519,11 @@ GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool allow_split, bool allow
 // Convolutions pay for the gather in every stage.
 struct DxTile { int t; bool ring; int bpc; double lone[2], full[2], f32[2], fast[2]; };
 static const DxTile kDxTiles[] = {{64, true, 3, {0.28, 5.6}, {0.73, 4.5}, {0.1, 1.0}, {0.0, 0.0}},
-                                  {64, false, 4, {0.465, 4.4}, {0.97, 4.5}, {0.1, 2.1}, {0.0, 0.0}},
-                                  {128, true, 1, {0.535, 8.9}, {0.535, 8.9}, {0.2, 0.2}, {-2.0, -2.0}},
-                                  {128, false, 2, {0.735, 8.0}, {1.08, 10.0}, {0.6, 2.3}, {-1.7, -2.4}},
-                                  {192, true, 1, {0.77, 15.8}, {0.77, 15.8}, {0.2, 0.2}, {-4.0, -4.0}},
-                                  {256, false, 1, {1.125, 20.0}, {1.125, 20.0}, {0.5, 0.5}, {-3.5, -3.5}}};
+                                  {64, false, 4, {0.465, 4.4}, {0.965, 4.4}, {0.1, 1.6}, {0.0, 0.0}},
+                                  {128, true, 1, {0.495, 9.2}, {0.587, 7.9}, {0.0, 1.4}, {-1.7, -1.7}},
+                                  {128, false, 2, {0.74, 8.0}, {1.075, 9.7}, {0.7, 3.5}, {-1.7, -2.0}},
+                                  {192, true, 1, {0.695, 15.6}, {0.98, 15.6}, {0.0, 4.8}, {-4.2, -4.2}},
+                                  {256, false, 1, {0.92, 23.3}, {1.61, 23.3}, {1.9, 12.0}, {-6.7, -6.7}}};
 static const DxTile kDxConvTiles[] = {{64, true, 3, {0.30, 6.3}, {0.575, 6.6}, {0.0, 0.0}, {0.0, 0.0}},
                                       {64, false, 4, {0.54, 5.2}, {0.71, 5.4}, {0.0, 0.1}, {0.0, 0.0}},
                                       {128, true, 1, {0.56, 10.0}, {0.56, 10.0}, {0.5, 0.5}, {-1.0, -1.0}},
@@ -552,7 +553,7 @@ GemmPlan dx_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const Con
     const double lone = c.lone[0] * stages + c.lone[1] + add[0], full = c.full[0] * stages + c.full[1] + add[1];
     double t = (double)(tiles / round) * full;
     if (const int64_t rest = tiles % round)
-      t += lone + (full - lone) * (double)(ceil_div(rest, 256) - 1) / (double)std::max(1, c.bpc - 1);
+      t += lone + (full - lone) * (c.bpc > 1 ? (double)(ceil_div(rest, 256) - 1) / (c.bpc - 1) : (double)rest / 256.0);
     // the others need W_q^T in bf16: the codes read, twice as many bytes written, at 4 TB/s
     if (int8_ok && c.t != 256) t += 3.0 * (double)N * (double)K / 4e6;
     if (best.tile == 0 || t < best_t) { best_t = t; best = GemmPlan{c.t, 1, (int)tm, (int)tn, c.ring}; }
