@@ -271,50 +271,67 @@ __global__ __launch_bounds__(256) void k_quantize_act_flat(const T* __restrict__
   }
 }
 
-// Eq. 4 + Eq. 3 with the row held in registers (weights, min/max initialisation, cols <= 8 * 64 * WPR * NIT <= 16384,
-// cols % 32 == 0, aligned pointers): WPR wavefronts per row (1, or the 4 of a block when there are few rows) issue all
-// loads of the row at once, take the abs-max, write S_w[c] and quantize from the registers, so the row is read once
-// and the reads are not a chain of dependent round trips.
-template <int NIT, int WPR>
-__global__ __launch_bounds__(256) void k_quantize_w_row_init(const float* __restrict__ w, int64_t rows, int64_t cols,
-                                                             int bits, float* __restrict__ scale,
-                                                             int8_t* __restrict__ codes, uint32_t* __restrict__ clip,
-                                                             double* __restrict__ scores) {
+// Eq. 3 (and Eq. 4 with INIT) with the row held in registers (weights, cols <= 8 * 64 * WPR * NIT <= 16384): WPR wavefronts
+// per row (1, or the 4 of a block when there are few rows) issue all loads of the row at once, take the abs-max and write
+// S_w[c] (INIT), sum |w| in double precision for Eq. 6, and quantize from the registers, so the row is read once and the
+// reads are not a chain of dependent round trips.  RAG: rows of any length and alignment; a lane's 8 values are one vector
+// access all the same (the hardware takes them at element alignment), except in the chunk that ends a row.
+// 1001 x 777 with scales from the data 5.0 us, 768 x 768 and 11008 x 4096 with given scales 3.8 and 40 us; a wavefront that
+// walked the row twice, or a kernel over 512-element segments, and a second kernel for the sums took 11.2, 6.6 and 62 us.
+template <int NIT, int WPR, bool INIT, bool RAG>
+__global__ __launch_bounds__(256) void k_quantize_w_row(const float* __restrict__ w, int64_t rows, int64_t cols, int bits,
+                                                        float* __restrict__ scale, int8_t* __restrict__ codes,
+                                                        uint32_t* __restrict__ clip, double* __restrict__ scores) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t row = WPR == 4 ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * 4 + wave;
   const int part = WPR == 4 ? wave : 0;               // which quarter of the row's chunks (interleaved by 64)
   const bool on = row < rows;                         // WPR == 1: whole wavefronts beyond the last row idle
   const float hi = (float)((1 << (bits - 1)) - 1), lo = -hi;
-  const int n8 = on ? (int)(cols >> 3) : 0;
+  const int n8 = on ? (int)((cols + 7) >> 3) : 0;     // chunks, the last one possibly shorter (RAG)
   const float* p = w + (on ? row : 0) * cols;
   float v[NIT][8];
 #pragma unroll
   for (int it = 0; it < NIT; ++it) {
     const int i = (it * WPR + part) * 64 + lane;
-    if (i < n8) load8<float>(p + (int64_t)i * 8, v[it]);
-  }
-  float m = 0.0f;
+    if constexpr (RAG) {
 #pragma unroll
-  for (int it = 0; it < NIT; ++it) {
-    if ((it * WPR + part) * 64 + lane < n8) {
+      for (int j = 0; j < 8; ++j) v[it][j] = 0.0f;
+      if ((int64_t)i * 8 + 8 <= cols && i < n8) __builtin_memcpy(v[it], p + (int64_t)i * 8, 32);
+      else if (i < n8) {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) m = fmaxf(m, fabsf(v[it][j]));
+        for (int j = 0; j < 7; ++j)
+          if ((int64_t)i * 8 + j < cols) v[it][j] = p[(int64_t)i * 8 + j];
+      }
+    } else {
+      if (i < n8) load8<float>(p + (int64_t)i * 8, v[it]);
     }
   }
-  m = wave_max(m);
+  float s;
+  if constexpr (!INIT) s = on ? scale[row] : 1.0f;
+  float m = 0.0f;
+  if constexpr (INIT) {
+#pragma unroll
+    for (int it = 0; it < NIT; ++it) {
+      if (RAG || (it * WPR + part) * 64 + lane < n8) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) m = fmaxf(m, fabsf(v[it][j]));
+      }
+    }
+    m = wave_max(m);
+  }
   // optional by-product (Eq. 6): the row's mean |w| in double precision, fixed summation order, from the registers
   double asum = 0.0;
   if (scores) {
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
-      if ((it * WPR + part) * 64 + lane < n8) {
+      if (RAG || (it * WPR + part) * 64 + lane < n8) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) asum += (double)fabsf(v[it][j]);
       }
     }
     asum = wave_sum(asum);
   }
-  if (WPR == 4) {
+  if (WPR == 4 && (INIT || scores)) {
     __shared__ float s_m[4];
     __shared__ double s_a[4];
     if (lane == 0) { s_m[wave] = m; s_a[wave] = asum; }
@@ -323,30 +340,41 @@ __global__ __launch_bounds__(256) void k_quantize_w_row_init(const float* __rest
     asum = (s_a[0] + s_a[1]) + (s_a[2] + s_a[3]);
   }
   if (scores && on && lane == 0 && part == 0) scores[row] = asum / (double)cols;
-  float s = __fdiv_rn(m, hi);
-  if (!(s > 0.0f)) s = 1.0f;                          // all-zero row
-  if (on && lane == 0 && part == 0) scale[row] = s;
+  if constexpr (INIT) {
+    s = __fdiv_rn(m, hi);
+    if (!(s > 0.0f)) s = 1.0f;                        // all-zero row
+    if (on && lane == 0 && part == 0) scale[row] = s;
+  }
   const float inv_s = __fdiv_rn(1.0f, s);
-  const int64_t wpr = cols >> 5;
+  const int64_t wpr = (cols + 31) >> 5;
 #pragma unroll
   for (int it = 0; it < NIT; ++it) {
     const int i = (it * WPR + part) * 64 + lane;
-    // n8 % 4 == 0: the four lanes of a mask word are in range together
-    if (i < n8) {
-      uint32_t bits8 = 0;
-      uint32_t cw[2] = {0u, 0u};
+    uint32_t bits8 = 0;
+    uint32_t cw[2] = {0u, 0u};
+    // n8 % 4 == 0 without RAG: the four lanes of a mask word are in range together
+    if (RAG || i < n8) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const float cu = round_quotient(v[it][j], s, inv_s);
         const float cc = __builtin_amdgcn_fmed3f(cu, lo, hi);
-        if (cu == cc) bits8 |= (1u << j);
+        if (cu == cc && (!RAG || (int64_t)i * 8 + j < cols)) bits8 |= (1u << j);
         cw[j >> 2] |= ((uint32_t)((int)cc & 0xFF)) << (8 * (j & 3));
       }
-      *reinterpret_cast<uint2*>(codes + row * cols + (int64_t)i * 8) = make_uint2(cw[0], cw[1]);
-      uint32_t word = bits8 << (8 * (lane & 3));
+      int8_t* c = codes + row * cols + (int64_t)i * 8;
+      if (!RAG) *reinterpret_cast<uint2*>(c) = make_uint2(cw[0], cw[1]);
+      else if (i < n8) {
+        if ((int64_t)i * 8 + 8 <= cols) __builtin_memcpy(c, cw, 8);
+        else {
+#pragma unroll
+          for (int j = 0; j < 7; ++j)
+            if ((int64_t)i * 8 + j < cols) c[j] = (int8_t)(cw[j >> 2] >> (8 * (j & 3)));
+        }
+      }
+      uint32_t word = i < n8 ? bits8 << (8 * (lane & 3)) : 0u;
       word |= __shfl_xor(word, 1, kWave);
       word |= __shfl_xor(word, 2, kWave);
-      if ((lane & 3) == 0) clip[row * wpr + (i >> 2)] = word;
+      if ((lane & 3) == 0 && i < n8) clip[row * wpr + (i >> 2)] = word;
     }
   }
 }
@@ -354,8 +382,8 @@ __global__ __launch_bounds__(256) void k_quantize_w_row_init(const float* __rest
 // ----------------------------------------------------------------------------------------------
 static inline bool aligned_to(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
-// scores (weights with min/max initialisation only): where the row-in-registers kernel runs, it also writes the
-// Eq. 6 importance of every row and *scores_done is set; otherwise the caller computes them in a pass of its own.
+// scores (weights only): where the row-in-registers kernel runs, it also writes the Eq. 6 importance of every row and
+// *scores_done is set; otherwise the caller computes them in a pass of its own.
 template <typename T>
 static int run_fakequant(const T* x, int64_t rows, int64_t cols, int mode, int bits, int init_minmax,
                          float* scale, float* zp, void* codes, uint32_t* clip, bf16_t* xq, void* ws,
@@ -377,6 +405,9 @@ static int run_fakequant(const T* x, int64_t rows, int64_t cols, int mode, int b
   const int64_t items = row_items ? rows : rows * ceil_div(cols, 512);
   int64_t blocks = ceil_div(items, 4);
   if (blocks > 256 * 32) blocks = 256 * 32;
+  // weights, few rows or long rows: a block per row, so that the chip still holds enough wavefronts to cover the memory
+  // latency and a lane holds at most 64 values
+  const bool wide = (rows < 4096 && cols > 8 * 64) || cols > 8 * 64 * 8;
   if (mode == EFQAT_QUANT_ACT_PER_TENSOR_ASYM && vec_row && (cols % 32) == 0) {
     const int64_t nchunks = n / 8;
     int64_t fb = ceil_div(nchunks, 512);             // two chunks per lane and iteration
@@ -386,24 +417,31 @@ static int run_fakequant(const T* x, int64_t rows, int64_t cols, int mode, int b
   } else if (mode == EFQAT_QUANT_ACT_PER_TENSOR_ASYM)
     hipLaunchKernelGGL((k_quantize<T, EFQAT_QUANT_ACT_PER_TENSOR_ASYM, false>), dim3((unsigned)blocks), dim3(256), 0,
                        st, x, rows, cols, vec_row, bits, scale, zp, (uint8_t*)codes, clip, xq);
-  else if (init_minmax && std::is_same<T, float>::value && vec_row && (cols % 32) == 0 && cols <= 8 * 64 * 4 * 8 && !xq) {
-    // few rows or long rows: a block per row, so that the chip still holds enough wavefronts to cover the memory
-    // latency and a lane holds at most 64 values
-    const bool wide = (rows < 4096 && cols > 8 * 64) || cols > 8 * 64 * 8;
+  // (a grid dimension holds less than 2^32 work items)
+  else if ((init_minmax || scores) && std::is_same<T, float>::value && cols <= 8 * 64 * 4 * 8 && !xq &&
+           rows < (wide ? 1 << 24 : 1 << 26)) {
+    const bool rag = !vec_row || (cols % 32) != 0;
     const float* wf = (const float*)x;
     int8_t* cd = (int8_t*)codes;
     const int per_wave = (int)ceil_div(cols, 8 * 64 * (wide ? 4 : 1));     // 8-element chunks per lane
     const dim3 grid((unsigned)(wide ? rows : ceil_div(rows, 4)));
-#define EFQAT_ROW_INIT(NIT, WPR) \
-  hipLaunchKernelGGL((k_quantize_w_row_init<NIT, WPR>), grid, dim3(256), 0, st, wf, rows, cols, bits, scale, cd, clip, \
-                     scores)
+    auto row_kernel = [&](auto nit, auto wpr) {
+      constexpr int NIT = decltype(nit)::value, WPR = decltype(wpr)::value;
+      auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, wf, rows, cols, bits, scale, cd, clip, scores); };
+      if (init_minmax) { if (rag) go(k_quantize_w_row<NIT, WPR, true, true>); else go(k_quantize_w_row<NIT, WPR, true, false>); }
+      else { if (rag) go(k_quantize_w_row<NIT, WPR, false, true>); else go(k_quantize_w_row<NIT, WPR, false, false>); }
+    };
+    using W1 = std::integral_constant<int, 1>;
+    using W2 = std::integral_constant<int, 2>;
+    using W4 = std::integral_constant<int, 4>;
+    using W6 = std::integral_constant<int, 6>;
+    using W8 = std::integral_constant<int, 8>;
     if (wide) {
-      if (per_wave <= 1) EFQAT_ROW_INIT(1, 4); else if (per_wave <= 2) EFQAT_ROW_INIT(2, 4);
-      else if (per_wave <= 4) EFQAT_ROW_INIT(4, 4); else if (per_wave <= 6) EFQAT_ROW_INIT(6, 4); else EFQAT_ROW_INIT(8, 4);
+      if (per_wave <= 1) row_kernel(W1{}, W4{}); else if (per_wave <= 2) row_kernel(W2{}, W4{});
+      else if (per_wave <= 4) row_kernel(W4{}, W4{}); else if (per_wave <= 6) row_kernel(W6{}, W4{}); else row_kernel(W8{}, W4{});
     } else {
-      if (per_wave <= 2) EFQAT_ROW_INIT(2, 1); else if (per_wave <= 4) EFQAT_ROW_INIT(4, 1); else EFQAT_ROW_INIT(8, 1);
+      if (per_wave <= 2) row_kernel(W2{}, W1{}); else if (per_wave <= 4) row_kernel(W4{}, W1{}); else row_kernel(W8{}, W1{});
     }
-#undef EFQAT_ROW_INIT
     if (scores && scores_done) *scores_done = true;
   } else if (init_minmax)
     hipLaunchKernelGGL((k_quantize<T, EFQAT_QUANT_W_PER_ROW_SYM, true>), dim3((unsigned)blocks), dim3(256), 0, st, x,
@@ -472,9 +510,9 @@ extern "C" int efqat_weight_quant_select(const float* w, int64_t c_out, int64_t 
   double* sc = scores ? scores : own;
   bool scores_done = false;
   int rc = run_fakequant<float>(w, c_out, block, EFQAT_QUANT_W_PER_ROW_SYM, bits, init_minmax, scale, nullptr, codes,
-                                clip_bits, nullptr, nullptr, st, init_minmax ? sc : nullptr, &scores_done);
+                                clip_bits, nullptr, nullptr, st, sc, &scores_done);
   if (rc) return rc;
-  if (!scores_done) {                                  // rows too long for the register kernel, or given scales
+  if (!scores_done) {                                  // rows too long for the register kernel
     rc = launch_row_importance(w, c_out, block, sc, st);
     if (rc) return rc;
   }
