@@ -318,7 +318,9 @@ typedef struct efqat_opt_step {
  *                and results are bit-identical.  The fork and join use two HIP events that the
  *                library creates at the first such call of a host thread on a device and keeps
  *                (no other state; nothing is created on later calls).  Ignored when k == 0, when it
- *                equals `stream`, and on the layouts whose dW product runs on staged copies.
+ *                equals `stream`, on the layouts whose dW product runs on staged copies, and for
+ *                layers whose two products share one launch on `stream` (small ones: neither
+ *                product fills the chip by itself).
  * Workspace: efqat_linear_bwd_workspace_bytes_ex with the same dx_kernel. */
 size_t efqat_linear_bwd_workspace_bytes_ex(int64_t T, int64_t c_in, int64_t c_out, int64_t k,
                                            int dy_dtype, int dy_layout, int dx_kernel);
@@ -383,6 +385,8 @@ int efqat_linear_fwd(const uint8_t* x_codes, const float* s_x, const float* z_x,
  * launches with HIP events on the stream they go to.  This is the only process-wide state of the
  * library; it is off by default and not thread-safe.
  *   efqat_profile_enable(on)  on != 0 starts a new measurement (counters reset), 0 stops it.
+ *                             While it is on, the two products of a layer are always launched apart
+ *                             (same blocks, same results), so that each class has its own time.
  *                             At most 4096 brackets per class are recorded.
  *   efqat_profile_read(which, total_ms, launches)  waits for the recorded events of one class
  *                             (host pointers out: summed time in ms, number of brackets). */

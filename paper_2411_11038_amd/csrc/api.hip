@@ -28,6 +28,7 @@ static hipEvent_t g_prof_ev[PROF_CLASSES][kMaxProf][2];
 static int g_prof_made[PROF_CLASSES];
 static int g_prof_used[PROF_CLASSES];
 
+bool prof_enabled() { return g_prof_on; }
 bool prof_begin(int which, hipStream_t st, int* slot) {
   if (!g_prof_on || g_prof_used[which] >= kMaxProf) return false;
   const int i = g_prof_used[which];

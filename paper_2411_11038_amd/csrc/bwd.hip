@@ -1,7 +1,7 @@
 // EfQAT backward of one quantized layer (Alg. 1 backward step, Eq. 5): operand preparation,
 // the two MFMA contractions, and the fused / second-pass epilogues that apply the straight-through
 // clip masks and reduce the quantizer-parameter gradients.
-#include "common.hpp"
+#include "gemm_epilogue.hpp"
 
 #include <algorithm>
 
@@ -566,7 +566,7 @@ struct BwdPlan {
   bool cdx;        // convolution dX product with the im2col gather inside the tile loads (no im2col matrix)
   bool cdxs;       // ... of a convolution with a stride: rows sorted by (h mod stride, w mod stride)
   bool dx8;        // dX product with the weight operand read from the int8 codes (no bf16 W_q^T copy)
-  bool kk;         // dX product from the bf16 copies by the 192 x 192 kernel with the pinned instruction order
+  bool pair;       // both products in one grid of 64-row tiles
   int dx8_tile;
   int64_t kp;      // k rounded up to 8 (pitch of the compacted dY columns)
   GemmPlan plan_dx, plan_dw;
@@ -586,11 +586,10 @@ static bool conv_stages_ok(const ConvGeom& g, int64_t ldc) {
 }
 
 // dxk: the caller's choice of the dX kernel (EFQAT_DX_KERNEL_*); it changes workspace sizes, so the size query takes
-// it as well.  wide: tiles of 128 and more by gemm_plan's rule, for callers whose workspace or weight codes do not fit
-// the plan by kDxTiles and kDwTiles (see choose_plan).
+// it as well.  wide: tiles of 128 and more by gemm_plan's rule, for callers whose workspace or weight codes do not fit the
+// plan by kDxTiles, kDwTiles and pair_plan (see choose_plan).
 static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_out, int taps, int64_t k,
-                         int dy_dtype, int dy_layout, bool im2col, int dxk, const ConvGeom* cg = nullptr,
-                         bool wide = false) {
+                         int dy_dtype, int dy_layout, bool im2col, int dxk, const ConvGeom* cg, bool wide) {
   BwdPlan p{};
   p.Mx = T_in; p.Tw = T_out; p.Nw = (int64_t)taps * c_in;
   p.ldc = round_up(c_out, 8); p.ldt = round_up(T_out, 8);
@@ -621,6 +620,7 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
   // strides have too many phases to sort the rows for.
   p.cdxs = im2col && cg && cg->stride > 1 && cg->stride <= kMaxConvStride && conv_stages_ok(*cg, p.ldc) &&
            dxk != EFQAT_DX_KERNEL_BF16_PINNED;
+  double price_dx = 0.0, price_dw = 0.0;
   const ConvDxStridedMap sm = p.cdxs ? strided_map(*cg) : ConvDxStridedMap{};
   const bool int8_ok = taps == 1 && !im2col && direct_tok && (c_in % 16) == 0 && dxk != EFQAT_DX_KERNEL_BF16;
   if (wide) {
@@ -629,7 +629,7 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
     p.plan_dx.ring = (p.plan_dx.tile == 192 && !p.cdx) ||
                      (p.plan_dx.tile == 128 && (int64_t)p.plan_dx.tiles_m * p.plan_dx.tiles_n <= 256);
   } else {
-    p.plan_dx = dx_plan(p.Mx, c_in, p.Kx, dy_dtype == EFQAT_F32, p.cdx || p.cdxs, p.cdxs ? &sm : nullptr, int8_ok);
+    p.plan_dx = dx_plan(p.Mx, c_in, p.Kx, dy_dtype == EFQAT_F32, p.cdx || p.cdxs, p.cdxs ? &sm : nullptr, int8_ok, &price_dx);
   }
   if (p.cdxs) p.cdx = true;
   p.dx8 = false; p.dx8_tile = 0;
@@ -644,10 +644,17 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
     p.dx8 = true; p.dx8_tile = (p.plan_dx.tile == 256 || (p.Mx >= 1024 && c_in >= 512)) ? 256 : 128;
     p.plan_dx.tiles_m = (int)ceil_div(p.Mx, p.dx8_tile); p.plan_dx.tiles_n = (int)ceil_div(c_in, p.dx8_tile);
   }
-  p.kk = !p.dx8 && !p.cdx && p.plan_dx.ring;
   if (k == 0) p.plan_dw = GemmPlan{128, 1, 0, 0, false};
   else if (wide || p.rdw) p.plan_dw = gemm_plan(k, p.Nw, p.ldt, true, !(p.tn || p.rdw), !p.cdw);
-  else p.plan_dw = dw_plan(p.cdw ? DW_CONV : p.tn ? DW_TOKENS : DW_STAGED, k, p.Nw, p.ldt);
+  else {
+    const DwKind kind = p.cdw ? DW_CONV : p.tn ? DW_TOKENS : DW_STAGED;
+    p.plan_dw = dw_plan(kind, k, p.Nw, p.ldt, &price_dw);
+    if (price_dw > 0.0 && !p.dx8 && dxk == EFQAT_DX_KERNEL_AUTO && (!im2col || p.cdx)) {
+      if (int8_ok) price_dx -= 3.0 * (double)c_in * (double)p.Kx / 4e6;   // W_q^T in bf16 (dx_plan): the pair needs it as well
+      p.pair = pair_plan(p.Mx, c_in, p.Kx, dy_dtype == EFQAT_F32, p.cdx, p.cdxs ? &sm : nullptr, kind, k, p.Nw, p.ldt,
+                         price_dx + price_dw, &p.plan_dx, &p.plan_dw);
+    }
+  }
   WsCarver cv(nullptr);
   p.b_wqT = p.dx8 ? 0 : (size_t)c_in * p.Kx * 2; cv.take(p.b_wqT);
   p.b_dyn = p.need_dyn ? (size_t)T_out * p.ldc * 2 : 0; cv.take(p.b_dyn);
@@ -663,15 +670,15 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
   return p;
 }
 
-// The plan of a call: by kDxTiles and kDwTiles, or the wide one where that needs less workspace than the call brings, or 16-byte aligned
-// weight codes that it does not.  A workspace of either size is taken, and the query returns the larger.
-// c_in beyond what the bf16 W_q^T may have (check_plan) also leaves the choice to gemm_plan's rule.
+// The plan of a call, or the wide one where that needs less workspace than the call brings, or 16-byte aligned weight codes
+// that it does not.  A workspace of either size is taken, and the query returns the larger.  c_in beyond what the bf16
+// W_q^T may have (check_plan) leaves the choice to gemm_plan's rule as well.
 template <class Plan>
 static BwdPlan choose_plan(const Plan& plan, int64_t c_in, const int8_t* w_codes, size_t ws_bytes) {
-  BwdPlan p = plan(c_in > kMaxStagedColumns);
+  const BwdPlan p = plan(c_in > kMaxStagedColumns);
   if (ws_bytes < p.total || (p.dx8 && ((uintptr_t)w_codes % 16) != 0)) {
     const BwdPlan w = plan(true);
-    if (ws_bytes >= w.total) p = w;
+    if (ws_bytes >= w.total) return w;
   }
   return p;
 }
@@ -735,13 +742,16 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   bf16_t* xcT = (bf16_t*)cv.take(p.b_xcT);
   bf16_t* sel = (bf16_t*)cv.take(p.b_sel);
   float* part_dw = (float*)cv.take(p.b_part_dw);
-  int rc;
+  int rc = EFQAT_OK;
 
   // ---- optional second stream.  The weight-gradient branch (compaction of the selected columns of dY, dW product)
   // reads the call's inputs only, so it may run beside the dX product: blocks of the two products then share the compute
   // units, and neither leaves a partly filled last round behind.  It is forked here, behind everything the caller's
   // stream held before the call, and joined before the second pass of the weight gradient.
-  const bool use_side = io.side && io.side != st && io.k > 0 && (p.tn || p.rdw);
+  // Products that share a grid run beside each other already, at no cost of events; with both products on one stream the
+  // result is the same bit for bit.  Launches that are timed by class are kept apart.
+  const bool pair = p.pair && !prof_enabled();
+  const bool use_side = io.side && io.side != st && io.k > 0 && (p.tn || p.rdw) && !p.pair;
   hipStream_t st2 = st;
   SideEvents ev{};
   if (use_side) {
@@ -795,7 +805,7 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   if (rc) return rc;
   const bf16_t* dy_tok = p.need_dyn ? dyn : (const bf16_t*)io.dy;
 
-  // ---- dX product with the fused straight-through / qparam epilogue
+  // ---- operands of the dX product with the fused straight-through / qparam epilogue
   const bf16_t* A = dy_tok;
   int64_t lda = p.ldc;
   if (im2col && !p.cdx) {
@@ -806,21 +816,49 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   }
   prep.close();
   GemmEpilogueDx epi{io.x_codes, io.x_clip, io.x, io.x_dtype, io.s_x, io.z_x, io.dx, io.dx_dtype, part_dx};
-  if (p.dx8) {
-    if (p.cmx)
-      rc = launch_gemm_dx8_cm((const bf16_t*)io.dy, T_out, io.w_codes, c_in, io.s_w, p.Mx, c_in, c_out,
-                              p.dx8_tile, epi, st);
-    else
-      rc = launch_gemm_dx8(dy_tok, c_out, io.w_codes, c_in, io.s_w, p.Mx, c_in, c_out, p.dx8_tile, epi, st);
-  } else if (p.cdxs) {
-    rc = launch_gemm_conv_dx_strided(dy_tok, p.ldc, wqT, p.Kx, p.Mx, c_in, strided_map(*cg), p.plan_dx, epi, st);
+  GemmStridedArgs dxa{};
+  const int conv = p.cdxs ? 2 : p.cdx ? 1 : 0;
+  if (p.cdxs) {
+    rc = dx_args_strided(&dxa, dy_tok, p.ldc, wqT, p.Kx, p.Mx, c_in, strided_map(*cg), p.plan_dx, epi);
   } else if (p.cdx) {
     const ConvDxMap cm{cg->H, cg->W, cg->Ho, cg->Wo, cg->KW, cg->pad};
-    rc = launch_gemm_nt_conv_dx(dy_tok, p.ldc, wqT, p.Kx, p.Mx, c_in, p.Kx, cm, p.plan_dx, epi, st);
-  } else if (p.kk) {
-    rc = launch_gemm_kk(A, lda, wqT, p.Kx, p.Mx, c_in, p.Kx, p.plan_dx, nullptr, &epi, st);
+    rc = dx_args_conv(&dxa, dy_tok, p.ldc, wqT, p.Kx, p.Mx, c_in, p.Kx, cm, p.plan_dx, epi);
+  } else if (!p.dx8) {
+    rc = dx_args_linear(&dxa, A, lda, wqT, p.Kx, p.Mx, c_in, p.Kx, p.plan_dx, epi);
+  }
+  if (rc) return rc;
+
+  // ---- operands of the dW product
+  GemmTnArgs tna{};
+  GemmArgs nta{};
+  if (p.tn) {
+    // straight from token-major operands: A = the selected columns of dY (compacted once, or dY itself when every channel is
+    // selected), B = the uint8 codes; transposition happens in the LDS reads
+    const bf16_t* At = gather ? sel : (const bf16_t*)io.dy;
+    const int64_t ldat = gather ? p.kp : c_out, acols = ldat;
+    if (p.cdw) {
+      const ConvDwMap cm{cg->H, cg->W, cg->Ho, cg->Wo, cg->KW, cg->stride, cg->pad, (int)c_in};
+      rc = dw_args_tn_conv(&tna, At, ldat, acols, io.x_codes, cm, io.z_x, io.k, p.Nw, T_out, p.plan_dw, part_dw);
+    } else {
+      rc = dw_args_tn(&tna, At, ldat, acols, io.x_codes, c_in, c_in, io.z_x, io.k, p.Nw, T_out, p.plan_dw, part_dw);
+    }
+  } else if (io.k > 0 && !p.rdw) {
+    // staged operands; channel-major bf16 dY that is not staged: the gather is fused into the tile loads
+    const bf16_t* Aw = p.need_sel ? sel : (const bf16_t*)io.dy;
+    const int64_t ldaw = p.need_sel ? p.ldt : T_out;
+    rc = dw_args_staged(&nta, Aw, ldaw, p.need_sel ? nullptr : io.idx, xcT, p.ldt, io.k, p.Nw, ldaw, p.plan_dw, part_dw);
+  }
+  if (rc) return rc;
+
+  // ---- the products
+  if (pair) {
+    rc = launch_pair(dxa, conv, p.plan_dx, p.tn ? &tna : nullptr, p.tn ? nullptr : &nta, p.plan_dw, st);
+  } else if (p.cmx) {
+    rc = launch_gemm_dx8_cm((const bf16_t*)io.dy, T_out, io.w_codes, c_in, io.s_w, p.Mx, c_in, c_out, p.dx8_tile, epi, st);
+  } else if (p.dx8) {
+    rc = launch_gemm_dx8(dy_tok, c_out, io.w_codes, c_in, io.s_w, p.Mx, c_in, c_out, p.dx8_tile, epi, st);
   } else {
-    rc = launch_gemm_nt(A, lda, nullptr, wqT, p.Kx, p.Mx, c_in, p.Kx, p.plan_dx, nullptr, &epi, st);
+    rc = launch_dx(dxa, conv, p.plan_dx, st);
   }
   if (rc) return rc;
   const int64_t n_part_dx = (int64_t)p.plan_dx.tiles_m * p.plan_dx.tiles_n;
@@ -830,47 +868,23 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
     EFQAT_LAUNCH_CHECK();
     return EFQAT_OK;
   }
-
-  if (p.tn) {
-    // ---- dW product straight from token-major operands: A = the selected columns of dY (compacted once, or dY
-    // itself when every channel is selected), B = the uint8 codes; transposition happens in the LDS reads
-    const bf16_t* At = (const bf16_t*)io.dy;
-    int64_t ldat = c_out, acols = c_out;
-    if (gather) {
-      if (use_side) {
-        ProfScope gat(PROF_PREP, st2);
-        if (io.dy_dtype == EFQAT_F32)
-          hipLaunchKernelGGL((k_gather_cols<float>), ggrid, dim3(256), 0, st2, (const float*)io.dy, c_out, T_out, io.idx,
-                             io.k, sel, p.kp);
-        else
-          hipLaunchKernelGGL((k_gather_cols<bf16_t>), ggrid, dim3(256), 0, st2, (const bf16_t*)io.dy, c_out, T_out,
-                             io.idx, io.k, sel, p.kp);
-        EFQAT_LAUNCH_CHECK();
-      }
-      At = sel; ldat = p.kp; acols = p.kp;
-    }
-    if (p.cdw) {
-      const ConvDwMap cm{cg->H, cg->W, cg->Ho, cg->Wo, cg->KW, cg->stride, cg->pad, (int)c_in};
-      rc = launch_gemm_tn_conv(At, ldat, acols, io.x_codes, cm, io.z_x, io.k, p.Nw, T_out, p.plan_dw,
-                               part_dw, st2);
-    } else {
-      rc = launch_gemm_tn(At, ldat, acols, io.x_codes, c_in, c_in, io.z_x, io.k, p.Nw, T_out, p.plan_dw,
-                          part_dw, st2);
-    }
-    if (rc) return rc;
-  } else if (p.rdw) {
-    // ---- channel-major dY: the selected rows are gathered by the tile loads, the codes are read as they lie
-    rc = launch_gemm_dw_rows((const bf16_t*)io.dy, T_out, io.idx, io.x_codes, c_in, io.z_x, io.k, p.Nw,
-                             T_out, p.plan_dw, part_dw, st2);
-    if (rc) return rc;
-  } else {
-    // channel-major bf16 dY that is not staged: the gather is fused into the tile loads
-    const bf16_t* Aw = p.need_sel ? sel : (const bf16_t*)io.dy;
-    const int64_t ldaw = p.need_sel ? p.ldt : T_out, Kw = ldaw;
-    const int32_t* a_rows = p.need_sel ? nullptr : io.idx;
-    rc = launch_gemm_nt(Aw, ldaw, a_rows, xcT, p.ldt, io.k, p.Nw, Kw, p.plan_dw, part_dw, nullptr, st);
-    if (rc) return rc;
+  if (gather && use_side) {
+    ProfScope gat(PROF_PREP, st2);
+    if (io.dy_dtype == EFQAT_F32)
+      hipLaunchKernelGGL((k_gather_cols<float>), ggrid, dim3(256), 0, st2, (const float*)io.dy, c_out, T_out, io.idx, io.k, sel,
+                         p.kp);
+    else
+      hipLaunchKernelGGL((k_gather_cols<bf16_t>), ggrid, dim3(256), 0, st2, (const bf16_t*)io.dy, c_out, T_out, io.idx, io.k,
+                         sel, p.kp);
+    EFQAT_LAUNCH_CHECK();
   }
+  if (pair) rc = EFQAT_OK;
+  else if (p.tn) rc = launch_gemm_tn(tna, p.plan_dw, st2);
+  else if (p.rdw)                                      // channel-major dY: the selected rows are gathered by the tile loads
+    rc = launch_gemm_dw_rows((const bf16_t*)io.dy, T_out, io.idx, io.x_codes, c_in, io.z_x, io.k, p.Nw, T_out, p.plan_dw,
+                             part_dw, st2);
+  else rc = launch_gemm_nt_raw(nta, p.plan_dw, st);
+  if (rc) return rc;
   if (use_side && (hipEventRecord(ev.join, st2) != hipSuccess || hipStreamWaitEvent(st, ev.join, 0) != hipSuccess))
     return EFQAT_ERR_HIP;
   const int fvec = (p.Nw % 4 == 0 && ((uintptr_t)io.w % 16) == 0 && ((uintptr_t)io.dw % 16) == 0 &&

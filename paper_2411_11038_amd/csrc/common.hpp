@@ -119,56 +119,27 @@ GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool allow_split, bool allow
 // Kernel and tile of a dX product (see kDxTiles).  conv: dY is gathered in the tile loads, by phase when `strided` is given;
 // int8_ok: tiles of 256 are run by k_gemm_dx8, which needs no bf16 W_q^T.
 struct ConvDxStridedMap;
-GemmPlan dx_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const ConvDxStridedMap* strided, bool int8_ok);
+GemmPlan dx_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const ConvDxStridedMap* strided, bool int8_ok,
+                 double* price = nullptr);
 // Tile and split of a dW product [M][N] over K tokens (see kDwTiles): by k_gemm_tn (tiles 64 x 128, 128 and 256), by it with the
 // gather of a convolution (64 x 128, 128), or from the staged operands by k_gemm_nt (64, 128, 192, 256).
 enum DwKind { DW_TOKENS = 0, DW_CONV = 1, DW_STAGED = 2 };
-GemmPlan dw_plan(DwKind kind, int64_t M, int64_t N, int64_t K);
+GemmPlan dw_plan(DwKind kind, int64_t M, int64_t N, int64_t K, double* price = nullptr);   // price: 0 where it has none
+// Plans of both products in one grid of 64-row tiles, if that is priced lower than one after the other (`apart` us)
+bool pair_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const ConvDxStridedMap* strided, DwKind kind, int64_t dw_m,
+               int64_t dw_n, int64_t dw_k, double apart, GemmPlan* dx, GemmPlan* dw);
 
-// C[M][N] = sum_k A[row(m)][k] * B[n][k]; both operands bf16 with K contiguous.
-//   a_rows: optional gather, row(m) = a_rows[m]; lda/ldb in elements (multiples of 8), K multiple of 8.
-//   plan.split_k > 1: K is cut in contiguous slices, slice s goes to out_partial + s*M*N (raw fp32).
-//   epi != nullptr (split_k must be 1): fused dX epilogue instead of the raw store; it writes one
-//   (dS_x, dZ_x) partial pair per block, plan.tiles_m * plan.tiles_n pairs in all.
-int launch_gemm_nt(const bf16_t* A, int64_t lda, const int32_t* a_rows, const bf16_t* B, int64_t ldb,
-                   int64_t M, int64_t N, int64_t K, const GemmPlan& plan, float* out_partial,
-                   const GemmEpilogueDx* epi, hipStream_t stream);
-
-// The same product as launch_gemm_nt (no row gather) by the kernel with a hand-pinned instruction order:
-// plan.tile 192, 128 or 64; A and B 16-byte aligned.
-int launch_gemm_kk(const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M,
-                   int64_t N, int64_t K, const GemmPlan& plan, float* out_partial, const GemmEpilogueDx* epi,
-                   hipStream_t stream);
-
-// Weight-gradient product from token-major operands (no transposed copies):
-//   out[s][m][n] = sum over the K-slice s of A[t][m] * (B[t][n] - round(z_x)),  A bf16 [K][lda], B uint8 [K][ldb].
-// Columns >= a_cols / b_cols and rows >= K are taken as zero.  plan.tile 256, 128 or 64 (64 x 128).
-int launch_gemm_tn(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* B, int64_t ldb, int64_t b_cols,
-                   const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
-                   float* out_partial, hipStream_t stream);
-// dW product of a convolution without a materialised im2col matrix: A = compacted dY columns [N*Ho*Wo][lda] as in
-// launch_gemm_tn, B = the activation codes x_codes NHWC gathered with the tap map inside the tile loads.
-// N = KH*KW*c_in, c_in % 128 == 0 (a 128-wide column tile lies inside one tap), plan.tile 128 or 64 (64 x 128).
+// Geometry of the products of a convolution (operands: gemm_epilogue.hpp).  dW: B = the activation codes NHWC gathered with the
+// tap map inside the tile loads, N = KH*KW*c_in, c_in % 128 == 0 (a 128-wide column tile lies inside one tap).
 struct ConvDwMap { int H, W, Ho, Wo, KW, stride, pad, c_in; };
-int launch_gemm_tn_conv(const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* x_codes, const ConvDwMap& cm,
-                        const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
-                        float* out_partial, hipStream_t stream);
-// dX product of a stride-1 convolution without a materialised im2col matrix: row m of the A operand is the input
-// pixel (n, h, w); its K = (tap, c_out) elements are gathered from the token-major dY [N*Ho*Wo][ldc] inside the
-// tile loads (zeros for taps that fall outside the output image).  ldc % 64 == 0, K = KH*KW*ldc, plan.tile 192, 128 or
-// 64, no split-K.
+// dX of a stride-1 convolution: row m of the A operand is the input pixel (n, h, w); its K = (tap, c_out) elements are gathered
+// from the token-major dY [N*Ho*Wo][ldc] inside the tile loads (zeros outside the output image).  ldc % 64 == 0.
 struct ConvDxMap { int H, W, Ho, Wo, KW, pad; };
-int launch_gemm_nt_conv_dx(const bf16_t* dy_tok, int64_t ldc, const bf16_t* wqT, int64_t ldb, int64_t M, int64_t N,
-                           int64_t K, const ConvDxMap& cm, const GemmPlan& plan, const GemmEpilogueDx& epi,
-                           hipStream_t stream);
 // The same for a stride of 2 to 4: rows sorted by (h mod stride, w mod stride), plan.tile 128 or 64, plan.tiles_m =
 // conv_dx_strided_row_tiles (whole tiles per phase).
 constexpr int kMaxConvStride = 4;
 struct ConvDxStridedMap { int N, H, W, Ho, Wo, KH, KW, stride, pad; };
 int64_t conv_dx_strided_row_tiles(const ConvDxStridedMap& cm, int tile);
-int launch_gemm_conv_dx_strided(const bf16_t* dy_tok, int64_t ldc, const bf16_t* wqT, int64_t ldb, int64_t M, int64_t N,
-                                const ConvDxStridedMap& cm, const GemmPlan& plan, const GemmEpilogueDx& epi,
-                                hipStream_t stream);
 // dX product with the weight operand read from the int8 codes (K-major [C_out][ldb]) and scaled by s_w[c] in
 // registers, fused dX epilogue.  dy: bf16 [M][lda]; N = C_in multiple of 16; tile 256 or 128.  The partial-sum
 // array of the epilogue needs ceil(M / tile) * ceil(N / tile) pairs.
@@ -192,6 +163,7 @@ enum ProfClass {
   PROF_DX = 0, PROF_DW = 1, PROF_FWD = 2, PROF_PREP = 3, PROF_FINISH = 4, PROF_QACT = 5, PROF_QW = 6,
   PROF_IMPORTANCE = 7, PROF_TOPK = 8, PROF_BIAS = 9, PROF_CLASSES = 10
 };
+bool prof_enabled();   // launches are timed by class: the two products of a layer are then launched apart
 bool prof_begin(int which, hipStream_t st, int* slot);
 void prof_end(int which, hipStream_t st, int slot);
 struct ProfScope {

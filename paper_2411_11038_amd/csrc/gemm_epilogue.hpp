@@ -15,7 +15,7 @@ struct GemmArgs {
   const void* A; int64_t lda; const int32_t* a_rows;   // lda / ldb / K in elements (bf16 or int8)
   const void* B; int64_t ldb;
   int M, N, K;
-  int k_per_split;        // multiple of KALIGN
+  int k_per_split;        // multiple of 64
   int tiles_m, tiles_n;
   int group_m;                        // row tiles per group of the tile order (the kernels of gemm_tn.hip)
   float* out;             // raw fp32 [split][M][N]
@@ -44,9 +44,54 @@ struct GemmStridedArgs : GemmArgs {
 template <int CONV> struct ConvArgs { typedef GemmArgs type; };
 template <> struct ConvArgs<2> { typedef GemmStridedArgs type; };
 
-// dX product of a convolution on 128 x 128 tiles by the kernel with the three-stage ring (gemm_kk.hip)
-int launch_gemm_kk_conv(const GemmArgs& a, int tile, bool fast, hipStream_t stream);
+struct GemmTnArgs {
+  const bf16_t* A; int64_t lda;       // [K][lda], lda multiple of 8; columns >= a_cols are not read
+  const uint8_t* B; int64_t ldb;      // [K][ldb], ldb multiple of 16
+  int a_cols, b_cols;                 // readable widths (multiples of 8 / 16): beyond them the zero page is read
+  const float* z_x;
+  int M, N, K;
+  int k_per_split;                    // multiple of 64
+  int tiles_m, tiles_n;
+  int group_m;                        // row tiles per group of the tile order (the kernels of gemm_tn.hip)
+  float* out;                         // raw fp32 [split][M][N]
+  // implicit im2col of the B operand (dW product of a convolution): row t is the output pixel (n, ho, wo), the
+  // N-tile at n0 belongs to tap n0 / cv_cin = (kh, kw), and the operand is the code of input pixel
+  // (n, ho*s + kh - p, wo*s + kw - p), channel n0 % cv_cin + column.  Outside the image the term is dropped by
+  // zeroing the A row of that token in this block (a padded activation is 0 after de-quantisation, which need not
+  // be a representable code).  cv_dn / cv_dh / cv_dw: how (n, ho, wo) moves when t advances by 64.
+  int cv_H, cv_W, cv_Ho, cv_Wo, cv_KW, cv_stride, cv_pad, cv_cin, cv_dn, cv_dh, cv_dw;
+};
+
+// ---- host side: argument blocks of the products (checked, nothing launched) and their launches
+// dX: A, B, epilogue as launch_dx takes them; linear, stride-1 convolution (K = KH*KW*ldc), strided convolution
+int dx_args_linear(GemmArgs* out, const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
+                   const GemmPlan& plan, const GemmEpilogueDx& epi);
+int dx_args_conv(GemmArgs* out, const bf16_t* dy_tok, int64_t ldc, const bf16_t* wqT, int64_t ldb, int64_t M, int64_t N, int64_t K,
+                 const ConvDxMap& cm, const GemmPlan& plan, const GemmEpilogueDx& epi);
+int dx_args_strided(GemmStridedArgs* out, const bf16_t* dy_tok, int64_t ldc, const bf16_t* wqT, int64_t ldb, int64_t M, int64_t N,
+                    const ConvDxStridedMap& cm, const GemmPlan& plan, const GemmEpilogueDx& epi);
+// conv: 0 linear, 1 stride 1, 2 strided (only then the phases of `a` are read)
+int launch_dx(const GemmStridedArgs& a, int conv, const GemmPlan& plan, hipStream_t stream);
+int launch_gemm_kk(const GemmArgs& a, int tile, hipStream_t stream);
+int launch_gemm_kk_conv(const GemmArgs& a, int tile, hipStream_t stream);
 int launch_gemm_kk_conv_strided(const GemmStridedArgs& a, int tile, hipStream_t stream);
+// dW from token-major operands (k_gemm_tn), linear or convolution (cv_cin > 0), or from staged ones (k_gemm_nt)
+int dw_args_tn(GemmTnArgs* out, const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* B, int64_t ldb, int64_t b_cols,
+               const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan, float* out_partial);
+int dw_args_tn_conv(GemmTnArgs* out, const bf16_t* A, int64_t lda, int64_t a_cols, const uint8_t* x_codes, const ConvDwMap& cm,
+                    const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan, float* out_partial);
+int dw_args_staged(GemmArgs* out, const bf16_t* A, int64_t lda, const int32_t* a_rows, const bf16_t* B, int64_t ldb, int64_t M,
+                   int64_t N, int64_t K, const GemmPlan& plan, float* out_partial);
+int launch_gemm_tn(const GemmTnArgs& a, const GemmPlan& plan, hipStream_t stream);
+int launch_gemm_nt_raw(const GemmArgs& a, const GemmPlan& plan, hipStream_t stream);
+// both products of one layer in one grid (pair.hip): tn or staged, the other one null
+int launch_pair(const GemmStridedArgs& dx, int conv, const GemmPlan& plan_dx, const GemmTnArgs* tn, const GemmArgs* staged,
+                const GemmPlan& plan_dw, hipStream_t stream);
+// nothing left to decide in the dX epilogue: bf16 in and out, whole tiles, 32-bit element offsets, aligned pointers
+inline bool dx_epilogue_fast(const GemmArgs& g, int bm, int bn) {
+  return g.epi_vec && g.x_dtype == EFQAT_BF16 && g.dx_dtype == EFQAT_BF16 && (g.M % bm) == 0 && (g.N % bn) == 0 &&
+         (int64_t)g.M * g.N <= (int64_t)INT32_MAX;
+}
 
 // phase and phase-local row tile / column tile of a block: each XCD gets a contiguous range of every phase's tiles
 __device__ __forceinline__ void strided_tile(const GemmStridedArgs& g, int block, ConvPhase* ph, int* tm, int* tn) {
@@ -308,14 +353,15 @@ struct EpiDxAny {
 // ... with the type of x decided at run time, all requests behind the main loop
 template <class C, bool MAP = false>
 __device__ __forceinline__ void epilogue_dx(const GemmArgs& g, floatx16_t (&acc)[C::TM][C::TN], char* smem, int m0,
-                                            int n0, int wm, int wn, int m_end, const int* rowmap = nullptr) {
+                                            int n0, int wm, int wn, int m_end, int part_idx,
+                                            const int* rowmap = nullptr) {
   const bool edge = m0 + C::BM > m_end || n0 + C::BN > g.N;
   auto all = [&](auto e, auto edgec) {
     constexpr bool EDGE = decltype(edgec)::value;
     e.template prefetch_tile<EDGE>(g, m0, n0, wm, wn, m_end, rowmap);
     float s1 = 0.0f, sd = 0.0f;
     e.template sum_tile<EDGE>(g, acc, smem, s1, sd);
-    e.finish(g, smem, s1, sd, blockIdx.x);
+    e.finish(g, smem, s1, sd, part_idx);
   };
   using Yes = std::integral_constant<bool, true>;
   using No = std::integral_constant<bool, false>;
@@ -445,10 +491,10 @@ struct EpiDxFast {
 
 template <class C>
 __device__ __forceinline__ void epilogue_dx_fast(const GemmArgs& g, floatx16_t (&acc)[C::TM][C::TN], char* smem,
-                                                 int m0, int n0, int wm, int wn) {
+                                                 int m0, int n0, int wm, int wn, int part_idx) {
   EpiDxFast<C> e;
   e.prefetch(g, m0, n0, wm, wn);
-  e.run(g, acc, smem, blockIdx.x);
+  e.run(g, acc, smem, part_idx);
 }
 
 }  // namespace efqat
