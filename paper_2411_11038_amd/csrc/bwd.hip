@@ -636,7 +636,7 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
   // Products on 256 x 256 tiles with a bf16 token-major dY read the weight operand straight from the int8 codes: same speed
   // as the bf16 kernel on these shapes, and no transposed bf16 copy of W_q.
   if (p.cmx) {
-    p.plan_dx = gemm_plan(p.Mx, c_in, p.Kx, false, false);
+    p.plan_dx = wide ? gemm_plan(p.Mx, c_in, p.Kx, false, false) : dx_cm_plan(p.Mx, c_in, p.Kx, &price_dx);
     p.dx8 = true; p.dx8_tile = p.plan_dx.tile;
   } else if (dxk == EFQAT_DX_KERNEL_BF16_PINNED) {
     if (!p.cdx) p.plan_dx = GemmPlan{192, 1, (int)ceil_div(p.Mx, 192), (int)ceil_div(c_in, 192), true};
@@ -645,10 +645,14 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
     p.plan_dx.tiles_m = (int)ceil_div(p.Mx, p.dx8_tile); p.plan_dx.tiles_n = (int)ceil_div(c_in, p.dx8_tile);
   }
   if (k == 0) p.plan_dw = GemmPlan{128, 1, 0, 0, false};
-  else if (wide || p.rdw) p.plan_dw = gemm_plan(k, p.Nw, p.ldt, true, !(p.tn || p.rdw), !p.cdw);
+  else if (wide) p.plan_dw = gemm_plan(k, p.Nw, p.ldt, true, !(p.tn || p.rdw), !p.cdw);
   else {
-    const DwKind kind = p.cdw ? DW_CONV : p.tn ? DW_TOKENS : DW_STAGED;
+    const DwKind kind = p.rdw ? DW_ROWS : p.cdw ? DW_CONV : p.tn ? DW_TOKENS : DW_STAGED;
     p.plan_dw = dw_plan(kind, k, p.Nw, p.ldt, &price_dw);
+    if (p.cmx && p.rdw && price_dw > 0.0) {
+      p.pair = pair_cm_plan(p.Mx, c_in, p.Kx, k, p.Nw, p.ldt, price_dx + price_dw, &p.plan_dx, &p.plan_dw);
+      p.dx8_tile = p.plan_dx.tile;
+    }
     if (price_dw > 0.0 && !p.dx8 && dxk == EFQAT_DX_KERNEL_AUTO && (!im2col || p.cdx)) {
       if (int8_ok) price_dx -= 3.0 * (double)c_in * (double)p.Kx / 4e6;   // W_q^T in bf16 (dx_plan): the pair needs it as well
       p.pair = pair_plan(p.Mx, c_in, p.Kx, dy_dtype == EFQAT_F32, p.cdx, p.cdxs ? &sm : nullptr, kind, k, p.Nw, p.ldt,
@@ -817,8 +821,11 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   prep.close();
   GemmEpilogueDx epi{io.x_codes, io.x_clip, io.x, io.x_dtype, io.s_x, io.z_x, io.dx, io.dx_dtype, part_dx};
   GemmStridedArgs dxa{};
+  GemmDx8Args cma{}, rwa{};
   const int conv = p.cdxs ? 2 : p.cdx ? 1 : 0;
-  if (p.cdxs) {
+  if (p.cmx) {
+    rc = dx_args_cm(&cma, (const bf16_t*)io.dy, T_out, io.w_codes, c_in, io.s_w, p.Mx, c_in, c_out, p.plan_dx, epi);
+  } else if (p.cdxs) {
     rc = dx_args_strided(&dxa, dy_tok, p.ldc, wqT, p.Kx, p.Mx, c_in, strided_map(*cg), p.plan_dx, epi);
   } else if (p.cdx) {
     const ConvDxMap cm{cg->H, cg->W, cg->Ho, cg->Wo, cg->KW, cg->pad};
@@ -842,7 +849,9 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
     } else {
       rc = dw_args_tn(&tna, At, ldat, acols, io.x_codes, c_in, c_in, io.z_x, io.k, p.Nw, T_out, p.plan_dw, part_dw);
     }
-  } else if (io.k > 0 && !p.rdw) {
+  } else if (p.rdw) {                                  // channel-major dY: the selected rows are gathered by the tile loads
+    rc = dw_args_rows(&rwa, (const bf16_t*)io.dy, T_out, io.idx, io.x_codes, c_in, io.z_x, io.k, p.Nw, T_out, p.plan_dw, part_dw);
+  } else if (io.k > 0) {
     // staged operands; channel-major bf16 dY that is not staged: the gather is fused into the tile loads
     const bf16_t* Aw = p.need_sel ? sel : (const bf16_t*)io.dy;
     const int64_t ldaw = p.need_sel ? p.ldt : T_out;
@@ -851,10 +860,12 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   if (rc) return rc;
 
   // ---- the products
-  if (pair) {
+  if (pair && p.cmx) {
+    rc = launch_pair_cm(cma, rwa, p.plan_dw.split_k, st);
+  } else if (pair) {
     rc = launch_pair(dxa, conv, p.plan_dx, p.tn ? &tna : nullptr, p.tn ? nullptr : &nta, p.plan_dw, st);
   } else if (p.cmx) {
-    rc = launch_gemm_dx8_cm((const bf16_t*)io.dy, T_out, io.w_codes, c_in, io.s_w, p.Mx, c_in, c_out, p.dx8_tile, epi, st);
+    rc = launch_gemm_dx8_cm(cma, p.dx8_tile, st);
   } else if (p.dx8) {
     rc = launch_gemm_dx8(dy_tok, c_out, io.w_codes, c_in, io.s_w, p.Mx, c_in, c_out, p.dx8_tile, epi, st);
   } else {
@@ -880,9 +891,7 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   }
   if (pair) rc = EFQAT_OK;
   else if (p.tn) rc = launch_gemm_tn(tna, p.plan_dw, st2);
-  else if (p.rdw)                                      // channel-major dY: the selected rows are gathered by the tile loads
-    rc = launch_gemm_dw_rows((const bf16_t*)io.dy, T_out, io.idx, io.x_codes, c_in, io.z_x, io.k, p.Nw, T_out, p.plan_dw,
-                             part_dw, st2);
+  else if (p.rdw) rc = launch_gemm_dw_rows(rwa, p.plan_dw, st2);
   else rc = launch_gemm_nt_raw(nta, p.plan_dw, st);
   if (rc) return rc;
   if (use_side && (hipEventRecord(ev.join, st2) != hipSuccess || hipStreamWaitEvent(st, ev.join, 0) != hipSuccess))

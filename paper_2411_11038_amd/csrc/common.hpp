@@ -123,8 +123,11 @@ GemmPlan dx_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const Con
                  double* price = nullptr);
 // Tile and split of a dW product [M][N] over K tokens (see kDwTiles): by k_gemm_tn (tiles 64 x 128, 128 and 256), by it with the
 // gather of a convolution (64 x 128, 128), or from the staged operands by k_gemm_nt (64, 128, 192, 256).
-enum DwKind { DW_TOKENS = 0, DW_CONV = 1, DW_STAGED = 2 };
+enum DwKind { DW_TOKENS = 0, DW_CONV = 1, DW_STAGED = 2, DW_ROWS = 3 };   // DW_ROWS: rows of a channel-major dY, k_gemm_dx8
 GemmPlan dw_plan(DwKind kind, int64_t M, int64_t N, int64_t K, double* price = nullptr);   // price: 0 where it has none
+// dX of a channel-major dY by k_gemm_dx8 (tiles 64 x 128, 128, 256), and it with its dW product in one grid
+GemmPlan dx_cm_plan(int64_t M, int64_t N, int64_t K, double* price);
+bool pair_cm_plan(int64_t M, int64_t N, int64_t K, int64_t dw_m, int64_t dw_n, int64_t dw_k, double apart, GemmPlan* dx, GemmPlan* dw);
 // Plans of both products in one grid of 64-row tiles, if that is priced lower than one after the other (`apart` us)
 bool pair_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const ConvDxStridedMap* strided, DwKind kind, int64_t dw_m,
                int64_t dw_n, int64_t dw_k, double apart, GemmPlan* dx, GemmPlan* dw);
@@ -146,17 +149,6 @@ int64_t conv_dx_strided_row_tiles(const ConvDxStridedMap& cm, int tile);
 int launch_gemm_dx8(const bf16_t* dy, int64_t lda, const int8_t* w_codes, int64_t ldb, const float* s_w,
                     int64_t M, int64_t N, int64_t K, int tile, const GemmEpilogueDx& epi,
                     hipStream_t stream);
-// The same product for a channel-major dY [C_out][lda] (lda >= M = T, T % 8 == 0): both operands have the contraction
-// index C_out as their row and are transposed by the LDS reads; no copy of dY or W_q is made.
-int launch_gemm_dx8_cm(const bf16_t* dy_cm, int64_t lda, const int8_t* w_codes, int64_t ldb, const float* s_w,
-                       int64_t M, int64_t N, int64_t K, int tile, const GemmEpilogueDx& epi,
-                       hipStream_t stream);
-// dW product for a channel-major bf16 dY [C_out][lda] (lda >= K = T, K % 8 == 0): row m of the A operand is row
-// idx[m] of dY, read through the index list in the tile loads; B = the uint8 codes [K][ldb] as they lie.
-//   out[s][m][n] = sum over the K-slice s of dY[idx[m]][t] * (codes[t][n] - round(z_x)),  plan.tile 256 or 128.
-int launch_gemm_dw_rows(const bf16_t* dy_cm, int64_t lda, const int32_t* idx, const uint8_t* x_codes, int64_t ldb,
-                        const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan,
-                        float* out_partial, hipStream_t stream);
 // Event timing of kernel classes (benchmarks only, off by default): a ProfScope brackets the launches made during its
 // lifetime with two HIP events on the stream they go to.  Classes = the `which` argument of efqat_profile_read.
 enum ProfClass {

@@ -127,9 +127,10 @@ GemmPlan dx_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const Con
 //   6848 x 1776, 1500    63 (3) / 54 (3)                          many tiles: fewer LDS bytes per product
 // The 256 x 256 and 192 x 192 tiles stay where gemm_plan prices them lowest: large products.
 struct DwTile { int bm, bn, bpc; double lone[2], full[2]; };
-static const DwTile kDwTiles[3][2] = {{{64, 128, 4, {0.515, 4.4}, {1.10, 6.2}}, {128, 128, 3, {0.575, 5.8}, {1.305, 8.3}}},
+static const DwTile kDwTiles[4][2] = {{{64, 128, 4, {0.515, 4.4}, {1.10, 6.2}}, {128, 128, 3, {0.575, 5.8}, {1.305, 8.3}}},
                                       {{64, 128, 4, {0.785, 5.0}, {1.51, 7.6}}, {128, 128, 3, {0.955, 6.6}, {1.68, 11.2}}},
-                                      {{64, 64, 4, {0.453, 3.0}, {0.95, 3.5}}, {128, 128, 2, {0.71, 4.5}, {0.88, 7.0}}}};
+                                      {{64, 64, 4, {0.453, 3.0}, {0.95, 3.5}}, {128, 128, 2, {0.71, 4.5}, {0.88, 7.0}}},
+                                      {{64, 128, 4, {0.485, 3.4}, {0.89, 7.7}}, {128, 128, 3, {0.547, 4.6}, {0.917, 9.7}}}};
 // the second pass over S slices of M x N values
 static double finish_price(int64_t M, int64_t N, int64_t S) {
   return 3.7 + 0.07 * (double)S + 0.119e-6 * (double)M * (double)N * (double)(4 * S + 9);
@@ -158,37 +159,68 @@ GemmPlan dw_plan(DwKind kind, int64_t M, int64_t N, int64_t K, double* price_out
   return best;
 }
 
+// dX of a channel-major dY by k_gemm_dx8, 64 x 128, 128 x 128 and 256 x 256; fitted to 90 layers (0.2 % from the fastest in the
+// mean).  T x C_out -> C_in in us on 64 / 128 / 256: 14248 x 1122 -> 176 22.4 / 23.2 / 45; 9696 x 27 -> 5696 70 / 74 / 92;
+// 8192 x 4096 -> 11008 on 256 643.
+static const DxTile kDxCmTiles[] = {{64, false, 3, {0.45, 6.2}, {0.935, 7.4}, {0.0, 0.0}, {0.0, 0.0}},
+                                    {128, false, 2, {0.55, 8.4}, {0.95, 9.1}, {0.0, 0.0}, {0.0, 0.0}},
+                                    {256, false, 1, {1.0, 21.6}, {1.34, 24.9}, {0.0, 0.0}, {0.0, 0.0}}};
+GemmPlan dx_cm_plan(int64_t M, int64_t N, int64_t K, double* price) {
+  GemmPlan best{};
+  const double stages = (double)ceil_div(K, KALIGN);
+  for (const DxTile& c : kDxCmTiles) {
+    const int64_t tm = ceil_div(M, c.t), tn = ceil_div(N, c.t == 64 ? 128 : c.t), tiles = tm * tn, round = 256 * c.bpc;
+    if (tiles >= (1 << 24) && c.t < 256) continue;      // a grid dimension holds less than 2^32 work items
+    const double lone = c.lone[0] * stages + c.lone[1], full = c.full[0] * stages + c.full[1];
+    double t = (double)(tiles / round) * full;
+    if (const int64_t rest = tiles % round)
+      t += lone + (full - lone) * (c.bpc > 1 ? (double)(ceil_div(rest, 256) - 1) / (c.bpc - 1) : (double)rest / 256.0);
+    if (best.tile == 0 || t < *price) { *price = t; best = GemmPlan{c.t, 1, (int)tm, (int)tn, false}; }
+  }
+  return best;
+}
+
 // Both products in one grid of 64-row tiles.  Neither fills the chip by itself where this is taken, and the shorter one, its
 // launch and its drain disappear beside the other.  By the tables above, the blocks of both share the places on the CUs;
-// more blocks than places are priced by the work in them, and half of the longest block at the end.
-bool pair_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const ConvDxStridedMap* strided, DwKind kind, int64_t dw_m,
-               int64_t dw_n, int64_t dw_k, double apart, GemmPlan* dx, GemmPlan* dw) {
+// more blocks than places are priced by the work in them, and a quarter of the longest block at the end.
+static bool pair_search(double stages, int64_t tm, int64_t tn, const DxTile& c, bool f32, double places, DwKind kind, int64_t dw_m,
+                        int64_t dw_n, int64_t dw_k, double* apart, GemmPlan* dx, GemmPlan* dw) {
   const DwTile& w = kDwTiles[kind][0];
   const int64_t wm = ceil_div(dw_m, w.bm), wn = ceil_div(dw_n, w.bn), wstages = ceil_div(dw_k, KALIGN);
+  bool found = false;
+  if (tm * tn + wm * wn * 64 >= (1 << 24)) return false;
+  const double xl = c.lone[0] * stages + c.lone[1] + (f32 ? c.f32[0] : 0.0), xf = c.full[0] * stages + c.full[1] + (f32 ? c.f32[1] : 0.0);
+  for (int64_t s = 1; s <= 64 && (s == 1 || 2 * s <= wstages); ++s) {
+    const int64_t per = ceil_div(wstages, s);
+    if (ceil_div(wstages, per) != s) continue;
+    const double wl = w.lone[0] * (double)per + w.lone[1], wf = w.full[0] * (double)per + w.full[1];
+    const double fx = (double)(tm * tn) / places, fw = (double)(wm * wn * s) / places, f = fx + fw;
+    const double load = f < 1.0 ? f : 1.0;
+    const double bx = xl + (xf - xl) * load, bw = wl + (wf - wl) * load;
+    const double t = (f <= 1.0 ? std::max(bx, bw) : fx * xf + fw * wf + 0.25 * std::max(xf, wf)) + finish_price(dw_m, dw_n, s);
+    if (t < *apart) {
+      *apart = t; found = true;
+      *dx = GemmPlan{64, 1, (int)tm, (int)tn, c.ring};
+      *dw = GemmPlan{64, (int)s, (int)wm, (int)wn, false};
+    }
+  }
+  return found;
+}
+bool pair_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const ConvDxStridedMap* strided, DwKind kind, int64_t dw_m,
+               int64_t dw_n, int64_t dw_k, double apart, GemmPlan* dx, GemmPlan* dw) {
   bool found = false;
   for (int ring = 0; ring < 2; ++ring) {
     const DxTile& c = conv ? kDxConvTiles[1 - ring] : kDxTiles[1 - ring];
     int64_t tm = 0;
-    const double stages = dx_stages(M, K, c.t, strided, &tm), places = 256.0 * (ring ? 3 : 4);
-    const int64_t tn = ceil_div(N, c.t);
-    if (tm * tn + wm * wn * 64 >= (1 << 24)) continue;
-    const double xl = c.lone[0] * stages + c.lone[1] + (f32 ? c.f32[0] : 0.0), xf = c.full[0] * stages + c.full[1] + (f32 ? c.f32[1] : 0.0);
-    for (int64_t s = 1; s <= 64 && (s == 1 || 2 * s <= wstages); ++s) {
-      const int64_t per = ceil_div(wstages, s);
-      if (ceil_div(wstages, per) != s) continue;
-      const double wl = w.lone[0] * (double)per + w.lone[1], wf = w.full[0] * (double)per + w.full[1];
-      const double fx = (double)(tm * tn) / places, fw = (double)(wm * wn * s) / places, f = fx + fw;
-      const double load = f < 1.0 ? f : 1.0;
-      const double bx = xl + (xf - xl) * load, bw = wl + (wf - wl) * load;
-      const double t = (f <= 1.0 ? std::max(bx, bw) : fx * xf + fw * wf + 0.5 * std::max(xf, wf)) + finish_price(dw_m, dw_n, s);
-      if (t < apart) {
-        apart = t; found = true;
-        *dx = GemmPlan{64, 1, (int)tm, (int)tn, ring == 1};
-        *dw = GemmPlan{64, (int)s, (int)wm, (int)wn, false};
-      }
-    }
+    const double stages = dx_stages(M, K, c.t, strided, &tm);
+    found |= pair_search(stages, tm, ceil_div(N, c.t), c, f32, 256.0 * (ring ? 3 : 4), kind, dw_m, dw_n, dw_k, &apart, dx, dw);
   }
   return found;
+}
+// channel-major dY: only beside a dX product of few rounds, larger tiles move fewer LDS bytes
+bool pair_cm_plan(int64_t M, int64_t N, int64_t K, int64_t dw_m, int64_t dw_n, int64_t dw_k, double apart, GemmPlan* dx, GemmPlan* dw) {
+  return pair_search((double)ceil_div(K, KALIGN), ceil_div(M, 64), ceil_div(N, 128), kDxCmTiles[0], false, 256.0 * 3, DW_ROWS, dw_m,
+                     dw_n, dw_k, &apart, dx, dw);
 }
 
 bool gemm_epilogue_vec_ok(const GemmEpilogueDx& e, int64_t N) {

@@ -62,6 +62,13 @@ struct GemmTnArgs {
   int cv_H, cv_W, cv_Ho, cv_Wo, cv_KW, cv_stride, cv_pad, cv_cin, cv_dn, cv_dh, cv_dw;
 };
 
+struct GemmDx8Args {
+  int a_cols;              // ATN: readable width of A (multiple of 8)
+  GemmArgs g;              // dX: A = dY, B = weight codes, M = T, N = C_in, K = C_out, fused dX epilogue fields
+                           // dW: A = dY channel-major with a_rows = idx, B = activation codes, M = k, N = C_in, K = T
+  int b_cols;              // readable width of B (multiple of 16)
+};
+
 // ---- host side: argument blocks of the products (checked, nothing launched) and their launches
 // dX: A, B, epilogue as launch_dx takes them; linear, stride-1 convolution (K = KH*KW*ldc), strided convolution
 int dx_args_linear(GemmArgs* out, const bf16_t* A, int64_t lda, const bf16_t* B, int64_t ldb, int64_t M, int64_t N, int64_t K,
@@ -84,6 +91,16 @@ int dw_args_staged(GemmArgs* out, const bf16_t* A, int64_t lda, const int32_t* a
                    int64_t N, int64_t K, const GemmPlan& plan, float* out_partial);
 int launch_gemm_tn(const GemmTnArgs& a, const GemmPlan& plan, hipStream_t stream);
 int launch_gemm_nt_raw(const GemmArgs& a, const GemmPlan& plan, hipStream_t stream);
+// channel-major dY: dX by k_gemm_dx8 from dY [C_out][lda] (lda >= M = T, T % 8 == 0) and the int8 weight codes, both with the
+// contraction index as their row; dW from the rows idx of dY [C_out][lda] (lda >= K = T, K % 8 == 0) and the uint8 codes:
+//   out[s][m][n] = sum over the K-slice s of dY[idx[m]][t] * (codes[t][n] - round(z_x)).  Tiles 256, 128, 64 (64 x 128).
+int dx_args_cm(GemmDx8Args* out, const bf16_t* dy_cm, int64_t lda, const int8_t* w_codes, int64_t ldb, const float* s_w, int64_t M,
+               int64_t N, int64_t K, const GemmPlan& plan, const GemmEpilogueDx& epi);
+int dw_args_rows(GemmDx8Args* out, const bf16_t* dy_cm, int64_t lda, const int32_t* idx, const uint8_t* x_codes, int64_t ldb,
+                 const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan, float* out_partial);
+int launch_gemm_dx8_cm(const GemmDx8Args& a, int tile, hipStream_t stream);
+int launch_gemm_dw_rows(const GemmDx8Args& a, const GemmPlan& plan, hipStream_t stream);
+int launch_pair_cm(const GemmDx8Args& dx, const GemmDx8Args& dw, int split_k, hipStream_t stream);
 // both products of one layer in one grid (pair.hip): tn or staged, the other one null
 int launch_pair(const GemmStridedArgs& dx, int conv, const GemmPlan& plan_dx, const GemmTnArgs* tn, const GemmArgs* staged,
                 const GemmPlan& plan_dw, hipStream_t stream);

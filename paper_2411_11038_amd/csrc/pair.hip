@@ -3,7 +3,9 @@
 // one behind the other costs the sum of two latencies: launch, first loads, K loop, drain.  pair_plan decides by the measured
 // costs of both; backward calls in one grid / one after the other, us: 192 x 640 -> 128, k = 6: 12.2 / 16.4; 64 x 7 x 7, 128 -> 256,
 // 1 x 1: 13.6 / 18.5; 792 x 256 -> 1464, k = 366: 21.7 / 27.4; 16 x 24 x 24, 120 -> 320, 3 x 3: 56.6 / 71.0; 100 drawn layers and
-// convolutions 1.125 x, none slower by 2 %.  64-row tiles only: four (two stages) or three (ring) blocks of either share a CU.
+// convolutions 1.125 x, none slower by 2 %.  64-row tiles only: four (two stages) or three (ring) blocks of either
+// share a CU.
+#include "gemm_dx8.hpp"
 #include "gemm_kk.hpp"
 #include "gemm_nt.hpp"
 #include "gemm_tn.hpp"
@@ -60,6 +62,28 @@ static int launch_conv(const GemmStridedArgs& dx, bool ring, const GemmTnArgs* t
   if (!ring) return launch_cfg<false, EPI_DX, CONV, STAGED>(dx, tn, staged, split_k, st);
   if (dx.x_dtype == EFQAT_F32) return launch_cfg<true, EPI_DXS, CONV, STAGED>(dx, tn, staged, split_k, st);
   return launch_cfg<true, EPI_DX, CONV, STAGED>(dx, tn, staged, split_k, st);
+}
+
+// The same for a channel-major dY, both products by k_gemm_dx8's loop on tiles of 64 x 128: 160 drawn bf16 layers 1.38 x as fast
+// as on 128 x 128 tiles in two launches (12288 x 768 -> 768, k = 192, training step 68.5 -> 58.2 us).
+struct PairCmArgs { GemmDx8Args dx, dw; int n_dx; };
+__global__ __launch_bounds__(256, 3) void k_pair_cm(const PairCmArgs p) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int b = blockIdx.x;
+  if (b < p.n_dx) gemm_dx8_block<64, 128, false, true>(p.dx, smem, b, p.n_dx);
+  else gemm_dx8_block<64, 128, true>(p.dw, smem, b - p.n_dx, gridDim.x - p.n_dx);
+}
+
+int launch_pair_cm(const GemmDx8Args& dx, const GemmDx8Args& dw, int split_k, hipStream_t st) {
+  constexpr int kLds = std::max(Dx8Cfg<64, 128, true>::lds_bytes<true>(), Dx8Cfg<64, 128>::lds_bytes<false>());
+  // set once per process (initialisation of a function-local static is thread-safe)
+  static const hipError_t attr = hipFuncSetAttribute((const void*)k_pair_cm, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  if (attr != hipSuccess) return EFQAT_ERR_HIP;
+  PairCmArgs p{dx, dw, dx.g.tiles_m * dx.g.tiles_n};
+  const dim3 grid((unsigned)(p.n_dx + dw.g.tiles_m * dw.g.tiles_n * split_k));
+  hipLaunchKernelGGL(k_pair_cm, grid, dim3(256), kLds, st, p);
+  EFQAT_LAUNCH_CHECK();
+  return EFQAT_OK;
 }
 
 int launch_pair(const GemmStridedArgs& dx, int conv, const GemmPlan& plan_dx, const GemmTnArgs* tn, const GemmArgs* staged,

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 KEYS = ("dx", "dw", "ds_w", "ds_x", "dz_x")
 # T, c_in, c_out, k
 LINEAR = [(64, 64, 64, 16), (65, 80, 72, 72), (1, 16, 8, 1), (300, 72, 520, 1), (129, 777, 65, 40), (96, 31, 4100, 30), (2048, 512, 512, 100),
-          (4000, 320, 136, 130), (16000, 48, 40, 7)]
+          (4000, 320, 136, 130), (16000, 48, 40, 7), (72, 80, 33, 5), (8, 16, 8, 8), (1000, 144, 200, 200)]
 # N, H, c_in, c_out, kernel, stride, k
 CONV = [(2, 9, 128, 64, 3, 1, 10), (2, 9, 72, 64, 3, 1, 64), (3, 8, 128, 40, 3, 2, 20), (2, 9, 20, 128, 5, 2, 3), (1, 7, 256, 64, 1, 2, 64),
         (40, 14, 128, 128, 3, 1, 32), (33, 15, 64, 64, 3, 2, 16)]
