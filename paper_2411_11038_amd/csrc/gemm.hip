@@ -6,8 +6,9 @@
 namespace efqat {
 
 // ---------------------------------------------------------------------------------------------- host
-// Tile / split-K choice: a small cost model in CU clock cycles, evaluated on the host and calibrated on
-// measured runs of this kernel (rates in flop per clock per block):
+// Tile / split-K choice of the large products (dw_plan asks it first and keeps its 256 and 192 row tiles) and of the plans
+// that fit a workspace without the smaller tiles' slices: a cost model in CU clock cycles, evaluated on the host and
+// calibrated on measured runs (rates in flop per clock per block):
 //   - a T x T block runs its K loop at `rate`: 256 -> 2500, 192 -> 2100, 128 -> 1000 with two blocks resident
 //     per CU.  The big tiles are bounded by what one CU's vector L1 pulls from L2 (about 19 B/clk) times their
 //     flop per byte, the small one additionally by its doubled L2 traffic;
@@ -48,12 +49,11 @@ GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool allow_split, bool allow
 
 // Kernel and tile of a dX product.  Microseconds per K stage of 64 and per block (launch, first loads, epilogue) with one
 // block on a CU (lone; of a tile that fits once: on few of the CUs, where clock and memory are its own) and with all `bpc`
-// that fit by LDS and registers (full), between the two by the number resident; what
-// x and dX in fp32 add and what the straight-line epilogue of whole bf16 tiles saves.  A product is its whole rounds of
-// 256 * bpc blocks plus what is left.  Fitted to measured launches of 300 linear layers (each dimension 64 .. 16384) and 28
-// convolutions; the choice is 0.9 % from the fastest of the six in the mean, the linear layers 1.33 x and the convolutions
-// 1.6 x as fast as with tiles of 128 and more only.  T x C_out -> C_in in us by k_gemm_kk 64 / nt 64 / kk 128 / nt 128 / kk 192 /
-// dx8 256, bf16:
+// that fit by LDS and registers (full), between the two by the number resident; what x and dX in fp32 add and what the
+// straight-line epilogue of whole bf16 tiles saves.  A product is its whole rounds of 256 * bpc blocks plus what is left.
+// Fitted to measured launches of 300 linear layers (each dimension 64 .. 16384) and 28 convolutions; the choice is 0.9 %
+// from the fastest of the six in the mean, the linear layers 1.33 x and the convolutions 1.6 x as fast as with tiles of
+// 128 and more only.  T x C_out -> C_in in us by k_gemm_kk 64 / nt 64 / kk 128 / nt 128 / kk 192 / dx8 256, bf16:
 //   256 x 256 -> 256         6.6 / 5.8 / 8.4 /  - /  18 / -      few tiles: the smallest, with the shortest epilogue
 //   64 x 4096 -> 4096         21 /  33 /  30 /  46 /  51 /  -    ... and the ring, where K is long
 //   2048 x 768 -> 3072        28 /  28 /  26 /  26 /  30 /  30   (C_out 320)
@@ -217,7 +217,8 @@ bool pair_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const ConvD
   }
   return found;
 }
-// channel-major dY: only beside a dX product of few rounds, larger tiles move fewer LDS bytes
+// The same for a channel-major bf16 dY (k_pair_cm): dX on 64 x 128 tiles of k_gemm_dx8, dW on those of its DW form, three
+// blocks a CU.
 bool pair_cm_plan(int64_t M, int64_t N, int64_t K, int64_t dw_m, int64_t dw_n, int64_t dw_k, double apart, GemmPlan* dx, GemmPlan* dw) {
   return pair_search((double)ceil_div(K, KALIGN), ceil_div(M, 64), ceil_div(N, 128), kDxCmTiles[0], false, 256.0 * 3, DW_ROWS, dw_m,
                      dw_n, dw_k, &apart, dx, dw);

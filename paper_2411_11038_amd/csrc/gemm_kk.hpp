@@ -10,10 +10,11 @@
 // cover a stall, so the order of these three instruction streams decides the speed; left to the compiler's
 // scheduler the reads and copies clump and the matrix cores idle for more than half of the loop.
 //
-// 256 threads; 192 x 192 tile, wavefront grid 2 x 2 (96 x 96 per wavefront, 9 accumulators);
-// v_mfma_f32_32x32x16_bf16; K-stage of 64; a ring of three LDS stages (144 KB): the copies of stage kt + 2 are issued
+// 256 threads; square tiles of 192 (96 x 96 per wavefront, 9 accumulators), 128 or 64, wavefront grid 2 x 2;
+// v_mfma_f32_32x32x16_bf16; K-stage of 64; a ring of three LDS stages (144, 96 or 48 KB; one block a CU, of the
+// 64 x 64 tile three, which serves products of too few larger tiles): the copies of stage kt + 2 are issued
 // while stage kt is multiplied and are only waited for at the end of stage kt + 1, so a copy may take more than a
-// whole stage (about 1200 cycles of MFMA work) before it stalls anything - with two stages the memory latency under
+// whole stage (about 1200 cycles of MFMA work at 192 x 192) before it stalls anything - with two stages the memory latency under
 // load did not fit.  Rows past M / N re-read the last valid row (their outputs are discarded), chunks past K come
 // from a zero page, so no copy needs a predicate.
 #pragma once

@@ -186,7 +186,7 @@ __device__ __forceinline__ void gemm_tn_block(const GemmTnArgs& g, char* smem, i
   //   A, transpose read r in {0,1}: lane addresses 8 bytes = 4 m at token 16*sub + 8h + 4r + s/4,
   //      m = 32 i + mb + 4 (s % 4);  result: lane owns m = 32 i + mb + s, tokens 8h + 4r + 0..3.
   //      Its 16-byte chunk is 4 i + c0 (c0 < 4), which the swizzle moves to 4 (i ^ (s/4)) + c0: four base
-  //      addresses per LDS buffer (one per i % 4) and compile-time offsets for i / 4, r and the sub-step.
+  //      addresses per LDS buffer (one per i % 4; a 64-row tile has two) and compile-time offsets for i / 4, r and the sub-step.
   //   B: lane addresses 8 bytes = 8 n at token 16*sub + 8h + s/2, n = wave_n + 32 j + mb + 8 (s % 2);
   //      result: lane owns n = ... + mb + s, tokens 8h + 0..7.
   static_assert(C::WGM == 1, "A fragment addressing");
