@@ -674,18 +674,6 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
   return p;
 }
 
-// The plan of a call, or the wide one where that needs less workspace than the call brings, or 16-byte aligned weight codes
-// that it does not.  A workspace of either size is taken, and the query returns the larger.  c_in beyond what the bf16
-// W_q^T may have (check_plan) leaves the choice to gemm_plan's rule as well.
-template <class Plan>
-static BwdPlan choose_plan(const Plan& plan, int64_t c_in, const int8_t* w_codes, size_t ws_bytes) {
-  const BwdPlan p = plan(c_in > kMaxStagedColumns);
-  if (ws_bytes < p.total || (p.dx8 && ((uintptr_t)w_codes % 16) != 0)) {
-    const BwdPlan w = plan(true);
-    if (ws_bytes >= w.total) return w;
-  }
-  return p;
-}
 template <class Plan>
 static size_t query_plan(const Plan& plan) { return std::max(plan(false).total, plan(true).total); }
 
@@ -698,6 +686,22 @@ struct BwdIo {
   const void* w_operand = nullptr;   // optional: the bf16 W_q^T matrix made beforehand
   hipStream_t side = nullptr;        // optional: second stream for the weight-gradient branch
 };
+
+// The plan of a call, or the wide one where that needs less workspace than the call brings, or 16-byte aligned weight codes
+// that it does not.  A workspace of either size is taken, and the query returns the larger.  c_in beyond what the bf16
+// W_q^T may have (check_plan) leaves the choice to gemm_plan's rule as well.  No operand is made beforehand for a layer whose
+// first plan reads the weight codes themselves (efqat_linear_bwd_weight_operand): what the call brings is ignored, and the
+// wide plan makes its own in the workspace.
+template <class Plan>
+static BwdPlan choose_plan(const Plan& plan, int64_t c_in, BwdIo& io, size_t ws_bytes) {
+  const BwdPlan p = plan(c_in > kMaxStagedColumns);
+  if (p.dx8) io.w_operand = nullptr;
+  if (ws_bytes < p.total || (p.dx8 && ((uintptr_t)io.w_codes % 16) != 0)) {
+    const BwdPlan w = plan(true);
+    if (ws_bytes >= w.total) return w;
+  }
+  return p;
+}
 
 // Fork / join events of the optional second stream: one pair per host thread and device, made at first use and kept
 // (recording an event again while an earlier wait on it is still queued is well defined: a wait refers to the
@@ -978,7 +982,7 @@ static int linear_bwd_entry(BwdIo& io, int64_t T, int64_t c_in, int64_t c_out, c
   if (io.w_operand && ((uintptr_t)io.w_operand % 256) != 0) return EFQAT_ERR_ALIGNMENT;
   const BwdPlan p = choose_plan([&](bool wide) {
     return make_plan(T, T, c_in, c_out, 1, io.k, io.dy_dtype, io.dy_layout, false, dxk, nullptr, wide);
-  }, c_in, io.w_codes, ws_bytes);
+  }, c_in, io, ws_bytes);
   if (ws_bytes < p.total) return EFQAT_ERR_WORKSPACE;
   rc = check_plan(p, io, T, c_in, c_out);
   if (rc) return rc;
@@ -1110,7 +1114,7 @@ static int conv_bwd_entry(BwdIo& io, int64_t N, int64_t H, int64_t W, int64_t c_
   if (rc) return rc;
   const BwdPlan p = choose_plan([&](bool wide) {
     return conv_plan(g, io.k, io.dy_dtype, io.dy_layout, dxk, wide);
-  }, c_in, io.w_codes, ws_bytes);
+  }, c_in, io, ws_bytes);
   if (ws_bytes < p.total) return EFQAT_ERR_WORKSPACE;
   const int64_t T_in = (int64_t)N * H * W, T_out = (int64_t)N * g.Ho * g.Wo;
   rc = check_plan(p, io, T_out, c_in, c_out);

@@ -8,7 +8,7 @@ import paper_2411_11038_amd as ef
 pytestmark = pytest.mark.gpu
 
 
-def _linear(T, c_in, c_out, dt, w_off=0, ws=None, kernel=0):
+def _linear(T, c_in, c_out, dt, w_off=0, ws=None, kernel=0, operand=None):
     g = torch.Generator(device="cuda")
     g.manual_seed(3)
     x = torch.randn(T, c_in, generator=g, device="cuda").to(dt)
@@ -20,7 +20,7 @@ def _linear(T, c_in, c_out, dt, w_off=0, ws=None, kernel=0):
     codes.copy_(fw["codes"])
     idx, _ = ef.channel_select(w, max(1, c_out // 4))
     return ef.linear_bwd(dy, fx["codes"], fx["clip_bits"], x, fx["scale"], fx["zero_point"], codes, fw["clip_bits"], w,
-                         fw["scale"], idx, ws=ws, dx_kernel=kernel)
+                         fw["scale"], idx, ws=ws, dx_kernel=kernel, w_operand=operand)
 
 
 def _same(a, b, exact_dx=True):
@@ -54,6 +54,35 @@ def test_unaligned_weight_codes_where_tiles_of_256_would_read_them():
     T, c_in, c_out = 8448, 1536, 496
     assert ef.lib().efqat_linear_bwd_weight_operand_bytes(T, c_in, c_out, ef.BF16, 0) == 0       # read as they lie
     _same(_linear(T, c_in, c_out, torch.bfloat16), _linear(T, c_in, c_out, torch.bfloat16, w_off=1))
+
+
+# A layer whose tiles of 256 read the weight codes has no operand made beforehand: a buffer handed over is ignored, also where the
+# call falls back to tiles that multiply by W_q^T.  The buffer is as large as W_q^T would be and holds no number.
+@pytest.mark.parametrize("less", (False, True), ids=("unaligned codes", "smallest workspace"))
+def test_operand_of_a_layer_that_has_none(less):
+    T, c_in, c_out, k = 8448, 1536, 496, 124
+    L = ef.lib()
+    assert L.efqat_linear_bwd_weight_operand_bytes(T, c_in, c_out, ef.BF16, 0) == 0
+    need = L.efqat_linear_bwd_workspace_bytes(T, c_in, c_out, k, ef.BF16, 0)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    if less:
+        lo, hi = 0, need // 256                        # the smallest workspace that is taken, in units of 256 bytes
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            try:
+                _linear(T, c_in, c_out, torch.bfloat16, ws=ws[:mid * 256])
+                hi = mid
+            except ef.EfqatError as e:
+                assert e.code == -6
+                lo = mid
+        assert hi * 256 < need
+        ws = ws[:hi * 256]
+    off = 0 if less else 1
+    want = _linear(T, c_in, c_out, torch.bfloat16, w_off=off, ws=ws)
+    bad = torch.full(((c_in * c_out * 2 + 256) // 2,), float("nan"), dtype=torch.bfloat16, device="cuda").view(torch.uint8)
+    got = _linear(T, c_in, c_out, torch.bfloat16, w_off=off, ws=ws, operand=bad)
+    for n in ("dx", "dw", "ds_w", "ds_x", "dz_x"):
+        assert torch.equal(got[n], want[n]), n
 
 
 @pytest.mark.parametrize("size", [(64, 64, 64), (63, 65, 8), (129, 128, 192), (640, 192, 136), (65, 1000, 4096), (1, 4096, 520)], ids=str)
