@@ -1,5 +1,5 @@
 """Range, scale, zero point and codes of an activation tensor, every block of the second kernel making the range from the
-partial ones for itself: tensors of less than a block up to more chunks than the grid takes at once, both kernels, bit for
+partial ones for itself, or a launch between the two: tensors of less than a block up to more chunks than the grid takes at once, both kernels, bit for
 bit against the oracle; the range's ends in the first, the last and an inner element."""
 import numpy as np
 import pytest
@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("kind", ("bf16", "f32"))
 @pytest.mark.parametrize("size", [(1, 1), (1, 7), (1, 32), (5, 96), (128, 32), (129, 32), (257, 160), (255, 33), (1000, 1000),
-                                  (4096, 1024), (4097, 1024), (8194, 1056)], ids=str)
+                                  (4096, 1024), (4097, 1024), (8194, 1056),
+                                  # ragged rows on both sides of the 16384 segments, short (a launch for the range) and not
+                                  (16384, 9), (16388, 9), (8194, 513), (16388, 300), (5463, 1337)], ids=str)
 def test_act_range(size, kind):
     rows, cols = size
     rng = np.random.default_rng(rows + cols)
