@@ -28,7 +28,7 @@ EXPORTS = [
     "efqat_linear_bwd_weight_operand_bytes", "efqat_linear_bwd_weight_operand",
     "efqat_conv_bwd_workspace_bytes", "efqat_conv_bwd_workspace_bytes_ex", "efqat_conv_bwd", "efqat_conv_bwd_ex",
     "efqat_linear_fwd_workspace_bytes", "efqat_linear_fwd",
-    "efqat_profile_enable", "efqat_profile_read",
+    "efqat_profile_enable", "efqat_profile_read", "efqat_linear_bwd_plan", "efqat_conv_bwd_plan",
 ]
 
 
@@ -123,6 +123,10 @@ def lib():
     L.efqat_profile_enable.argtypes = [ci]
     L.efqat_profile_read.restype = ci
     L.efqat_profile_read.argtypes = [ci, C.POINTER(C.c_double), C.POINTER(C.c_int64)]
+    L.efqat_linear_bwd_plan.restype = ci
+    L.efqat_linear_bwd_plan.argtypes = [i64] * 4 + [ci, ci, ci, C.POINTER(C.c_int32)]
+    L.efqat_conv_bwd_plan.restype = ci
+    L.efqat_conv_bwd_plan.argtypes = [i64] * 10 + [ci, ci, ci, C.POINTER(C.c_int32)]
     _LIB = L
     return L
 
@@ -191,6 +195,24 @@ def profile_read(which: int):
     ms, n = C.c_double(0.0), C.c_int64(0)
     _check(lib().efqat_profile_read(which, C.byref(ms), C.byref(n)), "efqat_profile_read")
     return ms.value, n.value
+
+
+_PLAN = ("one_grid", "side_stream", "dx_kernel", "dx_tile", "dx_rows", "dw_operands", "dw_tile", "dw_slices")
+
+
+def linear_bwd_plan(T, c_in, c_out, k, dy_dtype=BF16, dy_layout=DY_TOKEN_MAJOR, dx_kernel=0) -> dict:
+    """What linear_bwd launches for its two products (EFQAT_PLAN_* of include/efqat.h); needs no GPU."""
+    out = (C.c_int32 * len(_PLAN))()
+    _check(lib().efqat_linear_bwd_plan(T, c_in, c_out, k, dy_dtype, dy_layout, dx_kernel, out), "efqat_linear_bwd_plan")
+    return dict(zip(_PLAN, out))
+
+
+def conv_bwd_plan(N, H, W, c_in, c_out, KH, KW, stride, pad, k, dy_dtype=BF16, dy_layout=DY_TOKEN_MAJOR, dx_kernel=0) -> dict:
+    """The same for conv_bwd."""
+    out = (C.c_int32 * len(_PLAN))()
+    _check(lib().efqat_conv_bwd_plan(N, H, W, c_in, c_out, KH, KW, stride, pad, k, dy_dtype, dy_layout, dx_kernel, out),
+           "efqat_conv_bwd_plan")
+    return dict(zip(_PLAN, out))
 
 
 def k_from_ratio(c_out: int, num: int, den: int) -> int:

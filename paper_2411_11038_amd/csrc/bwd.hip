@@ -674,6 +674,19 @@ static BwdPlan make_plan(int64_t T_in, int64_t T_out, int64_t c_in, int64_t c_ou
   return p;
 }
 
+static bool takes_side_stream(const BwdPlan& p) { return (p.tn || p.rdw) && !p.pair; }   // tn, rdw: only where k > 0
+
+static int plan_info(const BwdPlan& p, bool im2col, int64_t k, int32_t* out) {
+  out[EFQAT_PLAN_ONE_GRID] = p.pair; out[EFQAT_PLAN_SIDE_STREAM] = takes_side_stream(p);
+  out[EFQAT_PLAN_DX_KERNEL] = p.dx8 ? 2 : p.plan_dx.ring ? 1 : 0;
+  out[EFQAT_PLAN_DX_TILE] = p.dx8 ? p.dx8_tile : p.plan_dx.tile;
+  out[EFQAT_PLAN_DX_ROWS] = p.cdxs ? 2 : p.cdx ? 1 : im2col ? 3 : 0;
+  out[EFQAT_PLAN_DW_OPERANDS] = k == 0 ? 0 : p.cdw ? 2 : p.tn ? 1 : p.rdw ? 4 : 3;
+  out[EFQAT_PLAN_DW_TILE] = k == 0 ? 0 : p.plan_dw.tile;
+  out[EFQAT_PLAN_DW_SLICES] = k == 0 ? 0 : p.plan_dw.split_k;
+  return EFQAT_OK;
+}
+
 template <class Plan>
 static size_t query_plan(const Plan& plan) { return std::max(plan(false).total, plan(true).total); }
 
@@ -759,7 +772,7 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   // Products that share a grid run beside each other already, at no cost of events; with both products on one stream the
   // result is the same bit for bit.  Launches that are timed by class are kept apart.
   const bool pair = p.pair && !prof_enabled();
-  const bool use_side = io.side && io.side != st && io.k > 0 && (p.tn || p.rdw) && !p.pair;
+  const bool use_side = io.side && io.side != st && takes_side_stream(p);
   hipStream_t st2 = st;
   SideEvents ev{};
   if (use_side) {
@@ -1032,6 +1045,23 @@ extern "C" int efqat_linear_bwd_ex(const void* dy, int dy_dtype, int dy_layout, 
   return linear_bwd_entry(io, T, c_in, c_out, step, w, s_w, dx_kernel, ws, ws_bytes, stream);
 }
 
+static int plan_args(int64_t c_out, int64_t k, int dy_dtype, int dy_layout, int dxk, const int32_t* plan) {
+  if (!plan) return EFQAT_ERR_NULL_PTR;
+  if (k < 0 || k > c_out) return EFQAT_ERR_BAD_K;
+  if (dy_dtype != EFQAT_F32 && dy_dtype != EFQAT_BF16) return EFQAT_ERR_BAD_DTYPE;
+  if (dy_layout != EFQAT_DY_TOKEN_MAJOR && dy_layout != EFQAT_DY_CHANNEL_MAJOR) return EFQAT_ERR_BAD_LAYOUT;
+  return dxk < EFQAT_DX_KERNEL_AUTO || dxk > EFQAT_DX_KERNEL_BF16_PINNED ? EFQAT_ERR_BAD_LAYOUT : EFQAT_OK;
+}
+
+extern "C" int efqat_linear_bwd_plan(int64_t T, int64_t c_in, int64_t c_out, int64_t k, int dy_dtype, int dy_layout,
+                                     int dx_kernel, int32_t* plan) {
+  if (!linear_shape_ok(T, c_in, c_out)) return EFQAT_ERR_BAD_SHAPE;
+  const int rc = plan_args(c_out, k, dy_dtype, dy_layout, dx_kernel, plan);
+  if (rc) return rc;
+  return plan_info(make_plan(T, T, c_in, c_out, 1, k, dy_dtype, dy_layout, false, dx_kernel, nullptr, c_in > kMaxStagedColumns), false,
+                   k, plan);
+}
+
 extern "C" size_t efqat_linear_bwd_weight_operand_bytes(int64_t T, int64_t c_in, int64_t c_out, int dy_dtype,
                                                         int dy_layout) {
   if (!linear_shape_ok(T, c_in, c_out)) return 0;
@@ -1078,10 +1108,20 @@ static int conv_geom(int64_t N, int64_t H, int64_t W, int64_t c_in, int64_t c_ou
   return EFQAT_OK;
 }
 
+static bool conv_im2col(const ConvGeom& g) { return !(g.KH * g.KW == 1 && g.stride == 1 && g.pad == 0); }
 static BwdPlan conv_plan(const ConvGeom& g, int64_t k, int dy_dtype, int dy_layout, int dxk, bool wide) {
-  const bool im2col = !(g.KH * g.KW == 1 && g.stride == 1 && g.pad == 0);
   return make_plan((int64_t)g.N * g.H * g.W, (int64_t)g.N * g.Ho * g.Wo, g.c_in, g.c_out, g.KH * g.KW, k, dy_dtype,
-                   dy_layout, im2col, dxk, &g, wide);
+                   dy_layout, conv_im2col(g), dxk, &g, wide);
+}
+
+extern "C" int efqat_conv_bwd_plan(int64_t N, int64_t H, int64_t W, int64_t c_in, int64_t c_out, int64_t KH, int64_t KW,
+                                   int64_t stride, int64_t pad, int64_t k, int dy_dtype, int dy_layout, int dx_kernel,
+                                   int32_t* plan) {
+  ConvGeom g;
+  int rc = conv_geom(N, H, W, c_in, c_out, KH, KW, stride, pad, &g);
+  if (!rc) rc = plan_args(c_out, k, dy_dtype, dy_layout, dx_kernel, plan);
+  if (rc) return rc;
+  return plan_info(conv_plan(g, k, dy_dtype, dy_layout, dx_kernel, c_in > kMaxStagedColumns), conv_im2col(g), k, plan);
 }
 
 extern "C" size_t efqat_conv_bwd_workspace_bytes_ex(int64_t N, int64_t H, int64_t W, int64_t c_in, int64_t c_out,

@@ -104,6 +104,18 @@ def test_argument_validation_needs_no_device():
     assert lin(ws=fake + 16) == -9
     assert lin(dy=fake + 2) == -9
 
+    # launch plans
+    plan = (C.c_int32 * 8)()
+    def lplan(T=384, c_in=192, c_out=384, k=96, dyd=1, lay=0, dxk=0, out=plan):
+        return L.efqat_linear_bwd_plan(T, c_in, c_out, k, dyd, lay, dxk, out)
+    assert lplan() == 0 and lplan(out=None) == -1 and lplan(T=0) == -2 and lplan(k=385) == -4 and lplan(k=-1) == -4
+    assert lplan(dyd=2) == -8 and lplan(lay=2) == -5 and lplan(dxk=4) == -5
+    assert L.efqat_conv_bwd_plan(2, 9, 9, 64, 64, 3, 3, 1, 1, 16, 1, 0, 0, plan) == 0
+    assert L.efqat_conv_bwd_plan(2, 1, 9, 64, 64, 5, 3, 1, 1, 16, 1, 0, 0, plan) == -2
+    assert L.efqat_conv_bwd_plan(2, 9, 9, 64, 64, 3, 3, 1, 1, 65, 1, 0, 0, plan) == -4
+    p = ef.linear_bwd_plan(8192, 4096, 11008, 0)
+    assert p["dw_operands"] == p["dw_tile"] == p["dw_slices"] == p["one_grid"] == p["side_stream"] == 0 and p["dx_kernel"] == 2
+
     # weight operand made beforehand
     need = L.efqat_linear_bwd_weight_operand_bytes(384, 192, 384, 1, 0)
     assert need == 192 * 384 * 2 + 256                 # bf16 [c_in][c_out] and a zero page

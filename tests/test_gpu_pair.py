@@ -14,7 +14,15 @@ LINEAR = [(64, 64, 64, 16), (65, 80, 72, 72), (1, 16, 8, 1), (300, 72, 520, 1), 
           (4000, 320, 136, 130), (16000, 48, 40, 7), (72, 80, 33, 5), (8, 16, 8, 8), (1000, 144, 200, 200)]
 # N, H, c_in, c_out, kernel, stride, k
 CONV = [(2, 9, 128, 64, 3, 1, 10), (2, 9, 72, 64, 3, 1, 64), (3, 8, 128, 40, 3, 2, 20), (2, 9, 20, 128, 5, 2, 3), (1, 7, 256, 64, 1, 2, 64),
-        (40, 14, 128, 128, 3, 1, 32), (33, 15, 64, 64, 3, 2, 16)]
+        (40, 14, 128, 128, 3, 1, 32), (33, 15, 64, 64, 3, 2, 16), (128, 9, 128, 64, 5, 1, 64), (6, 20, 128, 128, 5, 2, 32)]
+
+
+def _plan(size, dt, layout):
+    code = ef.BF16 if dt == torch.bfloat16 else ef.F32
+    if len(size) == 4:
+        return ef.linear_bwd_plan(*size, code, layout)
+    N, H, c_in, c_out, kernel, stride, k = size
+    return ef.conv_bwd_plan(N, H, H, c_in, c_out, kernel, kernel, stride, kernel // 2, k, code, layout)
 
 
 def _linear(size, dt, layout):
@@ -48,10 +56,24 @@ def _conv(size, dt, layout):
                                     stride=stride, pad=pad, dy_layout=layout, **kw)
 
 
+def test_every_form_of_the_shared_grid_is_reached():
+    got = set()
+    for size in LINEAR + CONV:
+        for dt in (torch.bfloat16, torch.float32):
+            for layout in (0, 1):
+                p = _plan(size, dt, layout)
+                got.add((p["dx_kernel"], p["dx_rows"], p["dw_operands"]) + ((dt,) if p["dx_kernel"] == 1 else ()))
+    want = {(2, 0, 4)}                                    # channel major
+    for rows, operands in ((0, 1), (0, 3), (1, 2), (1, 3), (2, 2), (2, 3)):
+        want |= {(0, rows, operands), (1, rows, operands, torch.bfloat16), (1, rows, operands, torch.float32)}
+    assert got == want
+
+
 @pytest.mark.parametrize("dt", (torch.bfloat16, torch.float32), ids=("bf16", "f32"))
 @pytest.mark.parametrize("layout", (0, 1))
 @pytest.mark.parametrize("size", LINEAR + CONV, ids=str)
 def test_one_grid_is_two_launches(size, layout, dt):
+    assert _plan(size, dt, layout)["one_grid"] == 1
     call = (_linear if len(size) == 4 else _conv)(size, dt, layout)
     ef.profile_enable(True)
     try:
@@ -68,6 +90,7 @@ def test_one_grid_is_two_launches(size, layout, dt):
 
 @pytest.mark.parametrize("size", [LINEAR[0], LINEAR[4], CONV[0], CONV[2]], ids=str)
 def test_one_grid_captured(size):
+    assert _plan(size, torch.bfloat16, 0)["one_grid"] == 1
     call = (_linear if len(size) == 4 else _conv)(size, torch.bfloat16, 0)
     want = call()
     out = {k: torch.zeros_like(v) for k, v in want.items()}
