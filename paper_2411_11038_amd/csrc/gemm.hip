@@ -59,8 +59,10 @@ GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool allow_split, bool allow
 //   2048 x 768 -> 3072        28 /  28 /  26 /  26 /  30 /  30   (C_out 320)
 //   4224 x 112 -> 6144        46 /  37 /  46 /  34 /  38 /  44   two blocks a CU hide each other's epilogues
 //   12288 x 3072 -> 768       89 /  99 /  87 /  85 /  54 /  -    one round of 192 x 192
-//   13824 x 2504 -> 768      135 / 132 /  93 /  93 /  95 /  65   long K and whole rounds: 256 x 256 (without int8 operand:
-//                                                               k_gemm_nt, priced the same)
+//   13824 x 2504 -> 768      135 / 132 /  93 /  93 /  95 /  65   long K and whole rounds: 256 x 256
+// Without int8 operand the 256 x 256 tiles are k_gemm_nt's, which has no straight-line epilogue: a row of its own, fitted to 154
+// more calls (0.4 % from the fastest in the mean; with the row of dx8 0.6 %, and whole bf16 tiles were taken where they lose:
+// 5888 x 1716 -> 5888 205 us, now 175 on 192 x 192; 16384 x 1020 -> 2048 118, now 105 on 128 x 128).
 // Convolutions pay for the gather in every stage.
 struct DxTile { int t; bool ring; int bpc; double lone[2], full[2], f32[2], fast[2]; };
 static const DxTile kDxTiles[] = {{64, true, 3, {0.28, 5.6}, {0.73, 4.5}, {0.1, 1.0}, {0.0, 0.0}},
@@ -68,7 +70,8 @@ static const DxTile kDxTiles[] = {{64, true, 3, {0.28, 5.6}, {0.73, 4.5}, {0.1, 
                                   {128, true, 1, {0.495, 9.2}, {0.587, 7.9}, {0.0, 1.4}, {-1.7, -1.7}},
                                   {128, false, 2, {0.74, 8.0}, {1.075, 9.7}, {0.7, 3.5}, {-1.7, -2.0}},
                                   {192, true, 1, {0.695, 15.6}, {0.98, 15.6}, {0.0, 4.8}, {-4.2, -4.2}},
-                                  {256, false, 1, {0.92, 23.3}, {1.61, 23.3}, {1.9, 12.0}, {-6.7, -6.7}}};
+                                  {256, false, 1, {0.92, 23.3}, {1.61, 23.3}, {1.9, 12.0}, {-6.7, -6.7}}};   // k_gemm_dx8
+static const DxTile kDxNt256 = {256, false, 1, {0.97, 17.7}, {1.71, 26.1}, {1.7, 7.4}, {0.0, 0.0}};
 static const DxTile kDxConvTiles[] = {{64, true, 3, {0.30, 6.3}, {0.575, 6.6}, {0.0, 0.0}, {0.0, 0.0}},
                                       {64, false, 4, {0.54, 5.2}, {0.71, 5.4}, {0.0, 0.1}, {0.0, 0.0}},
                                       {128, true, 1, {0.56, 10.0}, {0.56, 10.0}, {0.5, 0.5}, {-1.0, -1.0}},
@@ -112,7 +115,7 @@ GemmPlan dx_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const Con
     if (best.tile == 0 || t < best_t) { best_t = t; best = GemmPlan{c.t, 1, (int)tm, (int)tn, c.ring}; }
   };
   if (conv) for (const DxTile& c : kDxConvTiles) price(c);
-  else for (const DxTile& c : kDxTiles) price(c);
+  else for (const DxTile& c : kDxTiles) price(c.t == 256 && !int8_ok ? kDxNt256 : c);
   if (price_out) *price_out = best_t;
   return best;
 }
