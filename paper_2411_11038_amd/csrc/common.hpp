@@ -117,7 +117,8 @@ struct GemmPlan {
 // with the fused dX epilogue.
 GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool allow_split, bool allow_192 = true, bool allow_256 = true);
 // Kernel and tile of a dX product (see kDxTiles).  conv: dY is gathered in the tile loads, by phase when `strided` is given;
-// int8_ok: tiles of 256 are run by k_gemm_dx8, which needs no bf16 W_q^T.
+// int8_ok: tiles of 256 are run by k_gemm_dx8, which needs no bf16 W_q^T.  price: us of the cheapest tile, without what memory may
+// bound it to (pair_plan has a rule of its own for that).
 struct ConvDxStridedMap;
 GemmPlan dx_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const ConvDxStridedMap* strided, bool int8_ok,
                  double* price = nullptr);

@@ -79,6 +79,20 @@ static const DxTile kDxConvTiles[] = {{64, true, 3, {0.30, 6.3}, {0.575, 6.6}, {
                                       {192, false, 1, {1.12, 15.6}, {1.12, 15.6}, {0.2, 0.2}, {-1.0, -1.0}}};
 static int64_t conv_phases(const ConvDxStridedMap& cm, int tile, ConvPhase* out, int* nphase);
 
+// MB of x, its codes and masks and dX of a linear layer
+static double dx_traffic_mb(int64_t M, int64_t N, bool f32) { return (double)M * (double)N * (f32 ? 9.125 : 5.125) / 1e6; }
+// What they take to move, beyond what the caches hold: products of few K stages under a large dX are bound by that, and narrow
+// tiles and lone blocks move it more slowly.  T x C_out -> C_in, k = 0, the call on 64 / 128 wide tiles, us: 11474 x 128 -> 7176
+// bf16 177 / 142, 16384 x 16 -> 5872 fp32 271 / 230 (256: 264), 13840 x 96 -> 7232 fp32 273 / 236, 15872 x 17 -> 8704 bf16, k = 17,
+// 256 / 207 (ring of 128: 245); but 5248 x 64 -> 5114 fp32 (245 MB) 62.6 / 63.6.  Of 524 layers the choice is 0.7 % from the
+// fastest with it and 0.9 % without; where it changes the choice the calls are up to 1.23 x as fast, the worst found 0.975 x.
+static double dx_memory_price(int64_t M, int64_t N, const DxTile& c, bool f32) {
+  const double mb = dx_traffic_mb(M, N, f32);
+  if (c.bpc == 1) return f32 ? (mb - 50.0) / 3.3 : (mb - 60.0) / 2.5;
+  if (c.t == 64) return f32 ? (mb - 100.0) / 2.9 : (mb - 80.0) / 2.0;
+  return f32 ? (mb - 50.0) / 3.95 : (mb - 60.0) / 2.8;
+}
+
 // K stages of a row tile of t rows (strided: in the mean) and the number of row tiles
 static double dx_stages(int64_t M, int64_t K, int t, const ConvDxStridedMap* strided, int64_t* tiles_m) {
   double stages = (double)ceil_div(K, KALIGN);
@@ -111,12 +125,13 @@ GemmPlan dx_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const Con
     if (const int64_t rest = tiles % round)
       t += lone + (full - lone) * (c.bpc > 1 ? (double)(ceil_div(rest, 256) - 1) / (c.bpc - 1) : (double)rest / 256.0);
     // the others need W_q^T in bf16: the codes read, twice as many bytes written, at 4 TB/s
-    if (int8_ok && c.t != 256) t += 3.0 * (double)N * (double)K / 4e6;
+    const double wqt = int8_ok && c.t != 256 ? 3.0 * (double)N * (double)K / 4e6 : 0.0;
+    if (price_out && (best.tile == 0 || t + wqt < *price_out)) *price_out = t + wqt;
+    t = (conv ? t : std::max(t, dx_memory_price(M, N, c, f32))) + wqt;
     if (best.tile == 0 || t < best_t) { best_t = t; best = GemmPlan{c.t, 1, (int)tm, (int)tn, c.ring}; }
   };
   if (conv) for (const DxTile& c : kDxConvTiles) price(c);
   else for (const DxTile& c : kDxTiles) price(c.t == 256 && !int8_ok ? kDxNt256 : c);
-  if (price_out) *price_out = best_t;
   return best;
 }
 
@@ -211,6 +226,10 @@ static bool pair_search(double stages, int64_t tm, int64_t tn, const DxTile& c, 
 }
 bool pair_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const ConvDxStridedMap* strided, DwKind kind, int64_t dw_m,
                int64_t dw_n, int64_t dw_k, double apart, GemmPlan* dx, GemmPlan* dw) {
+  // A dX that is bound by memory takes the wider tiles of a launch of its own.  One grid / two launches, us: fp32 13888 x 128 -> 3248,
+  // k = 32 (412 MB) 158 / 140, 13184 x 64 -> 2616 (315 MB) 162 / 146, but 7776 x 24 -> 4234 (300 MB) 187 / 197; bf16 5824 x 64 -> 9856
+  // (294 MB) 125 / 105, 9984 x 75 -> 4672 (239 MB) 82 / 86.
+  if (!conv && dx_traffic_mb(M, N, f32) > (f32 ? 312.0 : 270.0)) return false;
   bool found = false;
   for (int ring = 0; ring < 2; ++ring) {
     const DxTile& c = conv ? kDxConvTiles[1 - ring] : kDxTiles[1 - ring];

@@ -10,6 +10,11 @@ LINEAR = [
     (5888, 5888, 1716, ef.BF16, (1, 192)),        # 175; two stages of 256: 205
     (16384, 2048, 1020, ef.BF16, (0, 128)),       # 105; 119
     (8192, 4096, 4100, ef.BF16, (0, 256)),        # 346; ring of 192: 389
+    # few K stages under a large dX: bound by memory, more so on 64-wide tiles
+    (11474, 7176, 128, ef.BF16, (0, 128)),        # 142; 64: 177
+    (16384, 5872, 16, ef.F32, (0, 128)),          # 230; 64: 271
+    (15488, 6656, 64, ef.F32, (0, 128)),          # 227; 64: 262
+    (15872, 8704, 17, ef.BF16, (0, 128)),         # 207; 64: 256, ring of 128: 245
 ]
 
 
