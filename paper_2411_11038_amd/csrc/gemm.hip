@@ -144,9 +144,12 @@ GemmPlan dx_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const Con
 //   12144 x 688, 40      13.9 (32) / 15.5 (32), before 16.7 (22)  half of a 128-row tile would be padding
 //   6848 x 1776, 1500    63 (3) / 54 (3)                          many tiles: fewer LDS bytes per product
 // The 256 x 256 and 192 x 192 tiles stay where gemm_plan prices them lowest: large products.
+// Gathered codes on 128-row tiles: two blocks a CU, by the registers of the pixel coordinates; priced as three before, 64 x 47 x 47,
+// 512 -> 384, 2 x 2, k = 192 took 24 slices of them: 616 us, now 21 of 64-row tiles 582.  Fitted to 50 convolutions, 0.46 % from the
+// fastest in the mean (0.53 %).
 struct DwTile { int bm, bn, bpc; double lone[2], full[2]; };
 static const DwTile kDwTiles[4][2] = {{{64, 128, 4, {0.515, 4.4}, {1.10, 6.2}}, {128, 128, 3, {0.575, 5.8}, {1.305, 8.3}}},
-                                      {{64, 128, 4, {0.785, 5.0}, {1.51, 7.6}}, {128, 128, 3, {0.955, 6.6}, {1.68, 11.2}}},
+                                      {{64, 128, 4, {0.785, 5.0}, {1.51, 7.6}}, {128, 128, 2, {1.007, 5.9}, {1.303, 7.0}}},
                                       {{64, 64, 4, {0.453, 3.0}, {0.95, 3.5}}, {128, 128, 2, {0.71, 4.5}, {0.88, 7.0}}},
                                       {{64, 128, 4, {0.485, 3.4}, {0.89, 7.7}}, {128, 128, 3, {0.547, 4.6}, {0.917, 9.7}}}};
 // the second pass over S slices of M x N values

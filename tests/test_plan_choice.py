@@ -1,4 +1,4 @@
-"""Kernel and tile of the dX product where the cost tables chose measurably worse ones before: sizes with the measured times of
+"""Kernels and tiles of the products where the cost tables chose measurably worse ones before: sizes with the measured times of
 the candidates beside them (us, the whole backward call with k = 0).  Host queries, no GPU."""
 import pytest
 
@@ -23,3 +23,9 @@ def test_dx_plan(case):
     T, c_in, c_out, dtype, want = case
     p = ef.linear_bwd_plan(T, c_in, c_out, 0, dtype)
     assert (p["dx_kernel"], p["dx_tile"]) == want
+
+
+def test_dw_plan_of_gathered_codes():
+    # two blocks of 128 x 128 a CU, not three: 64-row tiles 582 us, 24 slices of 128-row tiles 616
+    p = ef.conv_bwd_plan(64, 47, 47, 512, 384, 2, 2, 1, 1, 192)
+    assert (p["dw_operands"], p["dw_tile"]) == (2, 64)
