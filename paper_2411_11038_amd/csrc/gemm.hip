@@ -336,9 +336,8 @@ int launch_dx(const GemmStridedArgs& a, int conv, const GemmPlan& plan, hipStrea
       default: return EFQAT_ERR_BAD_SHAPE;
     }
   }
-  switch (plan.tile) {
+  switch (plan.tile) {                                  // tiles of 192 always take the ring
     case 256: return launch_cfg<256, 256, EPI_DX, false>(a, 1, stream);
-    case 192: return launch_cfg<192, 192, EPI_DX, false>(a, 1, stream);
     case 128: return fast ? launch_cfg<128, 128, EPI_DXF, false>(a, 1, stream) : launch_cfg<128, 128, EPI_DX, false>(a, 1, stream);
     case 64: return launch_cfg<64, 64, EPI_DX, false>(a, 1, stream);
     default: return EFQAT_ERR_BAD_SHAPE;
