@@ -1,6 +1,7 @@
 """Convolutions whose dX product gathers dY by stride phase (strides 2 to 4) or from a copy padded to whole 64-channel
 stages, against the oracle: phases with different tap counts and without taps, images smaller than the stride, ragged last
-tiles of a phase, one and several column tiles, both block shapes (up to 256 tiles and more), both dY layouts."""
+tiles of a phase, one and several column tiles, both dY layouts.  These sizes run on 64 x 64 tiles beside dW; the larger tiles:
+test_gpu_large_tiles.py."""
 import numpy as np
 import pytest
 import torch
@@ -20,7 +21,7 @@ CASES = [
     (2, 11, 10, 48, 64, 5, 4, 3, 2, "bf16", 8, 0.8, (1, 4), 0, False),
     (2, 13, 9, 24, 64, 3, 5, 4, 1, "f32", 8, 0.8, (1, 4), 1, False),      # 16 phases, some without taps
     (2, 12, 12, 16, 64, 3, 3, 5, 1, "bf16", 8, 0.8, (1, 4), 0, False),    # beyond the rule: im2col matrix
-    (40, 29, 31, 136, 64, 3, 3, 2, 1, "bf16", 8, 0.8, (1, 4), 0, False),  # 282 row tiles x 2: two blocks per compute unit
+    (40, 29, 31, 136, 64, 3, 3, 2, 1, "bf16", 8, 0.8, (1, 4), 0, False),  # 563 row tiles x 3, the dW product beside them
     # stride 1 and 2 on padded channel counts
     (2, 9, 7, 32, 40, 3, 3, 1, 1, "bf16", 4, 0.8, (1, 4), 0, False),
     (2, 9, 7, 32, 97, 3, 3, 1, 1, "bf16", 8, 0.8, (1, 4), 0, False),      # rows of dY not 16-byte aligned

@@ -333,7 +333,7 @@ LIN_CASES = [
     (300, 208, 130, "bf16", 8, 8, 0.7, (1, 1), 0, False),         # ... C_out not a multiple of 8: compacted copy
     (333, 272, 200, "f32", 8, 8, 0.7, (1, 1), 0, True),
     (70, 16, 24, "bf16", 8, 8, 1.0, (1, 3), 0, False),
-    (2048, 512, 640, "bf16", 8, 8, 0.8, (1, 1), 0, False),        # several 256-wide tiles, split-K
+    (2048, 512, 640, "bf16", 8, 8, 0.8, (1, 1), 0, False),        # several tiles, split-K
     # channel-major bf16 dY, T % 8 == 0, c_in % 16 == 0: rows idx of dY gathered by the dW kernel's tile loads,
     # activation operand read from the uint8 codes as they lie
     (304, 208, 136, "bf16", 8, 4, 0.7, (1, 4), 1, False),         # tails in M (k = 34), N and K (304 = 4 * 64 + 48)
@@ -341,9 +341,9 @@ LIN_CASES = [
     (72, 16, 24, "bf16", 8, 8, 1.0, (1, 3), 1, False),
     (2048, 512, 640, "bf16", 8, 8, 0.8, (1, 1), 1, False),        # every channel; several tiles; split-K
     (1000, 768, 1096, "bf16", 8, 8, 0.8, (1, 20), 1, False),      # k = 54 of 1096
-    (384, 256, 136, "bf16", 8, 8, 0.6, (1, 4), 1, False),         # whole 128 tiles: straight-line dX epilogue
-    (256, 128, 136, "bf16", 8, 8, 0.6, (1, 4), 0, False),         # ... of the bf16-operand 128 x 128 kernel
-    (256, 136, 128, "bf16", 4, 8, 0.6, (1, 4), 0, False),         # (C_in = 136: general epilogue, same kernel family)
+    (384, 256, 136, "bf16", 8, 8, 0.6, (1, 4), 1, False),         # whole 64 x 128 tiles
+    (256, 128, 136, "bf16", 8, 8, 0.6, (1, 4), 0, False),         # whole 64 x 64 tiles
+    (256, 136, 128, "bf16", 4, 8, 0.6, (1, 4), 0, False),         # ... and a ragged last column tile
 ]
 
 
@@ -362,9 +362,11 @@ def test_linear_bwd_matches_oracle(case):
     check_backward(out, ref, idx, idx_ref, X, W, qp, kind, scatter, kind == "bf16", W.shape)
 
 
-# (T, c_in, c_out, layout): the pinned 192-tile kernel, the 128-tile kernel with ragged edges, a padded C_out,
-# and two layers whose dX product reads the int8 codes (no operand exists: the call must behave like the plain one)
-PREPARED_CASES = [(384, 192, 384, 0), (300, 200, 136, 0), (129, 72, 43, 0), (2048, 512, 640, 0), (384, 256, 136, 1)]
+# (T, c_in, c_out, layout): both products in one grid, with whole and with ragged tiles, with a padded C_out and by the ring;
+# two LDS stages on 128 x 128 tiles in a launch of their own; and two layers whose dX product reads the int8 codes (no operand
+# exists: the call must behave like the plain one)
+PREPARED_CASES = [(384, 192, 384, 0), (300, 200, 136, 0), (129, 72, 43, 0), (2048, 512, 640, 0), (4096, 2048, 136, 0), (384, 256, 136, 1),
+                  (2048, 4864, 248, 0)]
 
 
 @pytest.mark.parametrize("case", PREPARED_CASES, ids=lambda c: "T%d_%dx%d_L%d" % c)
@@ -662,7 +664,7 @@ CONV_CASES = [
     (1, 5, 5, 256, 64, 2, 2, 1, 0, "f32", 8, 0.8, (1, 1), 0, False),      # image smaller than a 64-token stage
     (2, 6, 10, 128, 64, 3, 1, 1, 1, "bf16", 8, 0.8, (1, 1), 0, False),    # every channel: dY itself is the A operand
     (7, 10, 9, 128, 64, 3, 3, 1, 1, "bf16", 4, 0.8, (1, 4), 0, False),    # 630 tokens: split-K with a ragged last stage
-    # 128 input pixels x 128 channels: whole tiles, the straight-line dX epilogue behind the implicit-im2col loop
+    # 128 input pixels x 128 channels: whole tiles behind the implicit-im2col loop
     (2, 8, 8, 128, 64, 3, 3, 1, 1, "bf16", 8, 0.6, (1, 4), 0, False),
     (3, 8, 16, 256, 128, 3, 3, 1, 1, "bf16", 8, 0.6, (1, 2), 0, True),
 ]
