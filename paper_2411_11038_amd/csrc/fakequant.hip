@@ -81,8 +81,8 @@ __global__ __launch_bounds__(256) void k_minmax_partial(const T* __restrict__ x,
 // Eq. 2: S_x = (beta - alpha) / (2^b - 1), Z_x = -round(alpha / S_x), each a single-precision op, from the partial ranges:
 // by every block of the kernel that makes the codes, for itself (minima and maxima do not depend on an order), and written
 // once.  The partials are at most 8 KiB, in L2; in k_quantize_act_flat the first loads of x are in flight meanwhile.  A launch of
-// one block in between was 2 to 4.5 us, this is 0.6 to 2.5: 65536 fp32 values 8.0 -> 6.8 us in all, 3.2 M bf16 9.8 -> 8.8,
-// 33.5 M fp32 51.8 -> 48.6 (9.4 M bf16 alone 13.4 -> 13.8, inside a training step 3 us less).  Ragged rows: see run_fakequant.
+// one block in between was 2 to 4.5 us, this is 0.6 to 2.5: 65536 fp32 values 7.6 -> 6.2 us in all, 3.2 M bf16 9.8 -> 8.6,
+// 9.4 M 12.7 -> 12.1, 33.5 M 33.5 -> 32.4, 33.5 M fp32 51.4 -> 49.4.  Ragged rows: see run_fakequant.
 __device__ __forceinline__ void act_qparams_block(const float* __restrict__ part, int nparts, int bits, float* s_out,
                                                   float* z_out, float* __restrict__ scale, float* __restrict__ zp) {
   float lo = INFINITY, hi = -INFINITY;
@@ -447,11 +447,10 @@ static int run_fakequant(const T* x, int64_t rows, int64_t cols, int mode, int b
   const bool flat = mode == EFQAT_QUANT_ACT_PER_TENSOR_ASYM && vec_row && (cols % 32) == 0;
   // Ragged rows with the range to make: two rounds of the blocks that are resident at a time.  19584 x 1496 bf16 34.9 us (8192
   // blocks 38.2, a launch for the range and 8192 blocks 35.4), 16384 x 1000 fp32 29.4 (32.4, 30.9), 12000 x 7777 bf16 154 (156,
-  // 155).  Where that does not hold every segment and the segments are short, there is too little work behind the range in a
-  // block to repay it, and more blocks balance better: a block of its own makes it.  us so / in every block: 20000 x 7 bf16
-  // 16.1 / 16.7, 100000 x 100 fp32 49.6 / 51.4, 36000 x 513 bf16 (256.5 of 512 values a segment) 43.8 / 46.3, but
-  // 36000 x 300 31.1 / 29.8, 60000 x 511 55.6 / 53.8.
-  if (part && !flat && blocks > 256 * 16 && n < 280 * items) {
+  // 155).  Many short segments: there is too little work behind the range in a block to repay it, and more blocks balance better,
+  // so a block of its own makes it.  us so / in every block: 100000 x 100 fp32 49.6 / 51.4, 20000 x 7 bf16 16.1 / 16.7, 7500 x 513
+  // (256.5 of 512 values a segment) 14.7 / 15.6, 13184 x 64 13.9 / 14.8, but 10000 x 64 13.2 / 12.8, 36000 x 300 31.1 / 29.8.
+  if (part && !flat && blocks > 256 * 10 && n < 280 * items) {
     hipLaunchKernelGGL(k_act_qparams, dim3(1), dim3(256), 0, st, part, nparts, bits, scale, zp);
     EFQAT_LAUNCH_CHECK();
     part = nullptr;
@@ -464,7 +463,9 @@ static int run_fakequant(const T* x, int64_t rows, int64_t cols, int mode, int b
   if (flat) {
     const int64_t nchunks = n / 8;
     int64_t fb = ceil_div(nchunks, 512);             // two chunks per lane and iteration
-    const int64_t most = part ? 256 * 4 : 256 * 16;  // with the range to make, blocks that are all resident at a time
+    // with the range to make, blocks that are all resident at a time (8192 x 4096 bf16 32.4 us; four blocks a CU 35.1, eight 33.0,
+    // sixteen 33.8, and 33.5 with a launch for the range between)
+    const int64_t most = part ? 256 * 6 : 256 * 16;
     if (fb > most) fb = most;
     if (part)
       hipLaunchKernelGGL((k_quantize_act_flat<T, true>), dim3((unsigned)fb), dim3(256), 0, st, x, nchunks, bits, scale, zp,

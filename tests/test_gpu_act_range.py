@@ -14,9 +14,10 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("kind", ("bf16", "f32"))
 @pytest.mark.parametrize("size", [(1, 1), (1, 7), (1, 32), (5, 96), (128, 32), (129, 32), (257, 160), (255, 33), (1000, 1000),
-                                  (4096, 1024), (4097, 1024), (8194, 1056),
-                                  # ragged rows on both sides of the 16384 segments, short (a launch for the range) and not
-                                  (16384, 9), (16388, 9), (8194, 513), (16388, 300), (5463, 1337)], ids=str)
+                                  (4096, 1024), (4097, 1024), (6145, 1024), (8194, 1056),
+                                  # ragged rows on both sides of the 10240 segments, short (a launch for the range) and not, and
+                                  # more segments than the blocks take at once
+                                  (10240, 9), (10244, 9), (5122, 513), (10244, 300), (16388, 300), (5463, 1337)], ids=str)
 def test_act_range(size, kind):
     rows, cols = size
     rng = np.random.default_rng(rows + cols)
