@@ -17,7 +17,8 @@ peak:
   workloads  the same sweep, compact, for the other configurations (config 2 BERT FFN pair, config 3 encoder linears
              at W4A8 and W8A8, config 4 ResNet convolutions) and for both layouts of dY.
 
-Prints ONE JSON line.
+Prints ONE JSON line, of at most MAX_LINE characters: of the sweep and the other workloads it has times and speedups.
+`--details FILE` writes the whole of it (per-layer and per-class times of every fraction and workload).
 """
 from __future__ import annotations
 
@@ -36,6 +37,7 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0
+MAX_LINE = 7200                # whoever records the output may keep its last 8000 characters only
 
 
 def parse_args():
@@ -60,6 +62,7 @@ def parse_args():
                     help="leave out the compact blocks for the other configurations and the other dY layout")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run a plain device copy of 256 MiB (for scaling rocprofv3 FETCH_SIZE / WRITE_SIZE)")
+    ap.add_argument("--details", default=None, metavar="FILE", help="write the unabridged JSON object there")
     return ap.parse_args()
 
 
@@ -482,6 +485,27 @@ def cpu_baseline(host_data, num, den, a_bits, w_bits):
                        "fp64 NumPy, %.1f s" % (reps, ", ".join(h[0] for h in host_data), num, den, dt))
 
 
+def output_line(out):
+    """The JSON line for stdout: `out` with its sweep and its blocks for other workloads cut to times and speedups; parts of
+    `roofline` that would still make it longer than MAX_LINE are left out, the least needed first."""
+    roofline = dict(out["roofline"])
+    keep = ("r", "k", "ms", "speedup_vs_full", "ideal_speedup")
+    if "sweep" in roofline:
+        roofline["sweep"] = [{n: e[n] for n in keep if n in e} for e in roofline["sweep"]]
+    if "workloads" in roofline:
+        roofline["workloads"] = [dict({n: b[n] for n in ("workload", "step_ms", "tflops", "dx_frac_of_mfma_peak")},
+                                      speedup_vs_full={e["r"]: e["speedup_vs_full"] for e in b["sweep"]})
+                                 for b in roofline["workloads"]]
+    if "extras" in roofline:
+        roofline["extras"] = {n: {a: b for a, b in e.items() if a != "note"} for n, e in roofline["extras"].items()}
+    line = dict(out, roofline=roofline)
+    for part in ("extras", "workloads", "products_per_layer", "sweep", "kernels"):
+        if len(json.dumps(line)) <= MAX_LINE:
+            break
+        roofline.pop(part, None)
+    return json.dumps(line)
+
+
 def main():
     args = parse_args()
     if args.gpus != 1:
@@ -713,7 +737,10 @@ def main():
     # would see its clocks ramp up again
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(host_data, num, den, cfg["a_bits"], w_bits)
-    print(json.dumps(out))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(out, f)
+    print(output_line(out))
 
 
 if __name__ == "__main__":
