@@ -146,6 +146,32 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// Eight columns of one row in the dX epilogue.  a: the product; becomes dX.  xf, cw, mb: x, codes and mask bits (1 = in range).
+// s1 += a gs with gs = in range ? (code - Z) - x / S : code - Z, term by term (in range |gs| <= 1/2); sd += a where clipped.
+// A block's four wavefronts are alone on their SIMDs here and each operation takes four cycles of one: what this costs is
+// the number of operations.  Nearly all values are in range (a per-tensor scale clips some in 10^4 or none), so a chunk in which
+// no lane of the wavefront has a clipped one leaves the mask out: 5 operations an element, 12 with it.  The sums are the same bit
+// for bit; sd takes (s1 - s1) in the end, so that an infinite or undefined a leaves it undefined as a - a did.
+__device__ __forceinline__ void epi_chunk(float (&a)[8], const float (&xf)[8], const uint2& cw, uint32_t mb, float z,
+                                          float ninv_s, float& s1, float& sd) {
+  auto code = [&](int t) { return (float)(((t < 4 ? cw.x : cw.y) >> (8 * (t & 3))) & 0xFFu) - z; };
+  if (__ballot((mb & 0xFFu) != 0xFFu) == 0ull) {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) s1 = fmaf(a[t], fmaf(xf[t], ninv_s, code(t)), s1);
+  } else {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const bool inr = (mb >> t) & 1u;
+      const float q = code(t);
+      const float gs = inr ? fmaf(xf[t], ninv_s, q) : q;
+      s1 = fmaf(a[t], gs, s1);
+      const float o = inr ? a[t] : 0.0f;
+      sd += a[t] - o;
+      a[t] = o;
+    }
+  }
+}
+
 // Fused epilogue of the dX product for a 256-thread block whose wavefront (wm, wn) holds the C::WM x C::WN
 // sub-tile at (m0 + wm * C::WM, n0 + wn * C::WN) of an M x N output in C::TM x C::TN 32x32 MFMA accumulators.
 //   dX = dX_q where the activation was not clipped (straight-through), 0 elsewhere; block partial sums of
@@ -253,7 +279,7 @@ struct EpiDxAny {
   }
   __device__ __forceinline__ void finish(const GemmArgs& g, char* smem, float s1, float sd, int part_idx) {
     const float ps = wave_sum(s1);
-    const float pz = wave_sum(sd);
+    const float pz = wave_sum(sd + (s1 - s1));       // see epi_chunk
     lds_barrier();                                   // staging area is dead: reuse for the block sum
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float* red = reinterpret_cast<float*>(smem);
@@ -323,33 +349,26 @@ struct EpiDxAny {
           }
           const uint32_t xw[8] = {q8.xa[0].x,      q8.xa[0].y,      q8.xa[0].z,      q8.xa[0].w,
                                   q8.xa[XW - 1].x, q8.xa[XW - 1].y, q8.xa[XW - 1].z, q8.xa[XW - 1].w};
-          float o[8];
+          float xf[8];
 #pragma unroll
-          for (int t = 0; t < 8; ++t) {
-            const float xv = XW == 2 ? __uint_as_float(xw[t])
-                                     : __uint_as_float((t & 1) ? xw[t >> 1] & 0xFFFF0000u : xw[t >> 1] << 16);
-            const uint32_t byte = ((t < 4 ? q8.cw.x : q8.cw.y) >> (8 * (t & 3))) & 0xFFu;
-            const bool inr = (mb >> t) & 1u;
-            const float q = (float)byte - z;
-            const float gs = inr ? fmaf(xv, ninv_s, q) : q;
-            s1 = fmaf(a[t], gs, s1);
-            o[t] = inr ? a[t] : 0.0f;
-            sd += a[t] - o[t];
-          }
+          for (int t = 0; t < 8; ++t)
+            xf[t] = XW == 2 ? __uint_as_float(xw[t])
+                            : __uint_as_float((t & 1) ? xw[t >> 1] & 0xFFFF0000u : xw[t >> 1] << 16);
+          epi_chunk(a, xf, q8.cw, mb, z, ninv_s, s1, sd);
           if (g.dx_dtype == EFQAT_F32) {
             float* d = (float*)g.dx + e;
-            if (!EDGE || n >= 8) __builtin_memcpy(d, o, 32);
+            if (!EDGE || n >= 8) __builtin_memcpy(d, a, 32);
             else
 #pragma unroll 1
               for (int t = 0; t < n; ++t) {
-                d[t] = o[0];
+                d[t] = a[0];
 #pragma unroll
-                for (int v = 0; v < 6; ++v) o[v] = o[v + 1];
+                for (int v = 0; v < 6; ++v) a[v] = a[v + 1];
               }
           } else {
             bf16_t* d = (bf16_t*)g.dx + e;
-            uint32_t w[4] = {pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]), pack_bf16x2(o[4], o[5]),
-                             pack_bf16x2(o[6], o[7])};
+            uint32_t w[4] = {pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]),
+                             pack_bf16x2(a[6], a[7])};
             if (!EDGE || n >= 8) __builtin_memcpy(d, w, 16);
             else
 #pragma unroll 1
@@ -459,42 +478,35 @@ struct EpiDxFast {
     float s1 = 0.0f, sd = 0.0f;
 #pragma unroll
     for (int i = 0; i < C::TM; ++i) {
-      if (i > 0) lds_barrier();
+      // a wavefront reads what it wrote itself: no barrier, its own LDS accesses have to be done
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
       for (int j = 0; j < C::TN; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r)
           stage[(8 * (r >> 2) + 4 * fh + (r & 3)) * PITCH + j * 32 + fr] = acc[i][j][r];
-      lds_barrier();
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       float4 n0v, n1v;
       lds_chunk(0, n0v, n1v);
 #pragma unroll
       for (int p = 0; p < NP; ++p) {
-        const float a[8] = {n0v.x, n0v.y, n0v.z, n0v.w, n1v.x, n1v.y, n1v.z, n1v.w};
+        float a[8] = {n0v.x, n0v.y, n0v.z, n0v.w, n1v.x, n1v.y, n1v.z, n1v.w};
         if (p + 1 < NP) lds_chunk(p + 1, n0v, n1v);
         const Inputs q8 = in[p];
         if (i + 1 < C::TM) fetch(i + 1, p);
         const uint32_t xw[4] = {q8.xa.x, q8.xa.y, q8.xa.z, q8.xa.w};
-        float o[8];
+        float xf[8];
 #pragma unroll
-        for (int t = 0; t < 8; ++t) {
-          const float xv = (t & 1) ? __uint_as_float(xw[t >> 1] & 0xFFFF0000u) : __uint_as_float(xw[t >> 1] << 16);
-          const uint32_t byte = ((t < 4 ? q8.cw.x : q8.cw.y) >> (8 * (t & 3))) & 0xFFu;
-          const bool inr = (q8.mb >> (msh + t)) & 1u;
-          const float q = (float)byte - z;
-          const float gs = inr ? fmaf(xv, ninv_s, q) : q;   // term by term: |gs| <= 1/2 in range, no cancellation later
-          s1 = fmaf(a[t], gs, s1);
-          o[t] = inr ? a[t] : 0.0f;
-          sd += a[t] - o[t];
-        }
+        for (int t = 0; t < 8; ++t) xf[t] = __uint_as_float((t & 1) ? xw[t >> 1] & 0xFFFF0000u : xw[t >> 1] << 16);
+        epi_chunk(a, xf, q8.cw, q8.mb >> msh, z, ninv_s, s1, sd);
         *reinterpret_cast<uint4*>(dxp + elem(i, p)) =
-            make_uint4(pack_bf16x2(o[0], o[1]), pack_bf16x2(o[2], o[3]), pack_bf16x2(o[4], o[5]),
-                       pack_bf16x2(o[6], o[7]));
+            make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]),
+                       pack_bf16x2(a[6], a[7]));
         __builtin_amdgcn_sched_barrier(0);            // keeps the passes from piling up in registers
       }
     }
     const float ps = wave_sum(s1);
-    const float pz = wave_sum(sd);
+    const float pz = wave_sum(sd + (s1 - s1));       // see epi_chunk
     lds_barrier();                                   // staging area is dead: reuse for the block sum
     float* red = reinterpret_cast<float*>(smem);
     if (lane == 0) { red[2 * wave] = ps; red[2 * wave + 1] = pz; }
