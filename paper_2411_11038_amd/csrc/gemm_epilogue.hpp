@@ -422,41 +422,62 @@ __device__ __forceinline__ void epilogue_dx(const GemmArgs& g, floatx16_t (&acc)
 // Per lane: s1 = sum a gs with gs = in range ? (code - Z) - x / S : code - Z, formed term by term as in EpiDxAny
 // (in range |gs| <= 1/2, whereas sum a (code - Z) and sum a x / S taken apart would each be some hundred times larger
 // and cancel); sd = sum (a - o) with o = in range ? a : 0.
-template <class C>
+// ALL: the inputs of the whole sub-tile are held in registers, requested a group of rows at a time while the main loop runs
+// (k_gemm_kk); else one slab of them.
+template <class C, bool ALL = false>
 struct EpiDxFast {
   static constexpr int PITCH = C::WN + 8;            // floats; 4*PITCH = 32 (mod 64) banks
   static constexpr int CPR = C::WN / 8;              // 8-column chunks per row
   static constexpr int LPR = (CPR % 8 == 0) ? 8 : 4;
   static_assert(CPR % LPR == 0, "chunks per row");
   static constexpr int KC = CPR / LPR, RP = 64 / LPR, HP = 32 / RP, NP = HP * KC;
-  struct Inputs { uint2 cw; uint4 xa; uint32_t mb; };
-  Inputs in[NP];
+  static constexpr int GROUPS = HP * C::TM;          // groups of RP rows in the sub-tile
+  // a group's loads: the mask words of a row, KC chunks of codes and of x.  No two of them have neighbouring addresses, so they
+  // stay as many instructions as they are here: the waits of a kernel that requests them in its main loop count them.
+  static constexpr int LOADS = LPR == 4 ? 1 + 2 * KC : 3 * KC;
+  struct Inputs { uint32_t mb[KC]; uint2 cw[KC]; uint4 xa[KC]; };
+  Inputs in[ALL ? GROUPS : HP];
   uint32_t un, uwpr, row_b, col_b;
   const uint8_t* codes; const uint32_t* clip; const bf16_t* xp; bf16_t* dxp;
+  float s, zp;
 
-  // element offset of pass p = (h, k) of slab i
-  __device__ __forceinline__ uint32_t elem(int i, int p) const {
-    return (row_b + (uint32_t)(32 * i + RP * (p / KC))) * un + col_b + (uint32_t)(8 * LPR * (p % KC));
+  // element offset of chunk k of the lane's row in group h of slab i
+  __device__ __forceinline__ uint32_t elem(int i, int h, int k) const {
+    return (row_b + (uint32_t)(32 * i + RP * h)) * un + col_b + (uint32_t)(8 * LPR * k);
   }
-  __device__ __forceinline__ void fetch(int i, int p) {
-    const uint32_t row = row_b + (uint32_t)(32 * i + RP * (p / KC));
-    const uint32_t col = col_b + (uint32_t)(8 * LPR * (p % KC));
-    const uint32_t e = row * un + col;
-    in[p].mb = clip[row * uwpr + (col >> 5)];        // shifted at use: no arithmetic on a value still in flight
-    in[p].cw = *reinterpret_cast<const uint2*>(codes + e);
-    in[p].xa = *reinterpret_cast<const uint4*>(xp + e);
+  __device__ __forceinline__ Inputs& inputs(int i, int h) { return in[ALL ? HP * i + h : h]; }
+  __device__ __forceinline__ void fetch(int i, int h) {
+    const uint32_t row = row_b + (uint32_t)(32 * i + RP * h);
+    Inputs& q = inputs(i, h);
+    // shifted at use: no arithmetic on a value still in flight
+    if constexpr (LPR == 4) {                         // chunks 32 columns apart: consecutive words
+      __builtin_memcpy(q.mb, clip + row * uwpr + (col_b >> 5), 4 * KC);
+    } else {
+#pragma unroll
+      for (int k = 0; k < KC; ++k) q.mb[k] = clip[row * uwpr + (col_b >> 5) + (uint32_t)(LPR / 4 * k)];
+    }
+#pragma unroll
+    for (int k = 0; k < KC; ++k) {
+      const uint32_t e = elem(i, h, k);
+      q.cw[k] = *reinterpret_cast<const uint2*>(codes + e);
+      q.xa[k] = *reinterpret_cast<const uint4*>(xp + e);
+    }
   }
-  // Addresses of this wavefront's sub-tile, and the requests for the inputs of its first slab.  A kernel may call
-  // this before its main loop has ended, provided none of its own global -> LDS copies is still outstanding or
-  // issued later (a wavefront's loads complete in order).
-  __device__ __forceinline__ void prefetch(const GemmArgs& g, int m0, int n0, int wm, int wn) {
+  // Addresses of this wavefront's sub-tile, scale and zero point.
+  __device__ __forceinline__ void begin(const GemmArgs& g, int m0, int n0, int wm, int wn) {
     const int lane = threadIdx.x & 63;
     un = (uint32_t)g.N; uwpr = (uint32_t)((g.N + 31) >> 5);
     row_b = (uint32_t)(m0 + wm * C::WM) + (uint32_t)lane / LPR;
     col_b = (uint32_t)(n0 + wn * C::WN) + ((uint32_t)lane % LPR) * 8u;
     codes = g.x_codes; clip = g.x_clip; xp = (const bf16_t*)g.x; dxp = (bf16_t*)g.dx;
+    s = g.s_x[0]; zp = g.z_x[0];
+  }
+  // Requests the inputs of the first slab (ALL: of all slabs).  A kernel may call
+  // this before its main loop has ended, provided none of its own global -> LDS copies is still outstanding or
+  // issued later (a wavefront's loads complete in order).
+  __device__ __forceinline__ void prefetch() {
 #pragma unroll
-    for (int p = 0; p < NP; ++p) fetch(0, p);
+    for (int h = 0; h < (ALL ? GROUPS : HP); ++h) fetch(h / HP, h % HP);
   }
   // The epilogue proper; prefetch() has been called.  smem: at least 4 * 32 * (C::WN + 8) floats, no longer used by
   // the main loop (the caller has synchronised).  part_idx: the tile's slot in g.partial.
@@ -465,11 +486,10 @@ struct EpiDxFast {
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int fr = lane & 31, fh = lane >> 5;
     float* stage = reinterpret_cast<float*>(smem) + wave * 32 * PITCH;
-    const float s = g.s_x[0];
-    const float z = rintf(g.z_x[0]);
+    const float z = rintf(zp);
     const float ninv_s = -1.0f / s;
     const float* st_b = stage + ((uint32_t)lane / LPR) * PITCH + ((uint32_t)lane % LPR) * 8;
-    auto lds_chunk = [&](int p, float4& a0, float4& a1) {
+    auto lds_chunk = [&](int p, float4& a0, float4& a1) {   // pass p: chunk p % KC of group p / KC
       a0 = *reinterpret_cast<const float4*>(st_b + RP * (p / KC) * PITCH + 8 * LPR * (p % KC));
       a1 = *reinterpret_cast<const float4*>(st_b + RP * (p / KC) * PITCH + 8 * LPR * (p % KC) + 4);
     };
@@ -492,14 +512,17 @@ struct EpiDxFast {
       for (int p = 0; p < NP; ++p) {
         float a[8] = {n0v.x, n0v.y, n0v.z, n0v.w, n1v.x, n1v.y, n1v.z, n1v.w};
         if (p + 1 < NP) lds_chunk(p + 1, n0v, n1v);
-        const Inputs q8 = in[p];
-        if (i + 1 < C::TM) fetch(i + 1, p);
-        const uint32_t xw[4] = {q8.xa.x, q8.xa.y, q8.xa.z, q8.xa.w};
+        const int h = p / KC, k = p % KC;
+        const Inputs& q8 = inputs(i, h);
+        const uint32_t xw[4] = {q8.xa[k].x, q8.xa[k].y, q8.xa[k].z, q8.xa[k].w};
+        const uint2 cw = q8.cw[k];
+        const uint32_t mb = q8.mb[k] >> msh;
         float xf[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) xf[t] = __uint_as_float((t & 1) ? xw[t >> 1] & 0xFFFF0000u : xw[t >> 1] << 16);
-        epi_chunk(a, xf, q8.cw, q8.mb >> msh, z, ninv_s, s1, sd);
-        *reinterpret_cast<uint4*>(dxp + elem(i, p)) =
+        if (!ALL && k == KC - 1 && i + 1 < C::TM) fetch(i + 1, h);
+        epi_chunk(a, xf, cw, mb, z, ninv_s, s1, sd);
+        *reinterpret_cast<uint4*>(dxp + elem(i, h, k)) =
             make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]),
                        pack_bf16x2(a[6], a[7]));
         __builtin_amdgcn_sched_barrier(0);            // keeps the passes from piling up in registers
@@ -522,7 +545,8 @@ template <class C>
 __device__ __forceinline__ void epilogue_dx_fast(const GemmArgs& g, floatx16_t (&acc)[C::TM][C::TN], char* smem,
                                                  int m0, int n0, int wm, int wn, int part_idx) {
   EpiDxFast<C> e;
-  e.prefetch(g, m0, n0, wm, wn);
+  e.begin(g, m0, n0, wm, wn);
+  e.prefetch();
   e.run(g, acc, smem, part_idx);
 }
 

@@ -220,10 +220,13 @@ __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::typ
   // end of a stage: the copies of the next stage have landed (the LPS copies issued after them, which belong to
   // the stage after next, may still be in flight), every wavefront is done reading this stage's buffer
   // `tail`: one of the last two stages - every copy landed before it began and none is issued any more
-  auto stage_sync = [&](auto steadyc, bool tail) {
+  // `more`: loads issued since the last copy of the next stage, besides the copies
+  auto stage_sync = [&](auto steadyc, auto morec, bool tail) {
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (decltype(steadyc)::value) {
-      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LPS) : "memory");   // the LPS copies issued since stay in flight
+      constexpr int N = LPS + decltype(morec)::value;
+      static_assert(N < 64, "the counter has six bits");
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");   // what was issued since stays in flight
     } else if (tail) {
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     } else {
@@ -253,18 +256,38 @@ __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::typ
   };
 
   // the fused dX epilogue
-  typename std::conditional<EPI == EPI_DXF, EpiDxFast<C>,
+  typename std::conditional<EPI == EPI_DXF, EpiDxFast<C, true>,
                             EpiDxAny<C, typename std::conditional<EPI == EPI_DXS, float, bf16_t>::type, CONV == 2>>::type epi;
   const int m_end = CONV == 2 ? ph.rows : g.M;
   const bool edge = m0 + C::BM > m_end || n0 + C::BN > g.N;
   int* rowmap = reinterpret_cast<int*>(smem + C::template lds_bytes<EPI>());   // CONV = 2: the matrix row of every tile row
   const int kt_epi = nk >= 2 ? nk - 2 : 0;            // the first of the last two stages
+  bool peel = false;                                  // EPI_DXF: long enough to request the epilogue's inputs in the first stages
+  if constexpr (EPI == EPI_DXF) {
+    peel = nfull >= 9;                                // peeled stages are steady ones: kt + 3 < nfull
+    epi.begin(g, m0, n0, wm, wn);
+  }
 
   // ---- main loop.  Stage kt lives in buffer kt % 3.  On entry to stage kt the first P0 copies of stage kt + 2 have
   // been issued if and only if that stage is a full one (kt + 2 < nfull); both variants keep this true for kt + 1.
-  auto stage = [&](auto bufc, auto steadyc, int kt) {
+  //
+  // EPI_DXF: the first PEEL stages also request the epilogue's inputs, RG_S groups of rows each, behind the stage's copies.  They
+  // come out of HBM while the matrix cores work and are waited for one stage later than the copies before them.
+  constexpr int PEEL = 6;
+  // the requests of peeled stage ps, then its end
+  auto request_and_sync = [&](auto& e, auto psc) {
+    using E = typename std::remove_reference<decltype(e)>::type;
+    constexpr int PS = decltype(psc)::value;
+    constexpr int G0 = PS > 0 ? (PS - 1) * E::GROUPS / PEEL : 0, G1 = PS * E::GROUPS / PEEL, G2 = (PS + 1) * E::GROUPS / PEEL;
+    asm volatile("" ::: "memory");                    // behind the copies: stage_sync counts on this order
+#pragma unroll
+    for (int q = G1; q < G2; ++q) e.fetch(q / E::HP, q % E::HP);
+    stage_sync(std::integral_constant<bool, true>{}, std::integral_constant<int, E::LOADS * (G2 - G0)>{}, false);
+  };
+  auto stage = [&](auto bufc, auto steadyc, int kt, auto peelc) {
     constexpr int cur = decltype(bufc)::value;
     constexpr bool ST = decltype(steadyc)::value;
+    constexpr int PS = decltype(peelc)::value;        // peeled stage, -1: none
     constexpr int nxt = (cur + 1) % C::NST, nn = (cur + 2) % C::NST;
     using Next = std::integral_constant<int, nxt>;
     if constexpr (ST) {              // kt + 3 < nfull
@@ -272,7 +295,8 @@ __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::typ
       substep(bufc, 1, 0, kt + 2, nn, P0, P0 + P1);
       substep(bufc, 2, 1, kt + 2, nn, P0 + P1, P0 + P1 + P2);
       substep(bufc, 3, 0, kt + 2, nn, P0 + P1 + P2, LPS);
-      stage_sync(steadyc, false);
+      if constexpr (PS >= 0) request_and_sync(epi, peelc);
+      else stage_sync(steadyc, std::integral_constant<int, 0>{}, false);
       substep(Next{}, 0, 1, kt + 3, cur, 0, P0);
     } else {
       const bool more1 = kt + 1 < nk;
@@ -282,7 +306,7 @@ __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::typ
       if (kt + 2 < nfull) issue_range(Unchecked{}, kt + 2, nn, P0, LPS);
       else if (kt + 2 < nk) issue_range(Checked{}, kt + 2, nn, 0, LPS);
       if (kt == kt_epi) {
-        if constexpr (EPI == EPI_DXF) epi.prefetch(g, m0, n0, wm, wn);
+        if constexpr (EPI == EPI_DXF) { if (!peel) epi.prefetch(); }
         else epi.prefetch(g, m0, n0, wm, wn, m_end, edge, rowmap);
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -294,7 +318,7 @@ __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::typ
       __builtin_amdgcn_sched_barrier(0);
       load_frags(bufc, 3, 1);
       mfma_all(0);
-      stage_sync(steadyc, tail);
+      stage_sync(steadyc, std::integral_constant<int, 0>{}, tail);
       if (more1) load_frags(Next{}, 0, 0);
       if (kt + 3 < nfull) issue_range(Unchecked{}, kt + 3, cur, 0, P0);
       mfma_all(1);
@@ -323,15 +347,27 @@ __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::typ
   if (2 < nfull) issue_range(Unchecked{}, 2, 2, 0, P0);
   if (nk > 0) load_frags(B0{}, 0, 0);
   int kt = 0;
+  using No = std::integral_constant<int, -1>;
+  if constexpr (EPI == EPI_DXF) {
+    if (peel) {
+      stage(B0{}, Steady{}, 0, std::integral_constant<int, 0>{});
+      stage(B1{}, Steady{}, 1, std::integral_constant<int, 1>{});
+      stage(B2{}, Steady{}, 2, std::integral_constant<int, 2>{});
+      stage(B0{}, Steady{}, 3, std::integral_constant<int, 3>{});
+      stage(B1{}, Steady{}, 4, std::integral_constant<int, 4>{});
+      stage(B2{}, Steady{}, 5, std::integral_constant<int, 5>{});
+      kt = PEEL;
+    }
+  }
   for (; kt + 5 < nfull; kt += 3) {
-    stage(B0{}, Steady{}, kt);
-    stage(B1{}, Steady{}, kt + 1);
-    stage(B2{}, Steady{}, kt + 2);
+    stage(B0{}, Steady{}, kt, No{});
+    stage(B1{}, Steady{}, kt + 1, No{});
+    stage(B2{}, Steady{}, kt + 2, No{});
   }
   for (; kt < nk; kt += 3) {
-    stage(B0{}, Drain{}, kt);
-    if (kt + 1 < nk) stage(B1{}, Drain{}, kt + 1);
-    if (kt + 2 < nk) stage(B2{}, Drain{}, kt + 2);
+    stage(B0{}, Drain{}, kt, No{});
+    if (kt + 1 < nk) stage(B1{}, Drain{}, kt + 1, No{});
+    if (kt + 2 < nk) stage(B2{}, Drain{}, kt + 2, No{});
   }
   __syncthreads();
 
