@@ -28,6 +28,22 @@ __device__ __forceinline__ void load8<bf16_t>(const bf16_t* p, float (&v)[8]) {
   }
 }
 
+// the same at any element alignment, which the hardware takes for vector accesses
+template <typename T>
+__device__ __forceinline__ void load8_any(const T* p, float (&v)[8]) {
+  if constexpr (sizeof(T) == 4) {
+    __builtin_memcpy(v, p, 32);
+  } else {
+    uint32_t w[4];
+    __builtin_memcpy(w, p, 16);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[2 * i] = __uint_as_float(w[i] << 16);
+      v[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
+    }
+  }
+}
+
 // ----------------------------------------------------------------------------------------------
 // Eq. 2 range: alpha = min x, beta = max x over the whole tensor (MinMax observer).
 constexpr int kMaxParts = 1024;
@@ -130,13 +146,15 @@ __device__ __forceinline__ float round_quotient(float x, float s, float inv_s) {
 // ----------------------------------------------------------------------------------------------
 // Eq. 1 / Eq. 3: codes + clip-mask bits (+ optional de-quantised bf16 values).
 // One wavefront handles one 512-element segment of one row per iteration; a lane owns 8
-// consecutive elements, four neighbouring lanes assemble one 32-bit mask word.
+// consecutive elements, four neighbouring lanes assemble one 32-bit mask word.  Rows of any length and alignment: whole chunks are
+// one vector access, only the one that ends a row is read and written by elements.  With an access per element unless rows were
+// aligned and of whole chunks it took, codes alone / with the range, us: 12000 x 7777 fp32 215 / 282 (now 97 / 161), bf16 161 / 152
+// (68 / 96), 3000 x 12001 fp32 76 / 101 (29 / 54), 2049 x 777 fp32 6.3 / 10.0 (4.5 / 8.4), 20000 x 7 the same.
 // Activations: part, when given, are the partial ranges that scale and zero point are made from here.
 // INIT (weights only): the wavefront first takes the row's abs-max and writes its Eq. 4 scale
 // S_w[c] = max_j |w[c][j]| / (2^(b-1) - 1), then quantizes the row it has just pulled through the caches.
 template <typename T, int MODE, bool INIT>
-__global__ __launch_bounds__(256) void k_quantize(const T* __restrict__ x, int64_t rows, int64_t cols, int vec,
-                                                  int bits, float* __restrict__ scale,
+__global__ __launch_bounds__(256) void k_quantize(const T* __restrict__ x, int64_t rows, int64_t cols, int bits, float* __restrict__ scale,
                                                   float* __restrict__ zp, uint8_t* __restrict__ codes,
                                                   uint32_t* __restrict__ clip, bf16_t* __restrict__ xq,
                                                   const float* __restrict__ part, int nparts) {
@@ -166,17 +184,14 @@ __global__ __launch_bounds__(256) void k_quantize(const T* __restrict__ x, int64
    if (INIT) {
      const T* p = x + row * cols;
      float m = 0.0f;
-     if (vec) {
-       const int64_t n8 = cols >> 3;
-       for (int64_t i = lane; i < n8; i += 64) {
-         float t8[8];
-         load8<T>(p + i * 8, t8);
+     const int64_t n8 = cols >> 3;
+     for (int64_t i = lane; i < n8; i += 64) {
+       float t8[8];
+       load8_any<T>(p + i * 8, t8);
 #pragma unroll
-         for (int j = 0; j < 8; ++j) m = fmaxf(m, fabsf(t8[j]));
-       }
-     } else {
-       for (int64_t i = lane; i < cols; i += 64) m = fmaxf(m, fabsf(load_as_f32<T>(p, i)));
+       for (int j = 0; j < 8; ++j) m = fmaxf(m, fabsf(t8[j]));
      }
+     for (int64_t i = n8 * 8 + lane; i < cols; i += 64) m = fmaxf(m, fabsf(load_as_f32<T>(p, i)));
      m = wave_max(m);
      s_row = __fdiv_rn(m, hi);
      if (!(s_row > 0.0f)) s_row = 1.0f;             // all-zero row
@@ -192,8 +207,8 @@ __global__ __launch_bounds__(256) void k_quantize(const T* __restrict__ x, int64
     const int64_t base = row * cols + col0;
     float v[8];
     const bool full = col0 + 8 <= cols;
-    if (vec && full) {
-      load8<T>(x + base, v);
+    if (full) {
+      load8_any<T>(x + base, v);
     } else {
 #pragma unroll
       for (int j = 0; j < 8; ++j) v[j] = (col0 + j < cols) ? load_as_f32<T>(x, base + j) : 0.0f;
@@ -213,12 +228,12 @@ __global__ __launch_bounds__(256) void k_quantize(const T* __restrict__ x, int64
         cw[j >> 2] |= ((uint32_t)((int)cc & 0xFF)) << (8 * (j & 3));
       dq[j] = s * (cc - z);
     }
-    if (vec && full) {
-      *reinterpret_cast<uint2*>(codes + base) = make_uint2(cw[0], cw[1]);
+    if (full) {
+      __builtin_memcpy(codes + base, cw, 8);
       if (xq) {
-        uint4 o = make_uint4(pack_bf16x2(dq[0], dq[1]), pack_bf16x2(dq[2], dq[3]),
-                             pack_bf16x2(dq[4], dq[5]), pack_bf16x2(dq[6], dq[7]));
-        *reinterpret_cast<uint4*>(xq + base) = o;
+        const uint32_t o[4] = {pack_bf16x2(dq[0], dq[1]), pack_bf16x2(dq[2], dq[3]), pack_bf16x2(dq[4], dq[5]),
+                               pack_bf16x2(dq[6], dq[7])};
+        __builtin_memcpy(xq + base, o, 16);
       }
     } else {
 #pragma unroll
@@ -448,10 +463,9 @@ static int run_fakequant(const T* x, int64_t rows, int64_t cols, int mode, int b
   int64_t blocks = ceil_div(items, 4);
   const bool flat = mode == EFQAT_QUANT_ACT_PER_TENSOR_ASYM && vec_row && (cols % 32) == 0;
   // Ragged rows with the range to make: two rounds of the blocks that are resident at a time.  19584 x 1496 bf16 34.9 us (8192
-  // blocks 38.2, a launch for the range and 8192 blocks 35.4), 16384 x 1000 fp32 29.4 (32.4, 30.9), 12000 x 7777 bf16 154 (156,
-  // 155).  Many short segments: there is too little work behind the range in a block to repay it, and more blocks balance better,
-  // so a block of its own makes it.  us so / in every block: 100000 x 100 fp32 49.6 / 51.4, 20000 x 7 bf16 16.1 / 16.7, 7500 x 513
-  // (256.5 of 512 values a segment) 14.7 / 15.6, 13184 x 64 13.9 / 14.8, but 10000 x 64 13.2 / 12.8, 36000 x 300 31.1 / 29.8.
+  // blocks 38.2, a launch for the range and 8192 blocks 35.4), 16384 x 1000 fp32 29.4 (32.4, 30.9).  Many short segments: there is too little work behind the range in a block to repay it, and more blocks balance better,
+  // so a block of its own makes it.  us so / in every block: 100000 x 100 fp32 49.6 / 51.4, 20000 x 7 bf16 16.1 / 16.7,
+  // 13184 x 64 13.9 / 14.8, but 10000 x 64 13.2 / 12.8, 36000 x 300 31.1 / 29.8.
   if (part && !flat && blocks > 256 * 10 && n < 280 * items) {
     hipLaunchKernelGGL(k_act_qparams, dim3(1), dim3(256), 0, st, part, nparts, bits, scale, zp);
     EFQAT_LAUNCH_CHECK();
@@ -477,7 +491,7 @@ static int run_fakequant(const T* x, int64_t rows, int64_t cols, int mode, int b
                          (uint8_t*)codes, clip, xq, part, nparts);
   } else if (mode == EFQAT_QUANT_ACT_PER_TENSOR_ASYM)
     hipLaunchKernelGGL((k_quantize<T, EFQAT_QUANT_ACT_PER_TENSOR_ASYM, false>), dim3((unsigned)blocks), dim3(256), 0,
-                       st, x, rows, cols, vec_row, bits, scale, zp, (uint8_t*)codes, clip, xq, part, nparts);
+                       st, x, rows, cols, bits, scale, zp, (uint8_t*)codes, clip, xq, part, nparts);
   // (a grid dimension holds less than 2^32 work items)
   else if ((init_minmax || scores) && std::is_same<T, float>::value && cols <= 8 * 64 * 4 * 8 && !xq &&
            rows < (wide ? 1 << 24 : 1 << 26)) {
@@ -506,10 +520,10 @@ static int run_fakequant(const T* x, int64_t rows, int64_t cols, int mode, int b
     if (scores && scores_done) *scores_done = true;
   } else if (init_minmax)
     hipLaunchKernelGGL((k_quantize<T, EFQAT_QUANT_W_PER_ROW_SYM, true>), dim3((unsigned)blocks), dim3(256), 0, st, x,
-                       rows, cols, vec_row, bits, scale, zp, (uint8_t*)codes, clip, xq, nullptr, 0);
+                       rows, cols, bits, scale, zp, (uint8_t*)codes, clip, xq, nullptr, 0);
   else
     hipLaunchKernelGGL((k_quantize<T, EFQAT_QUANT_W_PER_ROW_SYM, false>), dim3((unsigned)blocks), dim3(256), 0, st, x,
-                       rows, cols, vec_row, bits, scale, zp, (uint8_t*)codes, clip, xq, nullptr, 0);
+                       rows, cols, bits, scale, zp, (uint8_t*)codes, clip, xq, nullptr, 0);
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
 }
