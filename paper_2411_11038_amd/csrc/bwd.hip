@@ -60,7 +60,7 @@ __device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int
                                                 int64_t ld_in, int64_t R, int64_t Cn, const int32_t* __restrict__ colmap,
                                                 const float* __restrict__ rowscale, const float* __restrict__ subz,
                                                 bf16_t* __restrict__ out, int64_t ldo, int64_t out_off, int64_t i_pad,
-                                                int vec, const TransposeExtra& ex) {
+                                                const TransposeExtra& ex) {
   const int64_t i0 = (int64_t)bx * 64, j0 = (int64_t)by * 64;
   const float sub = subz ? rintf(subz[0]) : 0.0f;
   in += (int64_t)tap * ex.z_in;
@@ -79,40 +79,50 @@ __device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int
     if (h < 0 || h >= g.H || w < 0 || w >= g.W) return -1;
     return ((int64_t)n * g.H + h) * g.W + w;
   };
-  if (vec && j0 + 64 <= Cn) {
-    // dense source, 4 consecutive columns per lane (one 4..16-byte load)
+  if (!colmap) {
+    // dense source, 4 consecutive columns per lane: one load of 4 to 16 bytes at any alignment, but for the chunk that ends a row
     const int jq = (threadIdx.x & 15) * 4, ib = threadIdx.x >> 4;
+    const int64_t left = Cn - j0 - jq;
+    float v[4][4];
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) {
+      const int64_t si = src_row(i0 + ib + 16 * rr);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[rr][t] = sub;
+      if (si >= 0 && left >= 4) {
+        typename Vec4<T>::type raw;
+        __builtin_memcpy(&raw, in + si * ld_in + j0 + jq, 4 * sizeof(T));
+        if constexpr (sizeof(T) == 1) unpack4b<T>(raw, v[rr]); else unpack4(raw, v[rr]);
+      } else if (si >= 0) {
+#pragma unroll
+        for (int t = 0; t < 3; ++t)
+          if (t < left) v[rr][t] = rd<T>(in, si * ld_in + j0 + jq + t);
+      }
+    }
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) {
       const int li = ib + 16 * rr;
-      const int64_t i = i0 + li;
-      const int64_t si = src_row(i);
-      float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (si >= 0) {
-        const typename Vec4<T>::type raw = *reinterpret_cast<const typename Vec4<T>::type*>(in + si * ld_in + j0 + jq);
-        if constexpr (sizeof(T) == 1) unpack4b<T>(raw, v); else unpack4(raw, v);
-        const float rs = rowscale ? rowscale[i] : 1.0f;
+      const float rs = rowscale && i0 + li < R ? rowscale[i0 + li] : 1.0f;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = (v[t] - sub) * rs;
-      }
-      *reinterpret_cast<uint32_t*>(&tile[li][jq]) = pack_bf16x2(v[0], v[1]);
-      *reinterpret_cast<uint32_t*>(&tile[li][jq + 2]) = pack_bf16x2(v[2], v[3]);
+      for (int t = 0; t < 4; ++t) v[rr][t] = (v[rr][t] - sub) * rs;
+      *reinterpret_cast<uint32_t*>(&tile[li][jq]) = pack_bf16x2(v[rr][0], v[rr][1]);
+      *reinterpret_cast<uint32_t*>(&tile[li][jq + 2]) = pack_bf16x2(v[rr][2], v[rr][3]);
     }
   } else {
     const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     const int64_t j = j0 + tx;
-    const int64_t jc = (j < Cn) ? (colmap ? (int64_t)colmap[j] : j) : 0;
-#pragma unroll 4
+    const int64_t jc = j < Cn ? (int64_t)colmap[j] : 0;
+    float v[16];                                       // all in flight
+#pragma unroll
+    for (int rr = 0; rr < 16; ++rr) {
+      const int64_t si = src_row(i0 + ty + 4 * rr);
+      v[rr] = si >= 0 && j < Cn ? rd<T>(in, si * ld_in + jc) : sub;
+    }
+#pragma unroll
     for (int rr = 0; rr < 16; ++rr) {
       const int li = ty + 4 * rr;
-      const int64_t i = i0 + li;
-      const int64_t si = src_row(i);
-      float v = 0.0f;
-      if (si >= 0 && j < Cn) {
-        v = rd<T>(in, si * ld_in + jc) - sub;
-        if (rowscale) v *= rowscale[i];
-      }
-      tile[li][tx] = f32_to_bf16(v);
+      const float rs = rowscale && i0 + li < R ? rowscale[i0 + li] : 1.0f;
+      tile[li][tx] = f32_to_bf16((v[rr] - sub) * rs);
     }
   }
   __syncthreads();
@@ -137,28 +147,38 @@ __device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int
 struct RowCut { uint32_t segs, cols; };
 
 // Row-wise cast/copy to bf16 with zero-padded pitch: out[m][j] = bf16(in[rm(m)][j]), j < Cn; 0 up to ldo (a multiple of
-// 8).  flat == 1: no padding, no row map and 16-byte aligned rows, i.e. one run of 8-element chunks; flat = 2 .. 64, a power
-// of two: aligned rows of whole chunks with a padded pitch, that many lanes to a row; 0: a wavefront per row segment, two
-// elements per lane and step.  block b of nb.
+// 8), a chunk of 8 a lane: one or two 16-byte loads at any alignment, but for the chunk that ends a row.  flat == 1: no
+// padding and no row map, i.e. one run of chunks; flat = 2 .. 64, a power of two: that many lanes to a row; 0: a wavefront
+// per row segment.  block b of nb.
 template <typename T>
 __device__ __forceinline__ void rows_block(int64_t b, int64_t nb, const T* __restrict__ in, int64_t ld_in, int64_t R,
                                            int64_t Cn, const int32_t* __restrict__ rowmap, bf16_t* __restrict__ out,
                                            int64_t ldo, int flat, const RowCut& cut) {
   auto chunk = [](const T* src, bf16_t* dst) {
+    uint32_t w[4];
     if constexpr (sizeof(T) == 4) {
-      const float4 p = *reinterpret_cast<const float4*>(src), q = *reinterpret_cast<const float4*>(src + 4);
-      *reinterpret_cast<uint4*>(dst) =
-          make_uint4(pack_bf16x2(p.x, p.y), pack_bf16x2(p.z, p.w), pack_bf16x2(q.x, q.y), pack_bf16x2(q.z, q.w));
+      float f[8];
+      __builtin_memcpy(f, src, 32);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) w[t] = pack_bf16x2(f[2 * t], f[2 * t + 1]);
     } else {
-      *reinterpret_cast<uint4*>(dst) = *reinterpret_cast<const uint4*>(src);
+      __builtin_memcpy(w, src, 16);
     }
+    *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
+  };
+  auto chunk_end = [](const T* src, int64_t n, bf16_t* dst) {   // of n < 8 values, then zeros
+    float f[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) f[t] = t < n ? rd<T>(src, t) : 0.0f;
+    *reinterpret_cast<uint4*>(dst) =
+        make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
   };
   if (flat > 1) {
     const int sub = threadIdx.x & (flat - 1), per = 256 / flat;
     for (int64_t m = b * per + threadIdx.x / flat; m < R; m += nb * per)
       for (int64_t j = 8 * sub; j < ldo; j += 8 * flat) {
-        if (j < Cn) chunk(in + m * ld_in + j, out + m * ldo + j);
-        else *reinterpret_cast<uint4*>(out + m * ldo + j) = make_uint4(0, 0, 0, 0);
+        if (j + 8 <= Cn) chunk(in + m * ld_in + j, out + m * ldo + j);
+        else chunk_end(in + m * ld_in + j, Cn - j, out + m * ldo + j);
       }
     return;
   }
@@ -174,9 +194,9 @@ __device__ __forceinline__ void rows_block(int64_t b, int64_t nb, const T* __res
     const int64_t s1 = s0 + cut.cols < ldo ? s0 + cut.cols : ldo;
     const T* src = in + (rowmap ? (int64_t)rowmap[m] : m) * ld_in;
 #pragma unroll 4
-    for (int64_t j = s0 + 2 * lane; j < s1; j += 128) {
-      const float v0 = j < Cn ? rd<T>(src, j) : 0.0f, v1 = j + 1 < Cn ? rd<T>(src, j + 1) : 0.0f;
-      *reinterpret_cast<uint32_t*>(out + m * ldo + j) = pack_bf16x2(v0, v1);
+    for (int64_t j = s0 + 8 * lane; j < s1; j += 512) {
+      if (j + 8 <= Cn) chunk(src + j, out + m * ldo + j);
+      else chunk_end(src + j, Cn - j, out + m * ldo + j);
     }
   }
 }
@@ -230,13 +250,13 @@ struct PrepArgs {
   bf16_t* dyn; int rows_flat;                                       // copy of a token-major dY
   RowCut rows_cut, sel_cut;                                         // of that copy, and of the selected rows
   int64_t c_in, w_ld, w_ldo;                                        // W_q^T
-  const int8_t* w_codes; const float* s_w; bf16_t* wqT; int w_vec;
+  const int8_t* w_codes; const float* s_w; bf16_t* wqT;
   TransposeExtra w_ex;
   uint32_t* zero_page;                                              // optional: the 256 zero bytes a made operand ends in
   const uint8_t* x_codes; const float* z_x; bf16_t* xcT;            // (codes - Z_x)^T
-  int64_t ldt; int x_vec;
+  int64_t ldt;
   TransposeExtra x_ex;
-  int chan, dyn_vec;                                                // dY is channel major; transposed to dyn
+  int chan;                                                         // dY is channel major; transposed to dyn
   uint32_t gather_x, w_x, w_y, x_x, x_y, sel_x, dyn_x;             // blocks along the first axes of a part
   uint32_t n_gather, n_rows, n_w, n_x, n_sel, n_dyn;
 };
@@ -259,13 +279,13 @@ __global__ __launch_bounds__(256) void k_prep(const PrepArgs p) {
     if (p.zero_page && b == 0 && threadIdx.x < 64) p.zero_page[threadIdx.x] = 0u;
     // wqT[ci][tap ldc + co] = S_w[co] code[co][tap][ci]
     transpose_block<int8_t>(tile, b % p.w_x, (b / p.w_x) % p.w_y, b / (p.w_x * p.w_y), p.w_codes, p.w_ld, p.c_out, p.c_in,
-                            nullptr, p.s_w, nullptr, p.wqT, p.w_ldo, 0, p.ldc, p.w_vec, p.w_ex);
+                            nullptr, p.s_w, nullptr, p.wqT, p.w_ldo, 0, p.ldc, p.w_ex);
     return;
   }
   b -= p.n_w;
   if (b < p.n_x) {                                     // xcT[(tap, ci)][t] = code - Z_x of the input pixel
     transpose_block<uint8_t>(tile, b % p.x_x, (b / p.x_x) % p.x_y, b / (p.x_x * p.x_y), p.x_codes, p.c_in, p.t_out, p.c_in,
-                             nullptr, nullptr, p.z_x, p.xcT, p.ldt, 0, p.ldt, p.x_vec, p.x_ex);
+                             nullptr, nullptr, p.z_x, p.xcT, p.ldt, 0, p.ldt, p.x_ex);
     return;
   }
   b -= p.n_x;
@@ -274,13 +294,13 @@ __global__ __launch_bounds__(256) void k_prep(const PrepArgs p) {
     if (p.chan) rows_block<T>(b, p.n_sel, dy, p.t_out, p.k, p.t_out, p.idx, p.sel, p.ldt, 0, p.sel_cut);
     else
       transpose_block<T>(tile, b % p.sel_x, b / p.sel_x, 0, dy, p.c_out, p.t_out, p.k, p.idx, nullptr, nullptr, p.sel,
-                         p.ldt, 0, p.ldt, 0, none);
+                         p.ldt, 0, p.ldt, none);
     return;
   }
   b -= p.n_sel;
   if (b < p.n_dyn)                                     // channel-major [c_out][t_out] -> [t_out][ldc]
     transpose_block<T>(tile, b % p.dyn_x, b / p.dyn_x, 0, dy, p.t_out, p.c_out, p.t_out, nullptr, nullptr, nullptr, p.dyn,
-                       p.ldc, 0, p.ldc, p.dyn_vec, none);
+                       p.ldc, 0, p.ldc, none);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -501,13 +521,13 @@ static inline unsigned grid1d(int64_t total) {
 // all selected: backward call 34.8 us, by k_prep 35.9 us; 4096 x 1024 -> 1024, nothing selected: 20.6, 21.3 us.
 __global__ __launch_bounds__(256) void k_prep_w(const int8_t* __restrict__ w_codes, int64_t w_ld, int64_t c_out, int64_t c_in,
                                                 const float* __restrict__ s_w, bf16_t* __restrict__ wqT, int64_t w_ldo,
-                                                int64_t ldc, int w_vec, uint32_t* __restrict__ zero_page) {
+                                                int64_t ldc, uint32_t* __restrict__ zero_page) {
   __shared__ TransposeTile tile;
   if (zero_page && (blockIdx.x | blockIdx.y | blockIdx.z) == 0 && threadIdx.x < 64) zero_page[threadIdx.x] = 0u;
   TransposeExtra ex{};
   ex.z_in = c_in; ex.z_out = ldc;
   transpose_block<int8_t>(tile, blockIdx.x, blockIdx.y, blockIdx.z, w_codes, w_ld, c_out, c_in, nullptr, s_w, nullptr, wqT,
-                          w_ldo, 0, ldc, w_vec, ex);
+                          w_ldo, 0, ldc, ex);
 }
 
 static uint32_t cut_rows(int64_t rows, int64_t ldo, RowCut* cut) {   // returns the blocks
@@ -522,7 +542,7 @@ static int launch_prep(const PrepArgs& a, int dy_dtype, hipStream_t st) {
   if (blocks == 0) return EFQAT_OK;
   if (blocks == a.n_w && a.w_y <= 65535) {
     hipLaunchKernelGGL(k_prep_w, dim3(a.w_x, a.w_y, a.n_w / (a.w_x * a.w_y)), dim3(256), 0, st, a.w_codes, a.w_ld, a.c_out,
-                       a.c_in, a.s_w, a.wqT, a.w_ldo, a.ldc, a.w_vec, a.zero_page);
+                       a.c_in, a.s_w, a.wqT, a.w_ldo, a.ldc, a.zero_page);
     EFQAT_LAUNCH_CHECK();
     return EFQAT_OK;
   }
@@ -540,7 +560,6 @@ static void prep_w_operand(PrepArgs& a, const int8_t* w_codes, const float* s_w,
   a.w_codes = w_codes; a.s_w = s_w; a.wqT = wqT; a.c_in = c_in; a.c_out = c_out; a.ldc = ldc;
   a.w_ld = (int64_t)taps * c_in; a.w_ldo = (int64_t)taps * ldc;
   a.w_ex.z_in = c_in; a.w_ex.z_out = ldc;
-  a.w_vec = ((c_in % 4) == 0 && ((uintptr_t)w_codes % 4) == 0) ? 1 : 0;
   a.w_x = (uint32_t)ceil_div(ldc, 64); a.w_y = (uint32_t)ceil_div(c_in, 64);
   a.n_w = a.w_x * a.w_y * (uint32_t)taps;
 }
@@ -801,12 +820,11 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   if (copy_dy) {
     // dY as a token-major bf16 matrix [T_out][ldc] (A operand of the dX product)
     a.rows_flat = p.ldc == c_out ? 1 : 0;
-    if (!a.rows_flat && (c_out % 8) == 0)
+    if (!a.rows_flat && ((c_out % 8) == 0 || p.ldc <= 512))
       for (a.rows_flat = 2; a.rows_flat < 64 && a.rows_flat < p.ldc / 8;) a.rows_flat *= 2;
     const int64_t nb = a.rows_flat ? ceil_div(T_out * p.ldc, 256 * 16) : cut_rows(T_out, p.ldc, &a.rows_cut);
     a.n_rows = (uint32_t)std::min<int64_t>(nb, 4096);
   } else if (p.need_dyn) {
-    a.dyn_vec = ((T_out % 4) == 0) ? 1 : 0;            // dY is 16-byte aligned
     a.dyn_x = (uint32_t)ceil_div(p.ldc, 64);
     a.n_dyn = a.dyn_x * (uint32_t)ceil_div(T_out, 64);
   }
@@ -814,7 +832,6 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   if (stage_dw) {
     a.x_codes = io.x_codes; a.z_x = io.z_x; a.xcT = xcT;
     if (im2col) { a.x_ex.z_orow = c_in; a.x_ex.conv = 1; a.x_ex.g = *cg; }
-    a.x_vec = ((c_in % 4) == 0 && ((uintptr_t)io.x_codes % 4) == 0) ? 1 : 0;
     a.x_x = (uint32_t)ceil_div(p.ldt, 64); a.x_y = (uint32_t)ceil_div(c_in, 64);
     a.n_x = a.x_x * a.x_y * (uint32_t)(im2col ? taps : 1);
     if (p.need_sel) {
