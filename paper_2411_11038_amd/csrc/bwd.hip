@@ -4,6 +4,7 @@
 #include "gemm_epilogue.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace efqat {
 
@@ -377,11 +378,15 @@ struct StepArgs {
 // Second pass of the restricted weight gradient: ordered split-K sum, S_x scaling, straight-through mask
 // of the weight quantizer and the per-row scale gradient
 //   dW[c][j] = in range ? dW_q : 0,  dS_w[c] = sum_j dW_q * (in range ? code - w/S_w : code),  c = idx[m].
-// One block of NTH threads per row: 256, or 1024 for long rows, so that a row is one trip through the loop.
-template <int NTH>
+// One block of NTH threads per row.  What bounds it is memory for large layers, else the chain of loads of a trip through the row.
+// ANY: rows of any width and alignment; a lane owns four neighbouring columns and reads them in vector accesses, the last lane of
+// a row that is no multiple of four starts earlier and leaves out the d columns that its neighbour has; everything but the slices
+// past the first is requested at once.  That holds 90 registers a lane; without ANY, 49, and twice the wavefronts, for
+// aligned rows of four where there are many rows or long ones (2752 x 4096: 26.8 us, with ANY 29 to 32).
+// 2049 x 777 -> 1001, k = 250, 3 slices: 4.1 us; by single columns, slices and weights behind one another, 7.3.
+template <int NTH, bool ANY>
 __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ part, int S, int64_t k, int64_t ncols,
-                                                   int vec, const float* __restrict__ s_x,
-                                                   const int8_t* __restrict__ w_codes,
+                                                   const float* __restrict__ s_x, const int8_t* __restrict__ w_codes,
                                                    const uint32_t* __restrict__ w_clip, const float* __restrict__ w,
                                                    const float* __restrict__ s_w, const int32_t* __restrict__ idx,
                                                    float* __restrict__ dw, int scatter, float* __restrict__ ds_w,
@@ -400,23 +405,23 @@ __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ par
   const int64_t orow = scatter ? c : m;
   const int64_t slice = k * ncols;
   float acc = 0.0f;
-  if (vec) {                                          // ncols % 4 == 0 and 16-byte aligned rows
+  if constexpr (!ANY) {
     for (int64_t j = (int64_t)threadIdx.x * 4; j < ncols; j += 4 * NTH) {
       const float* p = part + m * ncols + j;
       float4 a = *reinterpret_cast<const float4*>(p);
       int s = 1;
       for (; s + 7 < S; s += 8) {                     // eight slices in flight; summed in slice order as below
         float4 b[8];
-#pragma unroll
+  #pragma unroll
         for (int u = 0; u < 8; ++u) b[u] = *reinterpret_cast<const float4*>(p + (int64_t)(s + u) * slice);
-#pragma unroll
+  #pragma unroll
         for (int u = 0; u < 8; ++u) { a.x += b[u].x; a.y += b[u].y; a.z += b[u].z; a.w += b[u].w; }
       }
       for (; s + 3 < S; s += 4) {
         float4 b[4];
-#pragma unroll
+  #pragma unroll
         for (int u = 0; u < 4; ++u) b[u] = *reinterpret_cast<const float4*>(p + (int64_t)(s + u) * slice);
-#pragma unroll
+  #pragma unroll
         for (int u = 0; u < 4; ++u) { a.x += b[u].x; a.y += b[u].y; a.z += b[u].z; a.w += b[u].w; }
       }
       for (; s < S; ++s) {
@@ -429,7 +434,7 @@ __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ par
       const float4 wv = *reinterpret_cast<const float4*>(w + c * ncols + j);
       const float wf[4] = {wv.x, wv.y, wv.z, wv.w};
       float o[4];
-#pragma unroll
+  #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const bool inr = (bits >> t) & 1u;
         const float code = (float)(int8_t)((cw >> (8 * t)) & 0xFFu);
@@ -440,7 +445,7 @@ __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ par
       if (dw) *reinterpret_cast<float4*>(dw + orow * ncols + j) = make_float4(o[0], o[1], o[2], o[3]);
       if (sgd.w) {
         float gq[4];
-#pragma unroll
+  #pragma unroll
         for (int t = 0; t < 4; ++t) gq[t] = fmaf(sgd.wd, wf[t], o[t]);
         if (sgd.mom_w) {
           float4 mb = *reinterpret_cast<const float4*>(sgd.mom_w + c * ncols + j);
@@ -455,34 +460,73 @@ __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ par
       }
     }
   } else {
-    for (int64_t j = threadIdx.x; j < ncols; j += NTH) {
-      float a = 0.0f;
-      int s = 0;
-      for (; s + 3 < S; s += 4) {                     // four slices in flight
-        float b[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) b[u] = part[(int64_t)(s + u) * slice + m * ncols + j];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) a += b[u];
+    // columns j .. j + n - 1 of the row, n <= 4 (a row of fewer than four columns: one at a time)
+    auto columns = [&](int64_t j, auto width) {
+      constexpr int V = decltype(width)::value;
+      const int d = j + V > ncols ? (int)(j + V - ncols) : 0;
+      const int64_t e = c * ncols + j - d;
+      const float* p = part + m * ncols + j - d;
+      float a[V], wf[V], mb[V];
+      uint32_t cw = 0;
+      __builtin_memcpy(a, p, 4 * V);
+      __builtin_memcpy(wf, w + e, 4 * V);
+      __builtin_memcpy(&cw, w_codes + e, V);
+      const uint32_t bits = (w_clip[c * wpr + (j >> 5)] >> (j & 31)) << d;
+      if (sgd.w && sgd.mom_w) __builtin_memcpy(mb, sgd.mom_w + e, 4 * V);
+      int s = 1;
+      auto slices = [&](auto count) {                   // in flight together, added in slice order
+        constexpr int N = decltype(count)::value;
+        float b[N][V];
+  #pragma unroll
+        for (int u = 0; u < N; ++u) __builtin_memcpy(b[u], p + (int64_t)(s + u) * slice, 4 * V);
+  #pragma unroll
+        for (int u = 0; u < N; ++u)
+  #pragma unroll
+          for (int t = 0; t < V; ++t) a[t] += b[u][t];
+        s += N;
+      };
+      while (s + 7 < S) slices(std::integral_constant<int, 8>{});
+      if (s + 3 < S) slices(std::integral_constant<int, 4>{});
+      if (s + 2 < S) slices(std::integral_constant<int, 3>{});
+      else if (s + 1 < S) slices(std::integral_constant<int, 2>{});
+      else if (s < S) slices(std::integral_constant<int, 1>{});
+      float o[V];
+  #pragma unroll
+      for (int t = 0; t < V; ++t) {
+        const float dwq = sx * a[t];
+        const bool inr = (bits >> t) & 1u;
+        const float code = (float)(int8_t)((cw >> (8 * t)) & 0xFFu);
+        const float gs = inr ? (code - wf[t] / sw) : code;
+        acc = t >= d ? acc + dwq * gs : acc;
+        o[t] = inr ? dwq : 0.0f;
       }
-      for (; s < S; ++s) a += part[(int64_t)s * slice + m * ncols + j];
-      const float dwq = sx * a;
-      const bool inr = (w_clip[c * wpr + (j >> 5)] >> (j & 31)) & 1u;
-      const float code = (float)w_codes[c * ncols + j];
-      const float wv = w[c * ncols + j];
-      const float gs = inr ? (code - wv / sw) : code;
-      acc += dwq * gs;
-      const float ov = inr ? dwq : 0.0f;
-      if (dw) dw[orow * ncols + j] = ov;
-      if (sgd.w) {
-        float gq = fmaf(sgd.wd, wv, ov);
-        if (sgd.mom_w) {
-          gq = fmaf(sgd.mu, sgd.mom_w[c * ncols + j], gq);
-          sgd.mom_w[c * ncols + j] = gq;
+      auto store = [&](float* dst, const float (&v)[V]) {
+        if (d == 0) __builtin_memcpy(dst, v, 4 * V);
+        else {
+  #pragma unroll
+          for (int t = 1; t < V; ++t)
+            if (t >= d) dst[t] = v[t];
         }
-        sgd.w[c * ncols + j] = fmaf(-sgd.lr_w, gq, wv);
+      };
+      if (dw) store(dw + orow * ncols + j - d, o);
+      if (sgd.w) {
+        float gq[V];
+  #pragma unroll
+        for (int t = 0; t < V; ++t) gq[t] = fmaf(sgd.wd, wf[t], o[t]);
+        if (sgd.mom_w) {
+  #pragma unroll
+          for (int t = 0; t < V; ++t) gq[t] = fmaf(sgd.mu, mb[t], gq[t]);
+          store(sgd.mom_w + e, gq);
+        }
+  #pragma unroll
+        for (int t = 0; t < V; ++t) gq[t] = fmaf(-sgd.lr_w, gq[t], wf[t]);
+        store(sgd.w + e, gq);
       }
-    }
+    };
+    if (ncols >= 4)
+      for (int64_t j = (int64_t)threadIdx.x * 4; j < ncols; j += 4 * NTH) columns(j, std::integral_constant<int, 4>{});
+    else if ((int64_t)threadIdx.x < ncols)
+      columns(threadIdx.x, std::integral_constant<int, 1>{});
   }
   acc = wave_sum(acc);
   __shared__ float red[NTH / 64];
@@ -930,19 +974,21 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   if (rc) return rc;
   if (use_side && (hipEventRecord(ev.join, st2) != hipSuccess || hipStreamWaitEvent(st, ev.join, 0) != hipSuccess))
     return EFQAT_ERR_HIP;
-  const int fvec = (p.Nw % 4 == 0 && ((uintptr_t)io.w % 16) == 0 && ((uintptr_t)io.dw % 16) == 0 &&
-                    ((uintptr_t)io.w_codes % 4) == 0 && ((uintptr_t)io.sgd.mom_w % 16) == 0) ? 1 : 0;
   ProfScope fin(PROF_FINISH, st);
   // k blocks for the rows of dW plus one that finishes dS_x, dZ_x
-  // long rows and few of them: the chain of dependent loads per row, not bandwidth, sets the time
-  if (fvec && p.Nw >= 2048 && io.k < 512)
-    hipLaunchKernelGGL(k_dw_finish<1024>, dim3((unsigned)io.k + 1), dim3(1024), 0, st, part_dw, p.plan_dw.split_k, io.k,
-                       p.Nw, fvec, io.s_x, io.w_codes, io.w_clip, io.w, io.s_w, io.idx, io.dw, io.scatter, io.ds_w,
-                       part_dx, n_part_dx, io.ds_x, io.dz_x, io.sgd);
-  else
-    hipLaunchKernelGGL(k_dw_finish<256>, dim3((unsigned)io.k + 1), dim3(256), 0, st, part_dw, p.plan_dw.split_k, io.k,
-                       p.Nw, fvec, io.s_x, io.w_codes, io.w_clip, io.w, io.s_w, io.idx, io.dw, io.scatter, io.ds_w,
-                       part_dx, n_part_dx, io.ds_x, io.dz_x, io.sgd);
+  // few rows: the chain of dependent loads of a trip, not bandwidth, sets the time, and a row is one trip where that can be (k = 64
+  // rows of 1152, 25 slices, two trips of 256 threads 6.3 us, one of 512 4.8)
+  const bool few = io.k < 512;
+  const bool vec = p.Nw % 4 == 0 && ((uintptr_t)io.w % 16) == 0 && ((uintptr_t)io.dw % 16) == 0 && ((uintptr_t)io.w_codes % 4) == 0 &&
+                   ((uintptr_t)io.sgd.mom_w % 16) == 0;
+  auto finish = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)io.k + 1), dim3(threads), 0, st, part_dw, p.plan_dw.split_k, io.k, p.Nw, io.s_x, io.w_codes,
+                       io.w_clip, io.w, io.s_w, io.idx, io.dw, io.scatter, io.ds_w, part_dx, n_part_dx, io.ds_x, io.dz_x, io.sgd);
+  };
+  if (few && p.Nw > 1024 && p.Nw < 2048) finish(k_dw_finish<512, true>, 512);
+  else if (few && p.Nw >= 2048) { if (vec) finish(k_dw_finish<1024, false>, 1024); else finish(k_dw_finish<1024, true>, 1024); }
+  else if (vec && !few) finish(k_dw_finish<256, false>, 256);
+  else finish(k_dw_finish<256, true>, 256);
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
 }
