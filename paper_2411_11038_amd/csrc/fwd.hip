@@ -15,17 +15,8 @@ typedef int intx4_t __attribute__((ext_vector_type(4)));
 // weight rows, its 8 wavefronts split K, every lane loads its 16-byte MFMA fragments straight from memory (16 rows x 64
 // contiguous bytes per load, v_mfma_i32_16x16x64_i8) with a batch of loads in flight, and the int32 sums meet in LDS.
 // sum_k w, which the zero point needs, is taken from the same fragments.  Rows of any length and alignment.
-// One launch of 1 / 16 / 32 / 64 tokens, 4096 -> 11008 (45 MB of weight codes): 10 / 14 / 19 / 21 us; with 128 x 128
-// tiles on 86 CUs after a pass for the row sums it was 40 - 42 us.  NT = 1 spreads the rows over most blocks and wins at
-// up to 32 tokens (11008 -> 4096, 16 tokens: 13 us, NT = 2 18 us, NT = 4 28 us); at 33 to 64 tokens the token fragments are
-// the larger part of the loads, so NT = 4 shares them among more rows where that still leaves a block for half of the CUs,
-// 8192 columns on.  NT = 1 / NT = 4 at 64 tokens, us:
-//   C_in      -> 4096       8192         9000         16384       32768
-//   512        4.8 /  7.8   6.2 /  8.3   7.6 /  8.4   9.5 /  8.6   17 /  16
-//   2048       8.2 / 13     13 /  14     17 /  14     23 /  16     44 /  31
-//   4096       13 /  20     23 /  22     33 /  23     44 /  28     85 /  51
-//   11008      32 /  51     62 /  56     89 /  57    116 /  61    230 / 116
-// (short rows: the line lies higher, by at most 2 us)
+// One launch of 1 / 16 / 32 / 64 tokens, 4096 -> 11008 (45 MB of weight codes): 12 / 16 / 18 / 23 us; with 128 x 128
+// tiles on 86 CUs after a pass for the row sums it was 40 - 42 us.  NT: see skinny_columns.
 constexpr int kSkinnyWaves = 8;
 template <int MT, int NT, int BATCH>
 __global__ __launch_bounds__(64 * kSkinnyWaves) void k_fwd_skinny(
@@ -133,6 +124,32 @@ __global__ __launch_bounds__(256) void k_pad_rows_u8(const uint8_t* __restrict__
 
 constexpr int64_t kSkinnyTokens = 64;
 
+// Groups of 16 weight rows of a block (NT of k_fwd_skinny).  The fragments of the tokens are read from L2 by every block and cost as
+// much of the loads as T rows of weights, so a wide block saves loads; but what takes the time is the busiest CU, and a block that
+// leaves CUs idle, or a second one for a few of them, costs more.  Loads of the busiest CU in units of 16 rows, and half a unit for
+// every group, in which wide blocks hide latency worse.  Fitted to 18 sizes by NT = 1 / 2 / 3 / 4, us (* chosen):
+//   tokens  C_in  -> C_out
+//    1      4096     11008    11.9* / 14.7  / 14.1  / 16.0
+//   16      4096      6000    11.6  / 10.6* / 13.2  / 15.7
+//   16      4096     11008    17.1  / 18.3  / 15.8* / 17.7
+//   16     11008      4096    16.1* / 23.5  / 30.4  / 35.9
+//   16      8192     28672    70.4  / 66.2  / 66.6  / 60.1*
+//   32      4096     11008    22.9  / 22.9  / 18.1* / 21.1
+//   64      4096      6000    24.2  / 18.2* / 20.6  / 23.8
+//   64      4096     11008    35.2  / 30.6  / 23.1* / 26.1
+//   64      2048     16384    24.6  / 18.3  / 25.0  / 17.4*
+// (before, NT was 4 for 33 tokens and more on 8192 columns and more, else 1.)
+static int skinny_columns(int64_t T, int64_t c_out) {
+  int best = 1;
+  double best_t = 0.0;
+  for (int nt = 1; nt <= 4; ++nt) {
+    const double rounds = (double)ceil_div(ceil_div(c_out, 16 * nt), 256);
+    const double t = rounds * (nt + (double)T / 16.0) + 0.5 * nt;
+    if (nt == 1 || t < best_t) { best = nt; best_t = t; }
+  }
+  return best;
+}
+
 struct FwdPlan {
   int64_t ldk;       // C_in rounded up to 16
   bool pad;          // operands copied into zero-padded rows
@@ -183,10 +200,18 @@ extern "C" int efqat_linear_fwd(const uint8_t* x_codes, const float* s_x, const 
 #define EFQAT_SKINNY(MT, NT, BATCH)                                                                                      \
   hipLaunchKernelGGL((k_fwd_skinny<MT, NT, BATCH>), grid(16 * NT), dim3(64 * kSkinnyWaves), 0, st, x_codes, w_codes, (int)T, \
                      (int)c_out, (int)c_in, s_x, z_x, s_w, y, y_dtype)
-    if (T <= 16) EFQAT_SKINNY(1, 1, 4);
-    else if (T <= 32) EFQAT_SKINNY(2, 1, 4);
-    else if (c_out >= 8192) EFQAT_SKINNY(4, 4, 1);      // see k_fwd_skinny for both sides of this line
-    else EFQAT_SKINNY(4, 1, 2);
+    // steps of 64 columns whose loads are in flight together: what the registers allow, more measured the same
+#define EFQAT_SKINNY_NT(MT, B1, B2, B3, B4)                                                                              \
+  switch (skinny_columns(T, c_out)) {                                                                                    \
+    case 1: EFQAT_SKINNY(MT, 1, B1); break;                                                                              \
+    case 2: EFQAT_SKINNY(MT, 2, B2); break;                                                                              \
+    case 3: EFQAT_SKINNY(MT, 3, B3); break;                                                                              \
+    default: EFQAT_SKINNY(MT, 4, B4);                                                                                    \
+  }
+    if (T <= 16) { EFQAT_SKINNY_NT(1, 4, 4, 4, 2) }
+    else if (T <= 32) { EFQAT_SKINNY_NT(2, 4, 4, 2, 2) }
+    else { EFQAT_SKINNY_NT(4, 2, 2, 1, 1) }
+#undef EFQAT_SKINNY_NT
 #undef EFQAT_SKINNY
     EFQAT_LAUNCH_CHECK();
     return EFQAT_OK;
