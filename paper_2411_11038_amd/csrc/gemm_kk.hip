@@ -3,17 +3,19 @@
 
 namespace efqat {
 
-template <int BM, int BN, int EPI, int CONV = 0>
+constexpr int kKkDeep = 8;                             // stages of a 64 x 64 tile that has a CU for itself
+
+template <int BM, int BN, int EPI, int CONV = 0, int NST = 3>
 static int launch_kk_cfg(const typename ConvArgs<CONV>::type& a, hipStream_t st) {
-  using C = KkCfg<BM, BN>;
+  using C = KkCfg<BM, BN, NST>;
   // set once per process (initialisation of a function-local static is thread-safe)
   constexpr int kLds = C::template lds_bytes<EPI>() + (CONV == 2 ? C::BM * (int)sizeof(int) : 0);
-  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_kk<BM, BN, EPI, CONV>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_kk<BM, BN, EPI, CONV, NST>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return EFQAT_ERR_HIP;
   const dim3 grid((unsigned)(a.tiles_m * a.tiles_n));
   {
     ProfScope prof(PROF_DX, st);
-    hipLaunchKernelGGL((k_gemm_kk<BM, BN, EPI, CONV>), grid, dim3(256), kLds, st, a);
+    hipLaunchKernelGGL((k_gemm_kk<BM, BN, EPI, CONV, NST>), grid, dim3(256), kLds, st, a);
   }
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
@@ -22,6 +24,7 @@ static int launch_kk_cfg(const typename ConvArgs<CONV>::type& a, hipStream_t st)
 int launch_gemm_kk(const GemmArgs& a, int tile, hipStream_t stream) {
   // bf16 in and out, whole tiles, 32-bit element offsets: nothing to decide at run time, the straight-line epilogue
   const bool fast = dx_epilogue_fast(a, tile, tile);
+  const bool few = (int64_t)a.tiles_m * a.tiles_n <= 256;
   switch (tile) {
     case 192:
       if (fast) return launch_kk_cfg<192, 192, EPI_DXF>(a, stream);
@@ -30,6 +33,7 @@ int launch_gemm_kk(const GemmArgs& a, int tile, hipStream_t stream) {
       if (fast) return launch_kk_cfg<128, 128, EPI_DXF>(a, stream);
       return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<128, 128, EPI_DXS>(a, stream) : launch_kk_cfg<128, 128, EPI_DX>(a, stream);
     case 64:
+      if (few) return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<64, 64, EPI_DXS, 0, kKkDeep>(a, stream) : launch_kk_cfg<64, 64, EPI_DX, 0, kKkDeep>(a, stream);
       return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<64, 64, EPI_DXS>(a, stream) : launch_kk_cfg<64, 64, EPI_DX>(a, stream);
     default:
       return EFQAT_ERR_BAD_SHAPE;
@@ -38,6 +42,8 @@ int launch_gemm_kk(const GemmArgs& a, int tile, hipStream_t stream) {
 
 // dX product of a stride-1 convolution; `a` by dx_args_conv
 int launch_gemm_kk_conv(const GemmArgs& a, int tile, hipStream_t stream) {
+  if (tile == 64 && (int64_t)a.tiles_m * a.tiles_n <= 256)
+    return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<64, 64, EPI_DXS, 1, kKkDeep>(a, stream) : launch_kk_cfg<64, 64, EPI_DX, 1, kKkDeep>(a, stream);
   if (tile == 64)
     return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<64, 64, EPI_DXS, 1>(a, stream) : launch_kk_cfg<64, 64, EPI_DX, 1>(a, stream);
   if (dx_epilogue_fast(a, 128, 128)) return launch_kk_cfg<128, 128, EPI_DXF, 1>(a, stream);

@@ -12,7 +12,9 @@
 //
 // 256 threads; square tiles of 192 (96 x 96 per wavefront, 9 accumulators), 128 or 64, wavefront grid 2 x 2;
 // v_mfma_f32_32x32x16_bf16; K-stage of 64; a ring of three LDS stages (144, 96 or 48 KB; one block a CU, of the
-// 64 x 64 tile three, which serves products of too few larger tiles): the copies of stage kt + 2 are issued
+// 64 x 64 tile three, which serves products of too few larger tiles, and of that one eight stages, 128 KB, where there is no
+// more than a block a CU: 64 x 4096 -> 4096 36.3 -> 34.0 us, 200 x 8000 -> 100 fp32 43.6 -> 35.2; four stages of the 128 x 128
+// tile gain nothing): the copies of stage kt + 2 are issued
 // while stage kt is multiplied and are only waited for at the end of stage kt + 1, so a copy may take more than a
 // whole stage (about 1200 cycles of MFMA work at 192 x 192) before it stalls anything - with two stages the memory latency under
 // load did not fit.  Rows past M / N re-read the last valid row (their outputs are discarded), chunks past K come
@@ -21,13 +23,14 @@
 #include "common.hpp"
 
 #include <type_traits>
+#include <utility>
 
 #include "gemm_epilogue.hpp"
 #include "lds_copy.hpp"
 
 namespace efqat {
 
-template <int BM_, int BN_>
+template <int BM_, int BN_, int NST_ = 3>
 struct KkCfg {
   static constexpr int BM = BM_, BN = BN_;
   static constexpr int WGM = 2, WGN = 2;
@@ -36,7 +39,7 @@ struct KkCfg {
   static constexpr int A_G = BM / 8 / 4, B_G = BN / 8 / 4;       // 1-KiB copies (8 rows) per wavefront and stage
   static constexpr int LDS_A = BM * 128, LDS_B = BN * 128;
   static constexpr int LDS_STAGE = LDS_A + LDS_B;
-  static constexpr int NST = 3;                                  // LDS stages in the ring
+  static constexpr int NST = NST_;                               // LDS stages in the ring
   static constexpr int LDS_LOOP = NST * LDS_STAGE;
   static constexpr int LDS_EPI = 4 * 32 * (WN + 8) * 4;
   template <int EPI>
@@ -47,14 +50,18 @@ struct KkCfg {
   static_assert(WGM * WGN == 4 && WM % 32 == 0 && WN % 32 == 0 && BM % 32 == 0, "tile / wavefront grid");
 };
 
+// f(0), f(1), .. with compile-time numbers
+template <class F, int... B>
+__device__ __forceinline__ void kk_round(F f, std::integer_sequence<int, B...>) { (f(std::integral_constant<int, B>{}), ...); }
+
 // CONV = 1: the A operand is gathered from a token-major dY with the im2col map of a stride-1 convolution, as in
 // k_gemm_nt (see GemmArgs): every copy slot keeps (n, h, w) of its input pixel and forms its source address per stage
 // from the stage's tap; K = taps * ldc is a whole number of stages.  CONV = 2: a convolution with a stride, rows sorted
 // by phase (see ConvPhase); W_q^T is read at the stage's tap as well.
-template <int BM, int BN, int EPI, int CONV = 0>
+template <int BM, int BN, int EPI, int CONV = 0, int NST = 3>
 __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::type& g, char* smem, int bid, int ntile) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  using C = KkCfg<BM, BN>;
+  using C = KkCfg<BM, BN, NST>;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / C::WGN, wn = wave % C::WGN;
@@ -217,18 +224,24 @@ __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::typ
   // copies of one stage, by the sub-step that issues them: the first P0 go out one stage early (last sub-step of the
   // stage before, right after the barrier that frees their buffer), the rest in sub-steps 0, 1, 2
   constexpr int P0 = LPS / 4, P1 = (LPS - P0 + 2) / 3, P2 = (LPS - P0 - P1 + 1) / 2, P3 = LPS - P0 - P1 - P2;
-  // end of a stage: the copies of the next stage have landed (the LPS copies issued after them, which belong to
-  // the stage after next, may still be in flight), every wavefront is done reading this stage's buffer
-  // `tail`: one of the last two stages - every copy landed before it began and none is issued any more
-  // `more`: loads issued since the last copy of the next stage, besides the copies
-  auto stage_sync = [&](auto steadyc, auto morec, bool tail) {
+  // end of a stage: the copies of the next stage have landed, every wavefront is done reading this stage's buffer.
+  // steady: the copies of the NST - 2 stages behind the next, and `more` other loads issued since its last copy, stay in
+  // flight.  Otherwise the copies of `ahead` stages do; ahead < 0: one of the last two stages - every copy landed before it
+  // began and none is issued any more.
+  auto stage_sync = [&](auto steadyc, auto morec, int ahead) {
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (decltype(steadyc)::value) {
-      constexpr int N = LPS + decltype(morec)::value;
+      constexpr int N = (NST - 2) * LPS + decltype(morec)::value;
       static_assert(N < 64, "the counter has six bits");
-      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");   // what was issued since stays in flight
-    } else if (tail) {
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+    } else if (ahead < 0) {
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    } else if (ahead >= 4) {
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(4 * LPS < 64 ? 4 * LPS : 0) : "memory");
+    } else if (ahead >= 2) {
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(2 * LPS) : "memory");
+    } else if (ahead == 1) {
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LPS) : "memory");
     } else {
       asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     }
@@ -256,55 +269,60 @@ __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::typ
   };
 
   // the fused dX epilogue
-  typename std::conditional<EPI == EPI_DXF, EpiDxFast<C, true>,
+  // Inputs requested ahead: 192 x 192 tiles, whose epilogues are the longest.  Calls on buffers that the caches do not hold:
+  // 12288 x 768 -> 3072 124 -> 117 us, a step of 12288 x 3072 -> 768 212.5 -> 211 (the dX product alone on buffers that they do hold
+  // 57 -> 58.5); with 128 x 128 tiles it costs 2 %.
+  constexpr bool kAhead = EPI == EPI_DXF && BM == 192;
+  typename std::conditional<EPI == EPI_DXF, EpiDxFast<C, kAhead>,
                             EpiDxAny<C, typename std::conditional<EPI == EPI_DXS, float, bf16_t>::type, CONV == 2>>::type epi;
   const int m_end = CONV == 2 ? ph.rows : g.M;
   const bool edge = m0 + C::BM > m_end || n0 + C::BN > g.N;
   int* rowmap = reinterpret_cast<int*>(smem + C::template lds_bytes<EPI>());   // CONV = 2: the matrix row of every tile row
+  constexpr int PEEL = 2 * NST;                       // two rounds of the ring
   const int kt_epi = nk >= 2 ? nk - 2 : 0;            // the first of the last two stages
   bool peel = false;                                  // EPI_DXF: long enough to request the epilogue's inputs in the first stages
   if constexpr (EPI == EPI_DXF) {
-    peel = nfull >= 9;                                // peeled stages are steady ones: kt + 3 < nfull
+    peel = kAhead && nfull >= PEEL + NST;             // peeled stages are steady ones: kt + NST < nfull
     epi.begin(g, m0, n0, wm, wn);
   }
 
-  // ---- main loop.  Stage kt lives in buffer kt % 3.  On entry to stage kt the first P0 copies of stage kt + 2 have
-  // been issued if and only if that stage is a full one (kt + 2 < nfull); both variants keep this true for kt + 1.
+  // ---- main loop.  Stage kt lives in buffer kt % NST.  On entry to stage kt the first P0 copies of stage kt + NST - 1 have
+  // been issued if and only if that stage is a full one; both variants keep this true for kt + 1.
   //
-  // EPI_DXF: the first PEEL stages also request the epilogue's inputs, RG_S groups of rows each, behind the stage's copies.  They
+  // EPI_DXF: the first PEEL stages also request the epilogue's inputs, some groups of rows each, behind the stage's copies.  They
   // come out of HBM while the matrix cores work and are waited for one stage later than the copies before them.
-  constexpr int PEEL = 6;
   // the requests of peeled stage ps, then its end
   auto request_and_sync = [&](auto& e, auto psc) {
     using E = typename std::remove_reference<decltype(e)>::type;
     constexpr int PS = decltype(psc)::value;
-    constexpr int G0 = PS > 0 ? (PS - 1) * E::GROUPS / PEEL : 0, G1 = PS * E::GROUPS / PEEL, G2 = (PS + 1) * E::GROUPS / PEEL;
+    constexpr int G0 = PS >= NST - 2 ? (PS - NST + 2) * E::GROUPS / PEEL : 0, G1 = PS * E::GROUPS / PEEL, G2 = (PS + 1) * E::GROUPS / PEEL;
     asm volatile("" ::: "memory");                    // behind the copies: stage_sync counts on this order
 #pragma unroll
     for (int q = G1; q < G2; ++q) e.fetch(q / E::HP, q % E::HP);
-    stage_sync(std::integral_constant<bool, true>{}, std::integral_constant<int, E::LOADS * (G2 - G0)>{}, false);
+    stage_sync(std::integral_constant<bool, true>{}, std::integral_constant<int, E::LOADS * (G2 - G0)>{}, 0);
   };
   auto stage = [&](auto bufc, auto steadyc, int kt, auto peelc) {
     constexpr int cur = decltype(bufc)::value;
     constexpr bool ST = decltype(steadyc)::value;
     constexpr int PS = decltype(peelc)::value;        // peeled stage, -1: none
-    constexpr int nxt = (cur + 1) % C::NST, nn = (cur + 2) % C::NST;
+    constexpr int nxt = (cur + 1) % NST, nn = (cur + NST - 1) % NST;
     using Next = std::integral_constant<int, nxt>;
-    if constexpr (ST) {              // kt + 3 < nfull
+    const int ki = kt + NST - 1;     // the stage whose copies are issued
+    if constexpr (ST) {              // kt + NST < nfull
       __builtin_amdgcn_sched_barrier(0);
-      substep(bufc, 1, 0, kt + 2, nn, P0, P0 + P1);
-      substep(bufc, 2, 1, kt + 2, nn, P0 + P1, P0 + P1 + P2);
-      substep(bufc, 3, 0, kt + 2, nn, P0 + P1 + P2, LPS);
+      substep(bufc, 1, 0, ki, nn, P0, P0 + P1);
+      substep(bufc, 2, 1, ki, nn, P0 + P1, P0 + P1 + P2);
+      substep(bufc, 3, 0, ki, nn, P0 + P1 + P2, LPS);
       if constexpr (PS >= 0) request_and_sync(epi, peelc);
-      else stage_sync(steadyc, std::integral_constant<int, 0>{}, false);
-      substep(Next{}, 0, 1, kt + 3, cur, 0, P0);
+      else stage_sync(steadyc, std::integral_constant<int, 0>{}, 0);
+      substep(Next{}, 0, 1, ki + 1, cur, 0, P0);
     } else {
       const bool more1 = kt + 1 < nk;
-      // the last two stages: the preceding barrier was passed with every copy landed (all drain stages before
-      // them wait for vmcnt(0)), and nothing more is issued - the moment to request the epilogue's first inputs
-      const bool tail = kt + 2 >= nk;
-      if (kt + 2 < nfull) issue_range(Unchecked{}, kt + 2, nn, P0, LPS);
-      else if (kt + 2 < nk) issue_range(Checked{}, kt + 2, nn, 0, LPS);
+      // the last two stages: the preceding barrier was passed with every copy landed, and nothing more is issued - the
+      // moment to request the epilogue's first inputs
+      const int ahead = kt + 2 >= nk ? -1 : kt + 3 >= nk ? 0 : (ki < nk - 1 ? ki : nk - 1) - (kt + 1);
+      if (ki < nfull) issue_range(Unchecked{}, ki, nn, P0, LPS);
+      else if (ki < nk) issue_range(Checked{}, ki, nn, 0, LPS);
       if (kt == kt_epi) {
         if constexpr (EPI == EPI_DXF) { if (!peel) epi.prefetch(); }
         else epi.prefetch(g, m0, n0, wm, wn, m_end, edge, rowmap);
@@ -318,16 +336,13 @@ __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::typ
       __builtin_amdgcn_sched_barrier(0);
       load_frags(bufc, 3, 1);
       mfma_all(0);
-      stage_sync(steadyc, std::integral_constant<int, 0>{}, tail);
+      stage_sync(steadyc, std::integral_constant<int, 0>{}, ahead);
       if (more1) load_frags(Next{}, 0, 0);
-      if (kt + 3 < nfull) issue_range(Unchecked{}, kt + 3, cur, 0, P0);
+      if (ki + 1 < nfull) issue_range(Unchecked{}, ki + 1, cur, 0, P0);
       mfma_all(1);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  using B0 = std::integral_constant<int, 0>;
-  using B1 = std::integral_constant<int, 1>;
-  using B2 = std::integral_constant<int, 2>;
   using Steady = std::integral_constant<bool, true>;
   using Drain = std::integral_constant<bool, false>;
 
@@ -338,37 +353,31 @@ __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::typ
     }
   }
 
-  if (nk > 0) issue_range(Checked{}, 0, 0, 0, LPS);
-  if (nk > 1) issue_range(Checked{}, 1, 1, 0, LPS);
-  // stage 0 has to be there; the tail stages (see stage_sync) count on everything having landed
-  if (nk > 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LPS) : "memory");
+#pragma unroll
+  for (int s = 0; s < NST - 1; ++s)
+    if (s < nk) issue_range(Checked{}, s, s, 0, LPS);
+  // stage 0 has to be there; the last stages (see stage_sync) count on everything having landed
+  if (nk >= NST) asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NST - 2) * LPS) : "memory");
   else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (2 < nfull) issue_range(Unchecked{}, 2, 2, 0, P0);
-  if (nk > 0) load_frags(B0{}, 0, 0);
+  if (NST - 1 < nfull) issue_range(Unchecked{}, NST - 1, NST - 1, 0, P0);
+  if (nk > 0) load_frags(std::integral_constant<int, 0>{}, 0, 0);
   int kt = 0;
   using No = std::integral_constant<int, -1>;
-  if constexpr (EPI == EPI_DXF) {
+  // f(stage of the round) for a round of the ring
+  auto round = [&](auto f) { kk_round(f, std::make_integer_sequence<int, NST>{}); };
+  if constexpr (kAhead) {
     if (peel) {
-      stage(B0{}, Steady{}, 0, std::integral_constant<int, 0>{});
-      stage(B1{}, Steady{}, 1, std::integral_constant<int, 1>{});
-      stage(B2{}, Steady{}, 2, std::integral_constant<int, 2>{});
-      stage(B0{}, Steady{}, 3, std::integral_constant<int, 3>{});
-      stage(B1{}, Steady{}, 4, std::integral_constant<int, 4>{});
-      stage(B2{}, Steady{}, 5, std::integral_constant<int, 5>{});
+      round([&](auto b) { stage(b, Steady{}, decltype(b)::value, b); });
+      round([&](auto b) { stage(b, Steady{}, NST + decltype(b)::value, std::integral_constant<int, NST + decltype(b)::value>{}); });
       kt = PEEL;
     }
   }
-  for (; kt + 5 < nfull; kt += 3) {
-    stage(B0{}, Steady{}, kt, No{});
-    stage(B1{}, Steady{}, kt + 1, No{});
-    stage(B2{}, Steady{}, kt + 2, No{});
-  }
-  for (; kt < nk; kt += 3) {
-    stage(B0{}, Drain{}, kt, No{});
-    if (kt + 1 < nk) stage(B1{}, Drain{}, kt + 1, No{});
-    if (kt + 2 < nk) stage(B2{}, Drain{}, kt + 2, No{});
-  }
+  for (; kt + 2 * NST - 1 < nfull; kt += NST) round([&](auto b) { stage(b, Steady{}, kt + decltype(b)::value, No{}); });
+  for (; kt < nk; kt += NST)
+    round([&](auto b) {
+      if (kt + decltype(b)::value < nk) stage(b, Drain{}, kt + decltype(b)::value, No{});
+    });
   __syncthreads();
 
   if constexpr (EPI == EPI_DXF) {
@@ -380,10 +389,10 @@ __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::typ
 #endif
 }
 
-template <int BM, int BN, int EPI, int CONV = 0>
+template <int BM, int BN, int EPI, int CONV = 0, int NST = 3>
 __global__ __launch_bounds__(256) void k_gemm_kk(const typename ConvArgs<CONV>::type g) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  gemm_kk_block<BM, BN, EPI, CONV>(g, smem, blockIdx.x, gridDim.x);
+  gemm_kk_block<BM, BN, EPI, CONV, NST>(g, smem, blockIdx.x, gridDim.x);
 }
 
 }  // namespace efqat

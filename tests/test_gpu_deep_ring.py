@@ -1,0 +1,55 @@
+"""dX on 64 x 64 tiles with a ring of eight stages (no more than a block a CU): contractions shorter than the ring, around it and its
+multiples, ragged last stages, against the tiles of 192, which add the same products in the same order (bit for bit)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2411_11038_amd as ef
+from tests.gpu_util import clip_words
+
+pytestmark = pytest.mark.gpu
+
+
+def _in_range(fx, cols):
+    """The range made from the data can clip its own ends: dX is 0 there."""
+    words = clip_words(fx["clip_bits"])
+    bits = np.unpackbits(words.reshape(-1, words.shape[-1]).view(np.uint8), axis=1, bitorder="little")[:, :cols]
+    return torch.from_numpy(bits.astype(np.float64)).cuda()
+
+
+@pytest.mark.parametrize("dt", (torch.bfloat16, torch.float32), ids=("bf16", "f32"))
+@pytest.mark.parametrize("c_out", (8, 64, 72, 448, 504, 512, 520, 960, 1016, 1032, 1088, 1536, 2056))
+def test_against_tiles_of_192(c_out, dt):
+    T, c_in = 150, 200
+    g = torch.Generator(device="cuda")
+    g.manual_seed(c_out)
+    x = torch.randn(T, c_in, generator=g, device="cuda").to(dt)
+    w = torch.randn(c_out, c_in, generator=g, device="cuda") * 0.05
+    dy = torch.randn(T, c_out, generator=g, device="cuda").to(dt)
+    fx = ef.fakequant_fwd(x, ef.ACT_PER_TENSOR_ASYM, 8)
+    fw = ef.fakequant_fwd(w, ef.W_PER_ROW_SYM, 8)
+    args = (dy, fx["codes"], fx["clip_bits"], x, fx["scale"], fx["zero_point"], fw["codes"], fw["clip_bits"], w, fw["scale"], None)
+    got = [ef.linear_bwd(*args, dx_kernel=k)["dx"] for k in (ef.DX_KERNEL_AUTO, ef.DX_KERNEL_BF16_PINNED)]
+    ref = (dy.double() @ (fw["codes"].double() * fw["scale"].double()[:, None]) * _in_range(fx, c_in)).float()
+    assert torch.equal(got[0], got[1])
+    # W_q (and a fp32 dY) rounded to bf16, dX to its type: the bound of bwd_checks.py
+    assert (got[0].float() - ref).abs().max() <= 2e-2 * ref.abs().max()
+
+
+@pytest.mark.parametrize("size", [(2, 9, 7, 64, 3), (1, 14, 14, 192, 3), (4, 5, 5, 128, 5), (8, 7, 7, 512, 3)], ids=str)
+def test_convolutions(size):
+    N, H, W, c_out, kernel = size
+    c_in, pad = 96, kernel // 2
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N)
+    x = torch.randn(N, H, W, c_in, generator=g, device="cuda").abs().bfloat16()
+    w = torch.randn(c_out, kernel, kernel, c_in, generator=g, device="cuda") * 0.05
+    dy = torch.randn(N, H, W, c_out, generator=g, device="cuda").bfloat16()
+    fx = ef.fakequant_fwd(x, ef.ACT_PER_TENSOR_ASYM, 8)
+    fw = ef.fakequant_fwd(w.view(c_out, -1), ef.W_PER_ROW_SYM, 8)
+    got = ef.conv_bwd(dy.view(-1, c_out), fx["codes"].view(N, H, W, c_in), fx["clip_bits"], x, fx["scale"], fx["zero_point"],
+                      fw["codes"].view(w.shape), fw["clip_bits"], w, fw["scale"], None, pad=pad)["dx"]
+    wq = (fw["codes"].double() * fw["scale"].double()[:, None]).view(w.shape).permute(0, 3, 1, 2).cpu()
+    ref = torch.nn.functional.conv_transpose2d(dy.double().permute(0, 3, 1, 2).cpu(), wq, padding=pad).permute(0, 2, 3, 1).cuda()
+    ref = ref * _in_range(fx, c_in).view(ref.shape)
+    assert (got.double().view(ref.shape) - ref).abs().max() <= 2e-2 * ref.abs().max()
