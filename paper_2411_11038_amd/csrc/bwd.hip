@@ -943,7 +943,7 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   } else if (pair) {
     rc = launch_pair(dxa, conv, p.plan_dx, p.tn ? &tna : nullptr, p.tn ? nullptr : &nta, p.plan_dw, st);
   } else if (p.cmx) {
-    rc = launch_gemm_dx8_cm(cma, p.dx8_tile, st);
+    rc = launch_gemm_dx8_cm(cma, p.plan_dx, st);
   } else if (p.dx8) {
     rc = launch_gemm_dx8(dy_tok, c_out, io.w_codes, c_in, io.s_w, p.Mx, c_in, c_out, p.dx8_tile, epi, st);
   } else {

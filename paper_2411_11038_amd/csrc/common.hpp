@@ -111,7 +111,7 @@ struct GemmPlan {
   int tile;
   int split_k;
   int tiles_m, tiles_n;
-  bool ring;
+  bool ring;      // channel-major dX with tile 128: 128 x 256
 };
 // Pure host functions of the problem size (so the workspace query and the call agree).  allow_split = false: a product
 // with the fused dX epilogue.

@@ -180,23 +180,34 @@ GemmPlan dw_plan(DwKind kind, int64_t M, int64_t N, int64_t K, double* price_out
   return best;
 }
 
-// dX of a channel-major dY by k_gemm_dx8, 64 x 128, 128 x 128 and 256 x 256; fitted to 90 layers (0.2 % from the fastest in the
-// mean).  T x C_out -> C_in in us on 64 / 128 / 256: 14248 x 1122 -> 176 22.4 / 23.2 / 45; 9696 x 27 -> 5696 70 / 74 / 92;
-// 8192 x 4096 -> 11008 on 256 643.
+// dX of a channel-major dY by k_gemm_dx8, 64 x 128, 128 x 128, 128 x 256 (`ring` set) and 256 x 256; fitted to 90 layers (0.2 % from
+// the fastest in the mean), the row of 128 x 256 to 16.  A tile of 128 x 256 moves half of the bytes of two of 64 x 128 from L2 to LDS, which
+// is what the smaller tiles are bound by, and two of them on a CU hide each other's epilogues.
+// T x C_out -> C_in, backward call without selected channels, us on 64 / 128 / 128 x 256 / 256:
+//   14248 x 1122 -> 176    22.4 / 23.2 /  -   / 45
+//    9696 x 27   -> 5696   70   / 74   /  -   / 92
+//    8192 x 1024 -> 1024   30.7 / 26.6 / 25.1 / 33.0
+//    4096 x 4096 -> 2048   92   / 75   / 67   / 80
+//   12288 x 768  -> 3072   95   / 82   / 74   / 93
+//   16384 x 512  -> 512    21.2 / 18.4 / 19.2 / 25.3
+//    8192 x 4096 -> 4096  341   / 285  / 234  / 220
+//    8192 x 4096 -> 11008  -    /  -   /  -   / 643
 static const DxTile kDxCmTiles[] = {{64, false, 3, {0.45, 6.2}, {0.935, 7.4}, {0.0, 0.0}, {0.0, 0.0}},
                                     {128, false, 2, {0.55, 8.4}, {0.95, 9.1}, {0.0, 0.0}, {0.0, 0.0}},
+                                    {128, true, 2, {0.877, 9.8}, {1.605, 13.5}, {0.0, 0.0}, {0.0, 0.0}},   // 128 x 256
                                     {256, false, 1, {1.0, 21.6}, {1.34, 24.9}, {0.0, 0.0}, {0.0, 0.0}}};
 GemmPlan dx_cm_plan(int64_t M, int64_t N, int64_t K, double* price) {
   GemmPlan best{};
   const double stages = (double)ceil_div(K, KALIGN);
   for (const DxTile& c : kDxCmTiles) {
-    const int64_t tm = ceil_div(M, c.t), tn = ceil_div(N, c.t == 64 ? 128 : c.t), tiles = tm * tn, round = 256 * c.bpc;
+    if (c.ring && (M % 128 || N % 256)) continue;       // whole tiles only: what was measured
+    const int64_t tm = ceil_div(M, c.t), tn = ceil_div(N, c.t == 64 ? 128 : c.ring ? 256 : c.t), tiles = tm * tn, round = 256 * c.bpc;
     if (tiles >= (1 << 24) && c.t < 256) continue;      // a grid dimension holds less than 2^32 work items
     const double lone = c.lone[0] * stages + c.lone[1], full = c.full[0] * stages + c.full[1];
     double t = (double)(tiles / round) * full;
     if (const int64_t rest = tiles % round)
       t += lone + (full - lone) * (c.bpc > 1 ? (double)(ceil_div(rest, 256) - 1) / (c.bpc - 1) : (double)rest / 256.0);
-    if (best.tile == 0 || t < *price) { *price = t; best = GemmPlan{c.t, 1, (int)tm, (int)tn, false}; }
+    if (best.tile == 0 || t < *price) { *price = t; best = GemmPlan{c.t, 1, (int)tm, (int)tn, c.ring}; }
   }
   return best;
 }

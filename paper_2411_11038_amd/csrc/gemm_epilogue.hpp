@@ -98,7 +98,7 @@ int dx_args_cm(GemmDx8Args* out, const bf16_t* dy_cm, int64_t lda, const int8_t*
                int64_t N, int64_t K, const GemmPlan& plan, const GemmEpilogueDx& epi);
 int dw_args_rows(GemmDx8Args* out, const bf16_t* dy_cm, int64_t lda, const int32_t* idx, const uint8_t* x_codes, int64_t ldb,
                  const float* z_x, int64_t M, int64_t N, int64_t K, const GemmPlan& plan, float* out_partial);
-int launch_gemm_dx8_cm(const GemmDx8Args& a, int tile, hipStream_t stream);
+int launch_gemm_dx8_cm(const GemmDx8Args& a, const GemmPlan& plan, hipStream_t stream);
 int launch_gemm_dw_rows(const GemmDx8Args& a, const GemmPlan& plan, hipStream_t stream);
 int launch_pair_cm(const GemmDx8Args& dx, const GemmDx8Args& dw, int split_k, hipStream_t stream);
 // both products of one layer in one grid (pair.hip): tn or staged, the other one null
@@ -192,7 +192,8 @@ struct EpiDxAny {
   static constexpr int LPR = (CPR % 8 == 0) ? 8 : 4;
   static_assert(CPR % LPR == 0, "chunks per row");
   static constexpr int KC = CPR / LPR, RP = 64 / LPR, NP = 32 / RP * KC;   // NP: passes per slab
-  static constexpr int GS = C::TM * 512 * PITCH <= 160 * 1024 ? C::TM : C::TM / 2;
+  // half of them where that lets two blocks of 128 x 256 share a CU
+  static constexpr int GS = C::TM * 512 * PITCH <= (C::BM == 128 && C::BN == 256 ? 80 : 160) * 1024 ? C::TM : C::TM / 2;
   static constexpr int LDS = GS * 512 * PITCH;       // 4 wavefronts x 32 rows x 4 bytes
   static_assert(LDS <= 160 * 1024 && C::TM % GS == 0, "staging");
   static constexpr int U = KC == 1 ? (NP * GS < 4 ? NP * GS : 4) : 2 * KC;
