@@ -84,10 +84,11 @@ __device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int
     // dense source, 4 consecutive columns per lane: one load of 4 to 16 bytes at any alignment, but for the chunk that ends a row
     const int jq = (threadIdx.x & 15) * 4, ib = threadIdx.x >> 4;
     const int64_t left = Cn - j0 - jq;
-    float v[4][4];
+    float v[4][4], rs[4];
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) {
-      const int64_t si = src_row(i0 + ib + 16 * rr);
+      const int64_t i = i0 + ib + 16 * rr, si = src_row(i);
+      rs[rr] = rowscale ? rowscale[i < R ? i : R - 1] : 1.0f;
 #pragma unroll
       for (int t = 0; t < 4; ++t) v[rr][t] = sub;
       if (si >= 0 && left >= 4) {
@@ -103,9 +104,8 @@ __device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) {
       const int li = ib + 16 * rr;
-      const float rs = rowscale && i0 + li < R ? rowscale[i0 + li] : 1.0f;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) v[rr][t] = (v[rr][t] - sub) * rs;
+      for (int t = 0; t < 4; ++t) v[rr][t] = (v[rr][t] - sub) * rs[rr];
       *reinterpret_cast<uint32_t*>(&tile[li][jq]) = pack_bf16x2(v[rr][0], v[rr][1]);
       *reinterpret_cast<uint32_t*>(&tile[li][jq + 2]) = pack_bf16x2(v[rr][2], v[rr][3]);
     }

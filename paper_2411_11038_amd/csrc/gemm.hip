@@ -194,7 +194,7 @@ GemmPlan dw_plan(DwKind kind, int64_t M, int64_t N, int64_t K, double* price_out
 //    8192 x 4096 -> 11008  -    /  -   /  -   / 643
 static const DxTile kDxCmTiles[] = {{64, false, 3, {0.45, 6.2}, {0.935, 7.4}, {0.0, 0.0}, {0.0, 0.0}},
                                     {128, false, 2, {0.55, 8.4}, {0.95, 9.1}, {0.0, 0.0}, {0.0, 0.0}},
-                                    {128, true, 2, {0.877, 9.8}, {1.605, 13.5}, {0.0, 0.0}, {0.0, 0.0}},   // 128 x 256
+                                    {128, true, 2, {0.877, 9.8}, {1.72, 13.5}, {0.0, 0.0}, {0.0, 0.0}},   // 128 x 256
                                     {256, false, 1, {1.0, 21.6}, {1.34, 24.9}, {0.0, 0.0}, {0.0, 0.0}}};
 GemmPlan dx_cm_plan(int64_t M, int64_t N, int64_t K, double* price) {
   GemmPlan best{};

@@ -521,11 +521,11 @@ struct EpiDxFast {
         float xf[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) xf[t] = __uint_as_float((t & 1) ? xw[t >> 1] & 0xFFFF0000u : xw[t >> 1] << 16);
-        if (!ALL && k == KC - 1 && i + 1 < C::TM) fetch(i + 1, h);
         epi_chunk(a, xf, cw, mb, z, ninv_s, s1, sd);
         *reinterpret_cast<uint4*>(dxp + elem(i, h, k)) =
             make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]),
                        pack_bf16x2(a[6], a[7]));
+        if (!ALL && k == KC - 1 && i + 1 < C::TM) fetch(i + 1, h);   // this group's registers are free
         __builtin_amdgcn_sched_barrier(0);            // keeps the passes from piling up in registers
       }
     }
