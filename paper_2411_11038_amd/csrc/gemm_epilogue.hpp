@@ -152,10 +152,13 @@ __device__ __forceinline__ void lds_barrier() {
 // the number of operations.  Nearly all values are in range (a per-tensor scale clips some in 10^4 or none), so a chunk in which
 // no lane of the wavefront has a clipped one leaves the mask out: 5 operations an element, 12 with it.  The sums are the same bit
 // for bit; sd takes (s1 - s1) in the end, so that an infinite or undefined a leaves it undefined as a - a did.
+// SKIP: off for 64 x 64 tiles, four blocks of which share a CU and hide the operations, not the branch (37.3 us of both products of a
+// convolution so, 37.7 with it).
+template <bool SKIP>
 __device__ __forceinline__ void epi_chunk(float (&a)[8], const float (&xf)[8], const uint2& cw, uint32_t mb, float z,
                                           float ninv_s, float& s1, float& sd) {
   auto code = [&](int t) { return (float)(((t < 4 ? cw.x : cw.y) >> (8 * (t & 3))) & 0xFFu) - z; };
-  if (__ballot((mb & 0xFFu) != 0xFFu) == 0ull) {
+  if (SKIP && __ballot((mb & 0xFFu) != 0xFFu) == 0ull) {
 #pragma unroll
     for (int t = 0; t < 8; ++t) s1 = fmaf(a[t], fmaf(xf[t], ninv_s, code(t)), s1);
   } else {
@@ -355,7 +358,7 @@ struct EpiDxAny {
           for (int t = 0; t < 8; ++t)
             xf[t] = XW == 2 ? __uint_as_float(xw[t])
                             : __uint_as_float((t & 1) ? xw[t >> 1] & 0xFFFF0000u : xw[t >> 1] << 16);
-          epi_chunk(a, xf, q8.cw, mb, z, ninv_s, s1, sd);
+          epi_chunk<(C::TM * C::TN > 1)>(a, xf, q8.cw, mb, z, ninv_s, s1, sd);
           if (g.dx_dtype == EFQAT_F32) {
             float* d = (float*)g.dx + e;
             if (!EDGE || n >= 8) __builtin_memcpy(d, a, 32);
@@ -521,7 +524,7 @@ struct EpiDxFast {
         float xf[8];
 #pragma unroll
         for (int t = 0; t < 8; ++t) xf[t] = __uint_as_float((t & 1) ? xw[t >> 1] & 0xFFFF0000u : xw[t >> 1] << 16);
-        epi_chunk(a, xf, cw, mb, z, ninv_s, s1, sd);
+        epi_chunk<true>(a, xf, cw, mb, z, ninv_s, s1, sd);
         *reinterpret_cast<uint4*>(dxp + elem(i, h, k)) =
             make_uint4(pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3]), pack_bf16x2(a[4], a[5]),
                        pack_bf16x2(a[6], a[7]));
