@@ -147,13 +147,15 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // Eight columns of one row in the dX epilogue.  a: the product; becomes dX.  xf, cw, mb: x, codes and mask bits (1 = in range).
-// s1 += a gs with gs = in range ? (code - Z) - x / S : code - Z, term by term (in range |gs| <= 1/2); sd += a where clipped.
-// A block's four wavefronts are alone on their SIMDs here and each operation takes four cycles of one: what this costs is
-// the number of operations.  Nearly all values are in range (a per-tensor scale clips some in 10^4 or none), so a chunk in which
-// no lane of the wavefront has a clipped one leaves the mask out: 5 operations an element, 12 with it.  The sums are the same bit
-// for bit; sd takes (s1 - s1) in the end, so that an infinite or undefined a leaves it undefined as a - a did.
-// SKIP: off for 64 x 64 tiles, four blocks of which share a CU and hide the operations, not the branch (37.3 us of both products of a
-// convolution so, 37.7 with it).
+// s1 += a gs with gs = in range ? (code - Z) - x / S : code - Z, term by term (in range |gs| <= 1/2); sd += a where clipped, and
+// a - a where not: nothing, but undefined for an infinite or undefined a.
+// What this costs is the number of operations, each of which takes four cycles of a SIMD that few wavefronts share.  Nearly all
+// values are in range (a per-tensor scale clips some in 10^4 or none), so a chunk in which no lane of the wavefront has a clipped one
+// leaves the mask and sd out: 5 operations an element, 12 with them.  The sums are the same bit for bit where every a is finite; where
+// one is not, s1 is not either, and the epilogue adds the a - a of its rows behind the chunks (half an operation an element to keep
+// the largest |a| for that cost the dX products 1 %).
+// SKIP: off for tiles of 64 x 64, four or three blocks of which share a CU and hide the operations, not the branch (37.3 us of both
+// products of a convolution so, 37.7 with it).
 template <bool SKIP>
 __device__ __forceinline__ void epi_chunk(float (&a)[8], const float (&xf)[8], const uint2& cw, uint32_t mb, float z,
                                           float ninv_s, float& s1, float& sd) {
@@ -173,6 +175,14 @@ __device__ __forceinline__ void epi_chunk(float (&a)[8], const float (&xf)[8], c
       a[t] = o;
     }
   }
+}
+// a product may have been infinite or undefined
+__device__ __forceinline__ bool epi_undefined(float s1) { return __ballot(!(fabsf(s1) < __builtin_inff())) != 0ull; }
+// the a - a of a chunk in range
+__device__ __forceinline__ void epi_undefined_chunk(const float* a, uint32_t mb, float& sd) {
+#pragma unroll 1
+  for (int t = 0; t < 8; ++t)
+    if ((mb >> t) & 1u) sd += a[t] - a[t];
 }
 
 // Fused epilogue of the dX product for a 256-thread block whose wavefront (wm, wn) holds the C::WM x C::WN
@@ -202,6 +212,7 @@ struct EpiDxAny {
   static constexpr int U = KC == 1 ? (NP * GS < 4 ? NP * GS : 4) : 2 * KC;
   static_assert(NP * GS % U == 0 && U % KC == 0, "passes");
   static constexpr int XW = sizeof(XT) / 2;          // 16-byte words of x per chunk
+  static constexpr bool kSkip = C::TM * C::TN > 1;   // see epi_chunk
   struct Inputs { uint2 cw; uint4 xa[XW]; uint32_t mb; };
   Inputs in[U];
   int row_b, col_b, first_row, rows;                 // rows: of this wavefront's sub-tile that lie inside the matrix
@@ -283,7 +294,7 @@ struct EpiDxAny {
   }
   __device__ __forceinline__ void finish(const GemmArgs& g, char* smem, float s1, float sd, int part_idx) {
     const float ps = wave_sum(s1);
-    const float pz = wave_sum(sd + (s1 - s1));       // see epi_chunk
+    const float pz = wave_sum(sd);
     lds_barrier();                                   // staging area is dead: reuse for the block sum
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     float* red = reinterpret_cast<float*>(smem);
@@ -294,7 +305,7 @@ struct EpiDxAny {
       g.partial[2 * part_idx + 1] = -g.s_x[0] * ((red[1] + red[3]) + (red[5] + red[7]));
     }
   }
-  // the tile's dX; s1, sd: this lane's share of the sums (see EpiDxFast)
+  // the tile's dX; s1, sd: this lane's share of the sums (see epi_chunk)
   template <bool EDGE>
   __device__ __forceinline__ void sum_tile(const GemmArgs& g, floatx16_t (&acc)[C::TM][C::TN], char* smem, float& s1,
                                            float& sd) {
@@ -358,7 +369,7 @@ struct EpiDxAny {
           for (int t = 0; t < 8; ++t)
             xf[t] = XW == 2 ? __uint_as_float(xw[t])
                             : __uint_as_float((t & 1) ? xw[t >> 1] & 0xFFFF0000u : xw[t >> 1] << 16);
-          epi_chunk<(C::TM * C::TN > 1)>(a, xf, q8.cw, mb, z, ninv_s, s1, sd);
+          epi_chunk<kSkip>(a, xf, q8.cw, mb, z, ninv_s, s1, sd);
           if (g.dx_dtype == EFQAT_F32) {
             float* d = (float*)g.dx + e;
             if (!EDGE || n >= 8) __builtin_memcpy(d, a, 32);
@@ -385,6 +396,17 @@ struct EpiDxAny {
           }
           __builtin_amdgcn_sched_barrier(0);          // keeps the passes from piling up in registers
         }
+      }
+      if (kSkip && epi_undefined(s1)) {
+#pragma unroll 1
+        for (int r = 0; r < 32 * GS; r += RP)
+#pragma unroll 1
+          for (int k = 0; k < KC; ++k) {
+            const int row = 32 * i0 + r < rows ? row_of<EDGE>(32 * i0 + r) : -1, col = col_of(k), n = g.N - col;
+            if (row < 0 || n <= 0) continue;
+            const uint32_t mb = g.x_clip[row * (((int64_t)g.N + 31) >> 5) + (col >> 5)] >> (col & 31);
+            epi_undefined_chunk(st_b + r * PITCH + 8 * LPR * k, n < 8 ? mb & ((1u << n) - 1u) : mb, sd);
+          }
       }
     }
   }
@@ -531,9 +553,18 @@ struct EpiDxFast {
         if (!ALL && k == KC - 1 && i + 1 < C::TM) fetch(i + 1, h);   // this group's registers are free
         __builtin_amdgcn_sched_barrier(0);            // keeps the passes from piling up in registers
       }
+      if (epi_undefined(s1)) {
+#pragma unroll 1
+        for (int h = 0; h < HP; ++h)
+#pragma unroll 1
+          for (int k = 0; k < KC; ++k) {
+            const uint32_t row = row_b + (uint32_t)(32 * i + RP * h), col = col_b + (uint32_t)(8 * LPR * k);
+            epi_undefined_chunk(st_b + RP * h * PITCH + 8 * LPR * k, clip[row * uwpr + (col >> 5)] >> msh, sd);
+          }
+      }
     }
     const float ps = wave_sum(s1);
-    const float pz = wave_sum(sd + (s1 - s1));       // see epi_chunk
+    const float pz = wave_sum(sd);
     lds_barrier();                                   // staging area is dead: reuse for the block sum
     float* red = reinterpret_cast<float*>(smem);
     if (lane == 0) { red[2 * wave] = ps; red[2 * wave + 1] = pz; }
