@@ -419,6 +419,10 @@ int efqat_linear_bwd_plan(int64_t T, int64_t c_in, int64_t c_out, int64_t k, int
                           int32_t* plan);
 int efqat_conv_bwd_plan(int64_t N, int64_t H, int64_t W, int64_t c_in, int64_t c_out, int64_t KH, int64_t KW,
                         int64_t stride, int64_t pad, int64_t k, int dy_dtype, int dy_layout, int dx_kernel, int32_t* plan);
+/* What efqat_linear_fwd launches.  plan: int32_t[2], host pointer out. */
+#define EFQAT_FWD_PLAN_FEW_TOKENS 0 /* 1: fragments straight from memory, 0: tiles through LDS */
+#define EFQAT_FWD_PLAN_COLUMNS 1    /* output columns of a block */
+int efqat_linear_fwd_plan(int64_t T, int64_t c_in, int64_t c_out, int32_t* plan);
 
 #ifdef __cplusplus
 }

@@ -29,6 +29,7 @@ EXPORTS = [
     "efqat_conv_bwd_workspace_bytes", "efqat_conv_bwd_workspace_bytes_ex", "efqat_conv_bwd", "efqat_conv_bwd_ex",
     "efqat_linear_fwd_workspace_bytes", "efqat_linear_fwd",
     "efqat_profile_enable", "efqat_profile_read", "efqat_linear_bwd_plan", "efqat_conv_bwd_plan",
+    "efqat_linear_fwd_plan",
 ]
 
 
@@ -125,6 +126,8 @@ def lib():
     L.efqat_profile_read.argtypes = [ci, C.POINTER(C.c_double), C.POINTER(C.c_int64)]
     L.efqat_linear_bwd_plan.restype = ci
     L.efqat_linear_bwd_plan.argtypes = [i64] * 4 + [ci, ci, ci, C.POINTER(C.c_int32)]
+    L.efqat_linear_fwd_plan.restype = ci
+    L.efqat_linear_fwd_plan.argtypes = [i64] * 3 + [C.POINTER(C.c_int32)]
     L.efqat_conv_bwd_plan.restype = ci
     L.efqat_conv_bwd_plan.argtypes = [i64] * 10 + [ci, ci, ci, C.POINTER(C.c_int32)]
     _LIB = L
@@ -213,6 +216,13 @@ def conv_bwd_plan(N, H, W, c_in, c_out, KH, KW, stride, pad, k, dy_dtype=BF16, d
     _check(lib().efqat_conv_bwd_plan(N, H, W, c_in, c_out, KH, KW, stride, pad, k, dy_dtype, dy_layout, dx_kernel, out),
            "efqat_conv_bwd_plan")
     return dict(zip(_PLAN, out))
+
+
+def linear_fwd_plan(T, c_in, c_out) -> dict:
+    """What linear_fwd launches (EFQAT_FWD_PLAN_* of include/efqat.h); needs no GPU."""
+    out = (C.c_int32 * 2)()
+    _check(lib().efqat_linear_fwd_plan(T, c_in, c_out, out), "efqat_linear_fwd_plan")
+    return dict(few_tokens=out[0], columns=out[1])
 
 
 def k_from_ratio(c_out: int, num: int, den: int) -> int:

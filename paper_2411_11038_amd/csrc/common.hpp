@@ -186,5 +186,6 @@ int launch_topk_profiled(const double* scores, int64_t n, int64_t k, int32_t* id
 int launch_gemm_fwd_i8(const uint8_t* x_codes, int64_t lda, const int8_t* w_codes, int64_t ldb, int64_t M, int64_t N,
                        int64_t K, const float* s_x, const float* z_x, const float* s_w, void* y, int y_dtype,
                        hipStream_t stream);
+int fwd_tile_columns(int64_t M, int64_t N, int64_t K);   // of the tile that it takes
 
 }  // namespace efqat

@@ -126,8 +126,13 @@ constexpr int64_t kSkinnyTokens = 64;
 
 // Groups of 16 weight rows of a block (NT of k_fwd_skinny).  The fragments of the tokens are read from L2 by every block and cost as
 // much of the loads as T rows of weights, so a wide block saves loads; but what takes the time is the busiest CU, and a block that
-// leaves CUs idle, or a second one for a few of them, costs more.  Loads of the busiest CU in units of 16 rows, and half a unit for
-// every group, in which wide blocks hide latency worse.  Fitted to 18 sizes by NT = 1 / 2 / 3 / 4, us (* chosen):
+// leaves CUs idle, or a second one for a few of them, costs more.  In units of 16 bytes and column of C_in: the loads and the
+// reductions of the busiest CU's blocks, and per group the latency that a wide block hides worse.  Under a floor the loads are free:
+// several blocks of one group share a CU, and what is left of a wide block is its longer reduction.  Rows that are not aligned take
+// more loads a fragment, each with its own wait: where they are short, wide blocks pay late.  Fitted to 1398 sizes (1 to 64 tokens,
+// C_in 64 to 11008, C_out 4096 to 32768): 1.2 % from the fastest in the mean; 0.91 of the time of one group (four from 33 tokens and
+// 8192 columns on), the first rule, and 0.98 of the second, the loads alone, which was up to 1.4 x as slow as the first where rows
+// are short.  NT = 1 / 2 / 3 / 4, us (* chosen):
 //   tokens  C_in  -> C_out
 //    1      4096     11008    11.9* / 14.7  / 14.1  / 16.0
 //   16      4096      6000    11.6  / 10.6* / 13.2  / 15.7
@@ -137,14 +142,28 @@ constexpr int64_t kSkinnyTokens = 64;
 //   32      4096     11008    22.9  / 22.9  / 18.1* / 21.1
 //   64      4096      6000    24.2  / 18.2* / 20.6  / 23.8
 //   64      4096     11008    35.2  / 30.6  / 23.1* / 26.1
-//   64      2048     16384    24.6  / 18.3  / 25.0  / 17.4*
-// (before, NT was 4 for 33 tokens and more on 8192 columns and more, else 1.)
-static int skinny_columns(int64_t T, int64_t c_out) {
+//   16        96     11008     3.7* /  4.2  /  4.7  /  4.4
+//   16        96     28672     6.4  /  6.5  /  7.8  /  4.9*
+//   64       256      4112     4.4* /  5.4  /  6.2  /  7.1
+//   64       192      8192     4.5* /  5.1  /  6.0  /  6.8
+//   16      1024      4112     4.5* /  4.8  /  5.8  /  5.8
+//   32      1024     32768    18.2  / 15.6  / 14.6  / 12.8*
+//   16       333     11008     6.7* /  8.0  /  8.8  /  9.4
+//   20      1500      8192    10.2* / 10.9  / 13.3  / 15.6
+//   16      3001     28672    58.2  / 51.0  / 53.5  / 43.9*
+static int skinny_columns(int64_t T, int64_t c_in, int64_t c_out) {
+  if (T <= 4) return 1;                                 // next to no loads to save
+  if (c_in < 640 && c_out < 5120) return 1;             // a second block on some CUs runs beside the first
+  if (c_in % 16 && c_in < 2048 &&
+      (T <= 16 ? c_out < 16384 || c_in % 4 == 0 : T <= 32 ? c_in >= 1024 && c_out < 12288 : c_out < (c_in < 640 ? 8192 : 4608)))
+    return 1;
+  const double mt = T <= 16 ? 1.0 : T <= 32 ? 2.0 : 4.0, k = (double)c_in;
   int best = 1;
   double best_t = 0.0;
   for (int nt = 1; nt <= 4; ++nt) {
     const double rounds = (double)ceil_div(ceil_div(c_out, 16 * nt), 256);
-    const double t = rounds * (nt + (double)T / 16.0) + 0.5 * nt;
+    const double loads = rounds * (k * (nt + 1.2 * (double)T / 16.0) + 600.0 * mt * nt + 1000.0);
+    const double t = std::max(loads, 8000.0) + nt * (0.55 * k + 450.0 * mt);
     if (nt == 1 || t < best_t) { best = nt; best_t = t; }
   }
   return best;
@@ -202,7 +221,7 @@ extern "C" int efqat_linear_fwd(const uint8_t* x_codes, const float* s_x, const 
                      (int)c_out, (int)c_in, s_x, z_x, s_w, y, y_dtype)
     // steps of 64 columns whose loads are in flight together: what the registers allow, more measured the same
 #define EFQAT_SKINNY_NT(MT, B1, B2, B3, B4)                                                                              \
-  switch (skinny_columns(T, c_out)) {                                                                                    \
+  switch (skinny_columns(T, c_in, c_out)) {                                                                                    \
     case 1: EFQAT_SKINNY(MT, 1, B1); break;                                                                              \
     case 2: EFQAT_SKINNY(MT, 2, B2); break;                                                                              \
     case 3: EFQAT_SKINNY(MT, 3, B3); break;                                                                              \
@@ -231,4 +250,13 @@ extern "C" int efqat_linear_fwd(const uint8_t* x_codes, const float* s_x, const 
     xa = xpad; wb = (const int8_t*)wpad;
   }
   return launch_gemm_fwd_i8(xa, p.ldk, wb, p.ldk, T, c_out, p.ldk, s_x, z_x, s_w, y, y_dtype, st);
+}
+
+extern "C" int efqat_linear_fwd_plan(int64_t T, int64_t c_in, int64_t c_out, int32_t* plan) {
+  if (!plan) return EFQAT_ERR_NULL_PTR;
+  if (T <= 0 || c_in <= 0 || c_out <= 0 || T > (1 << 30) || c_out > (1 << 30) || c_in > (1 << 17)) return EFQAT_ERR_BAD_SHAPE;
+  const bool few = T <= kSkinnyTokens;
+  plan[EFQAT_FWD_PLAN_FEW_TOKENS] = few;
+  plan[EFQAT_FWD_PLAN_COLUMNS] = few ? 16 * skinny_columns(T, c_in, c_out) : fwd_tile_columns(T, c_out, make_fwd_plan(T, c_in, c_out).ldk);
+  return EFQAT_OK;
 }

@@ -10,8 +10,9 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("c_out", (4100, 6001, 8191, 8193, 11009, 12305, 16385, 28673))
 @pytest.mark.parametrize("T", (1, 5, 16, 17, 32, 33, 64))
-def test_against_integer_arithmetic(T, c_out):
-    c_in = 83 if T % 2 else 528
+@pytest.mark.parametrize("long", (False, True), ids=("short", "long"))   # short rows take wide blocks for many columns only
+def test_against_integer_arithmetic(T, c_out, long):
+    c_in = (2083 if T % 2 else 1552) if long else 83 if T % 2 else 528
     g = torch.Generator(device="cuda")
     g.manual_seed(T * c_out)
     x = torch.randint(0, 256, (T, c_in), generator=g, device="cuda", dtype=torch.uint8)

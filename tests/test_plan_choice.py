@@ -29,3 +29,25 @@ def test_dw_plan_of_gathered_codes():
     # two blocks of 128 x 128 a CU, not three: 64-row tiles 582 us, 24 slices of 128-row tiles 616
     p = ef.conv_bwd_plan(64, 47, 47, 512, 384, 2, 2, 1, 1, 192)
     assert (p["dw_operands"], p["dw_tile"]) == (2, 64)
+
+
+# tokens, C_in, C_out, columns of a block; us by 16 / 32 / 48 / 64 columns
+FEW_TOKENS = [
+    (16, 96, 11008, 16),      # 3.7 / 4.2 / 4.7 / 4.4    short rows: one group of 16
+    (64, 256, 4112, 16),      # 4.4 / 5.4 / 6.2 / 7.1
+    (16, 1024, 4112, 16),     # 4.5 / 4.8 / 5.8 / 5.8
+    (64, 192, 8192, 16),      # 4.5 / 5.1 / 6.0 / 6.8
+    (16, 333, 11008, 16),     # 6.7 / 8.0 / 8.8 / 9.4    ... not aligned
+    (20, 1500, 8192, 16),     # 10.2 / 10.9 / 13.3 / 15.6
+    (16, 96, 28672, 64),      # 6.4 / 6.5 / 7.8 / 4.9    many columns
+    (32, 1024, 32768, 64),    # 18.2 / 15.6 / 14.6 / 12.8
+    (16, 4096, 11008, 48),    # 17.1 / 18.3 / 15.8 / 17.7
+    (64, 4096, 6000, 32),     # 24.2 / 18.2 / 20.6 / 23.8
+    (16, 3001, 28672, 64),    # 58.2 / 51.0 / 53.5 / 43.9
+]
+
+
+@pytest.mark.parametrize("case", FEW_TOKENS, ids=str)
+def test_columns_of_a_block_of_few_tokens(case):
+    T, c_in, c_out, columns = case
+    assert ef.linear_fwd_plan(T, c_in, c_out) == dict(few_tokens=1, columns=columns)
