@@ -409,7 +409,7 @@ int efqat_profile_read(int which, double* total_ms, int64_t* launches);
  * Host functions; plan: int32_t[8], host pointer out. */
 #define EFQAT_PLAN_ONE_GRID 0    /* 1: both products in one launch */
 #define EFQAT_PLAN_SIDE_STREAM 1 /* 1: a side_stream of the call is used */
-#define EFQAT_PLAN_DX_KERNEL 2   /* 0 two LDS stages, 1 ring of three (both on bf16 operands), 2 int8 weight codes */
+#define EFQAT_PLAN_DX_KERNEL 2   /* 0 two LDS stages, 1 ring of three or more (both on bf16 operands), 2 int8 weight codes */
 #define EFQAT_PLAN_DX_TILE 3     /* rows of a tile */
 #define EFQAT_PLAN_DX_ROWS 4     /* A operand: 0 rows of a matrix, 1 gathered at stride 1, 2 gathered by stride phase, 3 im2col matrix */
 #define EFQAT_PLAN_DW_OPERANDS 5 /* 0 no dW product, 1 token major, 2 token major with gathered codes, 3 staged, 4 rows of a channel-major dY */
@@ -419,6 +419,12 @@ int efqat_linear_bwd_plan(int64_t T, int64_t c_in, int64_t c_out, int64_t k, int
                           int32_t* plan);
 int efqat_conv_bwd_plan(int64_t N, int64_t H, int64_t W, int64_t c_in, int64_t c_out, int64_t KH, int64_t KW,
                         int64_t stride, int64_t pad, int64_t k, int dy_dtype, int dy_layout, int dx_kernel, int32_t* plan);
+/* Tile of the dX product of a linear layer, with (1) or without (0) a side_stream.  tile: int32_t[3], host pointer out. */
+#define EFQAT_DX_TILE_ROWS 0
+#define EFQAT_DX_TILE_COLUMNS 1
+#define EFQAT_DX_TILE_STAGES 2   /* LDS stages */
+int efqat_linear_bwd_dx_tile(int64_t T, int64_t c_in, int64_t c_out, int64_t k, int dy_dtype, int dy_layout, int dx_kernel,
+                             int side_stream, int32_t* tile);
 /* What efqat_linear_fwd launches.  plan: int32_t[2], host pointer out. */
 #define EFQAT_FWD_PLAN_FEW_TOKENS 0 /* 1: fragments straight from memory, 0: tiles through LDS */
 #define EFQAT_FWD_PLAN_COLUMNS 1    /* output columns of a block */

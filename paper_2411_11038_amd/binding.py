@@ -29,7 +29,7 @@ EXPORTS = [
     "efqat_conv_bwd_workspace_bytes", "efqat_conv_bwd_workspace_bytes_ex", "efqat_conv_bwd", "efqat_conv_bwd_ex",
     "efqat_linear_fwd_workspace_bytes", "efqat_linear_fwd",
     "efqat_profile_enable", "efqat_profile_read", "efqat_linear_bwd_plan", "efqat_conv_bwd_plan",
-    "efqat_linear_fwd_plan",
+    "efqat_linear_bwd_dx_tile", "efqat_linear_fwd_plan",
 ]
 
 
@@ -126,6 +126,8 @@ def lib():
     L.efqat_profile_read.argtypes = [ci, C.POINTER(C.c_double), C.POINTER(C.c_int64)]
     L.efqat_linear_bwd_plan.restype = ci
     L.efqat_linear_bwd_plan.argtypes = [i64] * 4 + [ci, ci, ci, C.POINTER(C.c_int32)]
+    L.efqat_linear_bwd_dx_tile.restype = ci
+    L.efqat_linear_bwd_dx_tile.argtypes = [i64] * 4 + [ci, ci, ci, ci, C.POINTER(C.c_int32)]
     L.efqat_linear_fwd_plan.restype = ci
     L.efqat_linear_fwd_plan.argtypes = [i64] * 3 + [C.POINTER(C.c_int32)]
     L.efqat_conv_bwd_plan.restype = ci
@@ -208,6 +210,14 @@ def linear_bwd_plan(T, c_in, c_out, k, dy_dtype=BF16, dy_layout=DY_TOKEN_MAJOR, 
     out = (C.c_int32 * len(_PLAN))()
     _check(lib().efqat_linear_bwd_plan(T, c_in, c_out, k, dy_dtype, dy_layout, dx_kernel, out), "efqat_linear_bwd_plan")
     return dict(zip(_PLAN, out))
+
+
+def linear_bwd_dx_tile(T, c_in, c_out, k, dy_dtype=BF16, dy_layout=DY_TOKEN_MAJOR, dx_kernel=0, side_stream=False) -> dict:
+    """Tile of linear_bwd's dX product (EFQAT_DX_TILE_* of include/efqat.h); needs no GPU."""
+    out = (C.c_int32 * 3)()
+    _check(lib().efqat_linear_bwd_dx_tile(T, c_in, c_out, k, dy_dtype, dy_layout, dx_kernel, int(side_stream), out),
+           "efqat_linear_bwd_dx_tile")
+    return dict(rows=out[0], columns=out[1], stages=out[2])
 
 
 def conv_bwd_plan(N, H, W, c_in, c_out, KH, KW, stride, pad, k, dy_dtype=BF16, dy_layout=DY_TOKEN_MAJOR, dx_kernel=0) -> dict:

@@ -947,7 +947,7 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   } else if (p.dx8) {
     rc = launch_gemm_dx8(dy_tok, c_out, io.w_codes, c_in, io.s_w, p.Mx, c_in, c_out, p.dx8_tile, epi, st);
   } else {
-    rc = launch_dx(dxa, conv, p.plan_dx, st);
+    rc = launch_dx(dxa, conv, p.plan_dx, use_side, st);
   }
   if (rc) return rc;
   const int64_t n_part_dx = (int64_t)p.plan_dx.tiles_m * p.plan_dx.tiles_n;
@@ -1123,6 +1123,22 @@ extern "C" int efqat_linear_bwd_plan(int64_t T, int64_t c_in, int64_t c_out, int
   if (rc) return rc;
   return plan_info(make_plan(T, T, c_in, c_out, 1, k, dy_dtype, dy_layout, false, dx_kernel, nullptr, c_in > kMaxStagedColumns), false,
                    k, plan);
+}
+
+extern "C" int efqat_linear_bwd_dx_tile(int64_t T, int64_t c_in, int64_t c_out, int64_t k, int dy_dtype, int dy_layout, int dx_kernel,
+                                        int side_stream, int32_t* tile) {
+  if (!linear_shape_ok(T, c_in, c_out)) return EFQAT_ERR_BAD_SHAPE;
+  const int rc = plan_args(c_out, k, dy_dtype, dy_layout, dx_kernel, tile);
+  if (rc) return rc;
+  const BwdPlan p = make_plan(T, T, c_in, c_out, 1, k, dy_dtype, dy_layout, false, dx_kernel, nullptr, c_in > kMaxStagedColumns);
+  const int rows = p.dx8 ? p.dx8_tile : p.plan_dx.tile;
+  tile[EFQAT_DX_TILE_ROWS] = rows;
+  tile[EFQAT_DX_TILE_COLUMNS] = !p.dx8 ? rows : rows == 256 || (p.cmx && p.plan_dx.ring) ? 256 : 128;
+  tile[EFQAT_DX_TILE_STAGES] = p.dx8 || !p.plan_dx.ring ? 2
+                               : p.pair ? 3
+                                        : kk_ring_stages(rows, (int64_t)p.plan_dx.tiles_m * p.plan_dx.tiles_n, p.Kx,
+                                                         side_stream && takes_side_stream(p));
+  return EFQAT_OK;
 }
 
 extern "C" size_t efqat_linear_bwd_weight_operand_bytes(int64_t T, int64_t c_in, int64_t c_out, int dy_dtype,

@@ -332,11 +332,11 @@ int launch_gemm_nt_raw(const GemmArgs& a, const GemmPlan& plan, hipStream_t stre
   }
 }
 
-int launch_dx(const GemmStridedArgs& a, int conv, const GemmPlan& plan, hipStream_t stream) {
+int launch_dx(const GemmStridedArgs& a, int conv, const GemmPlan& plan, bool beside, hipStream_t stream) {
   const bool fast = dx_epilogue_fast(a, plan.tile, plan.tile);
   if (plan.ring)
     return conv == 2 ? launch_gemm_kk_conv_strided(a, plan.tile, stream)
-                     : conv == 1 ? launch_gemm_kk_conv(a, plan.tile, stream) : launch_gemm_kk(a, plan.tile, stream);
+                     : conv == 1 ? launch_gemm_kk_conv(a, plan.tile, stream) : launch_gemm_kk(a, plan.tile, beside, stream);
   if (conv == 2)
     return plan.tile == 64 ? launch_cfg<64, 64, EPI_DX, false, 2>(a, 1, stream) : launch_cfg<128, 128, EPI_DX, false, 2>(a, 1, stream);
   if (conv == 1) {

@@ -1,9 +1,20 @@
-// Launches of the dX kernels with the ring of three LDS stages (gemm_kk.hpp).
+// Launches of the dX kernels with the ring of LDS stages (gemm_kk.hpp).
 #include "gemm_kk.hpp"
 
 namespace efqat {
 
-constexpr int kKkDeep = 8;                             // stages of a 64 x 64 tile that has a CU for itself
+// LDS stages of the ring.  64 x 64 tiles of a linear layer that have a CU for themselves take eight, 128 KB, where the contraction is
+// long; before, the deeper prologue and drain of a block cost more than they hide.  Backward call, three / eight, us:
+//   512 x 2048 -> 768    18.2 / 17.7      512 x 1792 -> 768    17.6 / 17.8      512 x 512 -> 768   12.6 / 13.5
+//   1000 x 4096 -> 777   33.8 / 27.5      200 x 8000 -> 100    38.0 / 32.5
+// With the dW product on a second stream its blocks need room beside them, unless half of the CUs have no dX block:
+//   512 x 8000 -> 1024, k = 2000, 128 tiles, 58.4 / 53.8; 1024 x 8000 -> 1024, 256 tiles, 64.0 / 72.1.
+// Convolutions form an address for every copy, and eight stages of that code cost them 1 to 19 % at 1 to 196 tiles and 9 to 400 K stages.
+// Four stages of the 128 x 128 tile gain nothing.
+constexpr int kKkDeep = 8;
+int kk_ring_stages(int tile, int64_t tiles, int64_t K, bool beside) {
+  return tile == 64 && K >= 32 * 64 && tiles <= (beside ? 128 : 256) ? kKkDeep : 3;
+}
 
 template <int BM, int BN, int EPI, int CONV = 0, int NST = 3>
 static int launch_kk_cfg(const typename ConvArgs<CONV>::type& a, hipStream_t st) {
@@ -21,10 +32,10 @@ static int launch_kk_cfg(const typename ConvArgs<CONV>::type& a, hipStream_t st)
   return EFQAT_OK;
 }
 
-int launch_gemm_kk(const GemmArgs& a, int tile, hipStream_t stream) {
+int launch_gemm_kk(const GemmArgs& a, int tile, bool beside, hipStream_t stream) {
   // bf16 in and out, whole tiles, 32-bit element offsets: nothing to decide at run time, the straight-line epilogue
   const bool fast = dx_epilogue_fast(a, tile, tile);
-  const bool few = (int64_t)a.tiles_m * a.tiles_n <= 256;
+  const bool deep = kk_ring_stages(tile, (int64_t)a.tiles_m * a.tiles_n, a.K, beside) == kKkDeep;
   switch (tile) {
     case 192:
       if (fast) return launch_kk_cfg<192, 192, EPI_DXF>(a, stream);
@@ -33,7 +44,7 @@ int launch_gemm_kk(const GemmArgs& a, int tile, hipStream_t stream) {
       if (fast) return launch_kk_cfg<128, 128, EPI_DXF>(a, stream);
       return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<128, 128, EPI_DXS>(a, stream) : launch_kk_cfg<128, 128, EPI_DX>(a, stream);
     case 64:
-      if (few) return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<64, 64, EPI_DXS, 0, kKkDeep>(a, stream) : launch_kk_cfg<64, 64, EPI_DX, 0, kKkDeep>(a, stream);
+      if (deep) return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<64, 64, EPI_DXS, 0, kKkDeep>(a, stream) : launch_kk_cfg<64, 64, EPI_DX, 0, kKkDeep>(a, stream);
       return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<64, 64, EPI_DXS>(a, stream) : launch_kk_cfg<64, 64, EPI_DX>(a, stream);
     default:
       return EFQAT_ERR_BAD_SHAPE;
@@ -42,8 +53,6 @@ int launch_gemm_kk(const GemmArgs& a, int tile, hipStream_t stream) {
 
 // dX product of a stride-1 convolution; `a` by dx_args_conv
 int launch_gemm_kk_conv(const GemmArgs& a, int tile, hipStream_t stream) {
-  if (tile == 64 && (int64_t)a.tiles_m * a.tiles_n <= 256)
-    return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<64, 64, EPI_DXS, 1, kKkDeep>(a, stream) : launch_kk_cfg<64, 64, EPI_DX, 1, kKkDeep>(a, stream);
   if (tile == 64)
     return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<64, 64, EPI_DXS, 1>(a, stream) : launch_kk_cfg<64, 64, EPI_DX, 1>(a, stream);
   if (dx_epilogue_fast(a, 128, 128)) return launch_kk_cfg<128, 128, EPI_DXF, 1>(a, stream);

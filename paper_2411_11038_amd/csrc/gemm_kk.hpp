@@ -11,11 +11,9 @@
 // scheduler the reads and copies clump and the matrix cores idle for more than half of the loop.
 //
 // 256 threads; square tiles of 192 (96 x 96 per wavefront, 9 accumulators), 128 or 64, wavefront grid 2 x 2;
-// v_mfma_f32_32x32x16_bf16; K-stage of 64; a ring of three LDS stages (144, 96 or 48 KB; one block a CU, of the
-// 64 x 64 tile three, which serves products of too few larger tiles, and of that one eight stages, 128 KB, where there is no
-// more than a block a CU: 64 x 4096 -> 4096 36.3 -> 34.0 us, 200 x 8000 -> 100 fp32 43.6 -> 35.2; four stages of the 128 x 128
-// tile gain nothing): the copies of stage kt + 2 are issued
-// while stage kt is multiplied and are only waited for at the end of stage kt + 1, so a copy may take more than a
+// v_mfma_f32_32x32x16_bf16; K-stage of 64; a ring of NST LDS stages: three (144, 96 or 48 KB; one block a CU, of the 64 x 64 tile
+// three, which serves products of too few larger tiles), or eight (see kk_ring_stages).  The copies of stage kt + NST - 1 are issued
+// while stage kt is multiplied and are only waited for at the end of stage kt + NST - 2, so with three a copy may take more than a
 // whole stage (about 1200 cycles of MFMA work at 192 x 192) before it stalls anything - with two stages the memory latency under
 // load did not fit.  Rows past M / N re-read the last valid row (their outputs are discarded), chunks past K come
 // from a zero page, so no copy needs a predicate.

@@ -1,5 +1,7 @@
-"""dX on 64 x 64 tiles with a ring of eight stages (no more than a block a CU): contractions shorter than the ring, around it and its
-multiples, ragged last stages, against the tiles of 192, which add the same products in the same order (bit for bit)."""
+"""dX of few 64 x 64 tiles: on a ring of eight stages from 32 K stages on (linear layers), every remainder of the ring's rounds, whole and
+ragged last stages; shorter contractions on the ring of three or, below seven stages, without a ring.  Against the tiles of 192, which
+add the same products in the same order: dX bit for bit, the sums of dS_x and dZ_x in another order.  Convolutions of few tiles, on the
+ring of three, against double precision."""
 import numpy as np
 import pytest
 import torch
@@ -18,22 +20,33 @@ def _in_range(fx, cols):
 
 
 @pytest.mark.parametrize("dt", (torch.bfloat16, torch.float32), ids=("bf16", "f32"))
-@pytest.mark.parametrize("c_out", (8, 64, 72, 448, 504, 512, 520, 960, 1016, 1032, 1088, 1536, 2056))
+@pytest.mark.parametrize("c_out", (8, 64, 72, 392, 448, 504, 512, 520, 960, 1016, 1032, 1088, 1536, 2040) +
+                         tuple(range(2048, 2560, 64)) + tuple(range(2056, 2568, 64)) + (2560, 4104))
 def test_against_tiles_of_192(c_out, dt):
     T, c_in = 150, 200
+    tile = ef.linear_bwd_dx_tile(T, c_in, c_out, 0, ef.BF16 if dt == torch.bfloat16 else ef.F32)
+    assert tile["rows"] == 64 and (tile["stages"] == 8 if c_out >= 2041 else tile["stages"] in (2, 3))
     g = torch.Generator(device="cuda")
     g.manual_seed(c_out)
     x = torch.randn(T, c_in, generator=g, device="cuda").to(dt)
     w = torch.randn(c_out, c_in, generator=g, device="cuda") * 0.05
     dy = torch.randn(T, c_out, generator=g, device="cuda").to(dt)
     fx = ef.fakequant_fwd(x, ef.ACT_PER_TENSOR_ASYM, 8)
+    fx["scale"] *= 0.3                                 # a fifth is clipped
+    ef.fakequant_fwd(x, ef.ACT_PER_TENSOR_ASYM, 8, init_minmax=False, out=fx)
     fw = ef.fakequant_fwd(w, ef.W_PER_ROW_SYM, 8)
     args = (dy, fx["codes"], fx["clip_bits"], x, fx["scale"], fx["zero_point"], fw["codes"], fw["clip_bits"], w, fw["scale"], None)
-    got = [ef.linear_bwd(*args, dx_kernel=k)["dx"] for k in (ef.DX_KERNEL_AUTO, ef.DX_KERNEL_BF16_PINNED)]
-    ref = (dy.double() @ (fw["codes"].double() * fw["scale"].double()[:, None]) * _in_range(fx, c_in)).float()
-    assert torch.equal(got[0], got[1])
+    got = [ef.linear_bwd(*args, dx_kernel=k) for k in (ef.DX_KERNEL_AUTO, ef.DX_KERNEL_BF16_PINNED)]
+    inr, full = _in_range(fx, c_in), dy.double() @ (fw["codes"].double() * fw["scale"].double()[:, None])
+    ref = (full * inr).float()
+    assert torch.equal(got[0]["dx"], got[1]["dx"])
     # W_q (and a fp32 dY) rounded to bf16, dX to its type: the bound of bwd_checks.py
-    assert (got[0].float() - ref).abs().max() <= 2e-2 * ref.abs().max()
+    assert (got[0]["dx"].float() - ref).abs().max() <= 2e-2 * ref.abs().max()
+    # fp32 sums in two orders: 1e-5 of the 2-norm of their terms (bwd_checks.py)
+    q, s = fx["codes"].double() - fx["zero_point"].double().round(), fx["scale"].double()
+    terms = dict(ds_x=full * (q - inr * x.double() / s), dz_x=s * full * (1 - inr))
+    for n, t in terms.items():
+        assert (got[0][n].double() - got[1][n].double()).abs() <= 1e-5 * t.norm()
 
 
 @pytest.mark.parametrize("size", [(2, 9, 7, 64, 3), (1, 14, 14, 192, 3), (4, 5, 5, 128, 5), (8, 7, 7, 512, 3)], ids=str)

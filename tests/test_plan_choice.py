@@ -31,6 +31,25 @@ def test_dw_plan_of_gathered_codes():
     assert (p["dw_operands"], p["dw_tile"]) == (2, 64)
 
 
+# T, c_in, c_out, k, with a second stream, LDS stages of the ring on 64 x 64 tiles; us with three / eight
+RING = [
+    (512, 768, 512, 0, False, 3),        # 12.6 / 13.5    short contractions
+    (512, 768, 1792, 0, False, 3),       # 17.6 / 17.8
+    (512, 768, 2048, 0, False, 8),       # 18.2 / 17.7
+    (1000, 777, 4096, 0, False, 8),      # 33.8 / 27.5
+    (1024, 1024, 8000, 2000, False, 8),  # 70.6 / 67.0
+    (1024, 1024, 8000, 2000, True, 3),   # 64.0 / 72.1    no room for the blocks of the dW product
+    (512, 1024, 8000, 2000, True, 8),    # 58.4 / 53.8    ... but where half of the CUs have no dX block
+]
+
+
+@pytest.mark.parametrize("case", RING, ids=str)
+def test_ring_of_dx_tiles(case):
+    T, c_in, c_out, k, side, stages = case
+    assert ef.linear_bwd_plan(T, c_in, c_out, k)["one_grid"] == 0
+    assert ef.linear_bwd_dx_tile(T, c_in, c_out, k, side_stream=side) == dict(rows=64, columns=64, stages=stages)
+
+
 # tokens, C_in, C_out, columns of a block; us by 16 / 32 / 48 / 64 columns
 FEW_TOKENS = [
     (16, 96, 11008, 16),      # 3.7 / 4.2 / 4.7 / 4.4    short rows: one group of 16
