@@ -1133,7 +1133,7 @@ extern "C" int efqat_linear_bwd_dx_tile(int64_t T, int64_t c_in, int64_t c_out, 
   const BwdPlan p = make_plan(T, T, c_in, c_out, 1, k, dy_dtype, dy_layout, false, dx_kernel, nullptr, c_in > kMaxStagedColumns);
   const int rows = p.dx8 ? p.dx8_tile : p.plan_dx.tile;
   tile[EFQAT_DX_TILE_ROWS] = rows;
-  tile[EFQAT_DX_TILE_COLUMNS] = !p.dx8 ? rows : rows == 256 || (p.cmx && p.plan_dx.ring) ? 256 : 128;
+  tile[EFQAT_DX_TILE_COLUMNS] = !p.dx8 ? rows : rows == 256 || (p.cmx && p.plan_dx.wide) ? 256 : 128;
   tile[EFQAT_DX_TILE_STAGES] = p.dx8 || !p.plan_dx.ring ? 2
                                : p.pair ? 3
                                         : kk_ring_stages(rows, (int64_t)p.plan_dx.tiles_m * p.plan_dx.tiles_n, p.Kx,

@@ -105,13 +105,13 @@ struct GemmEpilogueDx {   // fused STE + activation-qparam partial sums (Eq. 5 l
 // true when the fused epilogue may use 8-element vector accesses on x_codes / x / dx
 bool gemm_epilogue_vec_ok(const GemmEpilogueDx& e, int64_t N);
 
-// Launch shape of one product: square block tile (256, 192, 128 or 64), split-K factor, tile grid; dX products: whether
-// the kernel with the ring of three LDS stages (k_gemm_kk) runs them.
+// Launch shape of one product: rows of its block tile (256, 192, 128 or 64), split-K factor, tile grid.
 struct GemmPlan {
   int tile;
   int split_k;
   int tiles_m, tiles_n;
-  bool ring;      // channel-major dX with tile 128: 128 x 256
+  bool ring;      // dX products: by the kernel with the ring of LDS stages (k_gemm_kk)
+  bool wide;      // dX of a channel-major dY: 128 x 256, where tile 128 is 128 x 128 otherwise
 };
 // Pure host functions of the problem size (so the workspace query and the call agree).  allow_split = false: a product
 // with the fused dX epilogue.
@@ -126,7 +126,7 @@ GemmPlan dx_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const Con
 // gather of a convolution (64 x 128, 128), or from the staged operands by k_gemm_nt (64, 128, 192, 256).
 enum DwKind { DW_TOKENS = 0, DW_CONV = 1, DW_STAGED = 2, DW_ROWS = 3 };   // DW_ROWS: rows of a channel-major dY, k_gemm_dx8
 GemmPlan dw_plan(DwKind kind, int64_t M, int64_t N, int64_t K, double* price = nullptr);   // price: 0 where it has none
-// dX of a channel-major dY by k_gemm_dx8 (tiles 64 x 128, 128, 256), and it with its dW product in one grid
+// dX of a channel-major dY by k_gemm_dx8 (tiles 64 x 128, 128 x 128, 128 x 256, 256 x 256), and it with its dW product in one grid
 GemmPlan dx_cm_plan(int64_t M, int64_t N, int64_t K, double* price);
 bool pair_cm_plan(int64_t M, int64_t N, int64_t K, int64_t dw_m, int64_t dw_n, int64_t dw_k, double apart, GemmPlan* dx, GemmPlan* dw);
 // Plans of both products in one grid of 64-row tiles, if that is priced lower than one after the other (`apart` us)

@@ -64,7 +64,7 @@ GemmPlan gemm_plan(int64_t M, int64_t N, int64_t K, bool allow_split, bool allow
 // more calls (0.4 % from the fastest in the mean; with the row of dx8 0.6 %, and whole bf16 tiles were taken where they lose:
 // 5888 x 1716 -> 5888 205 us, now 175 on 192 x 192; 16384 x 1020 -> 2048 118, now 105 on 128 x 128).
 // Convolutions pay for the gather in every stage.
-struct DxTile { int t; bool ring; int bpc; double lone[2], full[2], f32[2], fast[2]; };
+struct DxTile { int t; bool ring; int bpc; double lone[2], full[2], f32[2], fast[2]; int bn; };   // bn: columns, 0: as many as rows
 static const DxTile kDxTiles[] = {{64, true, 3, {0.28, 5.6}, {0.73, 4.5}, {0.1, 1.0}, {0.0, 0.0}},
                                   {64, false, 4, {0.465, 4.4}, {0.965, 4.4}, {0.1, 1.6}, {0.0, 0.0}},
                                   {128, true, 1, {0.495, 9.2}, {0.587, 7.9}, {0.0, 1.4}, {-1.7, -1.7}},
@@ -180,34 +180,39 @@ GemmPlan dw_plan(DwKind kind, int64_t M, int64_t N, int64_t K, double* price_out
   return best;
 }
 
-// dX of a channel-major dY by k_gemm_dx8, 64 x 128, 128 x 128, 128 x 256 (`ring` set) and 256 x 256; fitted to 90 layers (0.2 % from
-// the fastest in the mean), the row of 128 x 256 to 16.  A tile of 128 x 256 moves half of the bytes of two of 64 x 128 from L2 to LDS, which
-// is what the smaller tiles are bound by, and two of them on a CU hide each other's epilogues.
-// T x C_out -> C_in, backward call without selected channels, us on 64 / 128 / 128 x 256 / 256:
+// dX of a channel-major dY by k_gemm_dx8, 64 x 128, 128 x 128, 128 x 256 and 256 x 256; fitted to 90 layers (0.2 % from the fastest in the
+// mean), the row of 128 x 256 to 258 others, of which 198 have it: 0.85 % from the fastest, 5.8 % without that tile.  A tile of 128 x 256
+// moves half of the bytes from L2 to LDS that the four of 64 x 128 on its area do, which is what the smaller tiles are bound by, and
+// two of them on a CU hide each other's epilogues.
+// T x C_out -> C_in, backward call without selected channels, us on 64 / 128 / 128 x 256 / 256, in turn on two sets of buffers:
+//    2048 x 1536 -> 3072   34.0 / 32.0 / 29.4 / 39.6
+//    4096 x 4096 -> 2048   94.9 / 78.2 / 70.9 / 81.0
+//   12288 x 768  -> 3072  108   / 100  / 85.5 / 102
+//   12288 x 768  -> 768    32.1 / 32.6 / 31.4 / 29.5
+//   16384 x 64   -> 4096  105   / 117  / 92.9 / 89.5
+//   16384 x 512  -> 512    22.4 / 19.9 / 19.8 / 25.5
+//    8192 x 4096 -> 4096  360   / 316  / 250  / 229
+// on one set:
 //   14248 x 1122 -> 176    22.4 / 23.2 /  -   / 45
 //    9696 x 27   -> 5696   70   / 74   /  -   / 92
-//    8192 x 1024 -> 1024   30.7 / 26.6 / 25.1 / 33.0
-//    4096 x 4096 -> 2048   92   / 75   / 67   / 80
-//   12288 x 768  -> 3072   95   / 82   / 74   / 93
-//   16384 x 512  -> 512    21.2 / 18.4 / 19.2 / 25.3
-//    8192 x 4096 -> 4096  341   / 285  / 234  / 220
-//    8192 x 4096 -> 11008  -    /  -   /  -   / 643
-static const DxTile kDxCmTiles[] = {{64, false, 3, {0.45, 6.2}, {0.935, 7.4}, {0.0, 0.0}, {0.0, 0.0}},
-                                    {128, false, 2, {0.55, 8.4}, {0.95, 9.1}, {0.0, 0.0}, {0.0, 0.0}},
-                                    {128, true, 2, {0.877, 9.8}, {1.72, 13.5}, {0.0, 0.0}, {0.0, 0.0}},   // 128 x 256
-                                    {256, false, 1, {1.0, 21.6}, {1.34, 24.9}, {0.0, 0.0}, {0.0, 0.0}}};
+//    8192 x 4096 -> 11008  -    /  -   / 4 % more than 256 / 643
+static const DxTile kDxCmTiles[] = {{64, false, 3, {0.45, 6.2}, {0.935, 7.4}, {0.0, 0.0}, {0.0, 0.0}, 128},
+                                    {128, false, 2, {0.55, 8.4}, {0.95, 9.1}, {0.0, 0.0}, {0.0, 0.0}, 128},
+                                    {128, false, 2, {0.60, 12.0}, {1.70, 12.4}, {0.0, 0.0}, {0.0, 0.0}, 256},
+                                    {256, false, 1, {1.0, 21.6}, {1.34, 24.9}, {0.0, 0.0}, {0.0, 0.0}, 256}};
 GemmPlan dx_cm_plan(int64_t M, int64_t N, int64_t K, double* price) {
   GemmPlan best{};
   const double stages = (double)ceil_div(K, KALIGN);
   for (const DxTile& c : kDxCmTiles) {
-    if (c.ring && (M % 128 || N % 256)) continue;       // whole tiles only: what was measured
-    const int64_t tm = ceil_div(M, c.t), tn = ceil_div(N, c.t == 64 ? 128 : c.ring ? 256 : c.t), tiles = tm * tn, round = 256 * c.bpc;
+    const bool wide = c.t == 128 && c.bn == 256;
+    if (wide && (M % 128 || N % 256)) continue;         // whole tiles only: what was measured
+    const int64_t tm = ceil_div(M, c.t), tn = ceil_div(N, c.bn), tiles = tm * tn, round = 256 * c.bpc;
     if (tiles >= (1 << 24) && c.t < 256) continue;      // a grid dimension holds less than 2^32 work items
     const double lone = c.lone[0] * stages + c.lone[1], full = c.full[0] * stages + c.full[1];
     double t = (double)(tiles / round) * full;
     if (const int64_t rest = tiles % round)
       t += lone + (full - lone) * (c.bpc > 1 ? (double)(ceil_div(rest, 256) - 1) / (c.bpc - 1) : (double)rest / 256.0);
-    if (best.tile == 0 || t < *price) { *price = t; best = GemmPlan{c.t, 1, (int)tm, (int)tn, c.ring}; }
+    if (best.tile == 0 || t < *price) { *price = t; best = GemmPlan{c.t, 1, (int)tm, (int)tn, false, wide}; }
   }
   return best;
 }
@@ -256,7 +261,7 @@ bool pair_plan(int64_t M, int64_t N, int64_t K, bool f32, bool conv, const ConvD
 // The same for a channel-major bf16 dY (k_pair_cm): dX on 64 x 128 tiles of k_gemm_dx8, dW on those of its DW form, three
 // blocks a CU.
 bool pair_cm_plan(int64_t M, int64_t N, int64_t K, int64_t dw_m, int64_t dw_n, int64_t dw_k, double apart, GemmPlan* dx, GemmPlan* dw) {
-  return pair_search((double)ceil_div(K, KALIGN), ceil_div(M, 64), ceil_div(N, 128), kDxCmTiles[0], false, 256.0 * 3, DW_ROWS, dw_m,
+  return pair_search((double)ceil_div(K, KALIGN), ceil_div(M, 64), ceil_div(N, kDxCmTiles[0].bn), kDxCmTiles[0], false, 256.0 * 3, DW_ROWS, dw_m,
                      dw_n, dw_k, &apart, dx, dw);
 }
 

@@ -95,7 +95,7 @@ int launch_gemm_tn(const GemmTnArgs& a, const GemmPlan& plan, hipStream_t stream
 int launch_gemm_nt_raw(const GemmArgs& a, const GemmPlan& plan, hipStream_t stream);
 // channel-major dY: dX by k_gemm_dx8 from dY [C_out][lda] (lda >= M = T, T % 8 == 0) and the int8 weight codes, both with the
 // contraction index as their row; dW from the rows idx of dY [C_out][lda] (lda >= K = T, K % 8 == 0) and the uint8 codes:
-//   out[s][m][n] = sum over the K-slice s of dY[idx[m]][t] * (codes[t][n] - round(z_x)).  Tiles 256, 128, 64 (64 x 128).
+//   out[s][m][n] = sum over the K-slice s of dY[idx[m]][t] * (codes[t][n] - round(z_x)).  Tiles 256, 128 (dX also 128 x 256), 64 (64 x 128).
 int dx_args_cm(GemmDx8Args* out, const bf16_t* dy_cm, int64_t lda, const int8_t* w_codes, int64_t ldb, const float* s_w, int64_t M,
                int64_t N, int64_t K, const GemmPlan& plan, const GemmEpilogueDx& epi);
 int dw_args_rows(GemmDx8Args* out, const bf16_t* dy_cm, int64_t lda, const int32_t* idx, const uint8_t* x_codes, int64_t ldb,

@@ -109,7 +109,7 @@ int dx_args_cm(GemmDx8Args* out, const bf16_t* dy_cm, int64_t lda, const int8_t*
 }
 
 int launch_gemm_dx8_cm(const GemmDx8Args& a, const GemmPlan& plan, hipStream_t stream) {
-  if (plan.tile == 128 && plan.ring)                    // 128 x 256
+  if (plan.wide)
     return dx_epilogue_fast(a.g, 128, 256) ? launch_dx8_cfg<128, 256, false, true, true>(a, 1, stream)
                                            : launch_dx8_cfg<128, 256, false, true>(a, 1, stream);
   switch (plan.tile) {

@@ -31,6 +31,26 @@ def test_dw_plan_of_gathered_codes():
     assert (p["dw_operands"], p["dw_tile"]) == (2, 64)
 
 
+# T, c_in, c_out, rows and columns of a dX tile of a channel-major dY; us on 64 x 128 / 128 x 128 / 128 x 256 / 256 x 256
+CHANNEL_MAJOR = [
+    (12288, 768, 768, (128, 256)),     # 32.1 / 32.6 / 31.4 / 29.5
+    (2048, 3072, 1536, (128, 256)),    # 34.0 / 32.0 / 29.4 / 39.6
+    (8192, 768, 1536, (128, 256)),     # 34.0 / 32.1 / 29.6 / 39.8
+    (2048, 3072, 8192, (128, 256)),    # 139 / 126 / 105 / 138
+    (12288, 3072, 768, (128, 256)),    # 108 / 100 / 85.5 / 102
+    (8192, 4096, 4096, (256, 256)),    # 360 / 316 / 250 / 229
+    (8192, 11008, 4096, (256, 256)),   # 643, 4 % more on 128 x 256
+    (1024, 4096, 3072, (128, 128)),    # 42.1 / 39.6 / 44.4 / 61.8
+]
+
+
+@pytest.mark.parametrize("case", CHANNEL_MAJOR, ids=str)
+def test_dx_plan_of_a_channel_major_gradient(case):
+    T, c_in, c_out, want = case
+    t = ef.linear_bwd_dx_tile(T, c_in, c_out, 0, ef.BF16, ef.DY_CHANNEL_MAJOR)
+    assert (t["rows"], t["columns"]) == want
+
+
 # T, c_in, c_out, k, with a second stream, LDS stages of the ring on 64 x 64 tiles; us with three / eight
 RING = [
     (512, 768, 512, 0, False, 3),        # 12.6 / 13.5    short contractions
