@@ -412,16 +412,16 @@ __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ par
       int s = 1;
       for (; s + 7 < S; s += 8) {                     // eight slices in flight; summed in slice order as below
         float4 b[8];
-  #pragma unroll
+#pragma unroll
         for (int u = 0; u < 8; ++u) b[u] = *reinterpret_cast<const float4*>(p + (int64_t)(s + u) * slice);
-  #pragma unroll
+#pragma unroll
         for (int u = 0; u < 8; ++u) { a.x += b[u].x; a.y += b[u].y; a.z += b[u].z; a.w += b[u].w; }
       }
       for (; s + 3 < S; s += 4) {
         float4 b[4];
-  #pragma unroll
+#pragma unroll
         for (int u = 0; u < 4; ++u) b[u] = *reinterpret_cast<const float4*>(p + (int64_t)(s + u) * slice);
-  #pragma unroll
+#pragma unroll
         for (int u = 0; u < 4; ++u) { a.x += b[u].x; a.y += b[u].y; a.z += b[u].z; a.w += b[u].w; }
       }
       for (; s < S; ++s) {
@@ -434,7 +434,7 @@ __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ par
       const float4 wv = *reinterpret_cast<const float4*>(w + c * ncols + j);
       const float wf[4] = {wv.x, wv.y, wv.z, wv.w};
       float o[4];
-  #pragma unroll
+#pragma unroll
       for (int t = 0; t < 4; ++t) {
         const bool inr = (bits >> t) & 1u;
         const float code = (float)(int8_t)((cw >> (8 * t)) & 0xFFu);
@@ -445,7 +445,7 @@ __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ par
       if (dw) *reinterpret_cast<float4*>(dw + orow * ncols + j) = make_float4(o[0], o[1], o[2], o[3]);
       if (sgd.w) {
         float gq[4];
-  #pragma unroll
+#pragma unroll
         for (int t = 0; t < 4; ++t) gq[t] = fmaf(sgd.wd, wf[t], o[t]);
         if (sgd.mom_w) {
           float4 mb = *reinterpret_cast<const float4*>(sgd.mom_w + c * ncols + j);
@@ -477,11 +477,11 @@ __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ par
       auto slices = [&](auto count) {                   // in flight together, added in slice order
         constexpr int N = decltype(count)::value;
         float b[N][V];
-  #pragma unroll
+#pragma unroll
         for (int u = 0; u < N; ++u) __builtin_memcpy(b[u], p + (int64_t)(s + u) * slice, 4 * V);
-  #pragma unroll
+#pragma unroll
         for (int u = 0; u < N; ++u)
-  #pragma unroll
+#pragma unroll
           for (int t = 0; t < V; ++t) a[t] += b[u][t];
         s += N;
       };
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ par
       else if (s + 1 < S) slices(std::integral_constant<int, 2>{});
       else if (s < S) slices(std::integral_constant<int, 1>{});
       float o[V];
-  #pragma unroll
+#pragma unroll
       for (int t = 0; t < V; ++t) {
         const float dwq = sx * a[t];
         const bool inr = (bits >> t) & 1u;
@@ -503,7 +503,7 @@ __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ par
       auto store = [&](float* dst, const float (&v)[V]) {
         if (d == 0) __builtin_memcpy(dst, v, 4 * V);
         else {
-  #pragma unroll
+#pragma unroll
           for (int t = 1; t < V; ++t)
             if (t >= d) dst[t] = v[t];
         }
@@ -511,14 +511,14 @@ __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ par
       if (dw) store(dw + orow * ncols + j - d, o);
       if (sgd.w) {
         float gq[V];
-  #pragma unroll
+#pragma unroll
         for (int t = 0; t < V; ++t) gq[t] = fmaf(sgd.wd, wf[t], o[t]);
         if (sgd.mom_w) {
-  #pragma unroll
+#pragma unroll
           for (int t = 0; t < V; ++t) gq[t] = fmaf(sgd.mu, mb[t], gq[t]);
           store(sgd.mom_w + e, gq);
         }
-  #pragma unroll
+#pragma unroll
         for (int t = 0; t < V; ++t) gq[t] = fmaf(-sgd.lr_w, gq[t], wf[t]);
         store(sgd.w + e, gq);
       }
@@ -977,7 +977,8 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   ProfScope fin(PROF_FINISH, st);
   // k blocks for the rows of dW plus one that finishes dS_x, dZ_x
   // few rows: the chain of dependent loads of a trip, not bandwidth, sets the time, and a row is one trip where that can be (k = 64
-  // rows of 1152, 25 slices, two trips of 256 threads 6.3 us, one of 512 4.8)
+  // rows of 1152, 25 slices, two trips of 256 threads 6.3 us, one of 512 4.8).  One or two slices leave nothing behind the first to
+  // request together (256 x 768 -> 1000, k = 64, the call 19.6 us, with ANY 20.0; three slices and more gain 1 to 5 %).
   const bool few = io.k < 512;
   const bool vec = p.Nw % 4 == 0 && ((uintptr_t)io.w % 16) == 0 && ((uintptr_t)io.dw % 16) == 0 && ((uintptr_t)io.w_codes % 4) == 0 &&
                    ((uintptr_t)io.sgd.mom_w % 16) == 0;
@@ -987,7 +988,7 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   };
   if (few && p.Nw > 1024 && p.Nw < 2048) finish(k_dw_finish<512, true>, 512);
   else if (few && p.Nw >= 2048) { if (vec) finish(k_dw_finish<1024, false>, 1024); else finish(k_dw_finish<1024, true>, 1024); }
-  else if (vec && !few) finish(k_dw_finish<256, false>, 256);
+  else if (vec && (!few || p.plan_dw.split_k <= 2)) finish(k_dw_finish<256, false>, 256);
   else finish(k_dw_finish<256, true>, 256);
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
