@@ -1137,7 +1137,7 @@ extern "C" int efqat_linear_bwd_dx_tile(int64_t T, int64_t c_in, int64_t c_out, 
   tile[EFQAT_DX_TILE_COLUMNS] = !p.dx8 ? rows : rows == 256 || (p.cmx && p.plan_dx.wide) ? 256 : 128;
   tile[EFQAT_DX_TILE_STAGES] = p.dx8 || !p.plan_dx.ring ? 2
                                : p.pair ? 3
-                                        : kk_ring_stages(rows, (int64_t)p.plan_dx.tiles_m * p.plan_dx.tiles_n, p.Kx,
+                                        : kk_ring_stages(rows, (int64_t)p.plan_dx.tiles_m * p.plan_dx.tiles_n, c_in, p.Kx,
                                                          side_stream && takes_side_stream(p));
   return EFQAT_OK;
 }

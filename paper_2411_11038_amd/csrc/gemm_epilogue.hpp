@@ -81,7 +81,7 @@ int dx_args_strided(GemmStridedArgs* out, const bf16_t* dy_tok, int64_t ldc, con
 // beside: the dW product runs at the same time, on another stream
 int launch_dx(const GemmStridedArgs& a, int conv, const GemmPlan& plan, bool beside, hipStream_t stream);
 int launch_gemm_kk(const GemmArgs& a, int tile, bool beside, hipStream_t stream);
-int kk_ring_stages(int tile, int64_t tiles, int64_t K, bool beside);   // LDS stages that it takes
+int kk_ring_stages(int tile, int64_t tiles, int64_t N, int64_t K, bool beside);   // LDS stages that it takes
 int launch_gemm_kk_conv(const GemmArgs& a, int tile, hipStream_t stream);
 int launch_gemm_kk_conv_strided(const GemmStridedArgs& a, int tile, hipStream_t stream);
 // dW from token-major operands (k_gemm_tn), linear or convolution (cv_cin > 0), or from staged ones (k_gemm_nt)

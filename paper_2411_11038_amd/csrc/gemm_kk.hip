@@ -4,16 +4,26 @@
 namespace efqat {
 
 // LDS stages of the ring.  64 x 64 tiles of a linear layer that have a CU for themselves take eight, 128 KB, where the contraction is
-// long; before, the deeper prologue and drain of a block cost more than they hide.  Backward call, three / eight, us:
-//   512 x 2048 -> 768    18.2 / 17.7      512 x 1792 -> 768    17.6 / 17.8      512 x 512 -> 768   12.6 / 13.5
-//   1000 x 4096 -> 777   33.8 / 27.5      200 x 8000 -> 100    38.0 / 32.5
-// With the dW product on a second stream its blocks need room beside them, unless half of the CUs have no dX block:
-//   512 x 8000 -> 1024, k = 2000, 128 tiles, 58.4 / 53.8; 1024 x 8000 -> 1024, 256 tiles, 64.0 / 72.1.
+// long; before, the deeper prologue and drain of a block cost more than they hide.  Rows that are no whole number of 128-byte lines
+// are bound by their copies, each of which touches two lines; there eight stages lose on whole tiles of C_in.  Backward call
+// without selected channels, three / eight, us:
+//   512 x 512  -> 768    12.6 / 13.5     512 x 1792 -> 768    17.6 / 17.8     512 x 2048 -> 768    18.2 / 17.7
+//   64 x 4096  -> 1024   26.0 / 23.4     200 x 8000 -> 100    38.0 / 32.5    1000 x 8192 -> 777    56.7 / 42.8
+//   512 x 3000 -> 1024   29.6 / 30.8     512 x 8008 -> 1024   71.9 / 72.6    1000 x 6008 -> 777    48.1 / 43.2
+//   64 x 4816  -> 1024   38.1 / 39.0     256 x 8008 -> 200    45.6 / 47.1    2000 x 4104 -> 333    35.5 / 31.8
+// With the dW product on a second stream its blocks need room beside them:
+//   153 x 4608 -> 640, k = 2304, 30 tiles, 41.6 / 39.9; 512 x 4608 -> 1024, k = 2304, 128 tiles, 47.7 / 50.1
+//   512 x 8192 -> 1024, k = 4096, 128 tiles, 64.0 / 58.8; 1024 x 8000 -> 1024, k = 2000, 256 tiles, 64.0 / 72.1
+//   153 x 8008 -> 640, k = 8008, 66.6 / 67.3
 // Convolutions form an address for every copy, and eight stages of that code cost them 1 to 19 % at 1 to 196 tiles and 9 to 400 K stages.
 // Four stages of the 128 x 128 tile gain nothing.
 constexpr int kKkDeep = 8;
-int kk_ring_stages(int tile, int64_t tiles, int64_t K, bool beside) {
-  return tile == 64 && K >= 32 * 64 && tiles <= (beside ? 128 : 256) ? kKkDeep : 3;
+int kk_ring_stages(int tile, int64_t tiles, int64_t N, int64_t K, bool beside) {
+  if (tile != 64 || tiles > 256) return 3;
+  const int64_t stages = ceil_div(K, 64);
+  if (beside) return K % 64 == 0 && ((tiles <= 64 && stages >= 64) || (tiles <= 128 && stages >= 112)) ? kKkDeep : 3;
+  if (K % 64) return N % 64 && tiles >= 64 && stages >= 64 ? kKkDeep : 3;
+  return stages >= 32 ? kKkDeep : 3;
 }
 
 template <int BM, int BN, int EPI, int CONV = 0, int NST = 3>
@@ -35,7 +45,7 @@ static int launch_kk_cfg(const typename ConvArgs<CONV>::type& a, hipStream_t st)
 int launch_gemm_kk(const GemmArgs& a, int tile, bool beside, hipStream_t stream) {
   // bf16 in and out, whole tiles, 32-bit element offsets: nothing to decide at run time, the straight-line epilogue
   const bool fast = dx_epilogue_fast(a, tile, tile);
-  const bool deep = kk_ring_stages(tile, (int64_t)a.tiles_m * a.tiles_n, a.K, beside) == kKkDeep;
+  const bool deep = kk_ring_stages(tile, (int64_t)a.tiles_m * a.tiles_n, a.N, a.K, beside) == kKkDeep;
   switch (tile) {
     case 192:
       if (fast) return launch_kk_cfg<192, 192, EPI_DXF>(a, stream);

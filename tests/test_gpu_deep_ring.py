@@ -21,9 +21,9 @@ def _in_range(fx, cols):
 
 @pytest.mark.parametrize("dt", (torch.bfloat16, torch.float32), ids=("bf16", "f32"))
 @pytest.mark.parametrize("c_out", (8, 64, 72, 392, 448, 504, 512, 520, 960, 1016, 1032, 1088, 1536, 2040) +
-                         tuple(range(2048, 2560, 64)) + tuple(range(2056, 2568, 64)) + (2560, 4104))
+                         tuple(range(2048, 2624, 64)) + tuple(range(4040, 4616, 64)))
 def test_against_tiles_of_192(c_out, dt):
-    T, c_in = 150, 200
+    T, c_in = (150, 200) if c_out < 4000 else (500, 520)   # ragged rows of dY take eight stages on 64 tiles and more only
     tile = ef.linear_bwd_dx_tile(T, c_in, c_out, 0, ef.BF16 if dt == torch.bfloat16 else ef.F32)
     assert tile["rows"] == 64 and (tile["stages"] == 8 if c_out >= 2041 else tile["stages"] in (2, 3))
     g = torch.Generator(device="cuda")

@@ -60,6 +60,11 @@ RING = [
     (1024, 1024, 8000, 2000, False, 8),  # 70.6 / 67.0
     (1024, 1024, 8000, 2000, True, 3),   # 64.0 / 72.1    no room for the blocks of the dW product
     (512, 1024, 8000, 2000, True, 8),    # 58.4 / 53.8    ... but where half of the CUs have no dX block
+    (512, 1024, 4608, 2304, True, 3),    # 47.7 / 50.1    ... and the contraction is long
+    (153, 640, 4608, 2304, True, 8),     # 41.6 / 39.9
+    (64, 1024, 4816, 0, False, 3),       # 38.1 / 39.0    rows that are no whole number of lines
+    (512, 1024, 8008, 0, False, 3),      # 71.9 / 72.6
+    (2000, 333, 4104, 0, False, 8),      # 35.5 / 31.8    ... and tiles over the edge
 ]
 
 
