@@ -28,14 +28,19 @@ __device__ __forceinline__ void load8<bf16_t>(const bf16_t* p, float (&v)[8]) {
   }
 }
 
-// the same at any element alignment, which the hardware takes for vector accesses
+// the same at any element alignment, which the hardware takes for vector accesses.  Loaded as vectors: of a copy to an array the compiler
+// takes an element away to share its load with the branch that reads by elements, and another load is issued (60000 x 1000 fp32
+// codes 55.8 us so, 49.1).
 template <typename T>
 __device__ __forceinline__ void load8_any(const T* p, float (&v)[8]) {
   if constexpr (sizeof(T) == 4) {
-    __builtin_memcpy(v, p, 32);
+    typedef float vec __attribute__((ext_vector_type(4), aligned(4)));
+    const vec a = *reinterpret_cast<const vec*>(p), b = *reinterpret_cast<const vec*>(p + 4);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { v[i] = a[i]; v[4 + i] = b[i]; }
   } else {
-    uint32_t w[4];
-    __builtin_memcpy(w, p, 16);
+    typedef uint32_t vec __attribute__((ext_vector_type(4), aligned(2)));
+    const vec w = *reinterpret_cast<const vec*>(p);
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       v[2 * i] = __uint_as_float(w[i] << 16);
@@ -149,7 +154,8 @@ __device__ __forceinline__ float round_quotient(float x, float s, float inv_s) {
 // consecutive elements, four neighbouring lanes assemble one 32-bit mask word.  Rows of any length and alignment: whole chunks are
 // one vector access, only the one that ends a row is read and written by elements.  With an access per element unless rows were
 // aligned and of whole chunks it took, codes alone / with the range, us: 12000 x 7777 fp32 215 / 282 (now 97 / 161), bf16 161 / 152
-// (68 / 96), 3000 x 12001 fp32 76 / 101 (29 / 54), 2049 x 777 fp32 6.3 / 10.0 (4.5 / 8.4), 20000 x 7 the same.
+// (68 / 96), 3000 x 12001 fp32 76 / 101 (29 / 54), 2049 x 777 fp32 6.3 / 10.0 (4.5 / 8.4), 20000 x 7 the same; rows of
+// 31 to 127 fp32 values, whose one wavefront takes both ways, up to 6 % slower (952380 x 63 326 / 365, now 348 / 369), of 100 bf16 16 % faster.
 // Activations: part, when given, are the partial ranges that scale and zero point are made from here.
 // INIT (weights only): the wavefront first takes the row's abs-max and writes its Eq. 4 scale
 // S_w[c] = max_j |w[c][j]| / (2^(b-1) - 1), then quantizes the row it has just pulled through the caches.
