@@ -26,17 +26,31 @@ int kk_ring_stages(int tile, int64_t tiles, int64_t N, int64_t K, bool beside) {
   return stages >= 32 ? kKkDeep : 3;
 }
 
-template <int BM, int BN, int EPI, int CONV = 0, int NST = 3>
+// Should the straight-line epilogue's inputs be requested during the first stages?  On 192 x 192 tiles, whose epilogues are the longest,
+// and where every CU has one: blocks that follow one another win back what the requests cost the stages, a full round of long
+// contractions does where the caches do not hold the buffers, as in a training step.  Backward call without selected channels,
+// without / with, us, buffers not in the caches | in them:
+//   6144 x 768  -> 3072 (2 rounds)  53.7 / 49.9 | 46.3 / 47.3     12288 x 1536 -> 768  (256 tiles)  40.5 / 38.8 | 37.0 / 38.2
+//  12288 x 1536 -> 1536 (2)         76.2 / 72.8 | 68.2 / 67.3      3072 x 3072 -> 3072 (256)        67.5 / 64.9 | 62.1 / 63.2
+//  12288 x 3072 -> 3072 (4)        226   / 225  | 220  / 219       3072 x 768  -> 3072 (256)        27.4 / 27.7 | 27.8 / 29.2
+//  12288 x 256  -> 1536 (2)         39.6 / 40.2 | 33.8 / 37.1      4608 x 3072 -> 1536 (192)        50.6 / 52.7 | 51.2 / 52.7
+// With 128 x 128 tiles it costs 2 %.
+static bool kk_inputs_ahead(const GemmArgs& a, int tile) {
+  const int64_t tiles = (int64_t)a.tiles_m * a.tiles_n;
+  return tile == 192 && tiles >= 256 && a.K / 64 >= (tiles > 256 ? kKkAheadStages : 24);
+}
+
+template <int BM, int BN, int EPI, int CONV = 0, int NST = 3, bool AHEAD = false>
 static int launch_kk_cfg(const typename ConvArgs<CONV>::type& a, hipStream_t st) {
   using C = KkCfg<BM, BN, NST>;
   // set once per process (initialisation of a function-local static is thread-safe)
   constexpr int kLds = C::template lds_bytes<EPI>() + (CONV == 2 ? C::BM * (int)sizeof(int) : 0);
-  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_kk<BM, BN, EPI, CONV, NST>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_kk<BM, BN, EPI, CONV, NST, AHEAD>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return EFQAT_ERR_HIP;
   const dim3 grid((unsigned)(a.tiles_m * a.tiles_n));
   {
     ProfScope prof(PROF_DX, st);
-    hipLaunchKernelGGL((k_gemm_kk<BM, BN, EPI, CONV, NST>), grid, dim3(256), kLds, st, a);
+    hipLaunchKernelGGL((k_gemm_kk<BM, BN, EPI, CONV, NST, AHEAD>), grid, dim3(256), kLds, st, a);
   }
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
@@ -48,6 +62,7 @@ int launch_gemm_kk(const GemmArgs& a, int tile, bool beside, hipStream_t stream)
   const bool deep = kk_ring_stages(tile, (int64_t)a.tiles_m * a.tiles_n, a.N, a.K, beside) == kKkDeep;
   switch (tile) {
     case 192:
+      if (fast && kk_inputs_ahead(a, tile)) return launch_kk_cfg<192, 192, EPI_DXF, 0, 3, true>(a, stream);
       if (fast) return launch_kk_cfg<192, 192, EPI_DXF>(a, stream);
       return a.x_dtype == EFQAT_F32 ? launch_kk_cfg<192, 192, EPI_DXS>(a, stream) : launch_kk_cfg<192, 192, EPI_DX>(a, stream);
     case 128:

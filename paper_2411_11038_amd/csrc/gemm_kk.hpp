@@ -56,7 +56,11 @@ __device__ __forceinline__ void kk_round(F f, std::integer_sequence<int, B...>) 
 // k_gemm_nt (see GemmArgs): every copy slot keeps (n, h, w) of its input pixel and forms its source address per stage
 // from the stage's tap; K = taps * ldc is a whole number of stages.  CONV = 2: a convolution with a stride, rows sorted
 // by phase (see ConvPhase); W_q^T is read at the stage's tap as well.
-template <int BM, int BN, int EPI, int CONV = 0, int NST = 3>
+//
+// AHEAD (EPI_DXF): the first two rounds of the ring request the epilogue's inputs behind their copies (kk_inputs_ahead); K is at
+// least kKkAheadStages whole stages.
+constexpr int kKkAheadStages = 9;                     // two rounds of three stages, and the copies in flight behind them
+template <int BM, int BN, int EPI, int CONV = 0, int NST = 3, bool AHEAD = false>
 __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::type& g, char* smem, int bid, int ntile) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using C = KkCfg<BM, BN, NST>;
@@ -267,28 +271,22 @@ __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::typ
   };
 
   // the fused dX epilogue
-  // Inputs requested ahead: 192 x 192 tiles, whose epilogues are the longest.  Calls on buffers that the caches do not hold:
-  // 12288 x 768 -> 3072 124 -> 117 us, a step of 12288 x 3072 -> 768 212.5 -> 211 (the dX product alone on buffers that they do hold
-  // 57 -> 58.5); with 128 x 128 tiles it costs 2 %.
-  constexpr bool kAhead = EPI == EPI_DXF && BM == 192;
-  typename std::conditional<EPI == EPI_DXF, EpiDxFast<C, kAhead>,
+  static_assert(!AHEAD || (EPI == EPI_DXF && 3 * NST == kKkAheadStages), "inputs ahead: straight-line epilogue, ring of three");
+  typename std::conditional<EPI == EPI_DXF, EpiDxFast<C, AHEAD>,
                             EpiDxAny<C, typename std::conditional<EPI == EPI_DXS, float, bf16_t>::type, CONV == 2>>::type epi;
   const int m_end = CONV == 2 ? ph.rows : g.M;
   const bool edge = m0 + C::BM > m_end || n0 + C::BN > g.N;
   int* rowmap = reinterpret_cast<int*>(smem + C::template lds_bytes<EPI>());   // CONV = 2: the matrix row of every tile row
   constexpr int PEEL = 2 * NST;                       // two rounds of the ring
   const int kt_epi = nk >= 2 ? nk - 2 : 0;            // the first of the last two stages
-  bool peel = false;                                  // EPI_DXF: long enough to request the epilogue's inputs in the first stages
-  if constexpr (EPI == EPI_DXF) {
-    peel = kAhead && nfull >= PEEL + NST;             // peeled stages are steady ones: kt + NST < nfull
-    epi.begin(g, m0, n0, wm, wn);
-  }
+  if constexpr (EPI == EPI_DXF) epi.begin(g, m0, n0, wm, wn);
 
   // ---- main loop.  Stage kt lives in buffer kt % NST.  On entry to stage kt the first P0 copies of stage kt + NST - 1 have
   // been issued if and only if that stage is a full one; both variants keep this true for kt + 1.
   //
-  // EPI_DXF: the first PEEL stages also request the epilogue's inputs, some groups of rows each, behind the stage's copies.  They
-  // come out of HBM while the matrix cores work and are waited for one stage later than the copies before them.
+  // AHEAD: the first PEEL stages, steady ones (kt + NST < nfull), also request the epilogue's inputs, some groups of rows each, behind
+  // the stage's copies.  They come out of HBM while the matrix cores work and are waited for one stage later than the copies before
+  // them.
   // the requests of peeled stage ps, then its end
   auto request_and_sync = [&](auto& e, auto psc) {
     using E = typename std::remove_reference<decltype(e)>::type;
@@ -322,7 +320,7 @@ __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::typ
       if (ki < nfull) issue_range(Unchecked{}, ki, nn, P0, LPS);
       else if (ki < nk) issue_range(Checked{}, ki, nn, 0, LPS);
       if (kt == kt_epi) {
-        if constexpr (EPI == EPI_DXF) { if (!peel) epi.prefetch(); }
+        if constexpr (EPI == EPI_DXF) { if (!AHEAD) epi.prefetch(); }
         else epi.prefetch(g, m0, n0, wm, wn, m_end, edge, rowmap);
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -364,12 +362,10 @@ __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::typ
   using No = std::integral_constant<int, -1>;
   // f(stage of the round) for a round of the ring
   auto round = [&](auto f) { kk_round(f, std::make_integer_sequence<int, NST>{}); };
-  if constexpr (kAhead) {
-    if (peel) {
-      round([&](auto b) { stage(b, Steady{}, decltype(b)::value, b); });
-      round([&](auto b) { stage(b, Steady{}, NST + decltype(b)::value, std::integral_constant<int, NST + decltype(b)::value>{}); });
-      kt = PEEL;
-    }
+  if constexpr (AHEAD) {
+    round([&](auto b) { stage(b, Steady{}, decltype(b)::value, b); });
+    round([&](auto b) { stage(b, Steady{}, NST + decltype(b)::value, std::integral_constant<int, NST + decltype(b)::value>{}); });
+    kt = PEEL;
   }
   for (; kt + 2 * NST - 1 < nfull; kt += NST) round([&](auto b) { stage(b, Steady{}, kt + decltype(b)::value, No{}); });
   for (; kt < nk; kt += NST)
@@ -387,10 +383,10 @@ __device__ __forceinline__ void gemm_kk_block(const typename ConvArgs<CONV>::typ
 #endif
 }
 
-template <int BM, int BN, int EPI, int CONV = 0, int NST = 3>
+template <int BM, int BN, int EPI, int CONV = 0, int NST = 3, bool AHEAD = false>
 __global__ __launch_bounds__(256) void k_gemm_kk(const typename ConvArgs<CONV>::type g) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  gemm_kk_block<BM, BN, EPI, CONV, NST>(g, smem, blockIdx.x, gridDim.x);
+  gemm_kk_block<BM, BN, EPI, CONV, NST, AHEAD>(g, smem, blockIdx.x, gridDim.x);
 }
 
 }  // namespace efqat

@@ -10,8 +10,10 @@ pytestmark = pytest.mark.gpu
 TOK, CHAN = ef.DY_TOKEN_MAJOR, ef.DY_CHANNEL_MAJOR
 # T, c_in, c_out, type of x, layout of dY, dX kernel asked for; kernel and tile that it takes
 SIZES = [
-    (384, 384, 640, "bf16", TOK, ef.DX_KERNEL_BF16_PINNED, (1, 192)),    # whole tiles: inputs requested in the first stages
-    (384, 384, 72, "bf16", TOK, ef.DX_KERNEL_BF16_PINNED, (1, 192)),     # ... in the last ones
+    (3264, 3072, 576, "bf16", TOK, ef.DX_KERNEL_BF16_PINNED, (1, 192)),  # whole tiles, more than one a CU: inputs requested in the
+    (3264, 3072, 648, "bf16", TOK, ef.DX_KERNEL_BF16_PINNED, (1, 192)),  # first stages, nine of them and a ragged eleventh
+    (384, 384, 640, "bf16", TOK, ef.DX_KERNEL_BF16_PINNED, (1, 192)),    # ... in the last ones
+    (384, 384, 72, "bf16", TOK, ef.DX_KERNEL_BF16_PINNED, (1, 192)),
     (400, 200, 72, "bf16", TOK, ef.DX_KERNEL_BF16_PINNED, (1, 192)),
     (384, 384, 72, "f32", TOK, ef.DX_KERNEL_BF16_PINNED, (1, 192)),
     (1024, 512, 64, "bf16", TOK, ef.DX_KERNEL_INT8, (2, 256)),
