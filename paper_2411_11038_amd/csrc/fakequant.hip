@@ -468,11 +468,12 @@ static int run_fakequant(const T* x, int64_t rows, int64_t cols, int mode, int b
   const int64_t items = row_items ? rows : rows * ceil_div(cols, 512);
   int64_t blocks = ceil_div(items, 4);
   const bool flat = mode == EFQAT_QUANT_ACT_PER_TENSOR_ASYM && vec_row && (cols % 32) == 0;
-  // Ragged rows with the range to make: two rounds of the blocks that are resident at a time.  19584 x 1496 bf16 34.9 us (8192
-  // blocks 38.2, a launch for the range and 8192 blocks 35.4), 16384 x 1000 fp32 29.4 (32.4, 30.9).  Many short segments: there is too little work behind the range in a block to repay it, and more blocks balance better,
-  // so a block of its own makes it.  us so / in every block: 100000 x 100 fp32 49.6 / 51.4, 20000 x 7 bf16 16.1 / 16.7,
-  // 13184 x 64 13.9 / 14.8, but 10000 x 64 13.2 / 12.8, 36000 x 300 31.1 / 29.8.
-  if (part && !flat && blocks > 256 * 10 && n < 280 * items) {
+  // Ragged rows with the range to make: every block makes scale and zero point, in two rounds of the blocks that are resident at a time;
+  // or, where there are many segments and too little work behind the range in a block to repay it, a launch of its own does, and
+  // more blocks balance better.  us so / in every block: fp32 100000 x 100 46.2 / 48.4, 12000 x 400 14.0 / 14.7, 30000 x 700 (350 of 512
+  // values a segment) 38.9 / 39.9, but 50000 x 511 46.5 / 45.5, 16384 x 1000 30.2 / 29.5; bf16 12000 x 400 13.0 / 13.8, 19584 x 1496
+  // 35.6 / 36.4, 12000 x 7777 101 / 105; 10000 x 63 (2500 blocks) the same.
+  if (part && !flat && blocks > 256 * 10 && (sizeof(T) == 2 || n < 450 * items)) {
     hipLaunchKernelGGL(k_act_qparams, dim3(1), dim3(256), 0, st, part, nparts, bits, scale, zp);
     EFQAT_LAUNCH_CHECK();
     part = nullptr;
