@@ -156,8 +156,8 @@ __device__ __forceinline__ void lds_barrier() {
 // leaves the mask and sd out: 5 operations an element, 12 with them.  The sums are the same bit for bit where every a is finite; where
 // one is not, s1 is not either, and the epilogue adds the a - a of its rows behind the chunks (half an operation an element to keep
 // the largest |a| for that cost the dX products 1 %).
-// SKIP: off for tiles of 64 x 64, four or three blocks of which share a CU and hide the operations, not the branch (37.3 us of both
-// products of a convolution so, 37.7 with it).
+// SKIP: off for wavefronts of one 32 x 32 accumulator (tiles of 64 x 64), up to four blocks of which share a CU and hide the operations,
+// not the branch (37.3 us of both products of a convolution so, 37.7 with it).
 template <bool SKIP>
 __device__ __forceinline__ void epi_chunk(float (&a)[8], const float (&xf)[8], const uint2& cw, uint32_t mb, float z,
                                           float ninv_s, float& s1, float& sd) {
@@ -438,18 +438,14 @@ __device__ __forceinline__ void epilogue_dx(const GemmArgs& g, floatx16_t (&acc)
   }
 }
 
-// The same epilogue for the case that needs no decision at run time: bf16 x, bf16 dX, every tile of the block grid
-// entirely inside the matrix (M % BM == 0, N % BN == 0), M * N < 2^31 so that element offsets fit 32 bits, 16-byte
-// aligned x / dX and 8-byte aligned codes.  Straight-line code: LPR lanes share a row of the 32 x WN slab, each
-// taking KC of its 8-column chunks (chunk LPR k + lane % LPR), so a pass covers 64 / LPR rows with all 64 lanes busy
-// and every address is one per-lane base plus compile-time offsets; no exec-mask sequence or branch separates the
-// passes, the LDS reads of the next pass are issued before the arithmetic of the current one, and the global inputs
-// of pass p of the next slab are requested as soon as pass p of this slab has consumed its own (one register set, a
-// whole slab of prefetch distance).  With a single resident block per CU the predicated, branching formulation
-// above runs at about half this speed.
-// Per lane: s1 = sum a gs with gs = in range ? (code - Z) - x / S : code - Z, formed term by term as in EpiDxAny
-// (in range |gs| <= 1/2, whereas sum a (code - Z) and sum a x / S taken apart would each be some hundred times larger
-// and cancel); sd = sum (a - o) with o = in range ? a : 0.
+// The same epilogue for the case that needs no decision about type or edge at run time: bf16 x, bf16 dX, every tile of the block grid
+// entirely inside the matrix (M % BM == 0, N % BN == 0), M * N < 2^31 so that element offsets fit 32 bits, 16-byte aligned x / dX and
+// 8-byte aligned codes.  LPR lanes share a row of the 32 x WN slab, each taking KC of its 8-column chunks (chunk LPR k + lane % LPR), so
+// a pass covers 64 / LPR rows with all 64 lanes busy and every address is one per-lane base plus compile-time offsets.  The only branch
+// of a pass is epi_chunk's, one for the wavefront; the LDS reads of the next pass are issued before the arithmetic of the current one,
+// and the global inputs of a group of rows (KC passes) of the next slab are requested as soon as this slab's group is done (one
+// register set, a whole slab of prefetch distance).  With a single resident block per CU the predicated formulation above runs at
+// about half this speed.
 // ALL: the inputs of the whole sub-tile are held in registers, requested a group of rows at a time while the main loop runs
 // (k_gemm_kk); else one slab of them.
 template <class C, bool ALL = false>
