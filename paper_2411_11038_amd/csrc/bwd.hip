@@ -55,7 +55,7 @@ struct TransposeExtra {
 
 typedef bf16_t TransposeTile[64][66];                  // tile[i][j] of a block
 
-// tile (bx, by) of tap `tap`
+// tile (bx, by) of tap `tap`; colmap without rowscale and subz
 template <typename T>
 __device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int by, int tap, const T* __restrict__ in,
                                                 int64_t ld_in, int64_t R, int64_t Cn, const int32_t* __restrict__ colmap,
@@ -85,12 +85,14 @@ __device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int
     const int jq = (threadIdx.x & 15) * 4, ib = threadIdx.x >> 4;
     const int64_t left = Cn - j0 - jq;
     float v[4][4], rs[4];
+    bool is[4];
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) {
       const int64_t i = i0 + ib + 16 * rr, si = src_row(i);
+      is[rr] = si >= 0;
       rs[rr] = rowscale ? rowscale[i < R ? i : R - 1] : 1.0f;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) v[rr][t] = sub;
+      for (int t = 0; t < 4; ++t) v[rr][t] = 0.0f;
       if (si >= 0 && left >= 4) {
         typename Vec4<T>::type raw;
         __builtin_memcpy(&raw, in + si * ld_in + j0 + jq, 4 * sizeof(T));
@@ -105,7 +107,7 @@ __device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int
     for (int rr = 0; rr < 4; ++rr) {
       const int li = ib + 16 * rr;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) v[rr][t] = (v[rr][t] - sub) * rs[rr];
+      for (int t = 0; t < 4; ++t) v[rr][t] = is[rr] ? (v[rr][t] - sub) * rs[rr] : 0.0f;   // zero beside an infinite S_w or Z_x too
       *reinterpret_cast<uint32_t*>(&tile[li][jq]) = pack_bf16x2(v[rr][0], v[rr][1]);
       *reinterpret_cast<uint32_t*>(&tile[li][jq + 2]) = pack_bf16x2(v[rr][2], v[rr][3]);
     }
@@ -117,14 +119,10 @@ __device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int
 #pragma unroll
     for (int rr = 0; rr < 16; ++rr) {
       const int64_t si = src_row(i0 + ty + 4 * rr);
-      v[rr] = si >= 0 && j < Cn ? rd<T>(in, si * ld_in + jc) : sub;
+      v[rr] = si >= 0 && j < Cn ? rd<T>(in, si * ld_in + jc) : 0.0f;
     }
 #pragma unroll
-    for (int rr = 0; rr < 16; ++rr) {
-      const int li = ty + 4 * rr;
-      const float rs = rowscale && i0 + li < R ? rowscale[i0 + li] : 1.0f;
-      tile[li][tx] = f32_to_bf16((v[rr] - sub) * rs);
-    }
+    for (int rr = 0; rr < 16; ++rr) tile[ty + 4 * rr][tx] = f32_to_bf16(v[rr]);
   }
   __syncthreads();
   // out[j][i0 + 8a .. 8a+7]: one 16-byte store per lane, 8 lanes cover the 128 bytes of one output row
