@@ -146,15 +146,14 @@ __device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int
 struct RowCut { uint32_t segs, cols; };
 
 // Row-wise cast/copy to bf16 with zero-padded pitch: out[m][j] = bf16(in[rm(m)][j]), j < Cn; 0 up to ldo (a multiple of
-// 8), a chunk of 8 a lane: one or two 16-byte loads at any alignment, but for the chunk that ends a row.  flat == 1: no
-// padding and no row map, i.e. one run of chunks; flat = 2 .. 64, a power of two: that many lanes to a row; 0: a wavefront
-// per row segment.  block b of nb.
+// 8), a chunk of 8 a lane: one or two 16-byte loads at any alignment, of the row's last eight values where it ends.  flat == 1:
+// no padding and no row map, i.e. one run of chunks; flat = 2 .. 64, a power of two: that many lanes to a row; 0: a
+// wavefront per row segment.  block b of nb.
 template <typename T>
 __device__ __forceinline__ void rows_block(int64_t b, int64_t nb, const T* __restrict__ in, int64_t ld_in, int64_t R,
                                            int64_t Cn, const int32_t* __restrict__ rowmap, bf16_t* __restrict__ out,
                                            int64_t ldo, int flat, const RowCut& cut) {
-  auto chunk = [](const T* src, bf16_t* dst) {
-    uint32_t w[4];
+  auto load8 = [](const T* src, uint32_t (&w)[4]) {
     if constexpr (sizeof(T) == 4) {
       float f[8];
       __builtin_memcpy(f, src, 32);
@@ -163,27 +162,42 @@ __device__ __forceinline__ void rows_block(int64_t b, int64_t nb, const T* __res
     } else {
       __builtin_memcpy(w, src, 16);
     }
-    *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
   };
-  auto chunk_end = [](const T* src, int64_t n, bf16_t* dst) {   // of n < 8 values, then zeros
-    float f[8];
+  auto store8 = [](bf16_t* dst, const uint32_t (&w)[4]) { *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]); };
+  // columns j .. j + 7 of a row: past its end zeros, by moving the row's last eight values down
+  auto chunk = [&](const T* row, int64_t j, bf16_t* dst) {
+    uint32_t w[4];
+    const int64_t over = j + 8 - Cn;
+    if (Cn < 8) {
+      float f[8];
 #pragma unroll
-    for (int t = 0; t < 8; ++t) f[t] = t < n ? rd<T>(src, t) : 0.0f;
-    *reinterpret_cast<uint4*>(dst) =
-        make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
+      for (int t = 0; t < 8; ++t) f[t] = j + t < Cn ? rd<T>(row, j + t) : 0.0f;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) w[t] = pack_bf16x2(f[2 * t], f[2 * t + 1]);
+    } else {
+      load8(row + (over > 0 ? Cn - 8 : j), w);
+      if (over > 0) {
+        if (over & 4) { w[0] = w[2]; w[1] = w[3]; w[2] = w[3] = 0; }
+        if (over & 2) { w[0] = w[1]; w[1] = w[2]; w[2] = w[3]; w[3] = 0; }
+        if (over & 1) { w[0] = w[0] >> 16 | w[1] << 16; w[1] = w[1] >> 16 | w[2] << 16; w[2] = w[2] >> 16 | w[3] << 16; w[3] >>= 16; }
+        if (over >= 8) w[0] = w[1] = w[2] = w[3] = 0;
+      }
+    }
+    store8(dst, w);
   };
   if (flat > 1) {
-    const int sub = threadIdx.x & (flat - 1), per = 256 / flat;
-    for (int64_t m = b * per + threadIdx.x / flat; m < R; m += nb * per)
-      for (int64_t j = 8 * sub; j < ldo; j += 8 * flat) {
-        if (j + 8 <= Cn) chunk(in + m * ld_in + j, out + m * ldo + j);
-        else chunk_end(in + m * ld_in + j, Cn - j, out + m * ldo + j);
-      }
+    const int lg = 31 - __builtin_clz(flat), sub = threadIdx.x & (flat - 1), per = 256 >> lg;
+    for (int64_t m = b * per + (threadIdx.x >> lg); m < R; m += nb * per)
+      for (int64_t j = 8 * sub; j < ldo; j += 8 * flat) chunk(in + m * ld_in, j, out + m * ldo + j);
     return;
   }
   if (flat) {
     const int64_t n8 = R * (ldo >> 3);
-    for (int64_t e = b * 256 + threadIdx.x; e < n8; e += nb * 256) chunk(in + e * 8, out + e * 8);
+    for (int64_t e = b * 256 + threadIdx.x; e < n8; e += nb * 256) {
+      uint32_t w[4];
+      load8(in + e * 8, w);
+      store8(out + e * 8, w);
+    }
     return;
   }
   const int lane = threadIdx.x & 63;
@@ -193,10 +207,7 @@ __device__ __forceinline__ void rows_block(int64_t b, int64_t nb, const T* __res
     const int64_t s1 = s0 + cut.cols < ldo ? s0 + cut.cols : ldo;
     const T* src = in + (rowmap ? (int64_t)rowmap[m] : m) * ld_in;
 #pragma unroll 4
-    for (int64_t j = s0 + 8 * lane; j < s1; j += 512) {
-      if (j + 8 <= Cn) chunk(src + j, out + m * ldo + j);
-      else chunk_end(src + j, Cn - j, out + m * ldo + j);
-    }
+    for (int64_t j = s0 + 8 * lane; j < s1; j += 512) chunk(src, j, out + m * ldo + j);
   }
 }
 
@@ -862,9 +873,14 @@ static int run_bwd(const BwdIo& io, const BwdPlan& p, int64_t T_in, int64_t T_ou
   if (copy_dy) {
     // dY as a token-major bf16 matrix [T_out][ldc] (A operand of the dX product)
     a.rows_flat = p.ldc == c_out ? 1 : 0;
+    // lanes to a row: as many as it has chunks, or more of them idle while that makes 512 wavefronts or fewer, one trip each: with few
+    // tokens the call waits for the slowest wavefront.  Backward call, us, as many lanes as chunks in as few blocks as make two chunks
+    // a thread / so / a wavefront a row: 337 x 64, 19 channels, k = 3 fp32 11.7 / 11.0 / 10.9; 1635 x 128, 13 channels, k = 2 12.5 /
+    // 12.1 / 12.1; 14392 x 64, 39 channels fp32 10.3 / 10.1 / 13.0; 19932 x 333, 93 channels 23.5 / 23.1 / 27.0
     if (!a.rows_flat && ((c_out % 8) == 0 || p.ldc <= 512))
-      for (a.rows_flat = 2; a.rows_flat < 64 && a.rows_flat < p.ldc / 8;) a.rows_flat *= 2;
-    const int64_t nb = a.rows_flat ? ceil_div(T_out * p.ldc, 256 * 16) : cut_rows(T_out, p.ldc, &a.rows_cut);
+      for (a.rows_flat = 2; a.rows_flat < 64 && (a.rows_flat < p.ldc / 8 || T_out * a.rows_flat <= 32 * 512);) a.rows_flat *= 2;
+    int64_t nb = a.rows_flat ? ceil_div(T_out * p.ldc, 256 * 16) : cut_rows(T_out, p.ldc, &a.rows_cut);
+    if (a.rows_flat > 1) nb = std::max(nb, std::min<int64_t>(ceil_div(T_out * a.rows_flat, 256), 1024));
     a.n_rows = (uint32_t)std::min<int64_t>(nb, 4096);
   } else if (p.need_dyn) {
     a.dyn_x = (uint32_t)ceil_div(p.ldc, 64);
