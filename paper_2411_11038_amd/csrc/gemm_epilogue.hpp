@@ -157,7 +157,9 @@ __device__ __forceinline__ void lds_barrier() {
 // one is not, s1 is not either, and the epilogue adds the a - a of its rows behind the chunks (half an operation an element to keep
 // the largest |a| for that cost the dX products 1 %).
 // SKIP: off for wavefronts of one 32 x 32 accumulator (tiles of 64 x 64), up to four blocks of which share a CU and hide the operations,
-// not the branch (37.3 us of both products of a convolution so, 37.7 with it).
+// not the branch (37.3 us of both products of a convolution so, 37.7 with it); and in EpiDxAny for wavefronts of 256 rows (256 x 256 by
+// k_gemm_dx8; 2376 x 352 -> 6000 34.1 us before, 37.1 with it, 35.1 so; 40 such layers 1.005 of the time before, 1.03 with it), whereas
+// the straight-line epilogue of these tiles gains 3.5 %.
 template <bool SKIP>
 __device__ __forceinline__ void epi_chunk(float (&a)[8], const float (&xf)[8], const uint2& cw, uint32_t mb, float z,
                                           float ninv_s, float& s1, float& sd) {
@@ -214,7 +216,7 @@ struct EpiDxAny {
   static constexpr int U = KC == 1 ? (NP * GS < 4 ? NP * GS : 4) : 2 * KC;
   static_assert(NP * GS % U == 0 && U % KC == 0, "passes");
   static constexpr int XW = sizeof(XT) / 2;          // 16-byte words of x per chunk
-  static constexpr bool kSkip = C::TM * C::TN > 1;   // see epi_chunk
+  static constexpr bool kSkip = C::TM * C::TN > 1 && C::WM < 256;   // see epi_chunk
   struct Inputs { uint2 cw; uint4 xa[XW]; uint32_t mb; };
   Inputs in[U];
   int row_b, col_b, first_row, rows;                 // rows: of this wavefront's sub-tile that lie inside the matrix
