@@ -132,11 +132,14 @@ constexpr int64_t kSkinnyTokens = 64;
 // more loads a fragment, each with its own wait: where they are short, wide blocks pay late.  Fitted to 1398 sizes (1 to 64 tokens,
 // C_in 64 to 11008, C_out 4096 to 32768): 1.2 % from the fastest in the mean; 0.91 of the time of one group (four from 33 tokens and
 // 8192 columns on), the first rule, and 0.98 of the second, the loads alone, which was up to 1.4 x as slow as the first where rows
-// are short.  NT = 1 / 2 / 3 / 4, us (* chosen):
+// are short.  With up to 16 tokens three groups pay later than that (95 of 581 sizes of 5 to 16 tokens took them and lost 1 %): 0.950 of
+// the time of one group, 5 % of the sizes 3 to 19 % slower than it.  NT = 1 / 2 / 3 / 4, us (* chosen):
 //   tokens  C_in  -> C_out
 //    1      4096     11008    11.9* / 14.7  / 14.1  / 16.0
 //   16      4096      6000    11.6  / 10.6* / 13.2  / 15.7
 //   16      4096     11008    17.1  / 18.3  / 15.8* / 17.7
+//    9      1136     11251     4.7* /  5.3  /  5.2  /  5.8
+//    5      2980      8309    10.1* / 12.0  / 11.6  / 12.7
 //   16     11008      4096    16.1* / 23.5  / 30.4  / 35.9
 //   16      8192     28672    70.4  / 66.2  / 66.6  / 60.1*
 //   32      4096     11008    22.9  / 22.9  / 18.1* / 21.1
@@ -163,7 +166,7 @@ static int skinny_columns(int64_t T, int64_t c_in, int64_t c_out) {
   for (int nt = 1; nt <= 4; ++nt) {
     const double rounds = (double)ceil_div(ceil_div(c_out, 16 * nt), 256);
     const double loads = rounds * (k * (nt + 1.2 * (double)T / 16.0) + 600.0 * mt * nt + 1000.0);
-    const double t = std::max(loads, 8000.0) + nt * (0.55 * k + 450.0 * mt);
+    const double t = (std::max(loads, 8000.0) + nt * (0.55 * k + 450.0 * mt)) * (nt == 3 && T <= 16 ? 1.08 : 1.0);
     if (nt == 1 || t < best_t) { best = nt; best_t = t; }
   }
   return best;

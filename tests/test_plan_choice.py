@@ -83,6 +83,8 @@ FEW_TOKENS = [
     (64, 192, 8192, 16),      # 4.5 / 5.1 / 6.0 / 6.8
     (16, 333, 11008, 16),     # 6.7 / 8.0 / 8.8 / 9.4    ... not aligned
     (20, 1500, 8192, 16),     # 10.2 / 10.9 / 13.3 / 15.6
+    (9, 1136, 11251, 16),     # 4.7 / 5.3 / 5.2 / 5.8      few tokens: three groups pay late
+    (5, 2980, 8309, 16),      # 10.1 / 12.0 / 11.6 / 12.7
     (16, 96, 28672, 64),      # 6.4 / 6.5 / 7.8 / 4.9    many columns
     (32, 1024, 32768, 64),    # 18.2 / 15.6 / 14.6 / 12.8
     (16, 4096, 11008, 48),    # 17.1 / 18.3 / 15.8 / 17.7
