@@ -84,13 +84,12 @@ __device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int
     // dense source, 4 consecutive columns per lane: one load of 4 to 16 bytes at any alignment, but for the chunk that ends a row
     const int jq = (threadIdx.x & 15) * 4, ib = threadIdx.x >> 4;
     const int64_t left = Cn - j0 - jq;
-    float v[4][4], rs[4];
-    bool is[4];
+    float v[4][4], sb[4], rs[4];
 #pragma unroll
     for (int rr = 0; rr < 4; ++rr) {
       const int64_t i = i0 + ib + 16 * rr, si = src_row(i);
-      is[rr] = si >= 0;
-      rs[rr] = rowscale ? rowscale[i < R ? i : R - 1] : 1.0f;
+      sb[rr] = si >= 0 ? sub : 0.0f;                   // padding is zero beside an infinite Z_x or S_w too
+      rs[rr] = rowscale && i < R ? rowscale[i] : 1.0f;
 #pragma unroll
       for (int t = 0; t < 4; ++t) v[rr][t] = 0.0f;
       if (si >= 0 && left >= 4) {
@@ -107,7 +106,7 @@ __device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int
     for (int rr = 0; rr < 4; ++rr) {
       const int li = ib + 16 * rr;
 #pragma unroll
-      for (int t = 0; t < 4; ++t) v[rr][t] = is[rr] ? (v[rr][t] - sub) * rs[rr] : 0.0f;   // zero beside an infinite S_w or Z_x too
+      for (int t = 0; t < 4; ++t) v[rr][t] = (v[rr][t] - sb[rr]) * rs[rr];
       *reinterpret_cast<uint32_t*>(&tile[li][jq]) = pack_bf16x2(v[rr][0], v[rr][1]);
       *reinterpret_cast<uint32_t*>(&tile[li][jq + 2]) = pack_bf16x2(v[rr][2], v[rr][3]);
     }
@@ -146,9 +145,9 @@ __device__ __forceinline__ void transpose_block(TransposeTile& tile, int bx, int
 struct RowCut { uint32_t segs, cols; };
 
 // Row-wise cast/copy to bf16 with zero-padded pitch: out[m][j] = bf16(in[rm(m)][j]), j < Cn; 0 up to ldo (a multiple of
-// 8), a chunk of 8 a lane: one or two 16-byte loads at any alignment, of the row's last eight values where it ends.  flat == 1:
-// no padding and no row map, i.e. one run of chunks; flat = 2 .. 64, a power of two: that many lanes to a row; 0: a
-// wavefront per row segment.  block b of nb.
+// 8), a chunk of 8 a lane: one or two 16-byte loads at any alignment, but for the chunk that ends a long row.  flat == 1: no
+// padding and no row map, i.e. one run of chunks; flat = 2 .. 64, a power of two: that many lanes to a row; 0: a wavefront
+// per row segment.  block b of nb.
 template <typename T>
 __device__ __forceinline__ void rows_block(int64_t b, int64_t nb, const T* __restrict__ in, int64_t ld_in, int64_t R,
                                            int64_t Cn, const int32_t* __restrict__ rowmap, bf16_t* __restrict__ out,
@@ -164,40 +163,42 @@ __device__ __forceinline__ void rows_block(int64_t b, int64_t nb, const T* __res
     }
   };
   auto store8 = [](bf16_t* dst, const uint32_t (&w)[4]) { *reinterpret_cast<uint4*>(dst) = make_uint4(w[0], w[1], w[2], w[3]); };
-  // columns j .. j + 7 of a row: past its end zeros, by moving the row's last eight values down
-  auto chunk = [&](const T* row, int64_t j, bf16_t* dst) {
+  auto chunk = [&](const T* src, bf16_t* dst) {
     uint32_t w[4];
+    load8(src, w);
+    store8(dst, w);
+  };
+  auto chunk_end = [](const T* src, int64_t n, bf16_t* dst) {   // of n < 8 values, then zeros
+    float f[8];
+#pragma unroll
+    for (int t = 0; t < 8; ++t) f[t] = t < n ? rd<T>(src, t) : 0.0f;
+    *reinterpret_cast<uint4*>(dst) =
+        make_uint4(pack_bf16x2(f[0], f[1]), pack_bf16x2(f[2], f[3]), pack_bf16x2(f[4], f[5]), pack_bf16x2(f[6], f[7]));
+  };
+  // columns j .. j + 7 of a row; its end is its last eight values moved down, so that no lane reads value by value while its neighbours
+  // wait.  Long rows, few of whose chunks end one, are the faster without (2049 x 1001 fp32: 0.1 us of 8.3).
+  auto chunk_of_row = [&](const T* row, int64_t j, bf16_t* dst) {
     const int64_t over = j + 8 - Cn;
-    if (Cn < 8) {
-      float f[8];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) f[t] = j + t < Cn ? rd<T>(row, j + t) : 0.0f;
-#pragma unroll
-      for (int t = 0; t < 4; ++t) w[t] = pack_bf16x2(f[2 * t], f[2 * t + 1]);
-    } else {
-      load8(row + (over > 0 ? Cn - 8 : j), w);
-      if (over > 0) {
-        if (over & 4) { w[0] = w[2]; w[1] = w[3]; w[2] = w[3] = 0; }
-        if (over & 2) { w[0] = w[1]; w[1] = w[2]; w[2] = w[3]; w[3] = 0; }
-        if (over & 1) { w[0] = w[0] >> 16 | w[1] << 16; w[1] = w[1] >> 16 | w[2] << 16; w[2] = w[2] >> 16 | w[3] << 16; w[3] >>= 16; }
-        if (over >= 8) w[0] = w[1] = w[2] = w[3] = 0;
-      }
+    if (Cn < 8) return chunk_end(row + j, Cn - j, dst);
+    uint32_t w[4];
+    load8(row + (over > 0 ? Cn - 8 : j), w);
+    if (over > 0) {
+      if (over & 4) { w[0] = w[2]; w[1] = w[3]; w[2] = w[3] = 0; }
+      if (over & 2) { w[0] = w[1]; w[1] = w[2]; w[2] = w[3]; w[3] = 0; }
+      if (over & 1) { w[0] = w[0] >> 16 | w[1] << 16; w[1] = w[1] >> 16 | w[2] << 16; w[2] = w[2] >> 16 | w[3] << 16; w[3] >>= 16; }
+      if (over >= 8) w[0] = w[1] = w[2] = w[3] = 0;
     }
     store8(dst, w);
   };
   if (flat > 1) {
     const int lg = 31 - __builtin_clz(flat), sub = threadIdx.x & (flat - 1), per = 256 >> lg;
     for (int64_t m = b * per + (threadIdx.x >> lg); m < R; m += nb * per)
-      for (int64_t j = 8 * sub; j < ldo; j += 8 * flat) chunk(in + m * ld_in, j, out + m * ldo + j);
+      for (int64_t j = 8 * sub; j < ldo; j += 8 * flat) chunk_of_row(in + m * ld_in, j, out + m * ldo + j);
     return;
   }
   if (flat) {
     const int64_t n8 = R * (ldo >> 3);
-    for (int64_t e = b * 256 + threadIdx.x; e < n8; e += nb * 256) {
-      uint32_t w[4];
-      load8(in + e * 8, w);
-      store8(out + e * 8, w);
-    }
+    for (int64_t e = b * 256 + threadIdx.x; e < n8; e += nb * 256) chunk(in + e * 8, out + e * 8);
     return;
   }
   const int lane = threadIdx.x & 63;
@@ -207,7 +208,10 @@ __device__ __forceinline__ void rows_block(int64_t b, int64_t nb, const T* __res
     const int64_t s1 = s0 + cut.cols < ldo ? s0 + cut.cols : ldo;
     const T* src = in + (rowmap ? (int64_t)rowmap[m] : m) * ld_in;
 #pragma unroll 4
-    for (int64_t j = s0 + 8 * lane; j < s1; j += 512) chunk(src, j, out + m * ldo + j);
+    for (int64_t j = s0 + 8 * lane; j < s1; j += 512) {
+      if (j + 8 <= Cn) chunk(src + j, out + m * ldo + j);
+      else chunk_end(src + j, Cn - j, out + m * ldo + j);
+    }
   }
 }
 
