@@ -54,7 +54,8 @@ struct Dx8Cfg {
 };
 
 // FAST (dX only): the straight-line epilogue for bf16 x / dX and whole tiles (epilogue_dx_fast).
-template <int BM, int BN, bool DW = false, bool ATN = false, bool FAST = false>
+// MASK: the general epilogue keeps the mask in every chunk (see epi_chunk).
+template <int BM, int BN, bool DW = false, bool ATN = false, bool FAST = false, bool MASK = false>
 __device__ __forceinline__ void gemm_dx8_block(const GemmDx8Args& ga, char* smem, int bid, int nblk) {
 #if defined(__HIP_DEVICE_COMPILE__)
   using C = Dx8Cfg<BM, BN, ATN>;
@@ -374,15 +375,15 @@ __device__ __forceinline__ void gemm_dx8_block(const GemmDx8Args& ga, char* smem
   } else if constexpr (FAST) {
     epilogue_dx_fast<C>(g, acc, smem, m0, n0, wm, wn, bid);
   } else {
-    epilogue_dx<C>(g, acc, smem, m0, n0, wm, wn, g.M, bid);
+    epilogue_dx<C, false, MASK>(g, acc, smem, m0, n0, wm, wn, g.M, bid);
   }
 #endif
 }
 
-template <int BM, int BN, bool DW = false, bool ATN = false, bool FAST = false>
+template <int BM, int BN, bool DW = false, bool ATN = false, bool FAST = false, bool MASK = false>
 __global__ __launch_bounds__(256, BM == 64 ? 3 : BM == 128 ? 2 : 1) void k_gemm_dx8(const GemmDx8Args ga) {
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  gemm_dx8_block<BM, BN, DW, ATN, FAST>(ga, smem, blockIdx.x, gridDim.x);
+  gemm_dx8_block<BM, BN, DW, ATN, FAST, MASK>(ga, smem, blockIdx.x, gridDim.x);
 }
 
 }  // namespace efqat

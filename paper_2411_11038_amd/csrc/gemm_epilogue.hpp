@@ -159,7 +159,8 @@ __device__ __forceinline__ void lds_barrier() {
 // SKIP: off for wavefronts of one 32 x 32 accumulator (tiles of 64 x 64), up to four blocks of which share a CU and hide the operations,
 // not the branch (37.3 us of both products of a convolution so, 37.7 with it); and in EpiDxAny for wavefronts of 256 rows (256 x 256 by
 // k_gemm_dx8; 2376 x 352 -> 6000 34.1 us before, 37.1 with it, 35.1 so; 40 such layers 1.005 of the time before, 1.03 with it), whereas
-// the straight-line epilogue of these tiles gains 3.5 %.
+// the straight-line epilogue of these tiles gains 3.5 %.  MASK: off for 128 x 128 tiles of k_gemm_dx8 that have a CU for themselves (see
+// launch_gemm_dx8_cm).
 template <bool SKIP>
 __device__ __forceinline__ void epi_chunk(float (&a)[8], const float (&xf)[8], const uint2& cw, uint32_t mb, float z,
                                           float ninv_s, float& s1, float& sd) {
@@ -202,7 +203,7 @@ __device__ __forceinline__ void epi_undefined_chunk(const float* a, uint32_t mb,
 // lone block has nothing else to run meanwhile.  On 128 x 128 fp32 tiles of a lone block it takes 3.6 us, 4.2 us where the
 // width is odd; with branches on type and edge around each element and one 32-row slab of loads in flight (one column a
 // lane for odd widths) it took 6.5 and 12.6 us.
-template <class C, typename XT, bool MAP = false>
+template <class C, typename XT, bool MAP = false, bool MASK = false>
 struct EpiDxAny {
   static constexpr int PITCH = C::WN + 8;            // floats; 4*PITCH = 32 (mod 64) banks
   static constexpr int CPR = C::WN / 8;              // 8-column chunks per row
@@ -216,7 +217,7 @@ struct EpiDxAny {
   static constexpr int U = KC == 1 ? (NP * GS < 4 ? NP * GS : 4) : 2 * KC;
   static_assert(NP * GS % U == 0 && U % KC == 0, "passes");
   static constexpr int XW = sizeof(XT) / 2;          // 16-byte words of x per chunk
-  static constexpr bool kSkip = C::TM * C::TN > 1 && C::WM < 256;   // see epi_chunk
+  static constexpr bool kSkip = !MASK && C::TM * C::TN > 1 && C::WM < 256;   // see epi_chunk
   struct Inputs { uint2 cw; uint4 xa[XW]; uint32_t mb; };
   Inputs in[U];
   int row_b, col_b, first_row, rows;                 // rows: of this wavefront's sub-tile that lie inside the matrix
@@ -417,7 +418,7 @@ struct EpiDxAny {
 };
 
 // ... with the type of x decided at run time, all requests behind the main loop
-template <class C, bool MAP = false>
+template <class C, bool MAP = false, bool MASK = false>
 __device__ __forceinline__ void epilogue_dx(const GemmArgs& g, floatx16_t (&acc)[C::TM][C::TN], char* smem, int m0,
                                             int n0, int wm, int wn, int m_end, int part_idx,
                                             const int* rowmap = nullptr) {
@@ -432,11 +433,11 @@ __device__ __forceinline__ void epilogue_dx(const GemmArgs& g, floatx16_t (&acc)
   using Yes = std::integral_constant<bool, true>;
   using No = std::integral_constant<bool, false>;
   if (g.x_dtype == EFQAT_F32) {
-    if (edge) all(EpiDxAny<C, float, MAP>(), Yes{});
-    else all(EpiDxAny<C, float, MAP>(), No{});
+    if (edge) all(EpiDxAny<C, float, MAP, MASK>(), Yes{});
+    else all(EpiDxAny<C, float, MAP, MASK>(), No{});
   } else {
-    if (edge) all(EpiDxAny<C, bf16_t, MAP>(), Yes{});
-    else all(EpiDxAny<C, bf16_t, MAP>(), No{});
+    if (edge) all(EpiDxAny<C, bf16_t, MAP, MASK>(), Yes{});
+    else all(EpiDxAny<C, bf16_t, MAP, MASK>(), No{});
   }
 }
 

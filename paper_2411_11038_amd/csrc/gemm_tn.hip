@@ -74,16 +74,16 @@ int launch_gemm_tn(const GemmTnArgs& a, const GemmPlan& plan, hipStream_t stream
 }
 
 
-template <int BM, int BN, bool DW = false, bool ATN = false, bool FAST = false>
+template <int BM, int BN, bool DW = false, bool ATN = false, bool FAST = false, bool MASK = false>
 static int launch_dx8_cfg(const GemmDx8Args& a, int split_k, hipStream_t st) {
   constexpr int kLds = Dx8Cfg<BM, BN, ATN>::template lds_bytes<!DW && !FAST>();
   // set once per process (initialisation of a function-local static is thread-safe)
-  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_dx8<BM, BN, DW, ATN, FAST>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+  static const hipError_t attr = hipFuncSetAttribute((const void*)k_gemm_dx8<BM, BN, DW, ATN, FAST, MASK>, hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
   if (attr != hipSuccess) return EFQAT_ERR_HIP;
   const dim3 grid((unsigned)(a.g.tiles_m * a.g.tiles_n * split_k));
   {
     ProfScope prof(DW ? PROF_DW : PROF_DX, st);
-    hipLaunchKernelGGL((k_gemm_dx8<BM, BN, DW, ATN, FAST>), grid, dim3(256), kLds, st, a);
+    hipLaunchKernelGGL((k_gemm_dx8<BM, BN, DW, ATN, FAST, MASK>), grid, dim3(256), kLds, st, a);
   }
   EFQAT_LAUNCH_CHECK();
   return EFQAT_OK;
@@ -112,12 +112,16 @@ int launch_gemm_dx8_cm(const GemmDx8Args& a, const GemmPlan& plan, hipStream_t s
   if (plan.wide)
     return dx_epilogue_fast(a.g, 128, 256) ? launch_dx8_cfg<128, 256, false, true, true>(a, 1, stream)
                                            : launch_dx8_cfg<128, 256, false, true>(a, 1, stream);
+  // a block on a CU: the branch around the mask costs it 1 % (80 sizes; 1600 x 797 -> 1584 18.6 -> 19.4 us, without it 18.5), which two of
+  // them hide: more tiles gain 1 % (60 sizes) by it
+  const bool alone = (int64_t)plan.tiles_m * plan.tiles_n <= 256;
   switch (plan.tile) {
     case 64: return launch_dx8_cfg<64, 128, false, true>(a, 1, stream);
     case 256: return dx_epilogue_fast(a.g, 256, 256) ? launch_dx8_cfg<256, 256, false, true, true>(a, 1, stream)
                                                       : launch_dx8_cfg<256, 256, false, true>(a, 1, stream);
-    case 128: return dx_epilogue_fast(a.g, 128, 128) ? launch_dx8_cfg<128, 128, false, true, true>(a, 1, stream)
-                                                      : launch_dx8_cfg<128, 128, false, true>(a, 1, stream);
+    case 128:
+      if (dx_epilogue_fast(a.g, 128, 128)) return launch_dx8_cfg<128, 128, false, true, true>(a, 1, stream);
+      return alone ? launch_dx8_cfg<128, 128, false, true, false, true>(a, 1, stream) : launch_dx8_cfg<128, 128, false, true>(a, 1, stream);
     default: return EFQAT_ERR_BAD_SHAPE;
   }
 }

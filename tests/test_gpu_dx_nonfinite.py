@@ -27,6 +27,8 @@ SIZES = [
     (8192, 1024, 1000, "bf16", CHAN, ef.DX_KERNEL_AUTO, (2, 128)),
     (8192, 1024, 1000, "f32", CHAN, ef.DX_KERNEL_AUTO, (2, 128)),
     (8912, 1328, 623, "bf16", CHAN, ef.DX_KERNEL_AUTO, (2, 256)),
+    (2528, 784, 1000, "bf16", CHAN, ef.DX_KERNEL_AUTO, (2, 128)),        # up to 256 tiles: the mask in every chunk
+    (1528, 1328, 1000, "f32", CHAN, ef.DX_KERNEL_AUTO, (2, 128)),
 ]
 S, Z = 0.02, 128.0
 
