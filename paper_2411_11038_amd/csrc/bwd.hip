@@ -394,7 +394,7 @@ struct StepArgs {
 // One block of NTH threads per row.  What bounds it is memory for large layers, else the chain of loads of a trip through the row.
 // ANY: rows of any width and alignment; a lane owns four neighbouring columns and reads them in vector accesses, the last lane of
 // a row that is no multiple of four starts earlier and leaves out the d columns that its neighbour has; everything but the slices
-// past the first is requested at once.  That holds 90 registers a lane; without ANY, 49, and twice the wavefronts, for
+// past the first is requested at once.  That holds 92 registers a lane; without ANY, 48, and twice the wavefronts, for
 // aligned rows of four where there are many rows or long ones (2752 x 4096: 26.8 us, with ANY 29 to 32).
 // 2049 x 777 -> 1001, k = 250, 3 slices: 4.1 us; by single columns, slices and weights behind one another, 7.3.
 template <int NTH, bool ANY>
@@ -406,6 +406,10 @@ __global__ __launch_bounds__(NTH) void k_dw_finish(const float* __restrict__ par
                                                    const float* __restrict__ part_dx, int64_t n_part_dx,
                                                    float* __restrict__ ds_x, float* __restrict__ dz_x,
                                                    const StepArgs sgd) {
+  // the arguments in one batch: left to the compiler, some are requested where they are used, behind one another's waits (4384 x 1088 ->
+  // 6960, k = 54: 7.8 us, so 7.1; 2020 x 352 -> 6784, all selected, 12.5, 11.9)
+  asm volatile("" ::"s"(part), "s"(S), "s"(s_x), "s"(w_codes), "s"(w_clip), "s"(w), "s"(s_w), "s"(idx), "s"(dw), "s"(ds_w), "s"(scatter),
+               "s"(sgd.w), "s"(sgd.mom_w));
   if ((int64_t)blockIdx.x == k) {                     // one extra block: dS_x, dZ_x from the dX epilogue's partials
     sum_partials_block<NTH>(part_dx, n_part_dx, ds_x, dz_x);
     return;
